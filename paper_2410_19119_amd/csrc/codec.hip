@@ -22,12 +22,7 @@ enum : uint32_t {
 };
 
 __device__ __forceinline__ uint32_t varint_len(uint64_t x) {
-  uint32_t k = 1;
-  while (x >= 0x80) {
-    x >>= 7;
-    ++k;
-  }
-  return k;
+  return ((70u - (uint32_t)__clzll((long long)(x | 1u))) * 37u) >> 8;  // ceil(bits / 7) for 1..64 bits
 }
 
 __device__ __forceinline__ uint64_t zigzag(int64_t x) { return ((uint64_t)x << 1) ^ (uint64_t)(x >> 63); }
@@ -50,40 +45,20 @@ struct CsrIn {
   const int32_t* vwgt;
 };
 
-// Block-wide maxima of two values, then one atomic per block (256 threads).
-__device__ __forceinline__ void block_max2(unsigned long long a, unsigned long long b, unsigned long long* ga,
-                                           unsigned long long* gb) {
-  __shared__ unsigned long long sa[4], sb[4];
-  a = wave_reduce_max(a);
-  b = wave_reduce_max(b);
-  if (lane_id() == 0) {
-    sa[threadIdx.x / kWave] = a;
-    sb[threadIdx.x / kWave] = b;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < 4; ++i) {
-      a = max(a, sa[i]);
-      b = max(b, sb[i]);
-    }
-    atomicMax(ga, a);
-    atomicMax(gb, b);
-  }
-}
+// Work is handed out along the merged sequence of vertices and adjacency
+// entries: vertex u sits at key(u) = xadj[u] + u, its entries right after it,
+// so a stretch of T positions holds T vertices and entries together however
+// the degrees vary (hubs spread over many stretches, a run of isolated
+// vertices too). blk[c] is the first vertex at or after position c * T;
+// stretch c holds the vertices blk[c] .. blk[c + 1] - 1 and the entries from
+// c * T - blk[c] on (the first of them may belong to vertex blk[c] - 1).
 
-// The wave-per-vertex kernels below take their vertices in blocks, in order,
-// from a counter (one per launch). A vertex u costs its degree plus one, so
-// it starts at key(u) = xadj[u] + u (increasing in u), and block c holds the
-// vertices whose key lies in [c * kCodecWork, (c + 1) * kCodecWork), i.e.
-// vertices blk[c] .. blk[c + 1] - 1: at most kCodecWork vertices, and the
-// adjacency of those plus the rest of the last one. The resident waves then
-// read a window of the adjacency that slides over it, a run of high-degree
-// vertices (a degree-ordered graph starts with one) spreads over as many
-// blocks as its entries fill, and a run of isolated vertices (such a graph
-// ends with one) over as many as its count fills. With a static stride,
-// waves that met high-degree vertices fell behind and the reads spread over
-// the whole adjacency (R-MAT scale 26 in its given order compressed 30x
-// slower than the same graph numbered by degree).
+// The wave-per-vertex decoder takes its vertices in blocks of kCodecWork
+// positions, in order, from a counter (one per launch); the resident waves
+// then read a window of the adjacency that slides over it. With a static
+// stride, waves that met high-degree vertices fell behind and the reads
+// spread over the whole adjacency (R-MAT scale 26 in its given order went
+// 30x slower than the same graph numbered by degree).
 constexpr uint64_t kCodecWork = 16384;
 constexpr unsigned kCodecGrid = 2048;  // workgroups of 256 threads
 
@@ -93,19 +68,20 @@ struct CodecBlocks {
   unsigned long long* ctr;   // hand-out counter (zero before the launch)
 };
 
-// blk[c] = the smallest u with key(u) >= c * kCodecWork (c < nb), blk[nb] =
-// n. xadj must be non-decreasing from 0 (a decrease sets *err and leaves blk
+// blk[c] = the smallest u with key(u) >= c * work (c < nb), blk[nb] = n.
+// xadj must be non-decreasing from 0 (a decrease sets *err and leaves blk
 // incomplete).
-__global__ void k_codec_blocks(const uint64_t* xadj, int64_t n, int64_t nb, int64_t* blk, uint32_t* err) {
+__global__ void k_codec_blocks(const uint64_t* xadj, int64_t n, uint64_t work, int64_t nb, int64_t* blk,
+                               uint32_t* err) {
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u <= n; u += (int64_t)gridDim.x * blockDim.x) {
     if (u > 0 && xadj[u] < xadj[u - 1]) {
       atomicOr(err, 1u);
       continue;
     }
     const uint64_t hi = xadj[u] + (uint64_t)u;
-    // blocks c with key(u - 1) < c * kCodecWork <= key(u) (u > 0), or c = 0
-    const int64_t c0 = u ? (int64_t)((xadj[u - 1] + (uint64_t)(u - 1)) / kCodecWork) + 1 : 0;
-    const int64_t c1 = min((int64_t)(hi / kCodecWork), nb - 1);
+    // blocks c with key(u - 1) < c * work <= key(u) (u > 0), or c = 0
+    const int64_t c0 = u ? (int64_t)((xadj[u - 1] + (uint64_t)(u - 1)) / work) + 1 : 0;
+    const int64_t c1 = min((int64_t)(hi / work), nb - 1);
     for (int64_t c = c0; c <= c1; ++c) blk[c] = u;
     if (u == n) blk[nb] = n;
   }
@@ -117,40 +93,459 @@ __device__ __forceinline__ int64_t next_block(const CodecBlocks& cb) {
   return (int64_t)(uint32_t)__shfl((int)c, 0, kWave);
 }
 
-// One wave per vertex: range / self-loop / weight / order checks, weighted
-// degree and degree maxima.
-__global__ __launch_bounds__(256) void k_validate(CsrIn g, uint32_t* err, unsigned long long* max_wdeg,
-                                                  unsigned long long* max_deg, CodecBlocks cb) {
-  const int lane = lane_id();
-  uint32_t bad = 0;
-  unsigned long long mw = 0, md = 0;
-  for (int64_t c = next_block(cb); c < cb.nb; c = next_block(cb))
-  for (int64_t u = cb.blk[c]; u < cb.blk[c + 1]; ++u) {
-    const uint64_t b = g.xadj[u], e = g.xadj[u + 1];
-    if (e < b) {
-      bad |= kErrXadj;
-      continue;
-    }
-    int64_t wsum = 0;
-    for (uint64_t k = b + lane; k < e; k += kWave) {
-      const int32_t v = g.adjncy[k];
-      const int32_t w = g.adjwgt ? g.adjwgt[k] : 1;
-      if (v < 0 || v >= g.n) bad |= kErrRange;
-      if (v == u) bad |= kErrSelf;
-      if (w < 1) bad |= kErrWeight;
-      if (k > b) {
-        const int32_t pv = g.adjncy[k - 1];
-        const int32_t pw = g.adjwgt ? g.adjwgt[k - 1] : 1;
-        if (pv > v || (pv == v && pw > w)) bad |= kErrOrder;
-      }
-      wsum += w;
-    }
-    wsum = wave_reduce_add(wsum);
-    mw = max(mw, (unsigned long long)wsum);
-    md = max(md, (unsigned long long)(e - b));
+// ------------------------------------------------ compression of a CSR ----
+// One workgroup per stretch of kCtWork positions, kCtItems consecutive
+// entries per thread, so the adjacency is read in order at full width
+// whatever the degrees. Two passes: k_csr_scan checks the input and sums the
+// stretch's code bytes, k_csr_encode (after a prefix sum over the stretches)
+// computes the codes again, places them by a prefix sum inside the workgroup,
+// gathers them in LDS and stores them as 16-byte words. What bounds it is the
+// adjacency read twice and the codes written once. A wave per vertex, as
+// before, kept most lanes idle on low degrees and waited on a chain of
+// dependent loads per vertex: R-MAT with 2^23 vertices and 2.4e8 entries took
+// 7.0 ms to check, 11.1 ms to size and 10.7 ms to encode, and takes 0.35 ms
+// for the first two together and 0.65 ms for the last (0.97 GB of adjacency
+// and 0.5 GB of codes: 2.3 TB/s; the instructions per entry are what is left).
+constexpr int kCtThreads = 256;
+constexpr int kCtItems = 8;
+constexpr int kCtWork = kCtThreads * kCtItems;
+
+// What the passes find out about the input (device memory, zeroed).
+struct CsrAcc {
+  uint32_t xerr;  // xadj decreases (set before the passes, which then do nothing)
+  uint32_t err;
+  unsigned long long wdeg, deg, vtot;
+  uint64_t nbytes;
+  uint32_t nsplit, pad;  // vertices whose records are split into chunks (counted by the encoder)
+};
+
+// Code length of a VarInt below 2^32, and of the 32-bit zigzag of a
+// difference of two IDs or two weights (all in [0, 2^31), so it fits).
+__device__ __forceinline__ uint32_t varint_len32(uint32_t x) {
+  return ((38u - (uint32_t)__clz((int)(x | 1u))) * 37u) >> 8;  // ceil(bits / 7)
+}
+__device__ __forceinline__ uint32_t zigzag32(int32_t d) { return ((uint32_t)d << 1) ^ (uint32_t)(d >> 31); }
+
+// The part of the merged sequence a workgroup takes, and the two vertices of
+// it that may be split into chunks: the one whose entries it continues
+// (kind 0) and the last one it starts (kind 1). Others have fewer entries
+// than the stretch has positions.
+struct CtSpan {
+  int64_t v0;
+  int32_t nv, ne;       // vertices started here, entries
+  uint64_t e0;          // first entry
+  uint64_t x[2];        // first entry of the vertex of each kind
+  uint32_t chunked[2];  // it is split into chunks
+  uint64_t table;       // bytes of the chunk table that follows the header of the vertex of kind 1
+};
+static_assert(LP_CHUNK_THRESHOLD >= kCtWork, "only the last vertex a stretch starts can be split");
+
+__device__ __forceinline__ CtSpan ct_span(const CsrIn& g, const int64_t* blk, int64_t nb, int64_t c) {
+  CtSpan sp;
+  const uint64_t two_m = g.xadj[g.n];
+  const int64_t v0 = blk[c], v1 = blk[c + 1];
+  sp.v0 = v0;
+  sp.nv = (int32_t)(v1 - v0);
+  sp.e0 = (uint64_t)c * kCtWork - (uint64_t)v0;
+  uint64_t e1 = c + 1 < nb ? (uint64_t)(c + 1) * kCtWork - (uint64_t)v1 : two_m;
+  if (e1 > two_m) e1 = two_m;
+  sp.ne = e1 > sp.e0 ? (int32_t)(e1 - sp.e0) : 0;
+  sp.chunked[0] = sp.chunked[1] = 0;
+  sp.x[0] = sp.x[1] = 0;
+  sp.table = 0;
+  if (v0 > 0) {
+    sp.x[0] = g.xadj[v0 - 1];
+    sp.chunked[0] = g.xadj[v0] - sp.x[0] > LP_CHUNK_THRESHOLD;
   }
-  if (bad) atomicOr(err, bad);
-  block_max2(mw, md, max_wdeg, max_deg);
+  if (v1 > v0) {
+    sp.x[1] = g.xadj[v1 - 1];
+    const uint64_t d = g.xadj[v1] - sp.x[1];
+    sp.chunked[1] = d > LP_CHUNK_THRESHOLD;
+    if (sp.chunked[1]) sp.table = 4 * ((d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN - 1);
+  }
+  return sp;
+}
+
+// Owner marks: own[j] = 1 + the index (in the stretch) of the vertex whose
+// neighbourhood starts at entry j, 0 elsewhere. own must be zero. f(i, d) for
+// every vertex i with its degree.
+template <typename F>
+__device__ __forceinline__ void ct_mark(const CsrIn& g, const CtSpan& sp, uint16_t* own, F&& f) {
+  for (int32_t i = threadIdx.x; i < sp.nv; i += kCtThreads) {
+    const uint64_t x = g.xadj[sp.v0 + i], d = g.xadj[sp.v0 + i + 1] - x;
+    const uint64_t pos = x - sp.e0;
+    if (d > 0 && pos < (uint64_t)sp.ne) own[pos] = (uint16_t)(i + 1);
+    f(i, x, d);
+  }
+}
+
+// This thread's entries j0 .. j0 + kCtItems - 1 and the one before them,
+// loaded before anything is known about their vertices.
+template <bool WGT>
+struct CtEntries {
+  int32_t v[kCtItems], w[kCtItems];
+  int32_t pv, pw;
+
+  __device__ __forceinline__ CtEntries(const CsrIn& g, const CtSpan& sp) {
+    load(g.adjncy + sp.e0, sp.ne, v, 0);
+    pv = before(g.adjncy + sp.e0, sp, v[kCtItems - 1]);
+    pw = 0;
+    if constexpr (WGT) {
+      load(g.adjwgt + sp.e0, sp.ne, w, 1);
+      pw = before(g.adjwgt + sp.e0, sp, w[kCtItems - 1]);
+    }
+  }
+
+ private:
+  struct __attribute__((packed, aligned(4))) Four {
+    int32_t x[4];
+  };
+  static __device__ __forceinline__ void load(const int32_t* a, int32_t ne, int32_t* x, int32_t fill) {
+    const int32_t j0 = (int32_t)threadIdx.x * kCtItems;
+    static_assert(kCtItems == 8, "two 16-byte loads");
+    if (j0 + kCtItems <= ne) {
+      const Four p = *(const Four*)(a + j0), q = *(const Four*)(a + j0 + 4);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        x[k] = p.x[k];
+        x[4 + k] = q.x[k];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kCtItems; ++k) x[k] = j0 + k < ne ? a[j0 + k] : fill;
+    }
+  }
+  // the entry before this thread's first: the lane before has it
+  static __device__ __forceinline__ int32_t before(const int32_t* a, const CtSpan& sp, int32_t last) {
+    const int32_t j0 = (int32_t)threadIdx.x * kCtItems;
+    int32_t p = dpp_i32<0x138>(last);
+    if (lane_id() == 0 && j0 < sp.ne && sp.e0 + j0 > 0) p = a[j0 - 1];
+    return p;
+  }
+};
+
+// f(k, own, first, start, u, v, pv, w, pw) for each of this thread's entries;
+// own = 1 + index of the vertex (0: the one continued from the stretch
+// before), first: it begins the neighbourhood, start: it begins a chunk, pv /
+// pw the entry before (meaningless at `first`).
+template <bool WGT, typename F>
+__device__ __forceinline__ void ct_entries(const CtEntries<WGT>& en, const CtSpan& sp, const uint16_t* own,
+                                           int32_t* scan_sm, F&& f) {
+  const int32_t j0 = (int32_t)threadIdx.x * kCtItems;
+  int32_t pv = en.pv, pw = en.pw;
+  const uint4 ow = *(const uint4*)&own[j0];  // kCtItems == 8 marks
+  uint16_t o[kCtItems];
+  __builtin_memcpy(o, &ow, 16);
+  int32_t top = 0;
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) top = max(top, (int32_t)o[k]);
+  // exclusive prefix maximum over the threads
+  const int32_t inc = wave_incl_scan_max_i32(top);
+  const int wv = threadIdx.x / kWave;
+  if (lane_id() == kWave - 1) scan_sm[wv] = inc;
+  __syncthreads();
+  int32_t cur = dpp_i32<0x138>(inc);
+  for (int k = 0; k < wv; ++k) cur = max(cur, scan_sm[k]);
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) {
+    if (j0 + k >= sp.ne) continue;
+    if (o[k]) cur = o[k];
+    // the stretch before may end with the vertex whose first entry is this one's first
+    const bool first = o[k] != 0 || (cur == 0 && sp.e0 + j0 + k == sp.x[0]);
+    bool start = first;
+    if (sp.chunked[0] | sp.chunked[1]) {  // uniform
+      const int kind = cur == 0 ? 0 : 1;
+      if (!first && sp.chunked[kind] && (kind == 0 || cur == sp.nv))
+        start = (uint32_t)(sp.e0 + j0 + k - sp.x[kind]) % LP_CHUNK_LEN == 0;
+    }
+    f(k, (uint32_t)cur, first, start, (int32_t)(sp.v0 - 1 + cur), en.v[k], pv, en.w[k], pw);
+    pv = en.v[k];
+    pw = en.w[k];
+  }
+}
+
+// Checks (range, self-loops, weights, order), the largest degree of the
+// stretch's vertices (tdeg[c]) and weighted degree (tw[c]) and, with SIZE,
+// the stretch's code bytes (tsize[c], gap-only format). Weighted degrees of
+// vertices that continue into other stretches are summed in wspan[stretch
+// that starts them] (zeroed).
+template <bool WGT, bool SIZE>
+__global__ __launch_bounds__(kCtThreads) void k_csr_scan(CsrIn g, const int64_t* blk, int64_t nb, CsrAcc* acc,
+                                                         uint32_t* tdeg, unsigned long long* tw,
+                                                         unsigned long long* wspan, uint64_t* tsize) {
+  __shared__ __align__(16) uint16_t own[kCtWork];
+  __shared__ unsigned long long wsum[WGT ? kCtWork + 1 : 1];
+  __shared__ int32_t scan[kCtThreads / kWave];
+  __shared__ uint32_t red32[kCtThreads / kWave], redl[kCtThreads / kWave];
+  __shared__ unsigned long long red[kCtThreads / kWave];
+  if (acc->xerr) return;
+  const int64_t c = blockIdx.x;
+  const CtSpan sp = ct_span(g, blk, nb, c);
+  const CtEntries<WGT> en(g, sp);
+  *(uint4*)&own[threadIdx.x * kCtItems] = make_uint4(0, 0, 0, 0);
+  if constexpr (WGT)
+    for (int32_t i = threadIdx.x; i <= sp.nv; i += kCtThreads) wsum[i] = 0;
+  __syncthreads();
+  uint32_t md = 0, len = 0, bad = 0;
+  ct_mark(g, sp, own, [&](int32_t, uint64_t x, uint64_t d) {
+    md = max(md, (uint32_t)min(d, (uint64_t)0xFFFFFFFFu));
+    if constexpr (SIZE) len += varint_len(x);
+  });
+  __syncthreads();
+  uint32_t run_own = 0;
+  int64_t run = 0;
+  ct_entries<WGT>(en, sp, own, scan, [&](int k, uint32_t o, bool first, bool start, int32_t u, int32_t v, int32_t pv,
+                                        int32_t w, int32_t pw) {
+    if ((uint32_t)v >= (uint32_t)g.n) bad |= kErrRange;
+    if (v == u) bad |= kErrSelf;
+    if (!first && (pv > v || (WGT && pv == v && pw > w))) bad |= kErrOrder;
+    if constexpr (WGT) {
+      if (w < 1) bad |= kErrWeight;
+      if (k == 0) run_own = o;
+      if (o != run_own) {
+        atomicAdd(&wsum[run_own], (unsigned long long)run);
+        run = 0;
+        run_own = o;
+      }
+      run += w;
+    }
+    if constexpr (SIZE) {
+      len += varint_len32(start ? zigzag32(v - u) : (uint32_t)(v - pv));
+      if constexpr (WGT) len += varint_len32(zigzag32(w - (start ? 0 : pw)));
+    }
+  });
+  unsigned long long mw = 0;
+  if constexpr (WGT) {
+    if (run) atomicAdd(&wsum[run_own], (unsigned long long)run);
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i <= sp.nv; i += kCtThreads) {
+      const unsigned long long s = wsum[i];
+      if (i == 0) {
+        if (s) {
+          const int64_t u = sp.v0 - 1;
+          atomicAdd(&wspan[(int64_t)((g.xadj[u] + (uint64_t)u) / kCtWork)], s);
+        }
+      } else if (i == sp.nv && g.xadj[sp.v0 + sp.nv] > sp.e0 + (uint64_t)sp.ne) {
+        atomicAdd(&wspan[c], s);
+      } else {
+        mw = max(mw, s);
+      }
+    }
+    mw = wave_reduce_max(mw);
+    if (lane_id() == 0) red[threadIdx.x / kWave] = mw;
+  }
+  md = wave_reduce_max(md);
+  if (lane_id() == 0) red32[threadIdx.x / kWave] = md;
+  if (bad) atomicOr(&acc->err, bad);
+  len = wave_reduce_add(len);
+  if (lane_id() == 0) redl[threadIdx.x / kWave] = len;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < kCtThreads / kWave; ++k) {
+      md = max(md, red32[k]);
+      len += redl[k];
+      if constexpr (WGT) mw = max(mw, red[k]);
+    }
+    tdeg[c] = md;
+    if constexpr (WGT) tw[c] = mw;
+    if constexpr (SIZE) tsize[c] = (uint64_t)len + sp.table;
+  }
+}
+
+// Maxima over the stretches: degree (0xFFFFFFFF and more count as that) and
+// weighted degree, the latter also over the vertices that span several.
+__global__ __launch_bounds__(256) void k_csr_max(const uint32_t* tdeg, const unsigned long long* tw,
+                                                 const unsigned long long* wspan, int64_t nb, CsrAcc* acc) {
+  unsigned long long mw = 0, md = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nb; i += (int64_t)gridDim.x * blockDim.x) {
+    md = max(md, (unsigned long long)tdeg[i]);
+    if (tw) mw = max(mw, max(tw[i], wspan[i]));
+  }
+  md = wave_reduce_max(md);
+  mw = wave_reduce_max(mw);
+  if (lane_id() == 0 && md) atomicMax(&acc->deg, md);
+  if (lane_id() == 0 && mw) atomicMax(&acc->wdeg, mw);
+}
+
+// A VarInt of len <= 5 bytes (x below 2^35) into zeroed LDS at byte q: its
+// dwords are shared with the codes around it, hence the ORs.
+__device__ __forceinline__ void put5(uint32_t* buf, uint32_t q, uint64_t x, uint32_t len) {
+  const uint32_t l = (uint32_t)x;
+  const uint32_t lo = (l & 0x7Fu) | ((l << 1) & 0x7F00u) | ((l << 2) & 0x7F0000u) | ((l << 3) & 0x7F000000u) |
+                      (uint32_t)(0x80808080ull >> (40u - 8u * len));
+  const uint64_t y = (((uint64_t)(uint32_t)(x >> 28) << 32) | lo) << (8u * (q & 3u));
+  atomicOr(&buf[q >> 2], (uint32_t)y);
+  if ((q & 3u) + len > 4u) atomicOr(&buf[(q >> 2) + 1], (uint32_t)(y >> 32));
+}
+
+// Any VarInt, byte by byte.
+__device__ __forceinline__ void put_any(uint32_t* buf, uint32_t q, uint64_t x) {
+  for (;; ++q) {
+    const uint32_t c = (uint32_t)(x & 0x7F) | (x >= 0x80 ? 0x80u : 0u);
+    atomicOr(&buf[q >> 2], c << (8u * (q & 3u)));
+    if (x < 0x80) return;
+    x >>= 7;
+  }
+}
+
+// Bytes [lo, hi) of the output from LDS (byte p at buf[p - shift], shift a
+// multiple of 16): whole 16-byte words as such, the ends byte by byte (the
+// neighbouring stretches write the rest of those words).
+__device__ __forceinline__ void ct_flush(const uint8_t* buf, uint8_t* out, uint64_t lo, uint64_t hi, uint64_t shift) {
+  for (uint64_t q = (lo & ~15ull) + 16ull * threadIdx.x; q < hi; q += 16ull * kCtThreads) {
+    if (q >= lo && q + 16 <= hi) {
+      *(uint4*)(out + q) = *(const uint4*)(buf + (q - shift));
+    } else {
+      const uint64_t a = max(q, lo), b = min(q + 16, hi);
+      for (uint64_t p = a; p < b; ++p) out[p] = buf[p - shift];
+    }
+  }
+}
+
+// Writes the records of the stretch at tbase[c] and the record offsets of its
+// vertices. Chunks after a neighbourhood's first one note their position in
+// cpos[first entry / LP_CHUNK_LEN] (chunk starts are at least LP_CHUNK_LEN
+// entries apart), from which k_chunk_tables fills the chunk tables of the
+// vertices in split_list. WIDE: a number may take ten bytes (first-edge IDs
+// of 2^35 on), otherwise five.
+template <bool WGT, bool WIDE>
+__global__ __launch_bounds__(kCtThreads) void k_csr_encode(CsrIn g, const int64_t* blk, int64_t nb,
+                                                           const uint64_t* tbase, uint64_t* offs, uint64_t* cpos,
+                                                           int32_t* split_list, uint32_t* nsplit, uint8_t* out) {
+  // each position takes at most one header, or one neighbour code and weight code
+  constexpr uint32_t kBytes = (WGT || WIDE ? 10u : 5u) * kCtWork + 48u;
+  constexpr uint32_t kWords = (kBytes + 15u) / 16u * 4u;
+  __shared__ __align__(16) uint32_t buf[kWords];
+  __shared__ __align__(16) uint16_t own[kCtWork];
+  __shared__ uint16_t hx[kCtWork + 1];  // header bytes of the stretch's vertices before each one
+  __shared__ uint16_t sx[kCtWork + 1];  // code bytes of the stretch's entries before each one
+  __shared__ int32_t scan[kCtThreads / kWave];
+  const int64_t c = blockIdx.x;
+  const CtSpan sp = ct_span(g, blk, nb, c);
+  const CtEntries<WGT> en(g, sp);
+  const int32_t t0 = (int32_t)threadIdx.x * kCtItems;
+  *(uint4*)&own[t0] = make_uint4(0, 0, 0, 0);
+  for (uint32_t q = 4 * threadIdx.x; q < kWords; q += 4 * kCtThreads) *(uint4*)&buf[q] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  ct_mark(g, sp, own, [](int32_t, uint64_t, uint64_t) {});
+  // vertices are few in most stretches: `per` consecutive ones per thread, no more than are needed
+  const int32_t per = (sp.nv + kCtThreads - 1) / kCtThreads;
+  const int32_t i0 = (int32_t)threadIdx.x * per;
+  uint64_t hv[kCtItems];
+  uint32_t hl = 0;
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) {
+    if (k >= per) break;
+    hv[k] = 0;
+    if (i0 + k < sp.nv) {
+      hv[k] = g.xadj[sp.v0 + i0 + k];
+      hl += varint_len(hv[k]);
+    }
+  }
+  __syncthreads();
+  uint32_t code[kCtItems], wcode[kCtItems], ow[kCtItems], sl = 0;
+  uint32_t starts = 0;
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) code[k] = wcode[k] = ow[k] = 0;
+  ct_entries<WGT>(en, sp, own, scan, [&](int k, uint32_t o, bool first, bool start, int32_t u, int32_t v, int32_t pv,
+                                        int32_t w, int32_t pw) {
+    code[k] = start ? zigzag32(v - u) : (uint32_t)(v - pv);
+    sl += varint_len32(code[k]);
+    if constexpr (WGT) {
+      wcode[k] = zigzag32(w - (start ? 0 : pw));
+      sl += varint_len32(wcode[k]);
+    }
+    ow[k] = o;
+    starts |= (uint32_t)(start && !first) << k;
+  });
+  // both prefix sums at once: at most 10 * kCtWork bytes each, 16 bits
+  static_assert(10 * kCtWork < 65536, "two sums share a word");
+  int32_t tot;
+  const uint32_t pk = (hl << 16) | sl;
+  const uint32_t ex = (uint32_t)block_incl_scan_add<kCtThreads, int32_t>((int32_t)pk, scan, &tot) - pk;
+  uint32_t ho = ex >> 16, so = ex & 0xFFFFu;
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) {
+    if (k >= per) break;
+    if (i0 + k < sp.nv) {
+      hx[i0 + k] = (uint16_t)ho;
+      ho += varint_len(hv[k]);
+    }
+  }
+  uint32_t s = so;
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) {
+    if (t0 + k <= sp.ne) sx[t0 + k] = (uint16_t)s;
+    if (t0 + k < sp.ne) s += varint_len32(code[k]) + (WGT ? varint_len32(wcode[k]) : 0u);
+  }
+  if (threadIdx.x == 0) hx[sp.nv] = (uint16_t)((uint32_t)tot >> 16);
+  __syncthreads();
+  const uint64_t base = tbase[c];
+  const uint64_t shift = base & ~15ull;
+  // codes of the split vertex started here follow its table: their bytes sit
+  // in LDS as if the table took table % 16 bytes
+  const uint64_t gap = sp.table, lgap = gap & ~15ull;
+  const uint64_t cut = sp.nv > 0 ? base + hx[sp.nv] + sx[g.xadj[sp.v0 + sp.nv - 1] - sp.e0] : base;
+  const uint32_t b0 = (uint32_t)(base - shift);
+  // headers
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) {
+    if (k >= per) break;
+    if (i0 + k >= sp.nv) continue;
+    const uint32_t q = hx[i0 + k] + sx[hv[k] - sp.e0];
+    offs[sp.v0 + i0 + k] = base + q;
+    if constexpr (WIDE) put_any(buf, b0 + q, hv[k]);
+    else put5(buf, b0 + q, hv[k], varint_len(hv[k]));
+  }
+  // codes
+  uint32_t hb[kCtItems];
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) hb[k] = hx[ow[k]];
+#pragma unroll
+  for (int k = 0; k < kCtItems; ++k) {
+    if (t0 + k >= sp.ne) continue;
+    const uint32_t q = hb[k] + so;
+    uint32_t lq = b0 + q;
+    if (gap && (int32_t)ow[k] == sp.nv) lq += (uint32_t)(gap - lgap);
+    if ((starts >> k) & 1u)
+      cpos[(sp.e0 + t0 + k) / LP_CHUNK_LEN] = base + q + ((int32_t)ow[k] == sp.nv ? gap : 0);
+    const uint32_t l = varint_len32(code[k]);
+    put5(buf, lq, code[k], l);
+    so += l;
+    if constexpr (WGT) {
+      const uint32_t lw = varint_len32(wcode[k]);
+      put5(buf, lq + l, wcode[k], lw);
+      so += lw;
+    }
+  }
+  if (gap && threadIdx.x == 0) split_list[atomicAdd(nsplit, 1u)] = (int32_t)(sp.v0 + sp.nv - 1);
+  __syncthreads();
+  const uint64_t end = base + ((uint32_t)tot >> 16) + ((uint32_t)tot & 0xFFFFu);
+  if (gap) {
+    ct_flush((const uint8_t*)buf, out, base, cut, shift);
+    ct_flush((const uint8_t*)buf, out, cut + gap, end + gap, shift + lgap);
+  } else {
+    ct_flush((const uint8_t*)buf, out, base, end, shift);
+  }
+}
+
+// The chunk tables of the listed split records (wave per record).
+__global__ __launch_bounds__(256) void k_chunk_tables(CsrIn g, const int32_t* list, const uint32_t* cnt,
+                                                      const uint64_t* offs, const uint64_t* cpos, uint8_t* out) {
+  const uint32_t m = *cnt, nw = gridDim.x * blockDim.x / kWave;
+  for (uint32_t i = (blockIdx.x * blockDim.x + threadIdx.x) / kWave; i < m; i += nw) {
+    const int64_t u = list[i];
+    const uint64_t x = g.xadj[u], d = g.xadj[u + 1] - x, o = offs[u];
+    const uint64_t table = o + varint_len(x), nch = (d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN;
+    for (uint64_t j = 1 + (uint64_t)lane_id(); j < nch; j += kWave) {
+      const uint32_t rel = (uint32_t)(cpos[(x + j * LP_CHUNK_LEN) / LP_CHUNK_LEN] - o);
+      uint8_t* t = out + table + 4 * (j - 1);
+      t[0] = (uint8_t)rel;
+      t[1] = (uint8_t)(rel >> 8);
+      t[2] = (uint8_t)(rel >> 16);
+      t[3] = (uint8_t)(rel >> 24);
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void k_vwgt_check(const int32_t* vwgt, int32_t n, uint32_t* err,
@@ -159,90 +554,13 @@ __global__ __launch_bounds__(256) void k_vwgt_check(const int32_t* vwgt, int32_t
   int64_t s = 0;
   uint32_t bad = 0;
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t w = vwgt ? vwgt[u] : 1;
+    const int32_t w = vwgt[u];
     if (w < 1) bad = kErrVwgt;
     s += w;
   }
   s = block_reduce_add<256, int64_t>(s, sm);
   if (threadIdx.x == 0) atomicAdd(total, (unsigned long long)s);
   if (bad) atomicOr(err, bad);
-}
-
-// Record size of each vertex (wave per vertex).
-__global__ __launch_bounds__(256) void k_record_size(CsrIn g, uint64_t* size, CodecBlocks cb) {
-  const int lane = lane_id();
-  for (int64_t c = next_block(cb); c < cb.nb; c = next_block(cb))
-  for (int64_t u = cb.blk[c]; u < cb.blk[c + 1]; ++u) {
-    const uint64_t b = g.xadj[u], e = g.xadj[u + 1];
-    const uint64_t d = e - b;
-    const uint64_t nch = d > LP_CHUNK_THRESHOLD ? (d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN : 1;
-    uint64_t len = 0;
-    for (uint64_t k = b + lane; k < e; k += kWave) {
-      const uint64_t i = k - b;
-      const bool st = (nch > 1) ? (i % LP_CHUNK_LEN == 0) : (i == 0);
-      const int32_t v = g.adjncy[k];
-      const uint64_t code = st ? zigzag((int64_t)v - (int64_t)u) : (uint64_t)((int64_t)v - (int64_t)g.adjncy[k - 1]);
-      len += varint_len(code);
-      if (g.adjwgt) {
-        const int64_t w = g.adjwgt[k];
-        const int64_t pw = st ? 0 : g.adjwgt[k - 1];
-        len += varint_len(zigzag(w - pw));
-      }
-    }
-    len = wave_reduce_add(len);
-    if (lane == 0) size[u] = len + varint_len(b) + (nch > 1 ? 4 * (nch - 1) : 0);
-  }
-}
-
-// Writes every record at offs[u] (wave per vertex).
-__global__ __launch_bounds__(256) void k_encode(CsrIn g, const uint64_t* offs, uint8_t* out, CodecBlocks cb) {
-  const int lane = lane_id();
-  for (int64_t c = next_block(cb); c < cb.nb; c = next_block(cb))
-  for (int64_t u = cb.blk[c]; u < cb.blk[c + 1]; ++u) {
-    const uint64_t b = g.xadj[u], e = g.xadj[u + 1];
-    const uint64_t d = e - b;
-    const uint64_t nch = d > LP_CHUNK_THRESHOLD ? (d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN : 1;
-    uint8_t* rec = out + offs[u];
-    const uint32_t hdr = varint_len(b);
-    if (lane == 0) varint_put(rec, b);
-    const uint64_t table = hdr;
-    uint64_t pos = hdr + (nch > 1 ? 4 * (nch - 1) : 0);
-    for (uint64_t k0 = b; k0 < e; k0 += kWave) {
-      const uint64_t k = k0 + lane;
-      const bool valid = k < e;
-      uint64_t code = 0, wcode = 0;
-      uint32_t len = 0;
-      bool st = false;
-      uint64_t i = k - b;
-      if (valid) {
-        st = (nch > 1) ? (i % LP_CHUNK_LEN == 0) : (i == 0);
-        const int32_t v = g.adjncy[k];
-        code = st ? zigzag((int64_t)v - (int64_t)u) : (uint64_t)((int64_t)v - (int64_t)g.adjncy[k - 1]);
-        len = varint_len(code);
-        if (g.adjwgt) {
-          const int64_t w = g.adjwgt[k];
-          const int64_t pw = st ? 0 : g.adjwgt[k - 1];
-          wcode = zigzag(w - pw);
-          len += varint_len(wcode);
-        }
-      }
-      const uint64_t incl = wave_incl_scan_add((uint64_t)len);
-      const uint64_t my = pos + incl - len;
-      if (valid) {
-        uint32_t o = varint_put(rec + my, code);
-        if (g.adjwgt) varint_put(rec + my + o, wcode);
-        if (st && i > 0) {
-          const uint32_t rel = (uint32_t)my;
-          uint8_t* t = rec + table + 4 * (i / LP_CHUNK_LEN - 1);
-          t[0] = (uint8_t)rel;
-          t[1] = (uint8_t)(rel >> 8);
-          t[2] = (uint8_t)(rel >> 16);
-          t[3] = (uint8_t)(rel >> 24);
-        }
-      }
-      pos += __shfl(incl, kWave - 1, kWave);
-    }
-  }
 }
 
 // ------------------------------------------------- interval encoding ----
@@ -526,6 +844,8 @@ __global__ __launch_bounds__(256) void k_decode_all(GraphView g, const uint64_t*
   }
 }
 
+__global__ void k_set_u64(uint64_t* p, uint64_t v) { *p = v; }
+
 __global__ void k_fill_i32(int32_t* a, int64_t n, int32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) a[i] = v;
 }
@@ -542,7 +862,8 @@ lp_status codec_blocks(const uint64_t* xadj, int64_t n, uint64_t two_m, int nctr
   if (!blk || !ctr) return LP_ENOMEM;
   LP_CHECK_HIP(hipMemsetAsync(ctr, 0, ((size_t)nctr + 1) * sizeof(unsigned long long), s));
   uint32_t* err = (uint32_t*)(ctr + nctr);
-  hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for(n + 1, 256, 65536)), dim3(256), 0, s, xadj, n, nb, blk, err);
+  hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for(n + 1, 256, 65536)), dim3(256), 0, s, xadj, n, kCodecWork, nb, blk,
+                     err);
   LP_CHECK_LAUNCH();
   uint32_t h = 0;
   LP_CHECK_HIP(hipMemcpyAsync(&h, err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -552,40 +873,64 @@ lp_status codec_blocks(const uint64_t* xadj, int64_t n, uint64_t two_m, int nctr
   return LP_OK;
 }
 
-// Input checks of a CSR; also the codec hand-out blocks (counters for
-// validation, record sizes and encoding).
-lp_status check_csr(const CsrIn& in, hipStream_t s, uint64_t* two_m, int64_t* max_wdeg, int64_t* max_deg,
-                    int64_t* total_vwgt, Scratch& sc, CodecBlocks* cb) {
+// Input checks of a CSR, cut into stretches of the merged sequence; with
+// `size`, also the code bytes of every stretch (gap-only format) and their
+// prefix sum. Synchronises the scratch stream.
+struct CsrPlan {
+  uint64_t two_m = 0;
+  int64_t max_wdeg = 0, max_deg = 0, total_vwgt = 0;
+  uint64_t nbytes = 0;   // all records (with `size`)
+  int64_t* blk = nullptr;
+  int64_t nb = 0;
+  uint64_t* tbase = nullptr;  // first byte of every stretch (with `size`)
+  CsrAcc* acc = nullptr;
+};
+
+lp_status check_csr(const CsrIn& in, bool size, Scratch& sc, CsrPlan* P) {
+  hipStream_t s = sc.stream();
   uint64_t x0 = 0, xn = 0;
   LP_CHECK_HIP(hipMemcpyAsync(&x0, in.xadj, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
   LP_CHECK_HIP(hipMemcpyAsync(&xn, in.xadj + in.n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
   LP_CHECK_HIP(hipStreamSynchronize(s));
   if (x0 != 0) return LP_EINVAL;
-  LP_CHECK(codec_blocks(in.xadj, in.n, xn, 3, sc, cb));
-  struct Acc {
-    uint32_t err;
-    uint32_t pad;
-    unsigned long long wdeg, deg, tot;
-  };
-  Acc* acc = sc.alloc<Acc>(1);
-  if (!acc) return LP_ENOMEM;
-  LP_CHECK_HIP(hipMemsetAsync(acc, 0, sizeof(Acc), s));
-  if (in.n > 0) {
-    hipLaunchKernelGGL(k_validate, dim3(grid_for((int64_t)in.n * kWave, 256, kCodecGrid)), dim3(256), 0, s, in,
-                       &acc->err, &acc->wdeg, &acc->deg, *cb);
-    LP_CHECK_LAUNCH();
+  P->two_m = xn;
+  P->nb = (int64_t)((xn + (uint64_t)in.n) / kCtWork) + 1;
+  if (P->nb > 0x7FFFFFFFll) return LP_EUNSUPPORTED;
+  const bool wgt = in.adjwgt != nullptr;
+  P->blk = sc.alloc<int64_t>((size_t)P->nb + 1);
+  CsrAcc* acc = sc.alloc<CsrAcc>(1);
+  uint32_t* tdeg = sc.alloc<uint32_t>(P->nb);
+  unsigned long long* tw = wgt ? sc.alloc<unsigned long long>(P->nb) : nullptr;
+  unsigned long long* wspan = wgt ? sc.alloc<unsigned long long>(P->nb) : nullptr;
+  P->tbase = size ? sc.alloc<uint64_t>(P->nb) : nullptr;
+  P->acc = acc;
+  if (sc.failed) return LP_ENOMEM;
+  LP_CHECK_HIP(hipMemsetAsync(acc, 0, sizeof(CsrAcc), s));
+  if (wgt) LP_CHECK_HIP(hipMemsetAsync(wspan, 0, (size_t)P->nb * sizeof(unsigned long long), s));
+  hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for((int64_t)in.n + 1, 256, 65536)), dim3(256), 0, s, in.xadj,
+                     (int64_t)in.n, (uint64_t)kCtWork, P->nb, P->blk, &acc->xerr);
+  LP_CHECK_LAUNCH();
+  auto kern = wgt ? (size ? k_csr_scan<true, true> : k_csr_scan<true, false>)
+                  : (size ? k_csr_scan<false, true> : k_csr_scan<false, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)P->nb), dim3(kCtThreads), 0, s, in, P->blk, P->nb, acc, tdeg, tw,
+                     wspan, P->tbase);
+  LP_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_csr_max, dim3(grid_for(P->nb, 1024, 64)), dim3(256), 0, s, tdeg, tw, wspan, P->nb, acc);
+  LP_CHECK_LAUNCH();
+  if (in.vwgt && in.n > 0) {
     hipLaunchKernelGGL(k_vwgt_check, dim3(grid_for(in.n, 256, 4096)), dim3(256), 0, s, in.vwgt, in.n, &acc->err,
-                       &acc->tot);
+                       &acc->vtot);
     LP_CHECK_LAUNCH();
   }
-  Acc h;
-  LP_CHECK_HIP(hipMemcpyAsync(&h, acc, sizeof(Acc), hipMemcpyDeviceToHost, s));
+  if (size) LP_CHECK(scan_exclusive_u64(P->tbase, P->tbase, P->nb, &acc->nbytes, sc));
+  CsrAcc h;
+  LP_CHECK_HIP(hipMemcpyAsync(&h, acc, sizeof(CsrAcc), hipMemcpyDeviceToHost, s));
   LP_CHECK_HIP(hipStreamSynchronize(s));
-  if (h.err) return LP_EINVAL;
-  *two_m = xn;
-  *max_wdeg = (int64_t)h.wdeg;
-  *max_deg = (int64_t)h.deg;
-  *total_vwgt = (int64_t)h.tot;
+  if (h.xerr || h.err) return LP_EINVAL;
+  P->max_deg = (int64_t)h.deg;
+  P->max_wdeg = wgt ? (int64_t)h.wdeg : P->max_deg;
+  P->total_vwgt = in.vwgt ? (int64_t)h.vtot : (int64_t)in.n;
+  P->nbytes = h.nbytes;
   return LP_OK;
 }
 
@@ -626,19 +971,18 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
   hipStream_t s = (hipStream_t)stream;
   Scratch sc(s);
   CsrIn in{n, xadj, adjncy, adjwgt, vwgt};
-  uint64_t two_m = 0;
-  int64_t max_wdeg = 0, max_deg = 0, total = 0;
-  CodecBlocks cb{};
-  LP_CHECK(check_csr(in, s, &two_m, &max_wdeg, &max_deg, &total, sc, &cb));
-  if (max_deg > 0x7FFFFFFF) return LP_EUNSUPPORTED;
+  CsrPlan cp;
+  LP_CHECK(check_csr(in, compress && !intervals, sc, &cp));
+  const uint64_t two_m = cp.two_m;
+  if (cp.max_deg > 0x7FFFFFFF) return LP_EUNSUPPORTED;
   lp_graph* g = new lp_graph();
   (void)hipGetDevice(&g->device);
   g->n = n;
   g->two_m = two_m;
   g->weighted = adjwgt != nullptr;
-  g->total_vwgt = total;
-  g->max_wdeg = max_wdeg;
-  g->max_deg = max_deg;
+  g->total_vwgt = cp.total_vwgt;
+  g->max_wdeg = cp.max_wdeg;
+  g->max_deg = cp.max_deg;
   lp_status st = LP_OK;
   do {
     if (vwgt) {
@@ -658,37 +1002,34 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
     }
     g->compressed = 1;
     g->intervals = intervals ? 1 : 0;
-    uint64_t* size = sc.alloc<uint64_t>((size_t)n + 1);
-    uint64_t* total_dev = sc.alloc<uint64_t>(1);
-    if (!size || !total_dev) {
-      st = LP_ENOMEM;
-      break;
-    }
     if (hipMalloc((void**)&g->offs, ((size_t)n + 1) * sizeof(uint64_t)) != hipSuccess) {
       st = LP_ENOMEM;
       break;
     }
-    if (n > 0) {
-      if (intervals)
+    uint64_t nbytes = cp.nbytes;
+    if (intervals) {
+      uint64_t* size = sc.alloc<uint64_t>((size_t)n + 1);
+      uint64_t* total_dev = sc.alloc<uint64_t>(1);
+      if (!size || !total_dev) {
+        st = LP_ENOMEM;
+        break;
+      }
+      if (n > 0) {
         hipLaunchKernelGGL(k_record_size_itv, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, in, size);
-      else
-        hipLaunchKernelGGL(k_record_size, dim3(grid_for((int64_t)n * kWave, 256, kCodecGrid)), dim3(256), 0, s, in,
-                           size, CodecBlocks{cb.blk, cb.nb, cb.ctr + 1});
-      st = last_error();
+        st = last_error();
+        if (st) break;
+      }
+      st = scan_exclusive_u64(size, g->offs, n, total_dev, sc);
       if (st) break;
+      if (hipMemcpyAsync(&nbytes, total_dev, sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+          hipStreamSynchronize(s) != hipSuccess) {
+        st = LP_EDEVICE;
+        break;
+      }
     }
-    st = scan_exclusive_u64(size, g->offs, n, total_dev, sc);
+    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(1), 0, s, g->offs + n, nbytes);
+    st = last_error();
     if (st) break;
-    uint64_t nbytes = 0;
-    if (hipMemcpyAsync(&nbytes, total_dev, sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) {
-      st = LP_EDEVICE;
-      break;
-    }
-    if (hipMemcpyAsync(g->offs + n, total_dev, sizeof(uint64_t), hipMemcpyDeviceToDevice, s) != hipSuccess) {
-      st = LP_EDEVICE;
-      break;
-    }
     g->nbytes = nbytes;
     if (hipMalloc((void**)&g->bytes, nbytes + kBytePad) != hipSuccess) {
       st = LP_ENOMEM;
@@ -698,12 +1039,25 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
       st = LP_EDEVICE;
       break;
     }
-    if (n > 0) {
-      if (intervals)
-        hipLaunchKernelGGL(k_encode_itv, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, in, g->offs, g->bytes);
-      else
-        hipLaunchKernelGGL(k_encode, dim3(grid_for((int64_t)n * kWave, 256, kCodecGrid)), dim3(256), 0, s, in,
-                           g->offs, g->bytes, CodecBlocks{cb.blk, cb.nb, cb.ctr + 2});
+    if (n > 0 && intervals) {
+      hipLaunchKernelGGL(k_encode_itv, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, in, g->offs, g->bytes);
+      st = last_error();
+    } else if (n > 0) {
+      const bool split = cp.max_deg > LP_CHUNK_THRESHOLD;
+      uint64_t* cpos = split ? sc.alloc<uint64_t>(two_m / LP_CHUNK_LEN + 1) : nullptr;
+      int32_t* list = split ? sc.alloc<int32_t>(two_m / LP_CHUNK_THRESHOLD + 1) : nullptr;
+      if (sc.failed) {
+        st = LP_ENOMEM;
+        break;
+      }
+      auto kern = g->weighted ? k_csr_encode<true, true>
+                              : two_m < (1ull << 35) ? k_csr_encode<false, false> : k_csr_encode<false, true>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)cp.nb), dim3(kCtThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, g->offs,
+                         cpos, list, &cp.acc->nsplit, g->bytes);
+      st = last_error();
+      if (st || !split) break;
+      hipLaunchKernelGGL(k_chunk_tables, dim3(grid_for((int64_t)(two_m / LP_CHUNK_THRESHOLD + 1), 4, 1024)), dim3(256),
+                         0, s, in, list, &cp.acc->nsplit, g->offs, cpos, g->bytes);
       st = last_error();
     }
   } while (0);

@@ -124,6 +124,18 @@ __device__ __forceinline__ int32_t wave_incl_scan_add_i32(int32_t v) {
   return v;
 }
 
+// Inclusive wave64 maximum of a non-negative 32-bit value (lanes that receive
+// nothing from a move see 0).
+__device__ __forceinline__ int32_t wave_incl_scan_max_i32(int32_t v) {
+  v = max(v, dpp_i32<0x111>(v));
+  v = max(v, dpp_i32<0x112>(v));
+  v = max(v, dpp_i32<0x114>(v));
+  v = max(v, dpp_i32<0x118>(v));
+  v = max(v, dpp_i32<0x142, 0xa>(v));
+  v = max(v, dpp_i32<0x143, 0xc>(v));
+  return v;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan_add(T x) {
   if constexpr (sizeof(T) == 4) {

@@ -1,0 +1,55 @@
+"""The codec takes a CSR in stretches of 2048 positions of the merged sequence
+of vertices and adjacency entries (vertex u at xadj[u] + u, its entries after
+it). Stars whose centre lies right before, on and after a stretch's end, whose
+neighbourhoods end there, and whose chunked records start, continue and end in
+stretches of their own; all-integer, so the tolerance is zero."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _star(synth_mod, before, iso, d, weighted, tail=0):
+    """`before` leaves, `iso` isolated vertices, the centre (at position
+    2 * before + iso), the other d - before leaves, `tail` isolated vertices."""
+    c = before + iso
+    leaves = list(range(before)) + list(range(c + 1, c + 1 + d - before))
+    w = [1 + (i * 7919) % 100000 for i in range(d)] if weighted else None
+    g = synth_mod.from_edges(c + 1 + d - before, [(c, v) for v in leaves], w)
+    if tail:
+        g.n += tail
+        g.xadj = np.concatenate([g.xadj, np.full(tail, g.xadj[-1], dtype=np.uint64)])
+    return g
+
+
+CASES = [  # before, iso, degree, tail
+    (1023, 0, 1500, 0),     # centre two before the end of a stretch
+    (1023, 1, 1500, 0),     # the stretch's last position, all entries in the next
+    (1024, 0, 1500, 0),     # the next stretch's first position
+    (0, 0, 2047, 0), (0, 0, 2048, 1), (0, 0, 2049, 5000),  # entries that end at, before and after an end
+    (10, 2027, 4096, 2047),
+    (1023, 1, 10001, 0),    # a split record whose entries start with a stretch
+    (1022, 0, 10000, 3), (500, 3, 10001, 4096), (7, 0, 25003, 1),
+]
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("case", CASES)
+def test_records_across_stretches(lp, oracle_mod, synth_mod, case, weighted):
+    before, iso, d, tail = case
+    g = _star(synth_mod, before, iso, d, weighted, tail)
+    G = lp.lp_compress(g.n, g.xadj.view(np.int64), g.adjncy, g.adjwgt)
+    offs, data = lp.lp_graph_export(G)
+    o, b = oracle_mod.compress(g.n, g.xadj, g.adjncy, g.adjwgt)
+    assert np.array_equal(offs.cpu().numpy().view(np.uint64), o)
+    assert np.array_equal(data.cpu().numpy(), b)
+    x, a, w, _ = lp.lp_decompress(G)
+    assert np.array_equal(x.cpu().numpy().view(np.uint64), g.xadj)
+    assert np.array_equal(a.cpu().numpy(), g.adjncy)
+    if weighted:
+        assert np.array_equal(w.cpu().numpy(), g.adjwgt)
+    # the weighted-degree maximum sets the width of the sort keys of acceptance
+    P = lp.lp_graph_from_csr(g.n, g.xadj.view(np.int64), g.adjncy, g.adjwgt)
+    exp, _ = oracle_mod.lp_cluster(g, 40, 3, 5)
+    for h in (G, P):
+        assert np.array_equal(lp.lp_cluster(h, 40, 3, 5).cpu().numpy(), exp)
