@@ -35,7 +35,9 @@
  *  - Handles are immutable after creation; one handle may be used from
  *    several streams at once. Each handle must be freed with lp_graph_free.
  *    Handles made by lp_compress and lp_graph_from_csr use plain device
- *    allocations. Handles made inside a call on a stream (lp_contract's
+ *    allocations; lp_graph_free keeps up to 2 GiB of them per device for
+ *    later handles (lp_trim_memory returns them, lp_memory_info counts them
+ *    as cached). Handles made inside a call on a stream (lp_contract's
  *    coarse graph, lp_batch_create's batch) take their buffers from the
  *    memory cache on that stream ("its stream") and are released in that
  *    stream's order: work on any other stream that uses such a handle must
@@ -499,7 +501,7 @@ lp_status lp_set_allocator(const lp_allocator *a);
 lp_status lp_memory_info(uint64_t *live_bytes, uint64_t *cached_bytes, uint64_t *external_bytes);
 
 /* Frees a handle (NULL is ignored). A handle with plain allocations waits
- * for the device to be idle first; a handle made on a stream returns its
+ * for its device to be idle first; a handle made on a stream returns its
  * buffers to the library's memory cache in that stream's order, without
  * waiting: work already queued on the stream runs first, and a later call
  * reuses the buffers only after it. */

@@ -2529,9 +2529,11 @@ struct TilePlan {
 };
 
 // Device memory of a plan, freed with the plan. For a handle whose buffers
-// are stream-ordered the plan is too: taken from the memory cache on the
-// building call's stream (which is synchronised before the plan is used
-// elsewhere) and released in the order of the handle's stream.
+// are stream-ordered, and for a plan that lives for one call, it is too: taken
+// from the memory cache on the building call's stream (which is synchronised
+// before the plan is used elsewhere) and released in the order of the
+// handle's stream or the call's. Otherwise it is released once the device is
+// idle.
 struct PlanMem {
   std::vector<void*> ptrs;
   bool failed = false;
@@ -2542,7 +2544,7 @@ struct PlanMem {
     void* p = nullptr;
     const size_t bytes = (n ? n : 1) * sizeof(T);
     if (stream_mem) p = cache_alloc(bytes, alloc_stream);
-    else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
+    else p = handle_alloc(bytes);
     if (!p) {
       clear_error();
       failed = true;
@@ -2552,9 +2554,10 @@ struct PlanMem {
     return (T*)p;
   }
   ~PlanMem() {
+    if (!stream_mem && !ptrs.empty()) (void)hipDeviceSynchronize();
     for (void* p : ptrs) {
       if (stream_mem) cache_free(p, free_stream);
-      else (void)hipFree(p);
+      else handle_free(p);
     }
   }
 };
@@ -2628,7 +2631,7 @@ struct Plan {
 };
 
 lp_status build_plan(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t t_block, int32_t hub_part,
-                     hipStream_t s, Plan& P, int32_t sub_S = 1, int32_t sub_r = 0) {
+                     hipStream_t s, Plan& P, bool one_call, int32_t sub_S = 1, int32_t sub_r = 0) {
   const int32_t n = g->n;
   // interval-coded records above LP_ITV_CHUNK_THRESHOLD are chunked: the hub
   // path rates them, whatever the tile bucket's bound
@@ -2642,9 +2645,9 @@ lp_status build_plan(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t 
   P.hub_part = hub_part;
   P.wide = g->max_wdeg > 0x7FFFFFFFll;
   const bool batch = g->nbatch > 0;
-  P.mem.stream_mem = g->stream_mem;
+  P.mem.stream_mem = g->stream_mem || one_call;
   P.mem.alloc_stream = s;
-  P.mem.free_stream = g->mem_stream;
+  P.mem.free_stream = one_call ? s : g->mem_stream;
   Scratch sc(s);
   int32_t* deg = sub_S > 1 ? sc.alloc<int32_t>(n) : P.mem.alloc<int32_t>(n);
   if (sub_S == 1) P.deg = deg;
@@ -2941,15 +2944,14 @@ lp_status get_plan(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t t_
                     hub_part == kDefaultHubPart;
   if (!dflt) {
     tmp.reset(new Plan());
-    LP_CHECK(build_plan(g, t_lane, t_tile, t_block, hub_part, s, *tmp));
-    tmp->mem.free_stream = s;  // used by this call only
+    LP_CHECK(build_plan(g, t_lane, t_tile, t_block, hub_part, s, *tmp, true));
     *out = tmp.get();
     return LP_OK;
   }
   std::lock_guard<std::mutex> lock(g->plan_mu);
   if (!g->plan) {
     std::unique_ptr<Plan> p(new Plan());
-    LP_CHECK(build_plan(g, t_lane, t_tile, t_block, hub_part, s, *p));
+    LP_CHECK(build_plan(g, t_lane, t_tile, t_block, hub_part, s, *p, false));
     g->plan = p.release();
     const_cast<lp_graph*>(g)->plan_free = plan_delete;
   }
@@ -2982,8 +2984,7 @@ lp_status get_plans(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t t
     std::vector<std::unique_ptr<Plan>> built;
     for (int32_t r = 0; r < S; ++r) {
       std::unique_ptr<Plan> p(new Plan());
-      LP_CHECK(build_plan(g, t_lane, t_tile, t_block, hub_part, s, *p, S, r));
-      if (tmp) p->mem.free_stream = s;  // used by this call only
+      LP_CHECK(build_plan(g, t_lane, t_tile, t_block, hub_part, s, *p, tmp != nullptr, S, r));
       built.push_back(std::move(p));
     }
     v = std::move(built);
@@ -3157,10 +3158,12 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
   } ev;
   if (overlap)
     for (int i = 0; i < 4; ++i) LP_CHECK_HIP(hipEventCreateWithFlags(&ev.e[i], hipEventDisableTiming));
+  std::vector<const Plan*> plans;  // one per sub-round
+  std::unique_ptr<Plan> plan_tmp;
   // Joins the side streams back into the call's stream when a call returns
   // between fork and join (an error), so that no kernel still running on a
-  // side stream outlives the scratch memory released on the call's stream.
-  // Declared after the scratch, so it runs before the scratch is released.
+  // side stream outlives the memory released on the call's stream. Declared
+  // after the scratch and the call's own plan, so it runs before they go.
   struct JoinGuard {
     hipStream_t s;
     hipStream_t* side;
@@ -3206,8 +3209,6 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
     if (!Cc) return LP_ENOMEM;
   }
   const lp_graph* gr = use_ro ? ro->g : g;  // the graph the rating kernels read
-  std::vector<const Plan*> plans;  // one per sub-round
-  std::unique_ptr<Plan> plan_tmp;
   LP_CHECK(get_plans(gr, t_lane, t_tile, t_block, hub_part, S, s, plans, plan_tmp));
   uint64_t rsum = 0, psum = 0;
   int32_t tmax = 0, hmax = 0;

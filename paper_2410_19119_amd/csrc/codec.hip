@@ -938,7 +938,8 @@ template <typename T>
 lp_status dev_copy(T** dst, const T* src, size_t count, hipStream_t s, size_t pad = 0) {
   *dst = nullptr;
   size_t bytes = count * sizeof(T) + pad;
-  LP_CHECK_HIP(hipMalloc((void**)dst, bytes ? bytes : 1));
+  *dst = (T*)handle_alloc(bytes ? bytes : 1);
+  if (!*dst) return LP_ENOMEM;
   if (count) LP_CHECK_HIP(hipMemcpyAsync(*dst, src, count * sizeof(T), hipMemcpyDeviceToDevice, s));
   if (pad) LP_CHECK_HIP(hipMemsetAsync((uint8_t*)*dst + count * sizeof(T), 0, pad, s));
   return LP_OK;
@@ -1002,7 +1003,7 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
     }
     g->compressed = 1;
     g->intervals = intervals ? 1 : 0;
-    if (hipMalloc((void**)&g->offs, ((size_t)n + 1) * sizeof(uint64_t)) != hipSuccess) {
+    if (graph_alloc(g, (void**)&g->offs, ((size_t)n + 1) * sizeof(uint64_t)) != hipSuccess) {
       st = LP_ENOMEM;
       break;
     }
@@ -1031,7 +1032,7 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
     st = last_error();
     if (st) break;
     g->nbytes = nbytes;
-    if (hipMalloc((void**)&g->bytes, nbytes + kBytePad) != hipSuccess) {
+    if (graph_alloc(g, (void**)&g->bytes, nbytes + kBytePad) != hipSuccess) {
       st = LP_ENOMEM;
       break;
     }
@@ -1169,23 +1170,23 @@ extern "C" lp_status lp_graph_info(const lp_graph* g, int32_t* n, uint64_t* two_
 extern "C" void lp_graph_free(lp_graph* g) {
   if (!g) return;
   void* bufs[] = {g->offs, g->bytes, g->xadj, g->adjncy, g->adjwgt, g->vwgt, g->gid, g->gbase, g->deg};
+  int cur = g->device;
+  (void)hipGetDevice(&cur);
+  if (cur != g->device) (void)hipSetDevice(g->device);
   if (g->stream_mem) {
     // released in the order of the stream that made the handle, to the
     // memory cache of the handle's device
-    int cur = g->device;
-    (void)hipGetDevice(&cur);
-    if (cur != g->device) (void)hipSetDevice(g->device);
     if (g->plan && g->plan_free) g->plan_free(g->plan);
     if (g->reord && g->reord_free) g->reord_free(g->reord);
     for (void* p : bufs) cache_free(p, g->mem_stream);
-    if (cur != g->device) (void)hipSetDevice(cur);
-    clear_error();
   } else {
     (void)hipDeviceSynchronize();
     if (g->plan && g->plan_free) g->plan_free(g->plan);
     if (g->reord && g->reord_free) g->reord_free(g->reord);
-    for (void* p : bufs) (void)hipFree(p);
+    for (void* p : bufs) handle_free(p);
   }
+  if (cur != g->device) (void)hipSetDevice(cur);
+  clear_error();
   delete g;
 }
 

@@ -73,8 +73,7 @@ namespace lp {
 // Device buffer of a handle (see stream_mem).
 inline hipError_t graph_alloc(const lp_graph* g, void** p, size_t bytes) {
   if (!bytes) bytes = 1;
-  if (!g->stream_mem) return hipMalloc(p, bytes);
-  *p = cache_alloc(bytes, g->mem_stream);
+  *p = g->stream_mem ? cache_alloc(bytes, g->mem_stream) : handle_alloc(bytes);
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 

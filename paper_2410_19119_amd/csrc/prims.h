@@ -27,8 +27,18 @@ inline void clear_error() { (void)hipGetLastError(); }
 // nullptr when the device is out of memory even after the cache was emptied.
 void* cache_alloc(size_t bytes, hipStream_t s);
 void cache_free(void* p, hipStream_t s);
-// Frees every cached block of every device (waits for each device first).
+// Frees every cached block (also of handle_alloc) of every device (waits for each device first).
 void cache_trim_all();
+// Buffers of handles that are not ordered with a stream (lp_compress,
+// lp_graph_from_csr) and of their plans, on the current device. A block is
+// given back once the device is idle and up to kHandlePool bytes of them are
+// kept per device for later handles, blocks of at most half of that each:
+// mapping and unmapping such memory costs more than the work on it
+// (compressing an R-MAT graph of 2.4e8 entries takes 1.5 ms on the device; a
+// pass that mapped and unmapped its 0.6 GB took 2.9 to 16.7 ms).
+constexpr size_t kHandlePool = (size_t)2 << 30;
+void* handle_alloc(size_t bytes);
+void handle_free(void* p);  // the device that p is on has no work left that uses p
 // The caller's allocator for all later cache_alloc calls (nullptr: the cache).
 lp_status set_allocator(const lp_allocator* a);
 // Bytes of the current device handed out and kept by the cache, and bytes

@@ -5,6 +5,7 @@
 #include <map>
 #include <mutex>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 // Device-wide primitives written for wave64 / gfx950: reduce-then-scan prefix
@@ -83,6 +84,33 @@ void trim_locked(DevCache& c, size_t keep) {
   clear_error();
 }
 
+// Buffers of handles (handle_alloc): idle blocks by size, and the device and
+// size of every block handed out.
+struct HandlePool {
+  std::mutex mu;
+  std::multimap<size_t, void*> idle[kCacheDevices];
+  std::unordered_map<void*, std::pair<size_t, int>> live;
+  size_t cached[kCacheDevices] = {};
+};
+
+HandlePool& handle_pool() {
+  static HandlePool* const pool = new HandlePool();  // outlives every handle
+  return *pool;
+}
+
+// Frees idle handle blocks of a device (largest first) until at most `keep`
+// bytes of them are left. Caller holds the pool's lock.
+void handle_trim_locked(HandlePool& hp, int dev, size_t keep) {
+  auto& f = hp.idle[dev];
+  while (hp.cached[dev] > keep && !f.empty()) {
+    auto it = std::prev(f.end());
+    (void)hipFree(it->second);
+    hp.cached[dev] -= it->first;
+    f.erase(it);
+  }
+  clear_error();
+}
+
 // The caller's allocator (lp_set_allocator): when set, every scratch block
 // and every buffer of a handle made inside a call comes from it. Blocks keep
 // the allocator that made them, so switching allocators never mixes them up.
@@ -154,6 +182,12 @@ void* cache_alloc(size_t bytes, hipStream_t s) {
     if (cache_log()) fprintf(stderr, "[lpgpu-cache] out of memory for %zu bytes: emptying %zu cached\n", need, c->cached);
     (void)hipDeviceSynchronize();
     trim_locked(*c, 0);
+    int dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess) {
+      HandlePool& hp = handle_pool();
+      std::lock_guard<std::mutex> hlock(hp.mu);
+      handle_trim_locked(hp, dev, 0);
+    }
     if (hipMalloc(&p, need) != hipSuccess) {
       clear_error();
       return nullptr;
@@ -217,6 +251,55 @@ void cache_free(void* p, hipStream_t s) {
   if (c->cached > c->limit) trim_locked(*c, c->limit);
 }
 
+void* handle_alloc(size_t bytes) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kCacheDevices) {
+    clear_error();
+    return nullptr;
+  }
+  HandlePool& hp = handle_pool();
+  const size_t need = bytes > kHandlePool / 2 ? bytes : size_class(bytes);
+  std::lock_guard<std::mutex> lock(hp.mu);
+  auto& f = hp.idle[dev];
+  void* p = nullptr;
+  size_t size = need;
+  const auto it = f.lower_bound(need);
+  if (it != f.end() && it->first <= need + need / 4) {
+    p = it->second;
+    size = it->first;
+    hp.cached[dev] -= size;
+    f.erase(it);
+  } else if (hipMalloc(&p, need) != hipSuccess) {
+    clear_error();
+    handle_trim_locked(hp, dev, 0);
+    if (hipMalloc(&p, need) != hipSuccess) {
+      clear_error();
+      return nullptr;
+    }
+  }
+  hp.live[p] = {size, dev};
+  return p;
+}
+
+void handle_free(void* p) {
+  if (!p) return;
+  HandlePool& hp = handle_pool();
+  std::lock_guard<std::mutex> lock(hp.mu);
+  const auto lv = hp.live.find(p);
+  if (lv == hp.live.end()) return;
+  const size_t size = lv->second.first;
+  const int dev = lv->second.second;
+  hp.live.erase(lv);
+  if (size > kHandlePool / 2) {
+    (void)hipFree(p);
+    clear_error();
+    return;
+  }
+  handle_trim_locked(hp, dev, kHandlePool - size);
+  hp.idle[dev].insert({size, p});
+  hp.cached[dev] += size;
+}
+
 lp_status set_allocator(const lp_allocator* a) {
   if (a && (!a->alloc || !a->free)) return LP_EINVAL;
   std::lock_guard<std::mutex> lock(g_ext_mu);
@@ -232,6 +315,12 @@ void memory_info(uint64_t* live, uint64_t* cached, uint64_t* external) {
     std::lock_guard<std::mutex> lock(c->mu);
     l = c->live_bytes;
     k = c->cached;
+  }
+  int dev = 0;
+  if (c && hipGetDevice(&dev) == hipSuccess) {
+    HandlePool& hp = handle_pool();
+    std::lock_guard<std::mutex> lock(hp.mu);
+    k += hp.cached[dev];
   }
   {
     std::lock_guard<std::mutex> lock(g_ext_mu);
@@ -258,6 +347,11 @@ void cache_trim_all() {
     }
     DevCache* c = cache_of(nullptr);
     if (!c) continue;
+    {
+      HandlePool& hp = handle_pool();
+      std::lock_guard<std::mutex> lock(hp.mu);
+      handle_trim_locked(hp, d, 0);
+    }
     std::lock_guard<std::mutex> lock(c->mu);
     if (c->free_.empty()) continue;
     (void)hipDeviceSynchronize();
