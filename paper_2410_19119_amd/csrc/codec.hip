@@ -10,14 +10,11 @@ namespace lp {
 
 namespace {
 
-constexpr int kWavesPerBlock = 4;
-
 enum : uint32_t {
   kErrRange = 1,
   kErrSelf = 2,
   kErrWeight = 4,
   kErrOrder = 8,
-  kErrXadj = 16,
   kErrVwgt = 32,
 };
 
@@ -53,21 +50,6 @@ struct CsrIn {
 // stretch c holds the vertices blk[c] .. blk[c + 1] - 1 and the entries from
 // c * T - blk[c] on (the first of them may belong to vertex blk[c] - 1).
 
-// The wave-per-vertex decoder takes its vertices in blocks of kCodecWork
-// positions, in order, from a counter (one per launch); the resident waves
-// then read a window of the adjacency that slides over it. With a static
-// stride, waves that met high-degree vertices fell behind and the reads
-// spread over the whole adjacency (R-MAT scale 26 in its given order went
-// 30x slower than the same graph numbered by degree).
-constexpr uint64_t kCodecWork = 16384;
-constexpr unsigned kCodecGrid = 2048;  // workgroups of 256 threads
-
-struct CodecBlocks {
-  const int64_t* blk;        // nb + 1 entries
-  int64_t nb;
-  unsigned long long* ctr;   // hand-out counter (zero before the launch)
-};
-
 // blk[c] = the smallest u with key(u) >= c * work (c < nb), blk[nb] = n.
 // xadj must be non-decreasing from 0 (a decrease sets *err and leaves blk
 // incomplete).
@@ -85,12 +67,6 @@ __global__ void k_codec_blocks(const uint64_t* xadj, int64_t n, uint64_t work, i
     for (int64_t c = c0; c <= c1; ++c) blk[c] = u;
     if (u == n) blk[nb] = n;
   }
-}
-
-__device__ __forceinline__ int64_t next_block(const CodecBlocks& cb) {
-  uint32_t c = 0;
-  if (lane_id() == 0) c = (uint32_t)atomicAdd(cb.ctr, 1ull);
-  return (int64_t)(uint32_t)__shfl((int)c, 0, kWave);
 }
 
 // ------------------------------------------------ compression of a CSR ----
@@ -806,8 +782,6 @@ __global__ void k_degrees_plain(GraphView g, int32_t* deg) {
     deg[u] = (int32_t)(g.xadj[u + 1] - g.xadj[u]);
 }
 
-// Decompression: xadj from the first-edge headers, then one wave per vertex
-// decodes its chunks with the cooperative decoder.
 __global__ void k_xadj_from_headers(GraphView g, uint64_t* xadj) {
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u <= g.n; u += (int64_t)gridDim.x * blockDim.x) {
     uint64_t p;
@@ -815,62 +789,263 @@ __global__ void k_xadj_from_headers(GraphView g, uint64_t* xadj) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_decode_all(GraphView g, const uint64_t* xadj, int32_t* adjncy,
-                                                    int32_t* adjwgt, uint32_t* err, CodecBlocks cb) {
-  __shared__ DecodeSmem<kWave> smem[kWavesPerBlock];
-  const int w = threadIdx.x / kWave;
-  for (int64_t c = next_block(cb); c < cb.nb; c = next_block(cb))
-  for (int64_t u = cb.blk[c]; u < cb.blk[c + 1]; ++u) {
-    const uint64_t fe = xadj[u];
-    const uint32_t deg = (uint32_t)(xadj[u + 1] - fe);
-    if (deg == 0) continue;
-    const Nbh h = nbh_locate(g, (int32_t)u, deg);
-    for (uint32_t ch = 0; ch < h.nchunks; ++ch) {
-      uint64_t pos = nbh_chunk_pos(g, h, ch);
-      const uint32_t first = ch * LP_CHUNK_LEN;
-      const uint32_t cnt = (h.nchunks > 1) ? min((uint32_t)LP_CHUNK_LEN, deg - first) : deg;
-      int32_t pv = 0, pw = 0;
-      const uint64_t out = fe + first;
-      bool ok = group_decode<kWave>(g.bytes, pos, (int32_t)u, cnt, g.weighted, true, pv, pw, smem[w],
-                                    [&](uint32_t i, int32_t v, int32_t wt) {
-                                      adjncy[out + i] = v;
-                                      if (adjwgt) adjwgt[out + i] = wt;
-                                    });
-      if (!ok) {
-        if (lane_id() == 0) atomicOr(err, 1u);
-        break;
-      }
-    }
+// ------------------------------------------ decompression (gap format) ----
+// One workgroup per stretch of kDecWork positions of the merged sequence
+// (which is also the sequence of the numbers in the code bytes: a header per
+// vertex, a code per entry, two with weights). It decodes the unsplit
+// vertices that start in its stretch, whose records are one run of bytes, and
+// the chunks of split ones that start there, another. A run goes through in
+// windows of 4096 bytes, 16 per thread: every thread reads its bytes once,
+// the numbers that end in them go to LDS in order (prefix count of
+// terminators), then every thread takes an equal share of the numbers, a
+// segmented prefix sum (segments = vertices or chunks) turns them into IDs
+// and weights, and those leave through LDS as whole lines. kDecWork numbers
+// of a power-law graph (2.2 bytes on average) fill one window. Bound by the
+// instructions per byte. A wave per vertex, as before, took a round trip to
+// memory and a scan for every 64 numbers of every vertex: 7.5 ms for a
+// weighted R-MAT graph of 3e6 vertices and 8.6e7 entries, which now takes
+// 0.63 ms (1.0 GB read and written: 1.6 TB/s).
+constexpr int kDecThreads = 256;
+constexpr int kDecBytes = 16 * kDecThreads;  // bytes per window
+constexpr int kDecWork = 1664;
+constexpr int kDecShare = kDecBytes / kDecThreads;  // most numbers per thread and window
+
+struct DecShared {
+  uint32_t qs[kDecWork + 2];               // first number of every segment, and the end
+  __align__(16) int32_t val[kDecBytes + 4];  // the window's numbers, then its IDs (and weights)
+  int32_t scan[kDecThreads / kWave], scan2[kDecThreads / kWave];
+  uint32_t flags, flags2;
+  int32_t carry_v, carry_w;
+};
+
+struct DecRun {
+  uint64_t lo, hi;    // code bytes
+  uint32_t nseg, Q;   // segments (starts in DecShared::qs), numbers
+  int32_t u, ustep;   // vertex of segment i: u + i * ustep
+  uint32_t hdr;       // numbers before the first code of a segment (1: a header)
+  uint64_t out;       // first entry
+};
+
+// How many of the run's first q numbers are neighbour codes and weight codes.
+template <bool WGT>
+__device__ __forceinline__ void dec_counts(const DecShared& sh, const DecRun& r, uint32_t q, uint32_t& nv,
+                                           uint32_t& nw) {
+  nv = nw = 0;
+  if (q == 0) return;
+  const uint32_t i = (uint32_t)tile_find(sh.qs, (int32_t)r.nseg, q - 1);
+  const uint32_t before = sh.qs[i] - i * r.hdr;         // codes of the segments before
+  const uint32_t in = q - sh.qs[i] > r.hdr ? q - sh.qs[i] - r.hdr : 0u;
+  if constexpr (WGT) {
+    nv = before / 2 + (in + 1) / 2;
+    nw = before / 2 + in / 2;
+  } else {
+    nv = before + in;
   }
 }
+
+template <bool WGT>
+__device__ __forceinline__ bool decode_run(const uint8_t* __restrict__ bytes, DecShared& sh, const DecRun& r,
+                                           int32_t* adjncy, int32_t* adjwgt) {
+  const int tid = threadIdx.x;
+  uint32_t qb = 0, nb = 0, wb = 0;  // numbers, neighbours, weights of earlier windows
+  int32_t cv = 0, cw = 0;           // the segment's neighbour and weight so far
+  for (uint64_t base = r.lo & ~15ull; base < r.hi; base += kDecBytes) {
+    const uint64_t p = base + 16ull * (uint64_t)tid;
+    uint4 cur = make_uint4(0, 0, 0, 0);
+    uint32_t prev = 0;
+    if (p < r.hi) {
+      cur = *(const uint4*)(bytes + p);
+      if (p > r.lo) prev = *(const uint32_t*)(bytes + p - 4);  // p >= 16 then
+    }
+    uint32_t w[4] = {cur.x, cur.y, cur.z, cur.w};
+    // bytes before the run read as ends of numbers that are not counted,
+    // bytes behind it as numbers that go on
+    const int32_t b0 = p < r.lo ? (int32_t)min(r.lo - p, (uint64_t)16) : 0;
+    const int32_t b1 = p < r.hi ? (int32_t)min(r.hi - p, (uint64_t)16) : 0;
+    if (p > r.lo && p - r.lo < 4) prev &= ~0u << (8 * (4 - (uint32_t)(p - r.lo)));
+    uint32_t term = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t t = ~w[k] & 0x80808080u;
+      term |= (((t >> 7) | (t >> 14) | (t >> 21) | (t >> 28)) & 15u) << (4 * k);
+    }
+    term &= ((1u << b1) - 1u) & ~((1u << b0) - 1u);
+    int32_t tot;
+    const uint32_t idx0 = (uint32_t)(block_incl_scan_add<kDecThreads, int32_t>(__popc(term), sh.scan, &tot)) -
+                          (uint32_t)__popc(term);
+    // the first number may begin in the bytes before
+    uint32_t acc = 0, shift = 0;
+    {
+      const uint32_t t = ~prev & 0x80808080u;
+      const uint32_t s = t ? (32u - (uint32_t)__clz((int)t)) >> 3 : 0u;  // bytes up to the last end
+      if (b0 == 0) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+          if (k >= s) {
+            acc |= ((prev >> (8 * k)) & 0x7Fu) << shift;
+            shift += 7;
+          }
+      }
+    }
+    uint32_t idx = idx0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      if (k >= b0) {
+        acc |= ((w[k / 4] >> (8 * (k % 4))) & 0x7Fu) << (shift & 31u);
+        shift += 7;
+      }
+      if ((term >> k) & 1u) {
+        sh.val[idx++] = (int32_t)acc;
+        acc = 0;
+        shift = 0;
+      }
+    }
+    if (tid == 0) sh.flags = sh.flags2 = 0;
+    __syncthreads();
+    // this thread's share of the window's numbers
+    const uint32_t end = min((uint32_t)tot, r.Q - qb);
+    const uint32_t share = (end + kDecThreads - 1) / kDecThreads;
+    const uint32_t k0 = tid * share;
+    int32_t x[kDecShare];
+    uint32_t at[kDecShare];  // 2 * position in the window's output + (1 for a weight)
+    uint32_t hv = 0, hw = 0;   // numbers that begin a chain
+    int32_t a = tid == 0 ? cv : 0, aw = tid == 0 ? cw : 0;
+    uint32_t i = k0 < end ? (uint32_t)tile_find(sh.qs, (int32_t)r.nseg, qb + k0) : 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kDecShare; ++k) {
+      at[k] = ~0u;
+      if (k >= share || k0 + k >= end) continue;
+      const uint32_t q = qb + k0 + k;
+      if (q >= sh.qs[i + 1]) ++i;  // every segment has a number
+      const uint32_t in = q - sh.qs[i];
+      if (in < r.hdr) continue;
+      const uint32_t code = (uint32_t)sh.val[k0 + k];
+      const uint32_t c = in - r.hdr, first = sh.qs[i] - i * r.hdr;
+      if (!WGT || (c & 1u) == 0) {
+        if (c == 0) {
+          a = r.u + (int32_t)i * r.ustep + unzigzag32(code);
+          hv |= 1u << k;
+        } else {
+          a += (int32_t)code;
+        }
+        x[k] = a;
+        at[k] = 2 * ((WGT ? (first + c) / 2 : first + c) - nb);
+      } else {
+        if (c == 1) {
+          aw = unzigzag32(code);
+          hw |= 1u << k;
+        } else {
+          aw += unzigzag32(code);
+        }
+        x[k] = aw;
+        at[k] = 2 * ((first + c) / 2 - wb) + 1;
+      }
+    }
+    int32_t ex, exw = 0, unused;
+    tile_seg_scan<kDecThreads>(hv != 0, a, 0, sh.scan, sh.scan2, &sh.flags, ex, unused);
+    if constexpr (WGT) {
+      __syncthreads();
+      tile_seg_scan<kDecThreads>(hw != 0, aw, 0, sh.scan, sh.scan2, &sh.flags2, exw, unused);
+    }
+    if (tid == kDecThreads - 1) {
+      sh.carry_v = hv ? a : ex + a;
+      if constexpr (WGT) sh.carry_w = hw ? aw : exw + aw;
+    }
+    // the seg scan's barriers: every number has been read from val
+    uint32_t nb2, wb2;
+    dec_counts<WGT>(sh, r, qb + end, nb2, wb2);
+    const uint32_t fv = hv ? (uint32_t)__ffs(hv) - 1u : 32u, fw = hw ? (uint32_t)__ffs(hw) - 1u : 32u;
+    constexpr uint32_t kW = kDecBytes / 2 + 2;  // weights of a window start here
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kDecShare; ++k) {
+      if (at[k] == ~0u) continue;
+      if (WGT && (at[k] & 1u)) sh.val[kW + (at[k] >> 1)] = x[k] + (k < fw ? exw : 0);
+      else sh.val[at[k] >> 1] = x[k] + (k < fv ? ex : 0);
+    }
+    __syncthreads();
+    for (uint32_t j = tid; j < nb2 - nb; j += kDecThreads) adjncy[r.out + nb + j] = sh.val[j];
+    if (adjwgt) {
+      if constexpr (WGT) {
+        for (uint32_t j = tid; j < wb2 - wb; j += kDecThreads) adjwgt[r.out + wb + j] = sh.val[kW + j];
+      } else {
+        for (uint32_t j = tid; j < nb2 - nb; j += kDecThreads) adjwgt[r.out + nb + j] = 1;
+      }
+    }
+    cv = sh.carry_v;
+    cw = WGT ? sh.carry_w : 0;
+    nb = nb2;
+    wb = wb2;
+    qb += end;
+    __syncthreads();
+  }
+  return qb == r.Q;
+}
+
+// err[0]: malformed records; err[1]: the offsets decrease (blk is incomplete).
+template <bool WGT>
+__global__ __launch_bounds__(kDecThreads) void k_decode(GraphView g, const uint64_t* xadj, const int64_t* blk,
+                                                        int64_t nb, int32_t* adjncy, int32_t* adjwgt, uint32_t* err) {
+  __shared__ DecShared sh;
+  if (err[1]) return;
+  constexpr uint32_t per = WGT ? 2u : 1u;
+  const int64_t c = blockIdx.x;
+  const int64_t v0 = blk[c], v1 = blk[c + 1];
+  const uint64_t e0 = (uint64_t)c * kDecWork - (uint64_t)v0;
+  const uint64_t e1 = c + 1 < nb ? (uint64_t)(c + 1) * kDecWork - (uint64_t)v1 : g.two_m;
+  bool ok = true;
+  // chunks that start in [e0, e1) of the split vertex u
+  auto chunks = [&](int64_t u) {
+    const uint64_t x = xadj[u], d = xadj[u + 1] - x;
+    const uint64_t nch = (d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN;
+    const uint64_t j0 = e0 > x ? (e0 - x + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN : 0;
+    const uint64_t j1 = e1 > x ? min((e1 - x + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN, nch) : 0;
+    if (j0 >= j1) return;
+    const Nbh h = nbh_locate(g, (int32_t)u, (uint32_t)d);
+    DecRun r;
+    r.lo = nbh_chunk_pos(g, h, (uint32_t)j0);
+    r.hi = j1 < nch ? nbh_chunk_pos(g, h, (uint32_t)j1) : g.offs[u + 1];
+    r.nseg = (uint32_t)(j1 - j0);
+    r.Q = per * (uint32_t)(min(d, j1 * LP_CHUNK_LEN) - j0 * LP_CHUNK_LEN);
+    r.u = (int32_t)u;
+    r.ustep = 0;
+    r.hdr = 0;
+    r.out = x + j0 * LP_CHUNK_LEN;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i <= r.nseg; i += kDecThreads) sh.qs[i] = min(per * i * LP_CHUNK_LEN, r.Q);
+    __syncthreads();
+    ok &= r.hi >= r.lo && r.hi <= g.offs[u + 1] && decode_run<WGT>(g.bytes, sh, r, adjncy, adjwgt);
+  };
+  if (v0 > 0 && xadj[v0] - xadj[v0 - 1] > LP_CHUNK_THRESHOLD) chunks(v0 - 1);
+  if (v1 > v0) {
+    const bool split = xadj[v1] - xadj[v1 - 1] > LP_CHUNK_THRESHOLD;
+    const int64_t ve = v1 - (split ? 1 : 0);
+    const uint64_t x = xadj[v0];
+    if (ve > v0 && xadj[ve] > x) {
+      DecRun r;
+      r.lo = g.offs[v0];
+      r.hi = g.offs[ve];
+      r.nseg = (uint32_t)(ve - v0);
+      r.Q = per * (uint32_t)(xadj[ve] - x) + r.nseg;
+      r.u = (int32_t)v0;
+      r.ustep = 1;
+      r.hdr = 1;
+      r.out = x;
+      __syncthreads();
+      for (uint32_t i = threadIdx.x; i <= r.nseg; i += kDecThreads)
+        sh.qs[i] = per * (uint32_t)(xadj[v0 + i] - x) + i;
+      __syncthreads();
+      ok &= decode_run<WGT>(g.bytes, sh, r, adjncy, adjwgt);
+    }
+    if (split) chunks(v1 - 1);
+  }
+  if (!ok && threadIdx.x == 0) atomicOr(err, 1u);
+}
+static_assert(LP_CHUNK_THRESHOLD >= kDecWork, "only the last vertex a stretch starts can be split");
 
 __global__ void k_set_u64(uint64_t* p, uint64_t v) { *p = v; }
 
 __global__ void k_fill_i32(int32_t* a, int64_t n, int32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) a[i] = v;
-}
-
-// The hand-out blocks of a CSR whose offsets xadj[0..n] (xadj[n] = two_m)
-// are on the device, with nctr zeroed counters (one per launch that uses
-// them: cb.ctr + i). LP_EINVAL if xadj decreases somewhere. Synchronises the
-// scratch stream.
-lp_status codec_blocks(const uint64_t* xadj, int64_t n, uint64_t two_m, int nctr, Scratch& sc, CodecBlocks* cb) {
-  hipStream_t s = sc.stream();
-  const int64_t nb = (int64_t)((two_m + (uint64_t)n) / kCodecWork) + 1;
-  int64_t* blk = sc.alloc<int64_t>((size_t)nb + 1);
-  unsigned long long* ctr = sc.alloc<unsigned long long>((size_t)nctr + 1);  // counters, then an error word
-  if (!blk || !ctr) return LP_ENOMEM;
-  LP_CHECK_HIP(hipMemsetAsync(ctr, 0, ((size_t)nctr + 1) * sizeof(unsigned long long), s));
-  uint32_t* err = (uint32_t*)(ctr + nctr);
-  hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for(n + 1, 256, 65536)), dim3(256), 0, s, xadj, n, kCodecWork, nb, blk,
-                     err);
-  LP_CHECK_LAUNCH();
-  uint32_t h = 0;
-  LP_CHECK_HIP(hipMemcpyAsync(&h, err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  LP_CHECK_HIP(hipStreamSynchronize(s));
-  if (h) return LP_EINVAL;
-  *cb = CodecBlocks{blk, nb, ctr};
-  return LP_OK;
 }
 
 // Input checks of a CSR, cut into stretches of the merged sequence; with
@@ -1131,27 +1306,32 @@ extern "C" lp_status lp_decompress(const lp_graph* g, uint64_t* xadj, int32_t* a
     }
     return LP_OK;
   }
-  uint32_t* err = sc.alloc<uint32_t>(1);
+  uint32_t* err = sc.alloc<uint32_t>(2);
   if (!err) return LP_ENOMEM;
-  LP_CHECK_HIP(hipMemsetAsync(err, 0, sizeof(uint32_t), s));
+  LP_CHECK_HIP(hipMemsetAsync(err, 0, 2 * sizeof(uint32_t), s));
   GraphView v = g->view();
   hipLaunchKernelGGL(k_xadj_from_headers, dim3(grid_for((int64_t)g->n + 1, 256, 65536)), dim3(256), 0, s, v, xadj);
   LP_CHECK_LAUNCH();
-  CodecBlocks cb{};
-  if (g->n && !g->intervals) LP_CHECK(codec_blocks(xadj, g->n, g->two_m, 1, sc, &cb));
-  if (g->n) {
-    if (g->intervals)
-      hipLaunchKernelGGL(k_decode_all_itv, dim3(grid_for(g->n, 256, 65536)), dim3(256), 0, s, v, xadj, adjncy, adjwgt,
-                         err);
-    else
-      hipLaunchKernelGGL(k_decode_all, dim3(grid_for((int64_t)g->n * kWave, 256, kCodecGrid)), dim3(256), 0, s, v,
-                         xadj, adjncy, adjwgt, err, cb);
+  if (g->n && g->intervals) {
+    hipLaunchKernelGGL(k_decode_all_itv, dim3(grid_for(g->n, 256, 65536)), dim3(256), 0, s, v, xadj, adjncy, adjwgt,
+                       err);
+    LP_CHECK_LAUNCH();
+  } else if (g->two_m) {
+    const int64_t nb = (int64_t)((g->two_m + (uint64_t)g->n) / kDecWork) + 1;
+    if (nb > 0x7FFFFFFFll) return LP_EUNSUPPORTED;
+    int64_t* blk = sc.alloc<int64_t>((size_t)nb + 1);
+    if (!blk) return LP_ENOMEM;
+    hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for((int64_t)g->n + 1, 256, 65536)), dim3(256), 0, s, xadj,
+                       (int64_t)g->n, (uint64_t)kDecWork, nb, blk, err + 1);
+    LP_CHECK_LAUNCH();
+    hipLaunchKernelGGL(g->weighted ? k_decode<true> : k_decode<false>, dim3((unsigned)nb), dim3(kDecThreads), 0, s, v,
+                       xadj, blk, nb, adjncy, adjwgt, err);
     LP_CHECK_LAUNCH();
   }
-  uint32_t h = 0;
-  LP_CHECK_HIP(hipMemcpyAsync(&h, err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+  uint32_t h[2] = {0, 0};
+  LP_CHECK_HIP(hipMemcpyAsync(h, err, sizeof(h), hipMemcpyDeviceToHost, s));
   LP_CHECK_HIP(hipStreamSynchronize(s));
-  return h ? LP_EINVAL : LP_OK;
+  return h[0] || h[1] ? LP_EINVAL : LP_OK;
 }
 
 extern "C" lp_status lp_graph_info(const lp_graph* g, int32_t* n, uint64_t* two_m, uint64_t* nbytes,

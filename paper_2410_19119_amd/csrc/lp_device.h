@@ -252,4 +252,63 @@ __device__ __forceinline__ T block_incl_scan_add(T x, T* sm, T* total) {
   return s + off;
 }
 
+// Index i in [0, cnt) with base[i] <= x < base[i + 1].
+__device__ __forceinline__ int32_t tile_find(const uint32_t* base, int32_t cnt, uint32_t x) {
+  int32_t lo = 0, hi = cnt;
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (base[mid] <= x) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// Segmented scan over the workgroup of (head, s, s2): a head restarts the
+// sums. Gives the exclusive prefix of this thread.
+template <int NT>
+__device__ __forceinline__ void tile_seg_scan(bool head, int32_t s, int32_t s2, int32_t* sm, int32_t* sm2,
+                                             uint32_t* smf, int32_t& ex, int32_t& ex2) {
+  const int lane = lane_id();
+  int32_t f = head ? 1 : 0;
+  // inclusive segmented scan of the wave with DPP moves (as in
+  // wave_incl_scan_add_i32): a lane adds what reaches it only while it has
+  // not seen a head, and takes over the head flag
+  auto step = [&](int32_t fu, int32_t su, int32_t su2) {
+    if (!f) {
+      s += su;
+      s2 += su2;
+    }
+    f |= fu;
+  };
+  step(dpp_i32<0x111>(f), dpp_i32<0x111>(s), dpp_i32<0x111>(s2));
+  step(dpp_i32<0x112>(f), dpp_i32<0x112>(s), dpp_i32<0x112>(s2));
+  step(dpp_i32<0x114>(f), dpp_i32<0x114>(s), dpp_i32<0x114>(s2));
+  step(dpp_i32<0x118>(f), dpp_i32<0x118>(s), dpp_i32<0x118>(s2));
+  step(dpp_i32<0x142, 0xa>(f), dpp_i32<0x142, 0xa>(s), dpp_i32<0x142, 0xa>(s2));
+  step(dpp_i32<0x143, 0xc>(f), dpp_i32<0x143, 0xc>(s), dpp_i32<0x143, 0xc>(s2));
+  // exclusive values: one lane up (lane 0 gets zeros)
+  const int32_t ef = dpp_i32<0x138>(f), es = dpp_i32<0x138>(s), es2 = dpp_i32<0x138>(s2);
+  const int w = threadIdx.x / kWave;
+  __syncthreads();
+  if (lane == kWave - 1) {
+    sm[w] = s;
+    sm2[w] = s2;
+    atomicOr(smf, (uint32_t)f << w);
+  }
+  __syncthreads();
+  int32_t cs = 0, cs2 = 0;
+  const uint32_t flags = *smf;
+  for (int k = 0; k < w; ++k) {
+    if ((flags >> k) & 1u) {
+      cs = sm[k];
+      cs2 = sm2[k];
+    } else {
+      cs += sm[k];
+      cs2 += sm2[k];
+    }
+  }
+  ex = ef ? es : cs + es;
+  ex2 = ef ? es2 : cs2 + es2;
+}
+
 }  // namespace lp

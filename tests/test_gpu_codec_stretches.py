@@ -1,6 +1,6 @@
-"""The codec takes a CSR in stretches of 2048 positions of the merged sequence
-of vertices and adjacency entries (vertex u at xadj[u] + u, its entries after
-it). Stars whose centre lies right before, on and after a stretch's end, whose
+"""The codec takes a CSR in stretches of 2048 positions (decompression: 1664) of
+the merged sequence of vertices and adjacency entries (vertex u at xadj[u] + u,
+its entries after it). Stars whose centre lies right before, on and after a stretch's end, whose
 neighbourhoods end there, and whose chunked records start, continue and end in
 stretches of their own; all-integer, so the tolerance is zero."""
 import numpy as np
@@ -28,6 +28,8 @@ CASES = [  # before, iso, degree, tail
     (1024, 0, 1500, 0),     # the next stretch's first position
     (0, 0, 2047, 0), (0, 0, 2048, 1), (0, 0, 2049, 5000),  # entries that end at, before and after an end
     (10, 2027, 4096, 2047),
+    (831, 1, 1500, 0), (831, 2, 1500, 1000), (832, 0, 1663, 1), (0, 0, 1664, 3), (0, 0, 3328, 1664),
+    (831, 1, 10001, 0), (831, 2, 10500, 0), (300, 64, 11664, 1),  # 1000-entry chunks against 1664 positions
     (1023, 1, 10001, 0),    # a split record whose entries start with a stretch
     (1022, 0, 10000, 3), (500, 3, 10001, 4096), (7, 0, 25003, 1),
 ]
@@ -53,3 +55,22 @@ def test_records_across_stretches(lp, oracle_mod, synth_mod, case, weighted):
     exp, _ = oracle_mod.lp_cluster(g, 40, 3, 5)
     for h in (G, P):
         assert np.array_equal(lp.lp_cluster(h, 40, 3, 5).cpu().numpy(), exp)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("n,deg,seed", [(3000, 3, 1), (5000, 40, 2), (700, 300, 3)])
+def test_long_codes_and_windows(lp, synth_mod, n, deg, seed, weighted):
+    # spread-out neighbours (codes of up to five bytes, so a stretch takes
+    # several windows of bytes) with vertices of every degree in between
+    rng = np.random.default_rng(seed)
+    ids = np.sort(rng.choice(1 << 22, n, replace=False).astype(np.int64))
+    u = rng.integers(0, n, n * deg // 2)
+    v = rng.integers(0, n, n * deg // 2)
+    e = np.unique(np.stack([np.minimum(u, v), np.maximum(u, v)], 1)[u != v], axis=0)
+    w = rng.integers(1, 2**30, len(e)) if weighted else None
+    g = synth_mod.from_edges(1 << 22, ids[e], w)
+    G = lp.lp_compress(g.n, g.xadj.view(np.int64), g.adjncy, g.adjwgt)
+    x, a, ww, _ = lp.lp_decompress(G)
+    assert np.array_equal(x.cpu().numpy().view(np.uint64), g.xadj)
+    assert np.array_equal(a.cpu().numpy(), g.adjncy)
+    assert np.array_equal(ww.cpu().numpy(), g.adjwgt if weighted else np.ones(g.two_m, np.int32))
