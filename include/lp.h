@@ -210,7 +210,7 @@ typedef struct {
   int32_t reorder;   /* result-invariant: rate on a degree-ordered copy of the graph, built on the
                         first call and kept with the handle until lp_graph_free (about the size of
                         the graph again; the build synchronises the stream and takes one-time
-                        scratch of about 28 bytes per directed edge). Random label gathers then
+                        scratch of about 29 bytes per directed edge). Random label gathers then
                         find the labels of the vertices most edges point to in fewer cache lines.
                         0: automatic: from the second lp_cluster(_ex) call on a handle made by
                         lp_compress(_ex) or lp_graph_from_csr (not on coarse graphs) with at least

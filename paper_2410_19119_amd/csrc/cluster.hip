@@ -23,6 +23,7 @@
 #include "decode.h"
 #include "gain.h"
 #include "graph.h"
+#include "lookback.h"
 #include "reorder.h"
 
 namespace lp {
@@ -2125,108 +2126,259 @@ __global__ __launch_bounds__(256) void k_bucket_sums(const int32_t* deg, int32_t
 }
 
 // ------------------------------------------------------------ accept -----
+// Three steps, each one launch besides the sort's: the round's proposals in
+// vertex order (positions by look-back), sorted by (target, gain descending),
+// admitted against the start-of-round weights (a segmented sum by look-back)
+// and applied. A round of a small graph is bound by its launches: seven here
+// for a graph of 16384 vertices (three sort passes), where counting, scanning
+// and writing by separate launches took 24 and about as many microseconds
+// more per launch as the work itself.
 constexpr int kCpThreads = 256;
 constexpr int kCpItems = 8;
 constexpr int kCpTile = kCpThreads * kCpItems;
+// Stretches of kCpTile vertices per workgroup of the collection: one keeps
+// more workgroups busy on small graphs, four shorten the look-back of large
+// ones.
+constexpr int kCpSubFew = 1, kCpSubMany = 4;
+constexpr int64_t kCpFew = 1 << 18;
 
-__global__ __launch_bounds__(kCpThreads) void k_prop_count(const int32_t* ptgt, int32_t n, uint32_t* bc,
-                                                           const uint32_t* done) {
-  __shared__ uint32_t sm[kCpThreads / kWave];
-  if (*done) return;
-  const int64_t base = (int64_t)blockIdx.x * kCpTile + (int64_t)threadIdx.x * kCpItems;
-  uint32_t c = 0;
-#pragma unroll
-  for (int i = 0; i < kCpItems; ++i)
-    if (base + i < n && ptgt[base + i] >= 0) ++c;
-  c = block_reduce_add<kCpThreads, uint32_t>(c, sm);
-  if (threadIdx.x == 0) bc[blockIdx.x] = c;
-}
+// Control words of one call.
+struct RoundCtl {
+  uint32_t done;
+  uint32_t count;  // proposals of the (sub-)round
+  int32_t rounds_run;
+  uint32_t bad;    // a refinement block out of range
+  uint32_t ticket;
+  uint32_t pad;
+  unsigned long long round_props;
+  int64_t stats[128];
+};
 
 // Writes the proposals in increasing vertex order: key = target << G |
 // (2^G - 1 - gain), value = vertex. With sub-rounds, or when rating a
 // reordered copy (which writes proposals only), it clears the proposal slots
 // it took; otherwise every rated vertex writes its slot again in the next
-// round.
-__global__ __launch_bounds__(kCpThreads) void k_prop_write(int32_t* ptgt, const int64_t* pgain, int32_t n,
-                                                           const uint32_t* boff, int G, uint64_t* keys,
-                                                           uint32_t* vals, const uint32_t* done, int reset) {
+// round. The last tile knows the number of proposals: it counts towards the
+// round, and after the round's last sub-round a round without any ends the
+// call (every workgroup has looked at ctl->done by then).
+template <int SUB>
+__global__ __launch_bounds__(kCpThreads) void k_prop_collect(int32_t* ptgt, const int64_t* pgain, int32_t n, int G,
+                                                             uint64_t* keys, uint32_t* vals, int reset, LookArgs look,
+                                                             RoundCtl* ctl, int round, int last) {
   __shared__ uint32_t sm[kCpThreads / kWave];
   __shared__ uint64_t skey[kCpTile];
   __shared__ uint32_t sval[kCpTile];
-  if (*done) return;
-  const int64_t base = (int64_t)blockIdx.x * kCpTile + (int64_t)threadIdx.x * kCpItems;
-  int32_t t8[kCpItems];
+  __shared__ uint32_t tsm, bsm;
+  if (ctl->done) return;
+  const uint32_t tile = look_ticket(look, gridDim.x, &tsm);
+  const int64_t base = (int64_t)tile * (SUB * kCpTile) + (int64_t)threadIdx.x * kCpItems;
+  int32_t t8[SUB][kCpItems];
+  uint32_t off[SUB], cnt[SUB];  // this thread's place in each stretch, proposals of the stretch
+  uint32_t tot = 0;
   static_assert(kCpItems == 8, "two 16-byte loads per thread");
-  if (base + kCpItems <= n && ((uintptr_t)ptgt & 15u) == 0) {
-    const int4 a = *(const int4*)(ptgt + base), b = *(const int4*)(ptgt + base + 4);
-    t8[0] = a.x, t8[1] = a.y, t8[2] = a.z, t8[3] = a.w, t8[4] = b.x, t8[5] = b.y, t8[6] = b.z, t8[7] = b.w;
-  } else {
 #pragma unroll
-    for (int i = 0; i < kCpItems; ++i) t8[i] = base + i < n ? ptgt[base + i] : -1;
-  }
-  uint32_t c = 0;
+  for (int q = 0; q < SUB; ++q) {
+    const int64_t b0 = base + q * kCpTile;
+    if (b0 + kCpItems <= n && ((uintptr_t)ptgt & 15u) == 0) {
+      const int4 a = *(const int4*)(ptgt + b0), b = *(const int4*)(ptgt + b0 + 4);
+      t8[q][0] = a.x, t8[q][1] = a.y, t8[q][2] = a.z, t8[q][3] = a.w;
+      t8[q][4] = b.x, t8[q][5] = b.y, t8[q][6] = b.z, t8[q][7] = b.w;
+    } else {
 #pragma unroll
-  for (int i = 0; i < kCpItems; ++i) c += t8[i] >= 0 ? 1u : 0u;
-  uint32_t tot;
-  uint32_t incl = block_incl_scan_add<kCpThreads, uint32_t>(c, sm, &tot);
-  // the block's proposals in vertex order, staged in LDS and written out by
-  // consecutive threads
-  uint32_t o = incl - c;
-  const uint64_t dmax = (G >= 64) ? ~0ull : ((1ull << G) - 1);
-#pragma unroll
-  for (int i = 0; i < kCpItems; ++i) {
-    const int64_t u = base + i;
-    if (t8[i] >= 0) {
-      skey[o] = ((uint64_t)(uint32_t)t8[i] << G) | (dmax - (uint64_t)pgain[u]);
-      sval[o] = (uint32_t)u;
-      ++o;
-      if (reset) ptgt[u] = -1;
+      for (int i = 0; i < kCpItems; ++i) t8[q][i] = b0 + i < n ? ptgt[b0 + i] : -1;
     }
   }
+#pragma unroll
+  for (int q = 0; q < SUB; ++q) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < kCpItems; ++i) c += t8[q][i] >= 0 ? 1u : 0u;
+    off[q] = block_incl_scan_add<kCpThreads, uint32_t>(c, sm, &cnt[q]) - c;
+    tot += cnt[q];
+  }
+  if (threadIdx.x < kWave) {
+    const uint32_t before = look_sum(look, tile, tot);
+    if (threadIdx.x == 0) {
+      bsm = before;
+      if (tile + 1 == gridDim.x) {
+        const uint32_t all = before + tot;
+        ctl->count = all;
+        if (round < 64) ctl->stats[round] += all;
+        ctl->round_props += all;
+        if (last) {
+          if (ctl->round_props == 0) ctl->done = 1;
+          else ctl->rounds_run = round + 1;
+          ctl->round_props = 0;
+        }
+      }
+    }
+  }
+  // each stretch's proposals in vertex order, staged in LDS and written out
+  // by consecutive threads
+  const uint64_t dmax = (G >= 64) ? ~0ull : ((1ull << G) - 1);
+  uint32_t ob = 0;
+#pragma unroll
+  for (int q = 0; q < SUB; ++q) {
+    uint32_t o = off[q];
+#pragma unroll
+    for (int i = 0; i < kCpItems; ++i) {
+      const int64_t u = base + q * kCpTile + i;
+      if (t8[q][i] >= 0) {
+        skey[o] = ((uint64_t)(uint32_t)t8[q][i] << G) | (dmax - (uint64_t)pgain[u]);
+        sval[o] = (uint32_t)u;
+        ++o;
+        if (reset) ptgt[u] = -1;
+      }
+    }
+    __syncthreads();
+    if (q == 0) ob = bsm;
+    for (uint32_t j = threadIdx.x; j < cnt[q]; j += kCpThreads) {
+      keys[ob + j] = skey[j];
+      vals[ob + j] = sval[j];
+    }
+    ob += cnt[q];
+    if (q + 1 < SUB) __syncthreads();
+  }
+}
+
+// Segmented inclusive scan step over the lanes of a wavefront.
+__device__ __forceinline__ void wave_seg_scan_i64(uint32_t& f, int64_t& s) {
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const uint32_t fu = (uint32_t)__shfl_up((int)f, d, kWave);
+    const int64_t su = __shfl_up(s, d, kWave);
+    if (lane_id() >= d) {
+      if (!f) s += su;
+      f |= fu;
+    }
+  }
+}
+
+// Admission: the weights of the sorted proposals summed along each target's
+// segment; a proposal is admitted while the target's weight at the start of
+// the round plus the sum up to it fits under the cap. adm[i] = -1: refused;
+// the last admitted of a target (the admitted ones are a prefix of its
+// segment, since the sum grows along it) gets the target's total, the other
+// admitted ones 0.
+__global__ __launch_bounds__(kCpThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_admit(SortedPairs sp, const uint32_t* count, int G,
+                                                      const int32_t* vwgt, const int64_t* W, int64_t cap,
+                                                      const int32_t* gid, const int64_t* gcap, LookArgs look,
+                                                      int64_t* adm) {
+  constexpr int kW = kCpThreads / kWave;
+  __shared__ uint32_t wf[kW];
+  __shared__ int64_t wsum[kW];
+  __shared__ uint32_t tsm;
+  __shared__ int64_t carry;
+  const int64_t n = *count;
+  const uint32_t tiles = (uint32_t)((n + kCpTile - 1) / kCpTile);
+  if (blockIdx.x >= tiles) return;
+  const uint32_t tile = look_ticket(look, tiles, &tsm);
+  const uint64_t* keys = sp.k[*sp.sel];
+  const uint32_t* vals = sp.v[*sp.sel];
+  const int64_t base = (int64_t)tile * kCpTile + (int64_t)threadIdx.x * kCpItems;
+  int32_t seg[kCpItems], w[kCpItems];
+  int64_t wt[kCpItems];
+#pragma unroll
+  for (int i = 0; i < kCpItems; ++i) seg[i] = base + i < n ? (int32_t)(keys[base + i] >> G) : -1;
+#pragma unroll
+  for (int i = 0; i < kCpItems; ++i) w[i] = base + i >= n ? 0 : vwgt ? vwgt[vals[base + i]] : 1;
+  // the item before this thread's first one, and the one after its last
+  int32_t before = __shfl_up(seg[kCpItems - 1], 1, kWave), seg_next = __shfl_down(seg[0], 1, kWave);
+  int32_t w_next = __shfl_down(w[0], 1, kWave);
+  if (lane_id() == 0) before = base > 0 && base < n ? (int32_t)(keys[base - 1] >> G) : -1;
+  if (lane_id() == kWave - 1) {
+    const int64_t j = base + kCpItems;
+    seg_next = j < n ? (int32_t)(keys[j] >> G) : -1;
+    w_next = j >= n ? 0 : vwgt ? vwgt[vals[j]] : 1;
+  }
+  int64_t room[kCpItems];
+#pragma unroll
+  for (int i = 0; i < kCpItems; ++i) {
+    room[i] = -1;
+    if (seg[i] >= 0) room[i] = (gid ? gcap[gid[seg[i]]] : cap) - W[seg[i]];
+  }
+  uint32_t f = 0;
+  int64_t s = 0;
+  uint32_t heads = 0;
+#pragma unroll
+  for (int i = 0; i < kCpItems; ++i) {
+    const bool head = seg[i] != (i ? seg[i - 1] : before);
+    heads |= (uint32_t)head << i;
+    f |= head ? 1u : 0u;
+    s = head ? w[i] : s + w[i];
+    wt[i] = s;
+  }
+  uint32_t fi = f;
+  int64_t si = s;
+  wave_seg_scan_i64(fi, si);
+  const int wv = threadIdx.x / kWave;
+  if (lane_id() == kWave - 1) {
+    wf[wv] = fi;
+    wsum[wv] = si;
+  }
+  // exclusive over the wavefront
+  uint32_t fe = (uint32_t)__shfl_up((int)fi, 1, kWave);
+  int64_t se = __shfl_up(si, 1, kWave);
+  if (lane_id() == 0) {
+    fe = 0;
+    se = 0;
+  }
   __syncthreads();
-  const uint32_t ob = boff[blockIdx.x];
-  for (uint32_t j = threadIdx.x; j < tot; j += kCpThreads) {
-    keys[ob + j] = skey[j];
-    vals[ob + j] = sval[j];
+  if (threadIdx.x < kWave) {
+    uint32_t tf = 0;
+    int64_t ts = 0;
+    for (int k = 0; k < kW; ++k) {
+      ts = wf[k] ? wsum[k] : ts + wsum[k];
+      tf |= wf[k];
+    }
+    const int64_t c = look_seg_sum(look, tile, tf, ts);
+    if (threadIdx.x == 0) carry = c;
+  }
+  __syncthreads();
+  int64_t pre = carry;
+  for (int k = 0; k < wv; ++k) pre = wf[k] ? wsum[k] : pre + wsum[k];
+  pre = fe ? se : pre + se;
+  const uint32_t first = heads ? (uint32_t)__ffs(heads) - 1u : (uint32_t)kCpItems;
+#pragma unroll
+  for (int i = 0; i < kCpItems; ++i) {
+    if (base + i >= n) continue;
+    const int64_t sum = wt[i] + ((uint32_t)i < first ? pre : 0);
+    const bool ok = sum <= room[i];
+    const int32_t sn = i + 1 < kCpItems ? seg[(i + 1) % kCpItems] : seg_next;
+    const int32_t wn = i + 1 < kCpItems ? w[(i + 1) % kCpItems] : w_next;
+    const bool more = sn == seg[i] && sum + wn <= room[i];
+    adm[base + i] = !ok ? -1 : more ? 0 : sum;
   }
 }
 
-__global__ void k_admit_prep(const uint64_t* keys, const uint32_t* vals, const uint32_t* count, int G,
-                             const int32_t* vwgt, uint32_t* seg, int64_t* wv) {
-  const int64_t n = *count;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    seg[i] = (uint32_t)(keys[i] >> G);
-    wv[i] = vwgt ? vwgt[vals[i]] : 1;
-  }
-}
-
-__global__ void k_admit(const uint32_t* seg, const int64_t* prefix, const uint32_t* count, const int64_t* W,
-                        int64_t cap, const int32_t* gid, const int64_t* gcap, uint8_t* flag) {
-  const int64_t n = *count;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t t = seg[i];
-    const int64_t c = gid ? gcap[gid[t]] : cap;
-    flag[i] = (W[t] + prefix[i] <= c) ? 1 : 0;
-  }
-}
-
-// The admitted proposals of a target are a prefix of its segment (the
-// inclusive weight prefix grows along it), so the target's weight grows by
-// the prefix at the last admitted one: one atomic per target, not per move.
-__global__ __launch_bounds__(256) void k_apply(const uint32_t* seg, const uint32_t* vals, const uint8_t* flag,
-                                               const int64_t* wv, const int64_t* prefix, const uint32_t* count,
-                                               int32_t* C, int64_t* W, int64_t* stats, int round, int4* mv,
-                                               int32_t* Cc, const int32_t* pos) {
+// Moves the admitted proposals: the target's weight grows by one atomic per
+// target, the weights of the clusters left by one per move, or, with few
+// clusters (BINS: refinement into at most kInitBins blocks, where all moves
+// would meet on a few addresses), by LDS sums per workgroup.
+constexpr int kInitBins = 2048;
+template <bool BINS>
+__global__ __launch_bounds__(256) void k_apply(SortedPairs sp, const uint32_t* count, int G, const int64_t* adm,
+                                               const int32_t* vwgt, int32_t* C, int64_t* W, int64_t* stats, int round,
+                                               int4* mv, int32_t* Cc, const int32_t* pos, int32_t nbins) {
   __shared__ int64_t sm[4];
+  __shared__ unsigned long long left[BINS ? kInitBins : 1];
   const int64_t n = *count;
+  const uint64_t* keys = sp.k[*sp.sel];
+  const uint32_t* vals = sp.v[*sp.sel];
+  if constexpr (BINS) {
+    if ((int64_t)blockIdx.x * blockDim.x >= n) return;
+    for (int32_t i = threadIdx.x; i < nbins; i += blockDim.x) left[i] = 0;
+    __syncthreads();
+  }
   int64_t moves = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    if (!flag[i]) {
+    const int64_t a = adm[i];
+    if (a < 0) {
       if (mv) mv[i] = make_int4(-1, 0, 0, 0);
       continue;
     }
     const int32_t u = (int32_t)vals[i];
-    const int32_t t = (int32_t)seg[i];
+    const int32_t t = (int32_t)(keys[i] >> G);
     int32_t old;
     if (Cc) {
       // rating on the degree-ordered copy: only the copy's labels (indexed by
@@ -2240,14 +2392,19 @@ __global__ __launch_bounds__(256) void k_apply(const uint32_t* seg, const uint32
       C[u] = t;
     }
     if (mv) mv[i] = make_int4(u, old, t, 0);
-    if (i + 1 == n || seg[i + 1] != (uint32_t)t || !flag[i + 1])
-      atomicAdd((unsigned long long*)&W[t], (unsigned long long)prefix[i]);
-    atomicAdd((unsigned long long*)&W[old], (unsigned long long)(-wv[i]));
+    if (a) atomicAdd((unsigned long long*)&W[t], (unsigned long long)a);
+    const int64_t wu = vwgt ? vwgt[u] : 1;
+    if constexpr (BINS) atomicAdd(&left[old], (unsigned long long)wu);
+    else atomicAdd((unsigned long long*)&W[old], (unsigned long long)(-wu));
     ++moves;
   }
   moves = block_reduce_add<256, int64_t>(moves, sm);
   if (threadIdx.x == 0 && moves && round < 64)
     atomicAdd((unsigned long long*)&stats[64 + round], (unsigned long long)moves);
+  if constexpr (BINS) {
+    for (int32_t i = threadIdx.x; i < nbins; i += blockDim.x)
+      if (left[i]) atomicAdd((unsigned long long*)&W[i], 0ull - left[i]);
+  }
 }
 
 // The caller's labels after rounds on the degree-ordered copy: vertex i of
@@ -2255,20 +2412,6 @@ __global__ __launch_bounds__(256) void k_apply(const uint32_t* seg, const uint32
 __global__ void k_ro_labels(int32_t n, const int32_t* orig, const int32_t* Cc, int32_t* C) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     C[orig[i]] = Cc[i];
-}
-
-// End of a sub-round: its proposals count towards the round; after the
-// round's last sub-round, a round without any proposal ends the call.
-__global__ void k_round_end(const uint32_t* count, uint32_t* done, int64_t* stats, int round, int32_t* rounds_run,
-                            unsigned long long* round_props, int last) {
-  if (*done) return;
-  const uint32_t c = *count;
-  if (round < 64) stats[round] += c;
-  *round_props += c;
-  if (!last) return;
-  if (*round_props == 0) *done = 1;
-  else *rounds_run = round + 1;
-  *round_props = 0;
 }
 
 // Bytes of the compressed records of the listed vertices.
@@ -2293,7 +2436,6 @@ __global__ void k_init(int32_t n, const int32_t* vwgt, int32_t* C, int64_t* W, i
 // Start of a refinement: the given blocks stay as the labels; W[b] = weight
 // of block b (W zeroed before), summed per workgroup in LDS when there are
 // few blocks. A block outside [0, k) sets *bad and is not counted.
-constexpr int kInitBins = 2048;
 __global__ __launch_bounds__(256) void k_init_blocks(int32_t n, const int32_t* vwgt, const int32_t* C, int32_t k,
                                                      int64_t* W, int32_t* ptgt, uint32_t* bad) {
   __shared__ unsigned long long hist[kInitBins];
@@ -3016,30 +3158,28 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
   uint64_t* kb = sc.alloc<uint64_t>(n);
   uint32_t* va = sc.alloc<uint32_t>(n);
   uint32_t* vb = sc.alloc<uint32_t>(n);
-  uint32_t* seg = sc.alloc<uint32_t>(n);
-  int64_t* wv = sc.alloc<int64_t>(n);
-  int64_t* pref = sc.alloc<int64_t>(n);
-  uint8_t* flag = sc.alloc<uint8_t>(n);
+  int64_t* adm = sc.alloc<int64_t>(n);
   int4* mv = use_gt ? sc.alloc<int4>(n) : nullptr;
   const unsigned ncp = grid_for(n, kCpTile, 0x7FFFFFFF);
-  uint32_t* pcnt = sc.alloc<uint32_t>(ncp);
+  const bool few = n <= kCpFew;
+  const unsigned ncollect = grid_for(n, kCpTile * (few ? kCpSubFew : kCpSubMany), 0x7FFFFFFF);
   // per sub-round: hand-out counters of the small tiles, large tiles and pieces
   const int64_t nhand = (int64_t)std::max(rounds, 1) * S * 24;
   uint32_t* hand = sc.alloc<uint32_t>(nhand);
-  struct Ctl {
-    uint32_t done;
-    uint32_t count;
-    int32_t rounds_run;
-    uint32_t bad;  // a refinement block out of range
-    uint32_t bucket_tot[4];
-    unsigned long long round_props;
-    int64_t stats[128];
-  };
-  Ctl* ctl = sc.alloc<Ctl>(1);
+  // control words, then the look-back words of collection (one per tile) and admission (two)
+  const int64_t nctl = (int64_t)(sizeof(RoundCtl) / 4) + 2 * 3 * (int64_t)ncp;
+  static_assert(sizeof(RoundCtl) % 8 == 0, "the words follow the control block");
+  uint32_t* ctl_mem = sc.alloc<uint32_t>(nctl);
   if (sc.failed) return LP_ENOMEM;
-  LP_CHECK_HIP(hipMemsetAsync(ctl, 0, sizeof(Ctl), s));
-  hipLaunchKernelGGL(k_zero_u32, dim3(grid_for(nhand, 256, 64)), dim3(256), 0, s, hand, (int32_t)nhand);
-  LP_CHECK_LAUNCH();
+  RoundCtl* ctl = (RoundCtl*)ctl_mem;
+  uint64_t* look_c = (uint64_t*)(ctl_mem + sizeof(RoundCtl) / 4);
+  uint64_t* look_a = look_c + ncp;
+  uint32_t look_launch = 0;
+  PairSorter sorter;
+  LP_CHECK(sorter.init(ka, va, kb, vb, n, G + nbits, sc));
+  LP_CHECK(zero_u32(ctl_mem, nctl, s));
+  LP_CHECK(zero_u32(hand, nhand, s));
+  LP_CHECK(zero_u32(sorter.zero_base(), sorter.zero_words(), s));
   if (batch) {
     LP_CHECK_HIP(hipMemcpyAsync(gcap, caps, g->nbatch * sizeof(int64_t), hipMemcpyHostToDevice, s));
     LP_CHECK_HIP(hipMemcpyAsync(gseed, seeds, g->nbatch * sizeof(uint64_t), hipMemcpyHostToDevice, s));
@@ -3315,28 +3455,21 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
       }
       // acceptance: compact in vertex order, sort by (target, gain desc)
       LP_CHECK(begin(LP_PHASE_ACCEPT));
-      hipLaunchKernelGGL(k_prop_count, dim3(ncp), dim3(kCpThreads), 0, s, ptgt, n, pcnt, &ctl->done);
+      hipLaunchKernelGGL(few ? k_prop_collect<kCpSubFew> : k_prop_collect<kCpSubMany>, dim3(ncollect),
+                         dim3(kCpThreads), 0, s, ptgt, pgain, n, G, ka, va,
+                         (S > 1 || use_ro) ? 1 : 0, LookArgs{look_c, &ctl->ticket, ++look_launch}, ctl, r,
+                         sr == S - 1 ? 1 : 0);
       LP_CHECK_LAUNCH();
-      LP_CHECK(scan_exclusive_u32(pcnt, pcnt, ncp, &ctl->count, sc));
-      hipLaunchKernelGGL(k_prop_write, dim3(ncp), dim3(kCpThreads), 0, s, ptgt, pgain, n, pcnt, G, ka, va, &ctl->done,
-                         (S > 1 || use_ro) ? 1 : 0);
+      LP_CHECK(sorter.sort(&ctl->count));
+      hipLaunchKernelGGL(k_admit, dim3(ncp), dim3(kCpThreads), 0, s, sorter.out(), &ctl->count, G, g->vwgt, W, cap,
+                         x.gid, gcap, LookArgs{look_a, &ctl->ticket, look_launch}, adm);
       LP_CHECK_LAUNCH();
-      uint64_t* ks;
-      uint32_t* vs;
-      LP_CHECK(radix_sort_pairs(ka, va, kb, vb, &ctl->count, n, G + nbits, &ks, &vs, sc));
-      const unsigned ga = grid_for(n, 256, 8192);
-      hipLaunchKernelGGL(k_admit_prep, dim3(ga), dim3(256), 0, s, ks, vs, &ctl->count, G, g->vwgt, seg, wv);
-      LP_CHECK_LAUNCH();
-      LP_CHECK(seg_scan_incl_i64(seg, wv, pref, &ctl->count, n, sc));
-      hipLaunchKernelGGL(k_admit, dim3(ga), dim3(256), 0, s, seg, pref, &ctl->count, W, cap, x.gid, gcap, flag);
-      LP_CHECK_LAUNCH();
-      hipLaunchKernelGGL(k_apply, dim3(ga), dim3(256), 0, s, seg, vs, flag, wv, pref, &ctl->count, labels, W,
-                         ctl->stats, r, mv, Cc, use_ro ? ro->pos : nullptr);
+      const bool bins = init_k > 0 && init_k <= kInitBins;
+      hipLaunchKernelGGL(bins ? k_apply<true> : k_apply<false>, dim3(grid_for(n, 256, bins ? 1024 : 8192)), dim3(256), 0,
+                         s, sorter.out(), &ctl->count, G, adm, g->vwgt, labels, W, ctl->stats, r, mv, Cc,
+                         use_ro ? ro->pos : nullptr, init_k);
       LP_CHECK_LAUNCH();
       if (use_gt) LP_CHECK(gt_update(gt.t, mv, &ctl->count, n, labels, s));
-      hipLaunchKernelGGL(k_round_end, dim3(1), dim3(1), 0, s, &ctl->count, &ctl->done, ctl->stats, r, &ctl->rounds_run,
-                         &ctl->round_props, sr == S - 1 ? 1 : 0);
-      LP_CHECK_LAUNCH();
       LP_CHECK(end());
     }
     if (timing) LP_CHECK_HIP(hipEventRecord(marks[round_mark].b, s));
@@ -3348,8 +3481,8 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
   if (batch) LP_CHECK(batch_localize(g, labels, out_labels, labels_each, s));
 
   if (stats_out) {
-    Ctl h;
-    LP_CHECK_HIP(hipMemcpyAsync(&h, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    RoundCtl h;
+    LP_CHECK_HIP(hipMemcpyAsync(&h, ctl, sizeof(RoundCtl), hipMemcpyDeviceToHost, s));
     LP_CHECK_HIP(hipStreamSynchronize(s));
     stats_out->rounds_run = h.rounds_run;
     for (const Plan* p : plans) {

@@ -81,19 +81,42 @@ lp_status scan_exclusive_u64(const uint64_t* in, uint64_t* out, int64_t n, uint6
 lp_status scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total_dev,
                              Scratch& sc);
 
-// Segmented inclusive prefix sum: out[i] = sum of val[j] for j in the run of
-// equal seg[] values that ends at i (runs are maximal stretches of equal
-// consecutive seg values). count is read from *count_dev (<= max_n).
-lp_status seg_scan_incl_i64(const uint32_t* seg, const int64_t* val, int64_t* out,
-                            const uint32_t* count_dev, int64_t max_n, Scratch& sc);
+// Stable LSD radix sort of (key, val) pairs, at most max_n of them (their
+// number is *count_dev), on key bits [0, bits). The pairs start in buffers 0;
+// which of the two buffer sets holds the result is known on the device only
+// (*sel), since passes whose digit is the same in all keys are left out.
+struct SortedPairs {
+  uint64_t* k[2] = {nullptr, nullptr};
+  uint32_t* v[2] = {nullptr, nullptr};
+  const uint32_t* sel = nullptr;
+};
+struct SortPlan;
+class PairSorter {
+ public:
+  // Device memory of one sorter from `sc`; `zero` words of it, starting at
+  // zero_base(), must be cleared before the first sort (zeroed by the caller
+  // together with its own).
+  lp_status init(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, int64_t max_n, int bits,
+                 Scratch& sc);
+  uint32_t* zero_base() const { return zero_; }
+  int64_t zero_words() const { return zero_words_; }
+  // One sort of the pairs in buffers 0 on the scratch stream of init.
+  lp_status sort(const uint32_t* count_dev);
+  const SortedPairs& out() const { return out_; }
 
-// Stable LSD radix sort of (key, val) pairs on key bits [0, bits). The
-// number of valid pairs is *count_dev (<= max_n). Sorts in place using the
-// two buffer pairs; returns the buffers that hold the result in *keys_out,
-// *vals_out.
-lp_status radix_sort_pairs(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b,
-                           const uint32_t* count_dev, int64_t max_n, int bits, uint64_t** keys_out,
-                           uint32_t** vals_out, Scratch& sc);
+ private:
+  SortedPairs out_;
+  SortPlan* plan_ = nullptr;
+  uint64_t* words_ = nullptr;
+  uint32_t* zero_ = nullptr;
+  int64_t zero_words_ = 0, max_n_ = 0;
+  int passes_ = 0;
+  uint32_t launch_ = 0;
+  hipStream_t stream_ = nullptr;
+};
+
+// Clears n 32-bit words (a kernel, so that it can be captured).
+lp_status zero_u32(uint32_t* p, int64_t n, hipStream_t s);
 
 #define last_error() ::lp::hip_fail(hipGetLastError(), "kernel launch", __FILE__, __LINE__)
 

@@ -9,8 +9,9 @@
 #include <vector>
 
 // Device-wide primitives written for wave64 / gfx950: reduce-then-scan prefix
-// sums (plain and segmented) and a stable LSD radix sort of (key, value)
-// pairs with 8-bit digits. The LP acceptance step and contraction use them.
+// sums and a stable LSD radix sort of (key, value) pairs with 8-bit digits.
+// The LP acceptance step and contraction use them.
+#include "lookback.h"
 #include "lp_device.h"
 #include "prims.h"
 
@@ -422,19 +423,6 @@ struct SumOp {
   __device__ static T op(T a, T b) { return a + b; }
 };
 
-struct SegElem {
-  int64_t v;
-  uint32_t f;  // 1 = a run starts inside this element's range
-  uint32_t pad;
-};
-
-struct SegOp {
-  __device__ static SegElem id() { return SegElem{0, 0, 0}; }
-  __device__ static SegElem op(SegElem a, SegElem b) {
-    return SegElem{b.f ? b.v : a.v + b.v, a.f | b.f, 0};
-  }
-};
-
 // ---- plain sums --------------------------------------------------------
 template <typename T>
 struct LoadArr {
@@ -505,206 +493,234 @@ lp_status scan_exclusive_t(const T* in, T* out, int64_t n, T* total_dev, Scratch
   return LP_OK;
 }
 
-// ---- segmented sums ----------------------------------------------------
-struct LoadSeg {
-  const uint32_t* seg;
-  const int64_t* val;
-  __device__ SegElem operator()(int64_t i) const {
-    uint32_t f = (i == 0) || (seg[i] != seg[i - 1]);
-    return SegElem{val[i], f, 0};
-  }
+// ---- radix sort ----------------------------------------------------------
+// One histogram launch counts the digits of all passes, then every pass is one
+// launch: a workgroup ranks its tile's pairs by digit (per wavefront, in
+// order), learns each digit's position from the tiles before it by look-back
+// (lookback.h), gathers the pairs by digit in LDS and writes them out in runs.
+// Each pair is read and written once per pass. A pass in which all keys share
+// the digit (the high gain bits of proposals, mostly) is left out.
+constexpr int kRsThreads = 256;
+// Pairs per thread: tiles of 2048 pairs keep more workgroups busy on few
+// pairs, tiles of 4096 halve the look-back of many.
+constexpr int kRsItemsFew = 8, kRsItemsMany = 16;
+constexpr int64_t kRsFew = 1 << 20;  // most pairs sorted in small tiles
+constexpr int kRsBack = 4;           // predecessors read at a time in a look-back
+constexpr int kRsBins = 256;
+constexpr int kRsPasses = 8;
+constexpr int kRsHistGrid = 1024;  // most workgroups of the histogram launch
+constexpr int kRsHistUnroll = 4;   // keys in flight per thread
+constexpr int kRsHistRun = kRsThreads * kRsHistUnroll;
+
+}  // namespace
+
+struct SortPlan {
+  uint32_t hist[kRsPasses][kRsBins];  // zero between sorts
+  uint32_t base[kRsPasses][kRsBins];  // first position of every digit
+  uint32_t src[kRsPasses + 1];        // buffer set a pass reads (and the result's)
+  uint32_t skip[kRsPasses];
+  uint32_t finished, pad;             // workgroups of the histogram launch (zero between sorts)
+  uint32_t ticket;
 };
 
-struct LoadAggs {
-  const SegElem* a;
-  __device__ SegElem operator()(int64_t i) const { return a[i]; }
-};
+namespace {
 
-// Inclusive segmented scan of one tile, carry-in = exclusive prefix of the
-// block aggregates (carry[b]).
-template <typename Load>
-__global__ __launch_bounds__(kScanThreads) void k_seg_down(Load load, int64_t n, const SegElem* carry,
-                                                           SegElem* out_elems, int64_t* out_vals) {
-  __shared__ SegElem sm[kScanThreads / kWave];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  SegElem x[kScanItems];
-  SegElem acc = SegOp::id();
+// Digit counts of all passes; the last workgroup to finish turns them into
+// positions and decides which passes run.
+__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint64_t* __restrict__ keys, const uint32_t* count_dev,
+                                                        int passes, SortPlan* plan) {
+  __shared__ uint32_t h[kRsPasses][kRsBins];
+  __shared__ int32_t scan[kRsThreads / kWave];
+  __shared__ uint32_t last;
+  const int t = threadIdx.x;
+  for (int p = 0; p < passes; ++p) h[p][t] = 0;
+  __syncthreads();
+  const int64_t n = *count_dev;
+  for (int64_t j0 = (int64_t)blockIdx.x * kRsHistRun; j0 < n; j0 += (int64_t)gridDim.x * kRsHistRun) {
+    uint64_t k[kRsHistUnroll];
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    x[i] = (base + i < n) ? load(base + i) : SegOp::id();
-    acc = SegOp::op(acc, x[i]);
-  }
-  SegElem tot;
-  SegElem incl = block_scan_incl<SegElem, SegOp>(acc, sm, &tot);
-  // exclusive prefix of this thread = everything before it in the block,
-  // preceded by the block's carry-in
-  SegElem pre = shfl_up_any(incl, 1);
-  {
-    // lane 0 of each wave takes the previous wave's total
-    __shared__ SegElem wl[kScanThreads / kWave];
-    const int w = threadIdx.x / kWave;
-    if (lane_id() == kWave - 1) wl[w] = incl;
-    __syncthreads();
-    if (lane_id() == 0) pre = (w == 0) ? SegOp::id() : wl[w - 1];
-  }
-  SegElem run = SegOp::op(carry ? carry[blockIdx.x] : SegOp::id(), pre);
+    for (int i = 0; i < kRsHistUnroll; ++i) {
+      const int64_t j = j0 + i * kRsThreads + t;
+      k[i] = j < n ? keys[j] : 0;
+    }
+    for (int p = 0; p < passes; ++p) {
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    run = SegOp::op(run, x[i]);
-    if (base + i < n) {
-      if (out_vals) out_vals[base + i] = run.v;
-      if (out_elems) out_elems[base + i] = run;
+      for (int i = 0; i < kRsHistUnroll; ++i) {
+        if (j0 + i * kRsThreads + t >= n) continue;
+        const uint32_t dg = (uint32_t)(k[i] >> (8 * p)) & (kRsBins - 1);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)dg);
+        const uint64_t act = __ballot(1), same = __ballot(dg == d0);
+        if (same == act) {  // one digit in the whole wavefront: one addition
+          if (lane_id() == __ffsll((unsigned long long)act) - 1) atomicAdd(&h[p][d0], (uint32_t)__popcll(act));
+        } else {
+          atomicAdd(&h[p][dg], 1u);
+        }
+      }
     }
   }
-}
-
-// Exclusive segmented scan of an array of aggregates, in place (recursive).
-lp_status seg_scan_aggs_excl(SegElem* a, int64_t n, Scratch& sc) {
-  hipStream_t s = sc.stream();
-  // inclusive into tmp, then shift by one
-  SegElem* incl = sc.alloc<SegElem>(n);
-  if (!incl) return LP_ENOMEM;
-  int64_t nb = (n + kScanTile - 1) / kScanTile;
-  SegElem* carry = nullptr;
-  if (nb > 1) {
-    carry = sc.alloc<SegElem>(nb);
-    if (!carry) return LP_ENOMEM;
-    hipLaunchKernelGGL((k_scan_reduce<SegElem, SegOp, LoadAggs>), dim3((unsigned)nb), dim3(kScanThreads), 0, s,
-                       LoadAggs{a}, n, carry);
-    LP_CHECK_LAUNCH();
-    LP_CHECK(seg_scan_aggs_excl(carry, nb, sc));
-  }
-  hipLaunchKernelGGL(k_seg_down<LoadAggs>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, LoadAggs{a}, n,
-                     (const SegElem*)carry, incl, (int64_t*)nullptr);
-  LP_CHECK_LAUNCH();
-  // a[i] = incl[i-1], a[0] = identity
-  LP_CHECK_HIP(hipMemcpyAsync(a + 1, incl, (size_t)(n - 1) * sizeof(SegElem), hipMemcpyDeviceToDevice, s));
-  LP_CHECK_HIP(hipMemsetAsync(a, 0, sizeof(SegElem), s));
-  return LP_OK;
-}
-
-__global__ void k_read_count(const uint32_t* count_dev, int64_t* n_out) { *n_out = *count_dev; }
-
-template <typename Load>
-__global__ __launch_bounds__(kScanThreads) void k_seg_reduce_dyn(Load load, const uint32_t* count_dev,
-                                                                 SegElem* aggs) {
-  __shared__ SegElem sm[kScanThreads / kWave];
-  const int64_t n = *count_dev;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  SegElem acc = SegOp::id();
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n) acc = SegOp::op(acc, load(base + i));
-  SegElem tot;
-  (void)block_scan_incl<SegElem, SegOp>(acc, sm, &tot);
-  if (threadIdx.x == 0) aggs[blockIdx.x] = tot;
-}
-
-template <typename Load>
-__global__ __launch_bounds__(kScanThreads) void k_seg_down_dyn(Load load, const uint32_t* count_dev,
-                                                               const SegElem* carry, int64_t* out_vals) {
-  const int64_t n = *count_dev;
-  if ((int64_t)blockIdx.x * kScanTile >= n) return;
-  // identical to k_seg_down with a device-side count
-  __shared__ SegElem sm[kScanThreads / kWave];
-  __shared__ SegElem wl[kScanThreads / kWave];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  SegElem x[kScanItems];
-  SegElem acc = SegOp::id();
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    x[i] = (base + i < n) ? load(base + i) : SegOp::id();
-    acc = SegOp::op(acc, x[i]);
-  }
-  SegElem tot;
-  SegElem incl = block_scan_incl<SegElem, SegOp>(acc, sm, &tot);
-  SegElem pre = shfl_up_any(incl, 1);
-  const int w = threadIdx.x / kWave;
-  if (lane_id() == kWave - 1) wl[w] = incl;
   __syncthreads();
-  if (lane_id() == 0) pre = (w == 0) ? SegOp::id() : wl[w - 1];
-  SegElem run = SegOp::op(carry ? carry[blockIdx.x] : SegOp::id(), pre);
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    run = SegOp::op(run, x[i]);
-    if (base + i < n) out_vals[base + i] = run.v;
+  for (int p = 0; p < passes; ++p)
+    if (h[p][t]) atomicAdd(&plan->hist[p][t], h[p][t]);
+  __threadfence();
+  __syncthreads();
+  if (t == 0) last = atomicAdd(&plan->finished, 1u) + 1 == gridDim.x;
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  uint32_t src = 0;
+  for (int p = 0; p < passes; ++p) {
+    const uint32_t c = __hip_atomic_load(&plan->hist[p][t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    plan->hist[p][t] = 0;
+    int32_t tot;
+    const uint32_t inc = (uint32_t)block_incl_scan_add<kRsThreads, int32_t>((int32_t)c, scan, &tot);
+    plan->base[p][t] = inc - c;
+    const int skip = __syncthreads_or((int64_t)c == n);
+    if (t == 0) {
+      plan->skip[p] = skip ? 1u : 0u;
+      plan->src[p] = src;
+    }
+    if (!skip) src ^= 1u;
+  }
+  if (t == 0) {
+    plan->src[passes] = src;
+    plan->finished = 0;
   }
 }
 
-// ---- radix sort ----------------------------------------------------------
-constexpr int kRsThreads = 256;
-constexpr int kRsItems = 16;
-constexpr int kRsTile = kRsThreads * kRsItems;
-constexpr int kRsBins = 256;
-
-__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint64_t* __restrict__ keys,
-                                                        const uint32_t* count_dev, int shift,
-                                                        uint32_t* __restrict__ hist, uint32_t nblocks) {
-  __shared__ uint32_t h[kRsBins];
-  const int t = threadIdx.x;
-  h[t] = 0;
-  __syncthreads();
-  const int64_t n = *count_dev;
-  const int64_t base = (int64_t)blockIdx.x * kRsTile;
-#pragma unroll 4
-  for (int i = 0; i < kRsItems; ++i) {
-    int64_t j = base + (int64_t)i * kRsThreads + t;
-    if (j < n) atomicAdd(&h[(uint32_t)(keys[j] >> shift) & (kRsBins - 1)], 1u);
-  }
-  __syncthreads();
-  hist[(size_t)t * nblocks + blockIdx.x] = h[t];
-}
-
-__global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint64_t* __restrict__ kin,
-                                                           const uint32_t* __restrict__ vin,
-                                                           uint64_t* __restrict__ kout,
-                                                           uint32_t* __restrict__ vout,
-                                                           const uint32_t* count_dev, int shift,
-                                                           const uint32_t* __restrict__ offs,
-                                                           uint32_t nblocks) {
+template <int kRsItems>
+__global__ __launch_bounds__(kRsThreads) void k_rs_pass(SortedPairs b, const uint32_t* count_dev, const SortPlan* plan,
+                                                        int pass, LookArgs look) {
   constexpr int kW = kRsThreads / kWave;
-  __shared__ uint32_t running[kRsBins];
+  constexpr int kRsTile = kRsThreads * kRsItems;
+  __shared__ __align__(16) uint64_t stage[kRsTile];
   __shared__ uint32_t wcnt[kW][kRsBins];
-  const int t = threadIdx.x;
-  const int w = t / kWave;
+  __shared__ uint32_t dstart[kRsBins];  // first place of every digit in the tile
+  __shared__ uint32_t gbase[kRsBins];   // its first position in the output, minus dstart
+  __shared__ int32_t scan[kW];
+  __shared__ uint32_t tsm;
   const int64_t n = *count_dev;
-  const int64_t base = (int64_t)blockIdx.x * kRsTile;
-  if (base >= n) return;
-  running[t] = offs[(size_t)t * nblocks + blockIdx.x];
-  const uint64_t lt = lanemask_lt();
-  for (int i = 0; i < kRsItems; ++i) {
-    const int64_t j = base + (int64_t)i * kRsThreads + t;
-    const bool valid = j < n;
-    uint64_t key = valid ? kin[j] : 0;
-    uint32_t val = valid ? vin[j] : 0;
-    uint32_t d = (uint32_t)(key >> shift) & (kRsBins - 1);
+  const uint32_t tiles = (uint32_t)((n + kRsTile - 1) / kRsTile);
+  if (blockIdx.x >= tiles || plan->skip[pass]) return;
+  const int t = threadIdx.x, w = t / kWave, lane = lane_id();
+  const uint32_t tile = look_ticket(look, tiles, &tsm);
+  const uint32_t src = plan->src[pass];
+  const uint64_t* kin = b.k[src];
+  const uint32_t* vin = b.v[src];
+  uint64_t* kout = b.k[src ^ 1u];
+  uint32_t* vout = b.v[src ^ 1u];
+  // wavefront w holds the tile's pairs [w * 64 * kRsItems, ...), item by item
+  const int64_t base = (int64_t)tile * kRsTile + (int64_t)w * kWave * kRsItems;
+  uint64_t key[kRsItems];
+  uint32_t val[kRsItems];
 #pragma unroll
-    for (int k = 0; k < kW; ++k) wcnt[k][t] = 0;
-    __syncthreads();
+  for (int i = 0; i < kRsItems; ++i) {
+    const int64_t j = base + i * kWave + lane;
+    key[i] = j < n ? kin[j] : 0;
+    val[i] = j < n ? vin[j] : 0;
+  }
+  for (int k = 0; k < kW; ++k) wcnt[k][t] = 0;
+  __syncthreads();
+  // rank among the wavefront's earlier pairs of the same digit
+  const uint64_t lt = lanemask_lt();
+  uint32_t rank[kRsItems];
+#pragma unroll
+  for (int i = 0; i < kRsItems; ++i) {
+    const bool valid = base + i * kWave + lane < n;
+    const uint32_t d = (uint32_t)(key[i] >> (8 * pass)) & (kRsBins - 1);
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      uint64_t m = __ballot((d >> b) & 1u);
-      peers &= ((d >> b) & 1u) ? m : ~m;
+    for (int q = 0; q < 8; ++q) {
+      const uint64_t m = __ballot((d >> q) & 1u);
+      peers &= ((d >> q) & 1u) ? m : ~m;
     }
-    uint32_t rank = __popcll(peers & lt);
-    uint32_t cnt = __popcll(peers);
-    if (valid && rank == cnt - 1) wcnt[w][d] = cnt;
-    __syncthreads();
-    if (valid) {
-      uint32_t off = running[d] + rank;
+    const uint32_t r = (uint32_t)__popcll(peers & lt), cnt = (uint32_t)__popcll(peers);
+    uint32_t before = 0;
+    if (valid) before = wcnt[w][d];
+    wave_sync_lds();
+    if (valid && r + 1 == cnt) wcnt[w][d] = before + cnt;
+    wave_sync_lds();
+    rank[i] = before + r;
+  }
+  __syncthreads();
+  // thread t: digit t. Its count per wavefront becomes the wavefront's offset
+  uint32_t cnt = 0;
 #pragma unroll
-      for (int k = 0; k < kW; ++k)
-        if (k < w) off += wcnt[k][d];
-      kout[off] = key;
-      vout[off] = val;
+  for (int k = 0; k < kW; ++k) {
+    const uint32_t c = wcnt[k][t];
+    wcnt[k][t] = cnt;
+    cnt += c;
+  }
+  uint64_t* words = look.words + (uint64_t)tile * kRsBins + t;
+  look_put(words, look_word(look.launch, tile ? kLookTotal : kLookPrefix, 0, cnt));
+  int32_t tot;
+  const uint32_t ds = (uint32_t)block_incl_scan_add<kRsThreads, int32_t>((int32_t)cnt, scan, &tot) - cnt;
+  dstart[t] = ds;
+  __syncthreads();
+  uint32_t place[kRsItems];
+#pragma unroll
+  for (int i = 0; i < kRsItems; ++i) {
+    const uint32_t d = (uint32_t)(key[i] >> (8 * pass)) & (kRsBins - 1);
+    place[i] = dstart[d] + wcnt[w][d] + rank[i];
+    if (base + i * kWave + lane < n) stage[place[i]] = key[i];
+  }
+  uint32_t before = 0;
+  for (int64_t q = (int64_t)tile - 1; q >= 0;) {
+    uint64_t wd[kRsBack];
+#pragma unroll
+    for (int k = 0; k < kRsBack; ++k)
+      wd[k] = q >= k ? look_get(look.words + (uint64_t)(q - k) * kRsBins + t) : look_word(look.launch, kLookPrefix, 0, 0);
+    bool known = false, open = false;
+#pragma unroll
+    for (int k = 0; k < kRsBack; ++k) {
+      if (known || open) continue;
+      const uint32_t st = look_state(wd[k], look.launch);
+      if (st == 0) {
+        open = true;
+      } else {
+        before += (uint32_t)wd[k];
+        known = st == kLookPrefix;
+        --q;
+      }
     }
-    __syncthreads();
-    uint32_t add = 0;
+    if (known) break;
+    if (open) __builtin_amdgcn_s_sleep(1);
+  }
+  if (tile) look_put(words, look_word(look.launch, kLookPrefix, 0, before + cnt));
+  gbase[t] = plan->base[pass][t] + before - ds;
+  __syncthreads();
+  const uint32_t have = (uint32_t)min((int64_t)kRsTile, n - (int64_t)tile * kRsTile);
+  uint32_t dst[kRsItems];
 #pragma unroll
-    for (int k = 0; k < kW; ++k) add += wcnt[k][t];
-    running[t] += add;
-    __syncthreads();
+  for (int i = 0; i < kRsItems; ++i) {
+    const uint32_t j = i * kRsThreads + t;
+    dst[i] = 0;
+    if (j < have) {
+      const uint64_t k = stage[j];
+      dst[i] = gbase[(uint32_t)(k >> (8 * pass)) & (kRsBins - 1)] + j;
+      kout[dst[i]] = k;
+    }
+  }
+  __syncthreads();
+  uint32_t* vstage = (uint32_t*)stage;
+#pragma unroll
+  for (int i = 0; i < kRsItems; ++i)
+    if (base + i * kWave + lane < n) vstage[place[i]] = val[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kRsItems; ++i) {
+    const uint32_t j = i * kRsThreads + t;
+    if (j < have) vout[dst[i]] = vstage[j];
+  }
+}
+
+__global__ void k_zero_words(uint32_t* p, int64_t n) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (((uintptr_t)p & 15u) == 0) {
+    for (int64_t i = i0; i < n / 4; i += stride) ((uint4*)p)[i] = make_uint4(0, 0, 0, 0);
+    if (i0 < n % 4) p[n / 4 * 4 + i0] = 0;
+  } else {
+    for (int64_t i = i0; i < n; i += stride) p[i] = 0;
   }
 }
 
@@ -718,55 +734,48 @@ lp_status scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint3
   return scan_exclusive_t<uint32_t>(in, out, n, total_dev, sc);
 }
 
-lp_status seg_scan_incl_i64(const uint32_t* seg, const int64_t* val, int64_t* out, const uint32_t* count_dev,
-                            int64_t max_n, Scratch& sc) {
-  if (max_n <= 0) return LP_OK;
-  hipStream_t s = sc.stream();
-  int64_t nb = (max_n + kScanTile - 1) / kScanTile;
-  SegElem* carry = nullptr;
-  if (nb > 1) {
-    carry = sc.alloc<SegElem>(nb);
-    if (!carry) return LP_ENOMEM;
-    hipLaunchKernelGGL(k_seg_reduce_dyn<LoadSeg>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, LoadSeg{seg, val},
-                       count_dev, carry);
-    LP_CHECK_LAUNCH();
-    LP_CHECK(seg_scan_aggs_excl(carry, nb, sc));
-  }
-  hipLaunchKernelGGL(k_seg_down_dyn<LoadSeg>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, LoadSeg{seg, val},
-                     count_dev, (const SegElem*)carry, out);
-  LP_CHECK_LAUNCH();
+lp_status zero_u32(uint32_t* p, int64_t n, hipStream_t s) {
+  if (n <= 0) return LP_OK;
+  hipLaunchKernelGGL(k_zero_words, dim3(grid_for(n, 1024, 2048)), dim3(256), 0, s, p, n);
+  return last_error();
+}
+
+lp_status PairSorter::init(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, int64_t max_n,
+                           int bits, Scratch& sc) {
+  if (max_n > 0xFFFFFFFFll || bits > 8 * kRsPasses) return LP_EUNSUPPORTED;
+  stream_ = sc.stream();
+  max_n_ = max_n;
+  passes_ = bits > 0 ? (bits + 7) / 8 : 0;
+  const int per_tile = kRsThreads * (max_n <= kRsFew ? kRsItemsFew : kRsItemsMany);
+  const int64_t tiles = (max_n + per_tile - 1) / per_tile;
+  static_assert(sizeof(SortPlan) % 8 == 0, "the words follow the plan");
+  const size_t plan_words = sizeof(SortPlan) / 4;
+  zero_words_ = (int64_t)plan_words + (passes_ ? 2 * tiles * kRsBins : 0);
+  zero_ = sc.alloc<uint32_t>((size_t)zero_words_);
+  if (!zero_) return LP_ENOMEM;
+  plan_ = (SortPlan*)zero_;
+  words_ = (uint64_t*)(zero_ + plan_words);
+  out_.k[0] = keys_a;
+  out_.k[1] = keys_b;
+  out_.v[0] = vals_a;
+  out_.v[1] = vals_b;
+  out_.sel = &plan_->src[passes_];
   return LP_OK;
 }
 
-lp_status radix_sort_pairs(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b,
-                           const uint32_t* count_dev, int64_t max_n, int bits, uint64_t** keys_out,
-                           uint32_t** vals_out, Scratch& sc) {
-  hipStream_t s = sc.stream();
-  *keys_out = keys_a;
-  *vals_out = vals_a;
-  if (max_n <= 0 || bits <= 0) return LP_OK;
-  if (max_n > 0xFFFFFFFFll) return LP_EUNSUPPORTED;
-  const uint32_t nb = (uint32_t)((max_n + kRsTile - 1) / kRsTile);
-  uint32_t* hist = sc.alloc<uint32_t>((size_t)kRsBins * nb);
-  if (!hist) return LP_ENOMEM;
-  uint64_t *kin = keys_a, *kout = keys_b;
-  uint32_t *vin = vals_a, *vout = vals_b;
-  for (int shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(kRsThreads), 0, s, kin, count_dev, shift, hist, nb);
+lp_status PairSorter::sort(const uint32_t* count_dev) {
+  if (max_n_ <= 0 || passes_ == 0) return LP_OK;
+  const bool few = max_n_ <= kRsFew;
+  const int per_tile = kRsThreads * (few ? kRsItemsFew : kRsItemsMany);
+  const unsigned tiles = (unsigned)((max_n_ + per_tile - 1) / per_tile);
+  hipLaunchKernelGGL(k_rs_hist, dim3(grid_for(max_n_, kRsHistRun, kRsHistGrid)), dim3(kRsThreads), 0, stream_, out_.k[0],
+                     count_dev, passes_, plan_);
+  LP_CHECK_LAUNCH();
+  for (int p = 0; p < passes_; ++p) {
+    hipLaunchKernelGGL(few ? k_rs_pass<kRsItemsFew> : k_rs_pass<kRsItemsMany>, dim3(tiles), dim3(kRsThreads), 0, stream_, out_, count_dev, plan_, p,
+                       LookArgs{words_, &plan_->ticket, ++launch_});
     LP_CHECK_LAUNCH();
-    LP_CHECK(scan_exclusive_u32(hist, hist, (int64_t)kRsBins * nb, nullptr, sc));
-    hipLaunchKernelGGL(k_rs_scatter, dim3(nb), dim3(kRsThreads), 0, s, kin, vin, kout, vout, count_dev, shift,
-                       hist, nb);
-    LP_CHECK_LAUNCH();
-    uint64_t* tk = kin;
-    kin = kout;
-    kout = tk;
-    uint32_t* tv = vin;
-    vin = vout;
-    vout = tv;
   }
-  *keys_out = kin;
-  *vals_out = vin;
   return LP_OK;
 }
 

@@ -35,8 +35,9 @@ __global__ void k_ro_keys(int32_t n, const int32_t* deg, int32_t maxd, uint64_t*
   }
 }
 
-__global__ void k_ro_maps(int32_t n, const uint32_t* sorted, const int32_t* deg, const int32_t* vwgt, int32_t* orig,
+__global__ void k_ro_maps(int32_t n, SortedPairs sorted_by, const int32_t* deg, const int32_t* vwgt, int32_t* orig,
                           int32_t* pos, uint64_t* ndeg, int32_t* nvwgt) {
+  const uint32_t* sorted = sorted_by.v[*sorted_by.sel];
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const int32_t u = (int32_t)sorted[i];
     orig[i] = u;
@@ -64,8 +65,9 @@ __global__ __launch_bounds__(256) void k_ro_edges(int32_t n, const int32_t* orig
   }
 }
 
-__global__ void k_ro_split(uint64_t m, const uint64_t* key, const uint32_t* val, uint64_t mask, int32_t* adj,
-                           int32_t* wgt) {
+__global__ void k_ro_split(uint64_t m, SortedPairs edges, uint64_t mask, int32_t* adj, int32_t* wgt) {
+  const uint64_t* key = edges.k[*edges.sel];
+  const uint32_t* val = edges.v[*edges.sel];
   for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < m; j += (uint64_t)gridDim.x * blockDim.x) {
     adj[j] = (int32_t)(key[j] & mask);
     if (wgt) wgt[j] = (int32_t)val[j];
@@ -104,10 +106,11 @@ lp_status build(const lp_graph* g, hipStream_t s, Reorder* R) {
   LP_CHECK_HIP(hipMemcpyAsync(cnt, &nh, sizeof(uint32_t), hipMemcpyHostToDevice, s));
   hipLaunchKernelGGL(k_ro_keys, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, n, deg, (int32_t)g->max_deg, k1, v1);
   LP_CHECK_LAUNCH();
-  uint64_t* ks;
-  uint32_t* vs;
-  LP_CHECK(radix_sort_pairs(k1, v1, k2, v2, cnt, n, std::max(1, bitlen64((uint64_t)g->max_deg)), &ks, &vs, sc));
-  hipLaunchKernelGGL(k_ro_maps, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, n, vs, deg, g->vwgt, R->orig, R->pos,
+  PairSorter by_degree;
+  LP_CHECK(by_degree.init(k1, v1, k2, v2, n, std::max(1, bitlen64((uint64_t)g->max_deg)), sc));
+  LP_CHECK(zero_u32(by_degree.zero_base(), by_degree.zero_words(), s));
+  LP_CHECK(by_degree.sort(cnt));
+  hipLaunchKernelGGL(k_ro_maps, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, n, by_degree.out(), deg, g->vwgt, R->orig, R->pos,
                      nxadj, nvwgt);
   LP_CHECK_LAUNCH();
   LP_CHECK(scan_exclusive_u64(nxadj, nxadj, (int64_t)n + 1, nullptr, sc));
@@ -129,8 +132,11 @@ lp_status build(const lp_graph* g, hipStream_t s, Reorder* R) {
   LP_CHECK_LAUNCH();
   const uint32_t mh = (uint32_t)m;
   LP_CHECK_HIP(hipMemcpyAsync(mcnt, &mh, sizeof(uint32_t), hipMemcpyHostToDevice, s));
-  LP_CHECK(radix_sort_pairs(e1, w1, e2, w2, mcnt, (int64_t)m, 2 * nbits, &ks, &vs, sc));
-  hipLaunchKernelGGL(k_ro_split, dim3(grid_for((int64_t)m, 256, 1 << 20)), dim3(256), 0, s, m, ks, vs,
+  PairSorter by_edge;
+  LP_CHECK(by_edge.init(e1, w1, e2, w2, (int64_t)m, 2 * nbits, sc));
+  LP_CHECK(zero_u32(by_edge.zero_base(), by_edge.zero_words(), s));
+  LP_CHECK(by_edge.sort(mcnt));
+  hipLaunchKernelGGL(k_ro_split, dim3(grid_for((int64_t)m, 256, 1 << 20)), dim3(256), 0, s, m, by_edge.out(),
                      (1ull << nbits) - 1ull, adj, wgt);
   LP_CHECK_LAUNCH();
   if (g->compressed)
