@@ -310,7 +310,19 @@ constexpr int tile_waves_per_eu() {
 using TileSmall = TileCfg<256, 2048, 80>;
 using TileLarge = TileCfg<512, 4096, 4>;
 constexpr int kTileSeg = 128;  // vertices walked by one thread of the tiling pass
-constexpr int kTileGrab = 8;   // tiles taken per atomic of a hand-out counter
+// Work lists of the tile and piece kernels are handed out at run time, in
+// shares. The first share of every workgroup is its own by number; later ones
+// come from a counter, in shares of up to `most` items (a device-wide atomic
+// costs about as much as the setup of a tile, and all workgroups contend for
+// few counters) but small enough that the grid gets at least two each. Lists
+// that the first shares cover need no atomic at all: with eight tiles at a
+// time from counters alone, the 60 tiles of an RGG of 2^20 vertices (degree 8)
+// kept eight workgroups busy while 2048 queued on the counters, 0.27 ms per
+// round for what takes 0.02.
+__device__ __forceinline__ uint32_t grab_size(uint32_t items, uint32_t most) {
+  return max(1u, min(most, items / (3u * gridDim.x)));
+}
+constexpr int kTileGrab = 8;   // most tiles taken per atomic of a hand-out counter
 constexpr int kTileMaxDeg = 2048;  // largest degree of the small-tile bucket (default and bound of t_tile)
 
 template <int NT, int VT>
@@ -337,7 +349,7 @@ struct TileShared {
   int64_t red[NT / kWave];
   uint32_t seg_flags;
   uint32_t any_redo;
-  uint32_t next;  // tile handed to the workgroup
+  uint32_t next, region;  // tiles handed to the workgroup: first one, eighth of the list
 };
 
 // LDS layout of a tile workgroup: region A holds the staged bytes followed by
@@ -740,26 +752,51 @@ void k_rate_tile(RoundCtx x, VDesc vd, const int32_t* tiles,
   const int sgi = tid / SG;           // selection group of this thread
   const int sl = tid % SG;            // lane within the selection group
 
-  // Tiles are handed out at run time, kTileGrab at a time (a device-wide
-  // atomic costs about as much as the setup of a tile, and all workgroups
-  // contend for few counters): the workgroups of one XCD first take tiles of
-  // their own eighth of the list (one counter per eighth), then help with the
-  // other eighths, so that workgroups that become resident late (the kernel
-  // may share the device with the other rating paths) take fewer tiles.
+  // The workgroups of one XCD take tiles of their own eighth of the list (one
+  // counter per eighth), then help with the eighths that have some left.
   const uint32_t T_ = *ntiles_p;
-  const uint32_t xcd = blockIdx.x & 7u;
-  for (uint32_t k8 = 0; k8 < 8; ++k8) {
-    const uint32_t xr = (xcd + k8) & 7u;
-    const uint32_t lo = (uint32_t)(((uint64_t)T_ * xr) >> 3), hi = (uint32_t)(((uint64_t)T_ * (xr + 1)) >> 3);
-    uint32_t t = hi, tend = hi;
-    while (true) {
+  const uint32_t grab = grab_size(T_, kTileGrab);
+  auto lo_of = [&](uint32_t r) { return (uint32_t)(((uint64_t)T_ * r) >> 3); };
+  auto first_of = [&](uint32_t r) { return ((gridDim.x + 7u - r) >> 3) * grab; };  // tiles of first shares
+  uint32_t xr = blockIdx.x & 7u;
+  uint32_t t = lo_of(xr) + (blockIdx.x >> 3) * grab, tend = min(lo_of(xr + 1), t + grab);
+  while (true) {
+    {
       if (t >= tend) {
-        if (tid == 0) sh.next = lo + atomicAdd(&ctr[xr], (uint32_t)kTileGrab);
+        if (tid < kWave) {
+          uint32_t got = ~0u, r = xr;
+          while (true) {
+            const uint32_t size = lo_of(r + 1) - lo_of(r), f = first_of(r);
+            if (f < size) {
+              uint32_t v = 0;
+              if (tid == 0) v = atomicAdd(&ctr[r], grab);
+              v = f + (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+              if (v < size) {
+                got = lo_of(r) + v;
+                break;
+              }
+            }
+            // eighths with tiles left, the next one after r
+            const uint32_t q = (r + 1u + (uint32_t)tid) & 7u;
+            bool left = tid < 8 && first_of(q) < lo_of(q + 1) - lo_of(q);
+            if (left)
+              left = first_of(q) + __hip_atomic_load(&ctr[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                     lo_of(q + 1) - lo_of(q);
+            const uint64_t m = __ballot(left);
+            if (!m) break;
+            r = (r + (uint32_t)__ffsll((unsigned long long)m)) & 7u;
+          }
+          if (tid == 0) {
+            sh.next = got;
+            sh.region = r;
+          }
+        }
         __syncthreads();
         t = sh.next;
+        xr = sh.region;
         __syncthreads();
-        if (t >= hi) break;
-        tend = min(hi, t + (uint32_t)kTileGrab);
+        if (t == ~0u) break;
+        tend = min(lo_of(xr + 1), t + grab);
       }
       const uint32_t tcur = t++;
       const int32_t t0 = tiles[tcur];
@@ -1131,7 +1168,7 @@ static_assert(PieceHub::kEdges == PieceHub::kStreams * LP_CHUNK_LEN && PieceWhol
                   PieceWhole32::kEdges == PieceWhole32::kStreams * LP_CHUNK_LEN,
               "a piece holds whole chunks, one stream each");
 constexpr int kMaxParts = 1024;
-constexpr int kPieceGrab = 4;  // pieces taken per atomic of the hand-out counter
+constexpr int kPieceGrab = 4;  // most pieces taken per atomic of the hand-out counter
 constexpr int kDefaultHubPart = 2048;
 constexpr int kMaxSubrounds = 64;  // target partial records per (hub, partition) task
 constexpr uint32_t kStreamZig = 0x80000000u;  // first code is zigzag(v - base_v)
@@ -1298,16 +1335,18 @@ __global__ __launch_bounds__(Cfg::kThreads) void k_hub_piece(RoundCtx x, HubMeta
   uint32_t* nums = (uint32_t*)(A + L.nums_off);
   PieceShared<Cfg>& sh = *(PieceShared<Cfg>*)(A + L.abytes);
   V* rec_r = (V*)hm.rec_r;
-  // pieces are handed out at run time, kPieceGrab at a time (one counter)
-  uint32_t pnext = 0, pend = 0;
+  const uint32_t grab = grab_size((uint32_t)npieces, kPieceGrab);
+  const uint32_t first_all = gridDim.x * grab;  // pieces of first shares
+  uint32_t pnext = blockIdx.x * grab, pend = min((uint32_t)npieces, pnext + grab);
   while (true) {
     if (pnext >= pend) {
-      if (tid == 0) sh.next = atomicAdd(ctr, (uint32_t)kPieceGrab);
+      if (first_all >= (uint32_t)npieces) break;
+      if (tid == 0) sh.next = first_all + atomicAdd(ctr, grab);
       __syncthreads();
       pnext = sh.next;
       __syncthreads();
       if (pnext >= (uint32_t)npieces) break;
-      pend = min((uint32_t)npieces, pnext + (uint32_t)kPieceGrab);
+      pend = min((uint32_t)npieces, pnext + grab);
     }
     const int64_t pc = pnext++;
     const int2 pj = hm.pieces[pc];
