@@ -1069,7 +1069,7 @@ lp_status check_csr(const CsrIn& in, bool size, Scratch& sc, CsrPlan* P) {
   LP_CHECK_HIP(hipStreamSynchronize(s));
   if (x0 != 0) return LP_EINVAL;
   P->two_m = xn;
-  P->nb = (int64_t)((xn + (uint64_t)in.n) / kCtWork) + 1;
+  P->nb = merged_stretches(xn, in.n, kCtWork);
   if (P->nb > 0x7FFFFFFFll) return LP_EUNSUPPORTED;
   const bool wgt = in.adjwgt != nullptr;
   P->blk = sc.alloc<int64_t>((size_t)P->nb + 1);
@@ -1082,9 +1082,7 @@ lp_status check_csr(const CsrIn& in, bool size, Scratch& sc, CsrPlan* P) {
   if (sc.failed) return LP_ENOMEM;
   LP_CHECK_HIP(hipMemsetAsync(acc, 0, sizeof(CsrAcc), s));
   if (wgt) LP_CHECK_HIP(hipMemsetAsync(wspan, 0, (size_t)P->nb * sizeof(unsigned long long), s));
-  hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for((int64_t)in.n + 1, 256, 65536)), dim3(256), 0, s, in.xadj,
-                     (int64_t)in.n, (uint64_t)kCtWork, P->nb, P->blk, &acc->xerr);
-  LP_CHECK_LAUNCH();
+  LP_CHECK(merged_blocks(in.xadj, in.n, kCtWork, P->nb, P->blk, &acc->xerr, s));
   auto kern = wgt ? (size ? k_csr_scan<true, true> : k_csr_scan<true, false>)
                   : (size ? k_csr_scan<false, true> : k_csr_scan<false, false>);
   hipLaunchKernelGGL(kern, dim3((unsigned)P->nb), dim3(kCtThreads), 0, s, in, P->blk, P->nb, acc, tdeg, tw,
@@ -1121,6 +1119,12 @@ lp_status dev_copy(T** dst, const T* src, size_t count, hipStream_t s, size_t pa
 }
 
 }  // namespace
+
+lp_status merged_blocks(const uint64_t* xadj, int64_t n, uint64_t work, int64_t nb, int64_t* blk, uint32_t* err,
+                        hipStream_t s) {
+  hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for(n + 1, 256, 65536)), dim3(256), 0, s, xadj, n, work, nb, blk, err);
+  return last_error();
+}
 
 lp_status compute_degrees(const lp_graph* g, int32_t* deg, hipStream_t s) {
   if (g->n == 0) return LP_OK;
@@ -1317,13 +1321,11 @@ extern "C" lp_status lp_decompress(const lp_graph* g, uint64_t* xadj, int32_t* a
                        err);
     LP_CHECK_LAUNCH();
   } else if (g->two_m) {
-    const int64_t nb = (int64_t)((g->two_m + (uint64_t)g->n) / kDecWork) + 1;
+    const int64_t nb = merged_stretches(g->two_m, g->n, kDecWork);
     if (nb > 0x7FFFFFFFll) return LP_EUNSUPPORTED;
     int64_t* blk = sc.alloc<int64_t>((size_t)nb + 1);
     if (!blk) return LP_ENOMEM;
-    hipLaunchKernelGGL(k_codec_blocks, dim3(grid_for((int64_t)g->n + 1, 256, 65536)), dim3(256), 0, s, xadj,
-                       (int64_t)g->n, (uint64_t)kDecWork, nb, blk, err + 1);
-    LP_CHECK_LAUNCH();
+    LP_CHECK(merged_blocks(xadj, g->n, kDecWork, nb, blk, err + 1, s));
     hipLaunchKernelGGL(g->weighted ? k_decode<true> : k_decode<false>, dim3((unsigned)nb), dim3(kDecThreads), 0, s, v,
                        xadj, blk, nb, adjncy, adjwgt, err);
     LP_CHECK_LAUNCH();

@@ -829,42 +829,154 @@ __global__ void k_heavy_cdeg(Heavy hv, int32_t H, uint64_t* cdeg) {
 
 // ---------------------------------------------------------- placement ----
 // Light clusters: their aggregated neighbourhood sits at the start of their
-// record region (wave per coarse vertex; heavy clusters are skipped). Also
-// gathers the largest weighted degree and degree of the light coarse vertices
-// (mx[0], mx[1]).
-__global__ __launch_bounds__(256) void k_place_light(const uint64_t* cx, const uint64_t* rbase, const uint8_t* heavy,
-                                                     const Rec* rec, int32_t nc, int32_t* adjncy, int32_t* adjwgt,
-                                                     unsigned long long* mx) {
-  __shared__ unsigned long long sa[4], sb[4];
-  const int lane = lane_id();
-  const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-  unsigned long long mw = 0, md = 0;
-  for (int64_t a = wid; a < nc; a += nw) {
-    const uint64_t o = cx[a], d = cx[a + 1] - o;
-    if (d == 0 || heavy[a]) continue;
-    const Rec* r = rec + rbase[a];
-    int64_t sw = 0;
-    for (uint64_t i = lane; i < d; i += kWave) {
-      const Rec x = r[i];
-      adjncy[o + i] = x.b;
-      adjwgt[o + i] = x.w;
-      sw += x.w;
-    }
-    sw = wave_reduce_add(sw);
-    mw = max(mw, (unsigned long long)sw);
-    md = max(md, (unsigned long long)d);
-  }
-  if (lane == 0) {
-    sa[threadIdx.x / kWave] = mw;
-    sb[threadIdx.x / kWave] = md;
+// record region. One workgroup per stretch of kPlWork positions of the merged
+// sequence of coarse vertices and entries: owner marks and a prefix maximum
+// give every entry its vertex, then consecutive threads copy consecutive
+// entries. Entries of heavy clusters are skipped. Also the largest weighted
+// degree and degree of the light coarse vertices (tw[c], td[c] per stretch;
+// weighted degrees of vertices that continue in later stretches are summed in
+// wspan[stretch that starts them], zeroed). Bound by the copy: a wavefront
+// per coarse vertex spent its time on vertices of a few entries: R-MAT 2^23
+// with 2.2e8 coarse entries 1.48 ms, now 0.56 (29 KB of LDS, five workgroups a
+// CU); the four levels of an RGG of 2^20 vertices 1.50 ms, now 0.03.
+constexpr int kPlThreads = 256;
+constexpr int kPlItems = 8;
+constexpr int kPlWork = kPlThreads * kPlItems;
+
+__global__ __launch_bounds__(kPlThreads) void k_place_light(const uint64_t* cx, const int64_t* blk, int64_t nb,
+                                                            uint64_t two_m, const uint64_t* rbase,
+                                                            const uint8_t* heavy, const Rec* rec, int32_t* adjncy,
+                                                            int32_t* adjwgt, unsigned long long* tw, uint32_t* td,
+                                                            unsigned long long* wspan) {
+  __shared__ __align__(16) uint16_t own[kPlWork];  // marks, then every entry's vertex (1 + index; 0: the one continued)
+  __shared__ __align__(16) int32_t wt[kPlWork];
+  // record of the vertex's entry e: src + e (~0: heavy); then the sums of the vertices' weights
+  __shared__ unsigned long long src[kPlWork + 1];
+  unsigned long long* wsum = src;
+  __shared__ int32_t scan[kPlThreads / kWave];
+  __shared__ unsigned long long redw[kPlThreads / kWave];
+  __shared__ uint32_t redd[kPlThreads / kWave];
+  const int64_t c = blockIdx.x;
+  const int64_t v0 = blk[c], v1 = blk[c + 1];
+  const uint64_t e0 = (uint64_t)c * kPlWork - (uint64_t)v0;
+  const uint64_t e1 = c + 1 < nb ? (uint64_t)(c + 1) * kPlWork - (uint64_t)v1 : two_m;
+  const int32_t nv = (int32_t)(v1 - v0), ne = (int32_t)(e1 - e0);
+  const int tid = threadIdx.x;
+  *(uint4*)&own[tid * kPlItems] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  uint32_t md = 0;
+  for (int32_t i = tid; i <= nv; i += kPlThreads) {
+    const int64_t a = v0 - 1 + i;
+    src[i] = ~0ull;
+    if (a < 0) continue;
+    const uint64_t x = cx[a], d = cx[a + 1] - x;
+    const bool hv = heavy[a] != 0;
+    if (!hv) src[i] = rbase[a] - x;
+    if (i == 0) continue;
+    if (!hv) md = max(md, (uint32_t)d);  // a light vertex has at most 2048 neighbours
+    const uint64_t pos = x - e0;
+    if (d > 0 && pos < (uint64_t)ne) own[pos] = (uint16_t)i;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < 4; ++i) {
-      mw = max(mw, sa[i]);
-      md = max(md, sb[i]);
+  const int32_t j0 = tid * kPlItems;
+  uint16_t o[kPlItems];
+  {
+    const uint4 ow = *(const uint4*)&own[j0];
+    __builtin_memcpy(o, &ow, 16);
+    int32_t top = 0;
+#pragma unroll
+    for (int k = 0; k < kPlItems; ++k) top = max(top, (int32_t)o[k]);
+    const int32_t inc = wave_incl_scan_max_i32(top);
+    if (lane_id() == kWave - 1) scan[tid / kWave] = inc;
+    __syncthreads();
+    int32_t cur = dpp_i32<0x138>(inc);
+    for (int k = 0; k < tid / kWave; ++k) cur = max(cur, scan[k]);
+#pragma unroll
+    for (int k = 0; k < kPlItems; ++k) {
+      cur = max(cur, (int32_t)o[k]);
+      o[k] = (uint16_t)cur;
     }
+    uint4 ov;
+    __builtin_memcpy(&ov, o, 16);
+    *(uint4*)&own[j0] = ov;
+  }
+  __syncthreads();
+  Rec x[kPlItems];
+#pragma unroll
+  for (int k = 0; k < kPlItems; ++k) {
+    const int32_t j = k * kPlThreads + tid;
+    x[k] = Rec{-1, 0};
+    if (j < ne) {
+      const uint64_t s0 = src[own[j]];
+      if (s0 != ~0ull) x[k] = rec[s0 + e0 + j];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kPlItems; ++k) {
+    const int32_t j = k * kPlThreads + tid;
+    wt[j] = x[k].w;
+    if (x[k].b >= 0) {
+      adjncy[e0 + j] = x[k].b;
+      adjwgt[e0 + j] = x[k].w;
+    }
+  }
+  __syncthreads();
+  for (int32_t i = tid; i <= nv; i += kPlThreads) wsum[i] = 0;
+  __syncthreads();
+  // weighted degrees: each thread's runs of one vertex
+  {
+    int64_t run = 0;
+#pragma unroll
+    for (int k = 0; k < kPlItems; ++k) {
+      if (k && o[k] != o[k - 1]) {
+        if (run) atomicAdd(&wsum[o[k - 1]], (unsigned long long)run);
+        run = 0;
+      }
+      run += wt[j0 + k];  // 0 beyond the stretch's entries
+    }
+    if (run) atomicAdd(&wsum[o[kPlItems - 1]], (unsigned long long)run);
+  }
+  __syncthreads();
+  unsigned long long mw = 0;
+  for (int32_t i = tid; i <= nv; i += kPlThreads) {
+    const unsigned long long s = wsum[i];
+    if (i == 0) {
+      if (s) atomicAdd(&wspan[(int64_t)((cx[v0 - 1] + (uint64_t)(v0 - 1)) / kPlWork)], s);
+    } else if (i == nv && cx[v1] > e1) {
+      if (s) atomicAdd(&wspan[c], s);
+    } else {
+      mw = max(mw, s);
+    }
+  }
+  mw = wave_reduce_max(mw);
+  md = wave_reduce_max(md);
+  if (lane_id() == 0) {
+    redw[tid / kWave] = mw;
+    redd[tid / kWave] = md;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int k = 1; k < kPlThreads / kWave; ++k) {
+      mw = max(mw, redw[k]);
+      md = max(md, redd[k]);
+    }
+    tw[c] = mw;
+    td[c] = md;
+  }
+}
+
+// Maxima over the stretches into mx[0] (weighted degree) and mx[1] (degree).
+__global__ __launch_bounds__(256) void k_place_max(const unsigned long long* tw, const uint32_t* td,
+                                                   const unsigned long long* wspan, int64_t nb,
+                                                   unsigned long long* mx) {
+  unsigned long long mw = 0, md = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nb; i += (int64_t)gridDim.x * blockDim.x) {
+    mw = max(mw, max(tw[i], wspan[i]));
+    md = max(md, (unsigned long long)td[i]);
+  }
+  mw = wave_reduce_max(mw);
+  md = wave_reduce_max(md);
+  if (lane_id() == 0) {
     if (mw) atomicMax(&mx[0], mw);
     if (md) atomicMax(&mx[1], md);
   }
@@ -908,38 +1020,6 @@ __global__ void k_heavy_max(Heavy hv, int32_t H, const unsigned long long* hsum,
     const int32_t a = hv.clusters[h];
     atomicMax(&mx[0], hsum[h]);
     atomicMax(&mx[1], (unsigned long long)(cx[a + 1] - cx[a]));
-  }
-}
-
-__global__ __launch_bounds__(256) void k_wdeg(const uint64_t* xadj, const int32_t* adjwgt, int32_t n,
-                                              unsigned long long* max_wdeg, unsigned long long* max_deg) {
-  const int lane = lane_id();
-  const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-  unsigned long long mw = 0, md = 0;
-  for (int64_t u = wid; u < n; u += nw) {
-    const uint64_t b = xadj[u], e = xadj[u + 1];
-    int64_t s = 0;
-    for (uint64_t k = b + lane; k < e; k += kWave) s += adjwgt[k];
-    s = wave_reduce_add(s);
-    mw = max(mw, (unsigned long long)s);
-    md = max(md, (unsigned long long)(e - b));
-  }
-  __shared__ unsigned long long sa[4], sb[4];
-  mw = wave_reduce_max(mw);
-  md = wave_reduce_max(md);
-  if (lane == 0) {
-    sa[threadIdx.x / kWave] = mw;
-    sb[threadIdx.x / kWave] = md;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < 4; ++i) {
-      mw = max(mw, sa[i]);
-      md = max(md, sb[i]);
-    }
-    atomicMax(max_wdeg, mw);
-    atomicMax(max_deg, md);
   }
 }
 
@@ -1295,16 +1375,21 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
     cg->weighted = 1;
     if (graph_alloc(cg, (void**)&cg->adjncy, (h.two_mc ? h.two_mc : 1) * sizeof(int32_t)) != hipSuccess ||
         graph_alloc(cg, (void**)&cg->adjwgt, (h.two_mc ? h.two_mc : 1) * sizeof(int32_t)) != hipSuccess) { st = LP_ENOMEM; break; }
-    mx = sc.alloc<unsigned long long>(2);
+    // maxima, an error word, and the sums of light vertices that span stretches
+    const int64_t nst = merged_stretches(h.two_mc, nc, kPlWork);
+    mx = sc.alloc<unsigned long long>(3 + (size_t)nst);
+    unsigned long long* tw = sc.alloc<unsigned long long>(nst);
+    uint32_t* td = sc.alloc<uint32_t>(nst);
+    int64_t* blk = sc.alloc<int64_t>((size_t)nst + 1);
     unsigned long long* hsum = H > 0 ? sc.alloc<unsigned long long>(H) : nullptr;
-    if (!mx || (H > 0 && !hsum)) { st = LP_ENOMEM; break; }
-    if (hipMemsetAsync(mx, 0, 16, s) != hipSuccess ||
-        (H > 0 && hipMemsetAsync(hsum, 0, (size_t)H * sizeof(unsigned long long), s) != hipSuccess)) {
-      st = LP_EDEVICE;
-      break;
-    }
-    hipLaunchKernelGGL(k_place_light, dim3(grid_for((int64_t)nc * kWave, 256, 65536)), dim3(256), 0, s, cg->xadj,
-                       rbase, heavy, rec, nc, cg->adjncy, cg->adjwgt, mx);
+    if (sc.failed) { st = LP_ENOMEM; break; }
+    st = zero_u32((uint32_t*)mx, 2 * (3 + nst), s);
+    if (!st && H > 0) st = zero_u32((uint32_t*)hsum, 2 * (int64_t)H, s);
+    if (!st) st = merged_blocks(cg->xadj, nc, kPlWork, nst, blk, (uint32_t*)(mx + 2), s);
+    if (st) break;
+    hipLaunchKernelGGL(k_place_light, dim3((unsigned)nst), dim3(kPlThreads), 0, s, cg->xadj, blk, nst, h.two_mc, rbase,
+                       heavy, rec, cg->adjncy, cg->adjwgt, tw, td, mx + 3);
+    hipLaunchKernelGGL(k_place_max, dim3(grid_for(nst, 1024, 64)), dim3(256), 0, s, tw, td, mx + 3, nst, mx);
     if (T > 0) {
       hipLaunchKernelGGL(k_place_heavy, dim3(grid_for((int64_t)T * kWave, 256, 65536)), dim3(256), 0, s, hv, T, tscan,
                          cg->xadj, cg->adjncy, cg->adjwgt, hsum);

@@ -84,7 +84,15 @@ constexpr size_t kBytePad = 8192;
 // Degrees deg[u] (int32) of any handle; fe[u] optional first-edge IDs.
 lp_status compute_degrees(const lp_graph* g, int32_t* deg, hipStream_t s);
 
-// Max of deg over u (for launch sizing); host result.
-lp_status reduce_max_i32(const int32_t* a, int64_t n, int32_t* out_host, Scratch& sc);
+// Stretches of `work` positions of the merged sequence of vertices (u at
+// xadj[u] + u) and entries (after their vertex): blk[c] = the first vertex at
+// or after position c * work for c < nb, blk[nb] = n. xadj must be
+// non-decreasing from 0; a decrease sets *err (zeroed by the caller) and
+// leaves blk incomplete.
+inline int64_t merged_stretches(uint64_t two_m, int64_t n, uint64_t work) {
+  return (int64_t)((two_m + (uint64_t)n) / work) + 1;
+}
+lp_status merged_blocks(const uint64_t* xadj, int64_t n, uint64_t work, int64_t nb, int64_t* blk, uint32_t* err,
+                        hipStream_t s);
 
 }  // namespace lp
