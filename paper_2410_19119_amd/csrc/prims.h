@@ -110,7 +110,7 @@ class PairSorter {
   uint64_t* words_ = nullptr;
   uint32_t* zero_ = nullptr;
   int64_t zero_words_ = 0, max_n_ = 0;
-  int passes_ = 0;
+  int passes_ = 0, which_ = 0;
   uint32_t launch_ = 0;
   hipStream_t stream_ = nullptr;
 };
