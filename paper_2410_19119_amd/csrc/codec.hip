@@ -540,105 +540,389 @@ __global__ __launch_bounds__(256) void k_vwgt_check(const int32_t* vwgt, int32_t
 }
 
 // ------------------------------------------------- interval encoding ----
-// Interval-coded records (Section III-A; layout in lp.h): one lane writes a
-// whole record, chunk by chunk, in four passes over each chunk's sorted
-// neighbours: the interval count, the (start, length - 3) pairs, the weights
-// of the interval neighbours, and the remaining neighbours gap encoded.
-// A run is a maximal stretch of IDs each one above the previous neighbour's,
-// found left to right; runs of three or more are intervals.
-__device__ __forceinline__ uint32_t put_or_len(uint8_t* out, uint64_t pos, uint64_t x) {
-  return out ? varint_put(out + pos, x) : varint_len(x);
+// Interval-coded records (Section III-A; layout in lp.h), one workgroup per
+// stretch of the merged sequence, as above. It codes the segments (unsplit
+// neighbourhoods, chunks of split ones) that start in its stretch, run by
+// run; a run's entries lie one after another, kItvShare consecutive ones per
+// thread at most. Whether an entry is part of an interval is decided by the
+// entries next to it: it is if three in a row with consecutive IDs include
+// it. An interval's last entry codes the pair, prefix maxima give every entry
+// the residual and the interval neighbour before it, and prefix sums of the
+// bytes per section place everything. A lane per record, as before, read the
+// adjacency four times at a stride: an RGG-3D of 1e6 vertices with weights
+// (2.7e7 entries) took 1.1 ms to size and 1.6 ms to encode, and one hub of
+// 10^5 neighbours more than all other records; it takes 0.33 and 0.66 ms now,
+// bound by instructions (the code is long: with the run's body inlined at
+// every use, or sixteen entries per thread, it outgrew the instruction cache
+// and took twice as long).
+constexpr int kItvThreads = 512;
+constexpr int kItvShare = 8;
+constexpr int kItvMax = kItvThreads * kItvShare;  // most entries of a run
+constexpr int kItvWork = 2048;                    // positions of a stretch: 42 KB of LDS, three workgroups a CU
+static_assert(LP_ITV_CHUNK_THRESHOLD >= kItvWork && LP_ITV_CHUNK_THRESHOLD <= kItvMax &&
+                  kItvWork + LP_CHUNK_LEN <= kItvMax && LP_CHUNK_THRESHOLD >= LP_ITV_CHUNK_THRESHOLD,
+              "a run holds a stretch's neighbourhoods but the last, one unsplit neighbourhood, or a stretch's chunks");
+
+struct ItvShared {
+  __align__(16) uint16_t own[kItvMax + 8];  // 1 + segment that starts at the entry
+  uint16_t es[kItvWork + 2];                // first entry of every segment
+  uint16_t lastiv[kItvWork + 2];            // 1 + last interval neighbour up to the segment's end
+  uint32_t sa[kItvWork + 2];  // bytes before the segment's first entry: pairs << 16 | interval weights
+  uint32_t sb[kItvWork + 2];  // residuals << 16 | intervals (when sizing: the segment's intervals)
+  uint32_t sec[kItvWork + 2];    // first section of the segment, from the run's start
+  uint16_t cb[kItvThreads + 2];  // per thread: which of its entries continue a run of consecutive IDs
+  int32_t scan[3][kItvThreads / kWave];
+};
+
+struct ItvRun {
+  uint64_t e0;        // first entry
+  int32_t m, nseg;    // entries, segments (starts in ItvShared::es)
+  int64_t u;          // vertex of segment i: u + i * ustep
+  int32_t ustep;
+  bool hdr;           // segments are records: a first-edge header each
+  bool chunk0;        // segments are chunks, the first of them the neighbourhood's first
+};
+
+__device__ __forceinline__ void put_bytes(uint8_t* out, uint64_t pos, uint32_t x) {
+  while (x >= 0x80u) {
+    out[pos++] = (uint8_t)(x | 0x80u);
+    x >>= 7;
+  }
+  out[pos] = (uint8_t)x;
 }
 
-__device__ __forceinline__ uint64_t run_end(const int32_t* a, uint64_t i, uint64_t e) {
-  uint64_t j = i + 1;
-  while (j < e && (int64_t)a[j] == (int64_t)a[j - 1] + 1) ++j;
-  return j;
+// Exclusive prefix maxima over the workgroup of three values per thread.
+__device__ __forceinline__ void itv_scan_max3(int32_t (&x)[3], int32_t (*sm)[kItvThreads / kWave]) {
+  int32_t inc[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) inc[q] = wave_incl_scan_max_i32(x[q]);
+  const int wv = threadIdx.x / kWave;
+  if (lane_id() == kWave - 1)
+    for (int q = 0; q < 3; ++q) sm[q][wv] = inc[q];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    x[q] = dpp_i32<0x138>(inc[q]);
+    for (int k = 0; k < wv; ++k) x[q] = max(x[q], sm[q][k]);
+  }
+  __syncthreads();
 }
 
-// Size of u's record (out == nullptr) or the record written at out.
-__device__ uint64_t itv_record(const CsrIn& g, int64_t u, uint8_t* out) {
-  const uint64_t b = g.xadj[u], e = g.xadj[u + 1], d = e - b;
-  const int32_t* a = g.adjncy;
-  const uint64_t nch = d > LP_ITV_CHUNK_THRESHOLD ? (d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN : 1;
-  uint64_t k = put_or_len(out, 0, b);
-  const uint64_t table = k;
-  if (nch > 1) k += 4 * (nch - 1);
-  for (uint64_t ch = 0; ch < nch; ++ch) {
-    const uint64_t cb = nch > 1 ? b + ch * LP_CHUNK_LEN : b;
-    const uint64_t ce = nch > 1 ? min(e, cb + LP_CHUNK_LEN) : e;
-    if (ch > 0 && out) {
-      const uint32_t rel = (uint32_t)k;
-      uint8_t* t = out + table + 4 * (ch - 1);
-      t[0] = (uint8_t)rel;
-      t[1] = (uint8_t)(rel >> 8);
-      t[2] = (uint8_t)(rel >> 16);
-      t[3] = (uint8_t)(rel >> 24);
-    }
-    uint64_t cnt = 0;
-    for (uint64_t i = cb; i < ce;) {
-      const uint64_t j = run_end(a, i, ce);
-      if (j - i >= 3) {
-        ++cnt;
-        i = j;
-      } else {
-        ++i;
-      }
-    }
-    k += put_or_len(out, k, cnt);
-    for (uint64_t i = cb; i < ce;) {
-      const uint64_t j = run_end(a, i, ce);
-      if (j - i >= 3) {
-        k += put_or_len(out, k, zigzag((int64_t)a[i] - u));
-        k += put_or_len(out, k, j - i - 3);
-        i = j;
-      } else {
-        ++i;
-      }
-    }
-    int64_t wprev = 0;
-    if (g.adjwgt)
-      for (uint64_t i = cb; i < ce;) {
-        const uint64_t j = run_end(a, i, ce);
-        if (j - i >= 3) {
-          for (uint64_t t = i; t < j; ++t) {
-            k += put_or_len(out, k, zigzag((int64_t)g.adjwgt[t] - wprev));
-            wprev = g.adjwgt[t];
-          }
-          i = j;
-        } else {
-          ++i;
-        }
-      }
-    bool first = true;
-    int64_t rprev = 0;
-    for (uint64_t i = cb; i < ce;) {
-      const uint64_t j = run_end(a, i, ce);
-      if (j - i >= 3) {
-        i = j;
-        continue;
-      }
-      k += put_or_len(out, k, first ? zigzag((int64_t)a[i] - u) : (uint64_t)((int64_t)a[i] - rprev));
-      if (g.adjwgt) {
-        k += put_or_len(out, k, zigzag((int64_t)g.adjwgt[i] - wprev));
-        wprev = g.adjwgt[i];
-      }
-      rprev = a[i];
-      first = false;
-      ++i;
+// Codes one run (es[0..nseg] set and visible); returns its bytes. WRITE: at
+// `base`, with the record offsets (hdr) or the chunk positions (cpos, as for
+// the gap format).
+template <bool WGT, bool WRITE>
+__device__ uint32_t itv_run(const CsrIn& g, ItvShared& sh, const ItvRun& r, uint64_t base, uint64_t* offs,
+                            uint64_t* cpos, uint8_t* out) {
+  const int tid = threadIdx.x;
+  const int32_t per = (r.m + kItvThreads - 1) / kItvThreads;
+  const int32_t j0 = tid * per;
+  const int32_t* ids = g.adjncy + r.e0;
+  const int32_t* wts = WGT ? g.adjwgt + r.e0 : nullptr;
+  int32_t id[kItvShare], w[WGT ? kItvShare : 1];
+  int32_t before = 0;
+#pragma unroll
+  for (int32_t k = 0; k < kItvShare; ++k) {
+    id[k] = 0;
+    if (k < per && j0 + k < r.m) {
+      id[k] = ids[j0 + k];
+      if constexpr (WGT) w[k] = wts[j0 + k];
     }
   }
-  return k;
+  if (j0 > 0 && j0 < r.m) before = ids[j0 - 1];
+  for (int32_t q = 8 * tid; q < r.m + 8; q += 8 * kItvThreads) *(uint4*)&sh.own[q] = make_uint4(0, 0, 0, 0);
+  if constexpr (!WRITE)
+    for (int32_t i = tid; i < r.nseg; i += kItvThreads) sh.sb[i] = 0;
+  __syncthreads();
+  for (int32_t i = tid; i < r.nseg; i += kItvThreads)
+    if (sh.es[i + 1] > sh.es[i]) sh.own[sh.es[i]] = (uint16_t)(i + 1);
+  __syncthreads();
+  // runs of consecutive IDs
+  uint32_t c = 0, heads = 0;
+  int32_t top = 0;
+#pragma unroll
+  for (int32_t k = 0; k < kItvShare; ++k) {
+    if (k >= per || j0 + k >= r.m) continue;
+    const int32_t o = sh.own[j0 + k];
+    if (o) {
+      top = o;
+      heads |= 1u << k;
+    } else if (id[k] == (k ? id[(k + kItvShare - 1) % kItvShare] : before) + 1) {
+      c |= 1u << k;
+    }
+  }
+  sh.cb[tid + 1] = (uint16_t)c;
+  if (tid == 0) sh.cb[0] = sh.cb[kItvThreads + 1] = 0;
+  int32_t x3[3] = {top, 0, 0};
+  itv_scan_max3(x3, sh.scan);
+  const int32_t seg0 = x3[0];
+  // bit k: entry k - 1 of this thread continues a run
+  uint32_t win = 0;
+  if (per > 0) {
+    win = ((uint32_t)sh.cb[tid] >> (per - 1)) & 1u;
+    win |= c << 1;
+    win |= ((uint32_t)sh.cb[tid + 2] & 3u) << (per + 1);
+    // with one entry per thread the second one behind is the next thread's
+    if (per == 1) win = (win & 7u) | (tid + 3 <= kItvThreads + 1 ? ((uint32_t)sh.cb[tid + 3] & 1u) << 3 : 0u);
+  }
+  const uint32_t c0 = win, c1 = win >> 1, c2 = win >> 2, c3 = win >> 3;  // bit k: entry k - 1, k, k + 1, k + 2
+  const uint32_t ivm = (c0 & c1) | (c1 & c2) | (c2 & c3);
+  int32_t p3[3] = {0, 0, 0};  // 1 + last run start, last residual, last interval neighbour
+#pragma unroll
+  for (int32_t k = 0; k < kItvShare; ++k) {
+    if (k >= per || j0 + k >= r.m) continue;
+    if (!((c1 >> k) & 1u)) p3[0] = j0 + k + 1;
+    if ((ivm >> k) & 1u) p3[2] = j0 + k + 1;
+    else p3[1] = j0 + k + 1;
+  }
+  itv_scan_max3(p3, sh.scan);
+  if constexpr (WGT) {
+    int32_t seg = seg0, li = p3[2];
+#pragma unroll
+    for (int32_t k = 0; k < kItvShare; ++k) {
+      if (k >= per || j0 + k >= r.m) continue;
+      if ((heads >> k) & 1u) seg = sh.own[j0 + k];
+      if ((ivm >> k) & 1u) li = j0 + k + 1;
+      if (j0 + k + 1 == sh.es[seg]) sh.lastiv[seg - 1] = (uint16_t)li;
+    }
+    __syncthreads();
+  }
+  // the residual and the interval neighbour before this thread's entries
+  const int32_t rid0 = p3[1] ? ids[p3[1] - 1] : 0;
+  const int32_t rw0 = WGT && p3[1] ? wts[p3[1] - 1] : 0, iw0 = WGT && p3[2] ? wts[p3[2] - 1] : 0;
+  // codes: f(k, segment, interval neighbour, pair ends here, pair start code, pair length code, code, weight code)
+  auto entries = [&](auto&& f) {
+    int32_t seg = seg0, rs = p3[0], rid = rid0, rw = rw0, iw = iw0;
+    int32_t st = seg0 ? sh.es[seg0 - 1] : 0, u = (int32_t)(r.u + (int64_t)(seg0 - 1) * r.ustep);
+    bool res = p3[1] > st, ivb = p3[2] > st;  // the segment has had a residual, an interval neighbour
+#pragma unroll
+    for (int32_t k = 0; k < kItvShare; ++k) {
+      if (k >= per || j0 + k >= r.m) continue;
+      const int32_t j = j0 + k;
+      if ((heads >> k) & 1u) {
+        seg = sh.own[j];
+        u = (int32_t)(r.u + (int64_t)(seg - 1) * r.ustep);
+        st = j;
+        res = ivb = false;
+      }
+      if (!((c1 >> k) & 1u)) rs = j + 1;
+      const bool iv = (ivm >> k) & 1u;
+      uint32_t pa = 0, pb = 0, code = 0, wc = 0;
+      bool end = false;
+      if (iv) {
+        end = !((c2 >> k) & 1u);
+        const int32_t l = j + 2 - rs;
+        pa = zigzag32(id[k] - (l - 1) - u);
+        pb = (uint32_t)(l - 3);
+        if constexpr (WGT) {
+          wc = zigzag32(w[k] - (ivb ? iw : 0));
+          iw = w[k];
+        }
+        ivb = true;
+      } else {
+        code = res ? (uint32_t)(id[k] - rid) : zigzag32(id[k] - u);
+        if constexpr (WGT) {
+          int32_t pw = rw;
+          if (!res) {  // the chain goes on from the segment's interval neighbours
+            const int32_t lv = sh.lastiv[seg - 1];
+            pw = lv > st ? wts[lv - 1] : 0;
+          }
+          wc = zigzag32(w[k] - pw);
+          rw = w[k];
+        }
+        rid = id[k];
+        res = true;
+      }
+      f(k, seg - 1, iv, end, pa, pb, code, wc);
+    }
+  };
+  uint32_t A = 0, B = 0;
+  entries([&](int32_t, int32_t s, bool iv, bool end, uint32_t pa, uint32_t pb, uint32_t code, uint32_t wc) {
+    if (iv) {
+      if (end) {
+        A += (varint_len32(pa) + varint_len32(pb)) << 16;
+        B += 1;
+        if constexpr (!WRITE) atomicAdd(&sh.sb[s], 1u);
+      }
+      if constexpr (WGT) A += varint_len32(wc);
+    } else {
+      B += (varint_len32(code) + (WGT ? varint_len32(wc) : 0u)) << 16;
+    }
+  });
+  const int32_t sper = (r.nseg + kItvThreads - 1) / kItvThreads;
+  int32_t bytes;
+  if constexpr (!WRITE) {
+    __syncthreads();
+    uint32_t mine = (A >> 16) + (A & 0xFFFFu) + (B >> 16);
+    for (int32_t i = tid; i < r.nseg; i += kItvThreads)
+      mine += (r.hdr ? varint_len(r.e0 + sh.es[i]) : 0u) + varint_len32(sh.sb[i]);
+    (void)block_incl_scan_add<kItvThreads, int32_t>((int32_t)mine, sh.scan[0], &bytes);
+  } else {
+    static_assert(10 * kItvMax < 65536, "two sums share a word");
+    int32_t totA, totB;
+    uint32_t ea = (uint32_t)block_incl_scan_add<kItvThreads, int32_t>((int32_t)A, sh.scan[0], &totA) - A;
+    uint32_t eb = (uint32_t)block_incl_scan_add<kItvThreads, int32_t>((int32_t)B, sh.scan[1], &totB) - B;
+    {
+      uint32_t a = ea, b2 = eb;
+      entries([&](int32_t k, int32_t s, bool iv, bool end, uint32_t pa, uint32_t pb, uint32_t code, uint32_t wc) {
+        if ((heads >> k) & 1u) {
+          sh.sa[s] = a;
+          sh.sb[s] = b2;
+        }
+        if (iv) {
+          if (end) {
+            a += (varint_len32(pa) + varint_len32(pb)) << 16;
+            b2 += 1;
+          }
+          if constexpr (WGT) a += varint_len32(wc);
+        } else {
+          b2 += (varint_len32(code) + (WGT ? varint_len32(wc) : 0u)) << 16;
+        }
+      });
+    }
+    __syncthreads();
+    // a segment's section bytes and intervals: up to the next segment with entries
+    auto totals = [&](int32_t s, uint32_t& da, uint32_t& db) {
+      const int32_t e = sh.es[s + 1];
+      const int32_t nx = e < r.m ? (int32_t)sh.own[e] - 1 : -1;
+      da = (nx >= 0 ? sh.sa[nx] : (uint32_t)totA) - sh.sa[s];
+      db = (nx >= 0 ? sh.sb[nx] : (uint32_t)totB) - sh.sb[s];
+    };
+    uint32_t mine = 0;
+    for (int32_t k = 0; k < sper; ++k) {
+      const int32_t i = tid * sper + k;
+      if (i >= r.nseg) break;
+      uint32_t da = 0, db = 0;
+      if (sh.es[i + 1] > sh.es[i]) totals(i, da, db);
+      mine += (r.hdr ? varint_len(r.e0 + sh.es[i]) : 0u) + varint_len32(db & 0xFFFFu) + (da >> 16) + (da & 0xFFFFu) +
+              (db >> 16);
+    }
+    uint32_t at = (uint32_t)block_incl_scan_add<kItvThreads, int32_t>((int32_t)mine, sh.scan[2], &bytes) - mine;
+    for (int32_t k = 0; k < sper; ++k) {
+      const int32_t i = tid * sper + k;
+      if (i >= r.nseg) break;
+      uint32_t da = 0, db = 0;
+      if (sh.es[i + 1] > sh.es[i]) totals(i, da, db);
+      const uint32_t cnt = db & 0xFFFFu;
+      uint32_t q = at;
+      if (r.hdr) {
+        offs[r.u + i] = base + q;
+        q += varint_put(out + base + q, r.e0 + sh.es[i]);
+      } else if (i > 0 || !r.chunk0) {
+        // a first chunk has no entry in the table, and its place here may be
+        // that of the last chunk of the vertex before
+        cpos[(r.e0 + sh.es[i]) / LP_CHUNK_LEN] = base + q;
+      }
+      put_bytes(out, base + q, cnt);
+      q += varint_len32(cnt);
+      sh.sec[i] = q;
+      at = q + (da >> 16) + (da & 0xFFFFu) + (db >> 16);
+    }
+    __syncthreads();
+    int32_t last = -1;
+    uint32_t da = 0, db = 0, sa = 0, sb = 0;
+    uint64_t sec = 0;
+    entries([&](int32_t, int32_t s, bool iv, bool end, uint32_t pa, uint32_t pb, uint32_t code, uint32_t wc) {
+      if (s != last) {
+        totals(s, da, db);
+        sa = sh.sa[s];
+        sb = sh.sb[s];
+        sec = base + sh.sec[s];
+        last = s;
+      }
+      const uint32_t a = ea - sa, b2 = eb - sb;
+      if (iv) {
+        if (end) {
+          const uint32_t la = varint_len32(pa), lb = varint_len32(pb);
+          put_bytes(out, sec + (a >> 16), pa);
+          put_bytes(out, sec + (a >> 16) + la, pb);
+          ea += (la + lb) << 16;
+          eb += 1;
+        }
+        if constexpr (WGT) {
+          put_bytes(out, sec + (da >> 16) + (a & 0xFFFFu), wc);
+          ea += varint_len32(wc);
+        }
+      } else {
+        const uint64_t q = sec + (da >> 16) + (da & 0xFFFFu) + (b2 >> 16);
+        const uint32_t lc = varint_len32(code);
+        put_bytes(out, q, code);
+        if constexpr (WGT) put_bytes(out, q + lc, wc);
+        eb += (lc + (WGT ? varint_len32(wc) : 0u)) << 16;
+      }
+    });
+  }
+  __syncthreads();
+  return (uint32_t)bytes;
 }
 
-__global__ void k_record_size_itv(CsrIn g, uint64_t* size) {
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < g.n; u += (int64_t)gridDim.x * blockDim.x)
-    size[u] = itv_record(g, u, nullptr);
-}
-
-__global__ void k_encode_itv(CsrIn g, const uint64_t* offs, uint8_t* out) {
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < g.n; u += (int64_t)gridDim.x * blockDim.x)
-    (void)itv_record(g, u, out + offs[u]);
+// WRITE == false: the code bytes of every stretch (tsize). WRITE: the records
+// at tsize[c] (the stretch's first byte by then); vertices split into chunks
+// are listed for k_chunk_tables.
+template <bool WGT, bool WRITE>
+__global__ __launch_bounds__(kItvThreads) void k_itv(CsrIn g, const int64_t* blk, int64_t nb, uint64_t* tsize,
+                                                     uint64_t* offs, uint64_t* cpos, int32_t* split_list,
+                                                     uint32_t* nsplit, uint8_t* out) {
+  __shared__ ItvShared sh;
+  const int64_t c = blockIdx.x;
+  const int64_t v0 = blk[c], v1 = blk[c + 1];
+  const uint64_t two_m = g.xadj[g.n];
+  const uint64_t e0 = (uint64_t)c * kItvWork - (uint64_t)v0;
+  const uint64_t e1 = c + 1 < nb ? (uint64_t)(c + 1) * kItvWork - (uint64_t)v1 : two_m;
+  const uint64_t start = WRITE ? tsize[c] : 0;
+  uint64_t pos = start;
+  // the last vertex started here: split into chunks, or too long to share a run
+  const uint64_t xl = v1 > v0 ? g.xadj[v1 - 1] : 0, dl = v1 > v0 ? g.xadj[v1] - xl : 0;
+  const bool split = dl > LP_ITV_CHUNK_THRESHOLD;
+  const bool alone = !split && v1 > v0 && g.xadj[v1] - g.xadj[v0] > (uint64_t)kItvMax;
+  // chunks of the vertex continued from the stretch before; unsplit vertices;
+  // the last one alone; chunks of the last one (one call: the code is long)
+  for (int step = 0; step < 4; ++step) {
+    ItvRun r;
+    r.nseg = 0;
+    if (step == 0 || step == 3) {
+      const int64_t u = step == 0 ? v0 - 1 : v1 - 1;
+      if (step == 0 ? v0 == 0 : !split) continue;
+      const uint64_t x = g.xadj[u], d = g.xadj[u + 1] - x;
+      if (d <= LP_ITV_CHUNK_THRESHOLD) continue;
+      const uint64_t nch = (d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN;
+      if (step == 3) {
+        if (WRITE && threadIdx.x == 0) {
+          offs[u] = pos;
+          (void)varint_put(out + pos, x);
+          split_list[atomicAdd(nsplit, 1u)] = (int32_t)u;
+        }
+        pos += varint_len(x) + 4 * (nch - 1);
+      }
+      // the chunks that start in [e0, e1)
+      const uint64_t k0 = e0 > x ? (e0 - x + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN : 0;
+      const uint64_t k1 = e1 > x ? min((e1 - x + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN, nch) : 0;
+      if (k0 >= k1) continue;
+      r.e0 = x + k0 * LP_CHUNK_LEN;
+      r.m = (int32_t)(min(d, k1 * LP_CHUNK_LEN) - k0 * LP_CHUNK_LEN);
+      r.nseg = (int32_t)(k1 - k0);
+      r.u = u;
+      r.ustep = 0;
+      r.hdr = false;
+      r.chunk0 = k0 == 0;
+      for (int32_t i = threadIdx.x; i <= r.nseg; i += kItvThreads)
+        sh.es[i] = (uint16_t)min(i * (int32_t)LP_CHUNK_LEN, r.m);
+    } else {
+      const int64_t a = step == 1 ? v0 : v1 - 1, b = step == 2 || !(split || alone) ? v1 : v1 - 1;
+      if (a >= b || (step == 2 && !alone)) continue;
+      r.e0 = g.xadj[a];
+      r.m = (int32_t)(g.xadj[b] - r.e0);
+      r.nseg = (int32_t)(b - a);
+      r.u = a;
+      r.ustep = 1;
+      r.hdr = true;
+      r.chunk0 = false;
+      for (int32_t i = threadIdx.x; i <= r.nseg; i += kItvThreads) sh.es[i] = (uint16_t)(g.xadj[a + i] - r.e0);
+    }
+    __syncthreads();
+    pos += itv_run<WGT, WRITE>(g, sh, r, pos, offs, cpos, out);
+  }
+  if (!WRITE && threadIdx.x == 0) tsize[c] = pos - start;
 }
 
 // Bounded VarInt read for decompression: false past `end` or beyond 64 bits.
@@ -1091,7 +1375,8 @@ lp_status check_csr(const CsrIn& in, bool size, Scratch& sc, CsrPlan* P) {
   hipLaunchKernelGGL(k_csr_max, dim3(grid_for(P->nb, 1024, 64)), dim3(256), 0, s, tdeg, tw, wspan, P->nb, acc);
   LP_CHECK_LAUNCH();
   if (in.vwgt && in.n > 0) {
-    hipLaunchKernelGGL(k_vwgt_check, dim3(grid_for(in.n, 256, 4096)), dim3(256), 0, s, in.vwgt, in.n, &acc->err,
+    // few workgroups: each ends with an atomic on one address
+    hipLaunchKernelGGL(k_vwgt_check, dim3(grid_for(in.n, 2048, 512)), dim3(256), 0, s, in.vwgt, in.n, &acc->err,
                        &acc->vtot);
     LP_CHECK_LAUNCH();
   }
@@ -1187,21 +1472,23 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
       break;
     }
     uint64_t nbytes = cp.nbytes;
-    if (intervals) {
-      uint64_t* size = sc.alloc<uint64_t>((size_t)n + 1);
-      uint64_t* total_dev = sc.alloc<uint64_t>(1);
-      if (!size || !total_dev) {
-        st = LP_ENOMEM;
+    if (intervals && n > 0) {
+      cp.nb = merged_stretches(two_m, n, kItvWork);
+      cp.blk = sc.alloc<int64_t>((size_t)cp.nb + 1);
+      cp.tbase = sc.alloc<uint64_t>(cp.nb);
+      if (cp.nb > 0x7FFFFFFFll || sc.failed) {
+        st = sc.failed ? LP_ENOMEM : LP_EUNSUPPORTED;
         break;
       }
-      if (n > 0) {
-        hipLaunchKernelGGL(k_record_size_itv, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, in, size);
-        st = last_error();
-        if (st) break;
-      }
-      st = scan_exclusive_u64(size, g->offs, n, total_dev, sc);
+      st = merged_blocks(xadj, n, kItvWork, cp.nb, cp.blk, &cp.acc->xerr, s);
       if (st) break;
-      if (hipMemcpyAsync(&nbytes, total_dev, sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipLaunchKernelGGL((g->weighted ? k_itv<true, false> : k_itv<false, false>), dim3((unsigned)cp.nb),
+                         dim3(kItvThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, (uint64_t*)nullptr, (uint64_t*)nullptr,
+                         (int32_t*)nullptr, (uint32_t*)nullptr, (uint8_t*)nullptr);
+      st = last_error();
+      if (!st) st = scan_exclusive_u64(cp.tbase, cp.tbase, cp.nb, &cp.acc->nbytes, sc);
+      if (st) break;
+      if (hipMemcpyAsync(&nbytes, &cp.acc->nbytes, sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
           hipStreamSynchronize(s) != hipSuccess) {
         st = LP_EDEVICE;
         break;
@@ -1219,24 +1506,28 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
       st = LP_EDEVICE;
       break;
     }
-    if (n > 0 && intervals) {
-      hipLaunchKernelGGL(k_encode_itv, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, in, g->offs, g->bytes);
-      st = last_error();
-    } else if (n > 0) {
-      const bool split = cp.max_deg > LP_CHUNK_THRESHOLD;
+    if (n > 0) {
+      const uint64_t thr = chunk_threshold(intervals);
+      const bool split = cp.max_deg > (int64_t)thr;
       uint64_t* cpos = split ? sc.alloc<uint64_t>(two_m / LP_CHUNK_LEN + 1) : nullptr;
-      int32_t* list = split ? sc.alloc<int32_t>(two_m / LP_CHUNK_THRESHOLD + 1) : nullptr;
+      int32_t* list = split ? sc.alloc<int32_t>(two_m / thr + 1) : nullptr;
       if (sc.failed) {
         st = LP_ENOMEM;
         break;
       }
-      auto kern = g->weighted ? k_csr_encode<true, true>
-                              : two_m < (1ull << 35) ? k_csr_encode<false, false> : k_csr_encode<false, true>;
-      hipLaunchKernelGGL(kern, dim3((unsigned)cp.nb), dim3(kCtThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, g->offs,
-                         cpos, list, &cp.acc->nsplit, g->bytes);
+      if (intervals) {
+        hipLaunchKernelGGL((g->weighted ? k_itv<true, true> : k_itv<false, true>), dim3((unsigned)cp.nb),
+                           dim3(kItvThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, g->offs, cpos, list,
+                           &cp.acc->nsplit, g->bytes);
+      } else {
+        auto kern = g->weighted ? k_csr_encode<true, true>
+                                : two_m < (1ull << 35) ? k_csr_encode<false, false> : k_csr_encode<false, true>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)cp.nb), dim3(kCtThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, g->offs,
+                           cpos, list, &cp.acc->nsplit, g->bytes);
+      }
       st = last_error();
       if (st || !split) break;
-      hipLaunchKernelGGL(k_chunk_tables, dim3(grid_for((int64_t)(two_m / LP_CHUNK_THRESHOLD + 1), 4, 1024)), dim3(256),
+      hipLaunchKernelGGL(k_chunk_tables, dim3(grid_for((int64_t)(two_m / thr + 1), 4, 1024)), dim3(256),
                          0, s, in, list, &cp.acc->nsplit, g->offs, cpos, g->bytes);
       st = last_error();
     }

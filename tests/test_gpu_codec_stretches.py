@@ -74,3 +74,65 @@ def test_long_codes_and_windows(lp, synth_mod, n, deg, seed, weighted):
     assert np.array_equal(x.cpu().numpy().view(np.uint64), g.xadj)
     assert np.array_equal(a.cpu().numpy(), g.adjncy)
     assert np.array_equal(ww.cpu().numpy(), g.adjwgt if weighted else np.ones(g.two_m, np.int32))
+
+
+def _runs_graph(synth_mod, n, seed, hub, weighted, dup=False):
+    """Vertices whose neighbourhoods mix runs of consecutive IDs of every length
+    with single IDs; the last vertex of a stretch is often long."""
+    rng = np.random.default_rng(seed)
+    edges = []
+    for u in range(0, n, 37):
+        v = u + 1
+        while v < min(n, u + int(rng.integers(2, hub))):
+            ln = int(rng.integers(1, 7))
+            edges += [(u, x) for x in range(v, min(n, v + ln))]
+            v += ln + int(rng.integers(1, 4))
+    e = np.unique(np.array(edges, dtype=np.int64), axis=0)
+    if dup:
+        e = np.concatenate([e, e[::5]])
+    w = rng.integers(1, 5000, len(e)) if weighted else None
+    return synth_mod.from_edges(n, e, w)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("n,hub,dup", [(64, 40, False), (1500, 60, True), (6000, 3000, False), (9000, 4800, True),
+                                       (14000, 9000, False)])
+def test_interval_records(lp, oracle_mod, synth_mod, n, hub, dup, weighted):
+    g = _runs_graph(synth_mod, n, n + hub, hub, weighted, dup)
+    if n == 6000:  # a long tail of isolated vertices
+        g.n += 5000
+        g.xadj = np.concatenate([g.xadj, np.full(5000, g.xadj[-1], dtype=np.uint64)])
+    G = lp.lp_compress(g.n, g.xadj.view(np.int64), g.adjncy, g.adjwgt, intervals=True)
+    offs, data = lp.lp_graph_export(G)
+    o, b = oracle_mod.compress(g.n, g.xadj, g.adjncy, g.adjwgt, intervals=True)
+    assert np.array_equal(offs.cpu().numpy().view(np.uint64), o)
+    assert np.array_equal(data.cpu().numpy(), b)
+    x, a, w, _ = lp.lp_decompress(G)
+    assert np.array_equal(x.cpu().numpy().view(np.uint64), g.xadj)
+    assert np.array_equal(a.cpu().numpy(), g.adjncy)
+    assert np.array_equal(w.cpu().numpy(), g.adjwgt if weighted else np.ones(g.two_m, np.int32))
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("case", CASES + [(1023, 1, 4000, 0), (1023, 0, 4001, 2), (500, 1, 4096, 0), (40, 5, 13002, 9)])
+def test_interval_records_across_stretches(lp, oracle_mod, synth_mod, case, weighted):
+    before, iso, d, tail = case
+    g = _star(synth_mod, before, iso, d, weighted, tail)
+    G = lp.lp_compress(g.n, g.xadj.view(np.int64), g.adjncy, g.adjwgt, intervals=True)
+    offs, data = lp.lp_graph_export(G)
+    o, b = oracle_mod.compress(g.n, g.xadj, g.adjncy, g.adjwgt, intervals=True)
+    assert np.array_equal(offs.cpu().numpy().view(np.uint64), o)
+    assert np.array_equal(data.cpu().numpy(), b)
+
+
+@pytest.mark.parametrize("intervals", [False, True])
+@pytest.mark.parametrize("a,b", [(2, 16001), (3, 10999), (5, 4001), (4, 12000), (3, 5001)])
+def test_split_records_next_to_each_other(lp, oracle_mod, synth_mod, a, b, intervals):
+    # hubs 0 .. a - 1 with the same b neighbours: the last chunk of one and the
+    # first chunk of the next start within a chunk length of each other
+    g = synth_mod.from_edges(a + b, [(h, v) for h in range(a) for v in range(a, a + b)])
+    G = lp.lp_compress(g.n, g.xadj.view(np.int64), g.adjncy, intervals=intervals)
+    offs, data = lp.lp_graph_export(G)
+    o, d = oracle_mod.compress(g.n, g.xadj, g.adjncy, intervals=intervals)
+    assert np.array_equal(offs.cpu().numpy().view(np.uint64), o)
+    assert np.array_equal(data.cpu().numpy(), d)
