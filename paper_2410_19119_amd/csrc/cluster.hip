@@ -138,14 +138,16 @@ __global__ __launch_bounds__(256) void k_rate_lane(RoundCtx x, VDesc vd, int32_t
       uint64_t pos = vd_pos(v4);
       int32_t v = 0, w = 0;
       LaneDec dec;
+      VarCursor cur;
       if constexpr (ITV) dec.init(x.g, u, pos);
+      else if constexpr (COMP) cur.seek(x.g.bytes, pos);
       for (int k = 0; k < d; ++k) {
         if constexpr (ITV) {
           dec.next(v, w);
         } else if constexpr (COMP) {
-          const uint64_t code = varint_read(x.g.bytes, pos);
-          v = (k == 0) ? u + (int32_t)unzigzag(code) : v + (int32_t)code;
-          if (x.g.weighted) w = (k == 0 ? 0 : w) + (int32_t)unzigzag(varint_read(x.g.bytes, pos));
+          const uint32_t code = cur.next();
+          v = (k == 0) ? u + unzigzag32(code) : v + (int32_t)code;
+          if (x.g.weighted) w = (k == 0 ? 0 : w) + unzigzag32(cur.next());
           else w = 1;
         } else {
           v = x.g.adjncy[pos + k];
@@ -179,16 +181,17 @@ __global__ __launch_bounds__(256) void k_rate_lane(RoundCtx x, VDesc vd, int32_t
       }
     }
   } else if constexpr (COMP) {
-    uint64_t pos = vd_pos(v4);
+    VarCursor cur;
+    cur.seek(x.g.bytes, vd_pos(v4));
     int32_t v = 0, w = 0;
 #pragma unroll
     for (int k = 0; k < kMaxLane; ++k) {
       lab[k] = -1;
       wt[k] = 0;
       if (k < d) {
-        const uint64_t code = varint_read(x.g.bytes, pos);
-        v = (k == 0) ? u + (int32_t)unzigzag(code) : v + (int32_t)code;
-        if (x.g.weighted) w = (k == 0 ? 0 : w) + (int32_t)unzigzag(varint_read(x.g.bytes, pos));
+        const uint32_t code = cur.next();
+        v = (k == 0) ? u + unzigzag32(code) : v + (int32_t)code;
+        if (x.g.weighted) w = (k == 0 ? 0 : w) + unzigzag32(cur.next());
         else w = 1;
         lab[k] = x.C[v];
         wt[k] = w;
@@ -2446,6 +2449,273 @@ __global__ __launch_bounds__(256) void k_apply(SortedPairs sp, const uint32_t* c
   }
 }
 
+// The whole acceptance of a graph of at most kSaThreads * kSaRows vertices,
+// one workgroup, one launch: the same steps on proposals that stay in
+// registers and change places through LDS. Item (w, i, lane) - wavefront, row,
+// lane - is number w * 64 * rows + i * 64 + lane of the order, rows as few as
+// the round's proposals need. The launches are what such a round costs: six or
+// seven of them took 45 us for 2000 to 4000 vertices, this takes 17 to 22. With
+// sixteen rows (16384 vertices) it took 212 us against 52: one workgroup runs
+// all of its code once, and the unrolled rows made that 60 KB to fetch.
+constexpr int kSaThreads = 1024;
+constexpr int kSaWaves = kSaThreads / kWave;
+constexpr int kSaRows = 4;
+
+struct SaShared {
+  uint64_t stage[kSaThreads * kSaRows];
+  uint16_t cnt[kSaWaves][256];
+  uint64_t red[kSaWaves];
+  int64_t tail[kSaWaves];
+  int32_t scan[kSaWaves];
+  uint32_t head[kSaWaves];
+  int32_t first_seg[kSaWaves + 1], first_w[kSaWaves + 1];
+};
+
+__global__ __launch_bounds__(kSaThreads) void k_accept_small(int32_t* ptgt, const int64_t* pgain, int32_t n, int G,
+                                                             int passes, int reset, RoundCtl* ctl, int round, int last,
+                                                             const int32_t* vwgt, int64_t cap, const int32_t* gid,
+                                                             const int64_t* gcap, int32_t* C, int64_t* W, int4* mv,
+                                                             int32_t* Cc, const int32_t* pos) {
+  __shared__ SaShared sh;
+  if (ctl->done) return;
+  const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
+  const uint64_t lt = lanemask_lt();
+  const uint64_t dmax = (G >= 64) ? ~0ull : ((1ull << G) - 1);
+  uint64_t key[kSaRows];
+  uint32_t val[kSaRows];
+  // proposals in vertex order
+  uint32_t have = 0;
+  uint64_t valid[kSaRows];
+#pragma unroll
+  for (int i = 0; i < kSaRows; ++i) {
+    const int32_t u = w * kWave * kSaRows + i * kWave + lane;
+    const int32_t t = u < n ? ptgt[u] : -1;
+    val[i] = (uint32_t)u;
+    key[i] = 0;
+    if (t >= 0) {
+      key[i] = ((uint64_t)(uint32_t)t << G) | (dmax - (uint64_t)pgain[u]);
+      if (reset) ptgt[u] = -1;
+    }
+    valid[i] = __ballot(t >= 0);
+    have += (uint32_t)__popcll(valid[i]);
+  }
+  if (lane == 0) sh.scan[w] = (int32_t)have;
+  __syncthreads();
+  uint32_t before = 0, count = 0;
+#pragma unroll
+  for (int k = 0; k < kSaWaves; ++k) {
+    if (k < w) before += (uint32_t)sh.scan[k];
+    count += (uint32_t)sh.scan[k];
+  }
+  if (tid == 0) {
+    ctl->count = count;
+    if (round < 64) ctl->stats[round] += count;
+    ctl->round_props += count;
+    if (last) {
+      if (ctl->round_props == 0) ctl->done = 1;
+      else ctl->rounds_run = round + 1;
+      ctl->round_props = 0;
+    }
+  }
+  if (count == 0) return;
+  const int rows = (int)((count + kSaThreads - 1) / kSaThreads);
+  const uint32_t base = (uint32_t)(w * kWave * rows + lane);  // item (w, 0, lane)
+  uint32_t place[kSaRows];
+#pragma unroll
+  for (int i = 0; i < kSaRows; ++i) {
+    place[i] = (valid[i] >> lane) & 1u ? before + (uint32_t)__popcll(valid[i] & lt) : ~0u;
+    before += (uint32_t)__popcll(valid[i]);
+  }
+  // every item to its place: keys, then values, through the same memory
+  auto exchange = [&](int from_rows) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSaRows; ++i)
+      if (i < from_rows && place[i] != ~0u) sh.stage[place[i]] = key[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSaRows; ++i) {
+      const uint32_t q = base + (uint32_t)i * kWave;
+      key[i] = i < rows && q < count ? sh.stage[q] : 0;
+    }
+    __syncthreads();
+    uint32_t* st = (uint32_t*)sh.stage;
+#pragma unroll
+    for (int i = 0; i < kSaRows; ++i)
+      if (i < from_rows && place[i] != ~0u) st[place[i]] = val[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSaRows; ++i) {
+      const uint32_t q = base + (uint32_t)i * kWave;
+      val[i] = i < rows && q < count ? st[q] : 0;
+    }
+  };
+  exchange(kSaRows);
+  // digits that differ between keys
+  uint64_t diff = 0;
+  {
+    if (tid == 0) sh.red[0] = key[0];
+    __syncthreads();
+    const uint64_t k0 = sh.red[0];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSaRows; ++i)
+      if (i < rows && base + (uint32_t)i * kWave < count) diff |= key[i] ^ k0;
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) diff |= __shfl_xor((unsigned long long)diff, d, kWave);
+    if (lane == 0) sh.red[w] = diff;
+    __syncthreads();
+    diff = 0;
+#pragma unroll
+    for (int k = 0; k < kSaWaves; ++k) diff |= sh.red[k];
+  }
+  for (int p = 0; p < passes; ++p) {
+    if (((diff >> (8 * p)) & 255u) == 0) continue;
+    for (int q = tid; q < kSaWaves * 128; q += kSaThreads) ((uint32_t*)sh.cnt)[q] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSaRows; ++i) {
+      place[i] = ~0u;
+      if (i >= rows) continue;
+      const bool ok = base + (uint32_t)i * kWave < count;
+      const uint32_t d = (uint32_t)(key[i] >> (8 * p)) & 255u;
+      uint64_t peers = __ballot(ok);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const uint64_t m = __ballot((d >> q) & 1u);
+        peers &= ((d >> q) & 1u) ? m : ~m;
+      }
+      const uint32_t r = (uint32_t)__popcll(peers & lt), c = (uint32_t)__popcll(peers);
+      uint32_t b0 = 0;
+      if (ok) b0 = sh.cnt[w][d];
+      wave_sync_lds();
+      if (ok && r + 1 == c) sh.cnt[w][d] = (uint16_t)(b0 + c);
+      wave_sync_lds();
+      if (ok) place[i] = b0 + r;
+    }
+    __syncthreads();
+    // thread t < 256: digit t's count per wavefront becomes the first place
+    uint32_t c = 0;
+    if (tid < 256)
+      for (int k = 0; k < kSaWaves; ++k) c += sh.cnt[k][tid];
+    int32_t tot;
+    uint32_t at = (uint32_t)block_incl_scan_add<kSaThreads, int32_t>((int32_t)c, sh.scan, &tot) - c;
+    if (tid < 256)
+      for (int k = 0; k < kSaWaves; ++k) {
+        const uint32_t x = sh.cnt[k][tid];
+        sh.cnt[k][tid] = (uint16_t)at;
+        at += x;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSaRows; ++i)
+      if (i < rows && place[i] != ~0u) place[i] += sh.cnt[w][(uint32_t)(key[i] >> (8 * p)) & 255u];
+    exchange(rows);
+  }
+  // admission (as k_admit): running weights along each target's segment
+  auto seg_of = [&](int i) {
+    return i < rows && base + (uint32_t)i * kWave < count ? (int32_t)(key[i] >> G) : -1;
+  };
+  int32_t wt[kSaRows];
+#pragma unroll
+  for (int i = 0; i < kSaRows; ++i) {
+    wt[i] = 0;
+    if (seg_of(i) >= 0) wt[i] = vwgt ? vwgt[val[i]] : 1;
+  }
+  if (lane == 0) {
+    sh.first_seg[w] = seg_of(0);
+    sh.first_w[w] = wt[0];
+  }
+#pragma unroll
+  for (int i = 0; i < kSaRows; ++i)
+    if (i + 1 == rows && lane == kWave - 1) sh.scan[w] = seg_of(i);  // last item of the wavefront
+  if (tid == 0) {
+    sh.first_seg[kSaWaves] = -1;
+    sh.first_w[kSaWaves] = 0;
+  }
+  __syncthreads();
+  int64_t sum[kSaRows];
+  uint32_t f = 0;     // a segment has started in the wavefront's rows so far
+  int64_t run = 0;    // sum since then
+  uint32_t open = 0;  // rows' items before the wavefront's first start
+  int32_t last_seg = w ? sh.scan[w - 1] : -1;
+#pragma unroll
+  for (int i = 0; i < kSaRows; ++i) {
+    sum[i] = 0;
+    if (i >= rows) continue;
+    const int32_t sg = seg_of(i);
+    int32_t prev = __shfl_up(sg, 1, kWave);
+    if (lane == 0) prev = last_seg;
+    last_seg = __builtin_amdgcn_readlane(sg, kWave - 1);
+    uint32_t fi = sg != prev ? 1u : 0u;
+    int64_t si = wt[i];
+    wave_seg_scan_i64(fi, si);
+    if (!fi) {
+      si += run;
+      open |= (f ? 0u : 1u) << i;
+    }
+    sum[i] = si;
+    f |= (uint32_t)__builtin_amdgcn_readlane((int)fi, kWave - 1);
+    run = __shfl(si, kWave - 1, kWave);
+  }
+  if (lane == 0) {
+    sh.head[w] = f;
+    sh.tail[w] = run;
+  }
+  __syncthreads();
+  int64_t pre = 0;
+  for (int k = 0; k < w; ++k) pre = sh.head[k] ? sh.tail[k] : pre + sh.tail[k];
+  uint32_t okm = 0, lastm = 0;  // admitted; the target's last admitted
+#pragma unroll
+  for (int i = 0; i < kSaRows; ++i) {
+    if (i >= rows) continue;
+    if ((open >> i) & 1u) sum[i] += pre;
+    const int32_t t = seg_of(i);
+    int32_t sn = __shfl_down(t, 1, kWave), wn = __shfl_down(wt[i], 1, kWave);
+    const bool more_rows = i + 1 < rows;
+    const int32_t s0 = more_rows ? __builtin_amdgcn_readlane(seg_of((i + 1) % kSaRows), 0) : sh.first_seg[w + 1];
+    const int32_t w0 = more_rows ? __builtin_amdgcn_readlane(wt[(i + 1) % kSaRows], 0) : sh.first_w[w + 1];
+    if (lane == kWave - 1) {
+      sn = s0;
+      wn = w0;
+    }
+    if (t < 0) continue;
+    const int64_t room = (gid ? gcap[gid[t]] : cap) - W[t];
+    if (sum[i] > room) continue;
+    okm |= 1u << i;
+    if (!(sn == t && sum[i] + wn <= room)) lastm |= 1u << i;
+  }
+  __syncthreads();  // every weight has been read: the moves
+  int64_t moves = 0;
+#pragma unroll
+  for (int i = 0; i < kSaRows; ++i) {
+    const int32_t t = seg_of(i);
+    if (t < 0) continue;
+    const uint32_t q = base + (uint32_t)i * kWave;
+    if (!((okm >> i) & 1u)) {
+      if (mv) mv[q] = make_int4(-1, 0, 0, 0);
+      continue;
+    }
+    const int32_t u = (int32_t)val[i];
+    int32_t old;
+    if (Cc) {
+      const int32_t pu = pos[u];
+      old = Cc[pu];
+      Cc[pu] = t;
+    } else {
+      old = C[u];
+      C[u] = t;
+    }
+    if (mv) mv[q] = make_int4(u, old, t, 0);
+    if ((lastm >> i) & 1u) atomicAdd((unsigned long long*)&W[t], (unsigned long long)sum[i]);
+    atomicAdd((unsigned long long*)&W[old], (unsigned long long)(-(int64_t)wt[i]));
+    ++moves;
+  }
+  moves = block_reduce_add<kSaThreads, int64_t>(moves, sh.tail);
+  if (tid == 0 && moves && round < 64)
+    atomicAdd((unsigned long long*)&ctl->stats[64 + round], (unsigned long long)moves);
+}
+
 // The caller's labels after rounds on the degree-ordered copy: vertex i of
 // the copy is original vertex orig[i].
 __global__ void k_ro_labels(int32_t n, const int32_t* orig, const int32_t* Cc, int32_t* C) {
@@ -3193,11 +3463,13 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
   int64_t* W = sc.alloc<int64_t>(n);
   int32_t* ptgt = sc.alloc<int32_t>(n);
   int64_t* pgain = sc.alloc<int64_t>(n);
-  uint64_t* ka = sc.alloc<uint64_t>(n);
-  uint64_t* kb = sc.alloc<uint64_t>(n);
-  uint32_t* va = sc.alloc<uint32_t>(n);
-  uint32_t* vb = sc.alloc<uint32_t>(n);
-  int64_t* adm = sc.alloc<int64_t>(n);
+  // one workgroup accepts a whole round of a small graph
+  const bool tiny = n <= kSaThreads * kSaRows;
+  uint64_t* ka = tiny ? nullptr : sc.alloc<uint64_t>(n);
+  uint64_t* kb = tiny ? nullptr : sc.alloc<uint64_t>(n);
+  uint32_t* va = tiny ? nullptr : sc.alloc<uint32_t>(n);
+  uint32_t* vb = tiny ? nullptr : sc.alloc<uint32_t>(n);
+  int64_t* adm = tiny ? nullptr : sc.alloc<int64_t>(n);
   int4* mv = use_gt ? sc.alloc<int4>(n) : nullptr;
   const unsigned ncp = grid_for(n, kCpTile, 0x7FFFFFFF);
   const bool few = n <= kCpFew;
@@ -3215,10 +3487,10 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
   uint64_t* look_a = look_c + ncp;
   uint32_t look_launch = 0;
   PairSorter sorter;
-  LP_CHECK(sorter.init(ka, va, kb, vb, n, G + nbits, sc));
+  if (!tiny) LP_CHECK(sorter.init(ka, va, kb, vb, n, G + nbits, sc));
   LP_CHECK(zero_u32(ctl_mem, nctl, s));
   LP_CHECK(zero_u32(hand, nhand, s));
-  LP_CHECK(zero_u32(sorter.zero_base(), sorter.zero_words(), s));
+  if (!tiny) LP_CHECK(zero_u32(sorter.zero_base(), sorter.zero_words(), s));
   if (batch) {
     LP_CHECK_HIP(hipMemcpyAsync(gcap, caps, g->nbatch * sizeof(int64_t), hipMemcpyHostToDevice, s));
     LP_CHECK_HIP(hipMemcpyAsync(gseed, seeds, g->nbatch * sizeof(uint64_t), hipMemcpyHostToDevice, s));
@@ -3494,20 +3766,28 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
       }
       // acceptance: compact in vertex order, sort by (target, gain desc)
       LP_CHECK(begin(LP_PHASE_ACCEPT));
-      hipLaunchKernelGGL(few ? k_prop_collect<kCpSubFew> : k_prop_collect<kCpSubMany>, dim3(ncollect),
-                         dim3(kCpThreads), 0, s, ptgt, pgain, n, G, ka, va,
-                         (S > 1 || use_ro) ? 1 : 0, LookArgs{look_c, &ctl->ticket, ++look_launch}, ctl, r,
-                         sr == S - 1 ? 1 : 0);
-      LP_CHECK_LAUNCH();
-      LP_CHECK(sorter.sort(&ctl->count));
-      hipLaunchKernelGGL(k_admit, dim3(ncp), dim3(kCpThreads), 0, s, sorter.out(), &ctl->count, G, g->vwgt, W, cap,
-                         x.gid, gcap, LookArgs{look_a, &ctl->ticket, look_launch}, adm);
-      LP_CHECK_LAUNCH();
-      const bool bins = init_k > 0 && init_k <= kInitBins;
-      hipLaunchKernelGGL(bins ? k_apply<true> : k_apply<false>, dim3(grid_for(n, 256, bins ? 1024 : 8192)), dim3(256), 0,
-                         s, sorter.out(), &ctl->count, G, adm, g->vwgt, labels, W, ctl->stats, r, mv, Cc,
-                         use_ro ? ro->pos : nullptr, init_k);
-      LP_CHECK_LAUNCH();
+      const int reset = S > 1 || use_ro ? 1 : 0, last_sub = sr == S - 1 ? 1 : 0;
+      if (tiny) {
+        hipLaunchKernelGGL(k_accept_small, dim3(1), dim3(kSaThreads), 0, s, ptgt, pgain, n, G, (G + nbits + 7) / 8,
+                           reset, ctl, r, last_sub, g->vwgt, cap, x.gid, gcap, labels, W, mv, Cc,
+                           use_ro ? ro->pos : nullptr);
+        LP_CHECK_LAUNCH();
+      } else {
+        hipLaunchKernelGGL(few ? k_prop_collect<kCpSubFew> : k_prop_collect<kCpSubMany>, dim3(ncollect),
+                           dim3(kCpThreads), 0, s, ptgt, pgain, n, G, ka, va,
+                           reset, LookArgs{look_c, &ctl->ticket, ++look_launch}, ctl, r,
+                           last_sub);
+        LP_CHECK_LAUNCH();
+        LP_CHECK(sorter.sort(&ctl->count));
+        hipLaunchKernelGGL(k_admit, dim3(ncp), dim3(kCpThreads), 0, s, sorter.out(), &ctl->count, G, g->vwgt, W, cap,
+                           x.gid, gcap, LookArgs{look_a, &ctl->ticket, look_launch}, adm);
+        LP_CHECK_LAUNCH();
+        const bool bins = init_k > 0 && init_k <= kInitBins;
+        hipLaunchKernelGGL(bins ? k_apply<true> : k_apply<false>, dim3(grid_for(n, 256, bins ? 1024 : 8192)), dim3(256), 0,
+                           s, sorter.out(), &ctl->count, G, adm, g->vwgt, labels, W, ctl->stats, r, mv, Cc,
+                           use_ro ? ro->pos : nullptr, init_k);
+        LP_CHECK_LAUNCH();
+      }
       if (use_gt) LP_CHECK(gt_update(gt.t, mv, &ctl->count, n, labels, s));
       LP_CHECK(end());
     }

@@ -165,17 +165,15 @@ __device__ bool group_decode(const uint8_t* __restrict__ bytes, uint64_t& pos, i
 // interval weights (a second cursor), then the gap-coded residuals, whose
 // codes follow the interval weights.
 struct LaneDec {
-  const uint8_t* b;
-  uint64_t pos;   // next pair, then next residual code
-  uint64_t wpos;  // next interval weight
+  VarCursor c;   // next pair, then next residual code
+  VarCursor wc;  // next interval weight
   int32_t u, x, v, w;
   uint32_t kleft, rem;
   bool weighted, itv, first_res;
 
   __device__ __forceinline__ void init(const GraphView& g, int32_t u_, uint64_t p) {
-    b = g.bytes;
+    c.seek(g.bytes, p);
     u = u_;
-    pos = p;
     weighted = g.weighted != 0;
     itv = g.intervals != 0;
     x = v = w = 0;
@@ -183,30 +181,30 @@ struct LaneDec {
     kleft = 0;
     first_res = true;
     if (itv) {
-      kleft = (uint32_t)varint_read(b, pos);
-      wpos = pos;
-      for (uint32_t j = 0; j < 2 * kleft; ++j) (void)varint_read(b, wpos);
-      if (kleft == 0) pos = wpos;
+      kleft = c.next();
+      wc = c;
+      for (uint32_t j = 0; j < 2 * kleft; ++j) (void)wc.next();
+      if (kleft == 0) c = wc;
     }
   }
 
   __device__ __forceinline__ void next(int32_t& ov, int32_t& ow) {
     if (rem > 0 || kleft > 0) {
       if (rem == 0) {
-        x = u + (int32_t)unzigzag(varint_read(b, pos));
-        rem = 3 + (uint32_t)varint_read(b, pos);
+        x = u + unzigzag32(c.next());
+        rem = 3 + c.next();
         --kleft;
       }
       ov = x++;
       --rem;
-      if (weighted) w += (int32_t)unzigzag(varint_read(b, wpos));
-      if (rem == 0 && kleft == 0) pos = wpos;  // residuals follow the interval weights
+      if (weighted) w += unzigzag32(wc.next());
+      if (rem == 0 && kleft == 0) c = wc;  // residuals follow the interval weights
     } else {
-      const uint64_t code = varint_read(b, pos);
-      v = first_res ? u + (int32_t)unzigzag(code) : v + (int32_t)code;
+      const uint32_t code = c.next();
+      v = first_res ? u + unzigzag32(code) : v + (int32_t)code;
       first_res = false;
       ov = v;
-      if (weighted) w += (int32_t)unzigzag(varint_read(b, pos));
+      if (weighted) w += unzigzag32(c.next());
     }
     ow = weighted ? w : 1;
   }

@@ -62,19 +62,64 @@ __device__ __forceinline__ uint32_t part_hash(uint32_t c) {
 __device__ __forceinline__ int64_t unzigzag(uint64_t z) { return (int64_t)(z >> 1) ^ -(int64_t)(z & 1); }
 __device__ __forceinline__ int32_t unzigzag32(uint32_t z) { return (int32_t)(z >> 1) ^ -(int32_t)(z & 1); }
 
+// Sixteen bytes at any address (a record may be read past its end: the bytes
+// of a graph are followed by padding).
+struct __attribute__((packed, aligned(1))) Bytes16 {
+  uint64_t lo, hi;
+};
+
 // Serial VarInt read (one lane), LEB128 order: low 7-bit group first, high bit
-// of a byte = another byte follows.
+// of a byte = another byte follows. The bytes come in one load.
 __device__ __forceinline__ uint64_t varint_read(const uint8_t* __restrict__ b, uint64_t& pos) {
+  const Bytes16 w = *(const Bytes16*)(b + pos);
   uint64_t x = 0;
-  int shift = 0;
-  while (true) {
-    uint32_t c = b[pos++];
-    x |= (uint64_t)(c & 0x7F) << shift;
-    if (!(c & 0x80)) break;
-    shift += 7;
+#pragma unroll
+  for (int k = 0; k < 10; ++k) {
+    const uint64_t c = k < 8 ? w.lo >> (8 * k) : w.hi >> (8 * (k - 8));
+    x |= (c & 0x7F) << (7 * k);
+    if (!(c & 0x80)) {
+      pos += (uint64_t)(k + 1);
+      return x;
+    }
   }
+  pos += 10;
   return x;
 }
+
+// One lane's cursor over a stream of VarInts of at most five bytes: sixteen
+// bytes are loaded at a time and shifted out, so a neighbourhood takes a
+// memory round trip for every seven or so of its codes instead of one for
+// every byte.
+struct VarCursor {
+  const uint8_t* b;
+  uint64_t pos;
+  uint64_t lo, hi;
+  uint32_t left;  // bytes of the window not consumed yet
+
+  __device__ __forceinline__ void seek(const uint8_t* bytes, uint64_t p) {
+    b = bytes;
+    pos = p;
+    left = 0;
+  }
+  __device__ __forceinline__ uint32_t next() {
+    if (left < 5) {
+      const Bytes16 w = *(const Bytes16*)(b + pos);
+      lo = w.lo;
+      hi = w.hi;
+      left = 16;
+    }
+    const uint64_t t = ~lo & 0x8080808080ull;  // bytes that end a number
+    const uint32_t len = t ? ((uint32_t)__ffsll((unsigned long long)t)) >> 3 : 5u;
+    const uint64_t y = lo & (t ^ (t - 1ull));
+    const uint32_t v = ((uint32_t)y & 0x7Fu) | ((uint32_t)(y >> 1) & 0x3F80u) | ((uint32_t)(y >> 2) & 0x1FC000u) |
+                       ((uint32_t)(y >> 3) & 0xFE00000u) | ((uint32_t)((y >> 32) & 0xFu) << 28);
+    lo = (lo >> (8 * len)) | (hi << (64 - 8 * len));
+    hi >>= 8 * len;
+    left -= len;
+    pos += len;
+    return v;
+  }
+};
 
 // First edge ID header of vertex u and the byte position right after it.
 __device__ __forceinline__ uint64_t read_header(const GraphView& g, int32_t u, uint64_t& pos) {
