@@ -124,10 +124,9 @@ __device__ __forceinline__ void consider(const RoundCtx& x, const VParams& p, in
 }
 
 // ------------------------------------------------------- lane per vertex --
-template <bool COMP, int MODE = kModeRate, bool ITV = false>
-__global__ __launch_bounds__(256) void k_rate_lane(RoundCtx x, VDesc vd, int32_t cnt) {
-  if (*x.done) return;
-  const int32_t i = blockIdx.x * 256 + threadIdx.x;
+template <bool COMP, int MODE, bool ITV>
+__device__ __forceinline__ void rate_lane(const RoundCtx& x, VDesc vd, int32_t cnt, uint32_t block) {
+  const int32_t i = block * 256 + threadIdx.x;
   if constexpr (MODE == kModeCut) {
     __shared__ unsigned long long red[4];
     unsigned long long c = 0;
@@ -256,6 +255,12 @@ __global__ __launch_bounds__(256) void k_rate_lane(RoundCtx x, VDesc vd, int32_t
   emit(x, u, best, own);
 }
 
+template <bool COMP, int MODE = kModeRate, bool ITV = false>
+__global__ __launch_bounds__(256) void k_rate_lane(RoundCtx x, VDesc vd, int32_t cnt) {
+  if (*x.done) return;
+  rate_lane<COMP, MODE, ITV>(x, vd, cnt, blockIdx.x);
+}
+
 // ------------------------------------------- LDS rating table (phase one) --
 template <typename V>
 __device__ __forceinline__ void lds_add(V* p, V w) {
@@ -302,13 +307,15 @@ struct TileCfg {
   static constexpr int kSelGroup = VT > 8 ? kWave : NT;  // threads per selected vertex
 };
 
-// Waves per SIMD a tile kernel is compiled for: the small tiles' rating of a
-// compressed graph is capped at 80 registers, so six workgroups share a CU
-// (as many as their LDS allows) to hide the latency of their gathers and
-// barriers; other instances keep the compiler's choice.
+// Waves per SIMD a tile kernel is compiled for: the rating of a compressed
+// graph is capped at 80 registers, so as many workgroups share a CU as their
+// LDS allows (six of 256 threads, three of 512) to hide the latency of their
+// gathers and barriers: left alone the compiler takes 81 to 88 for the large
+// tiles, which then run two to a CU (R-MAT 2^24: 1.59 instead of 1.22 ms per
+// round). Other instances keep the compiler's choice.
 template <class T, int MODE, bool COMP>
 constexpr int tile_waves_per_eu() {
-  return T::kThreads == 256 && MODE == kModeRate && COMP ? 6 : 1;
+  return MODE == kModeRate && COMP ? 6 : 1;
 }
 using TileSmall = TileCfg<256, 2048, 80>;
 using TileLarge = TileCfg<512, 4096, 4>;
@@ -322,8 +329,8 @@ constexpr int kTileSeg = 128;  // vertices walked by one thread of the tiling pa
 // time from counters alone, the 60 tiles of an RGG of 2^20 vertices (degree 8)
 // kept eight workgroups busy while 2048 queued on the counters, 0.27 ms per
 // round for what takes 0.02.
-__device__ __forceinline__ uint32_t grab_size(uint32_t items, uint32_t most) {
-  return max(1u, min(most, items / (3u * gridDim.x)));
+__device__ __forceinline__ uint32_t grab_size(uint32_t items, uint32_t most, uint32_t grid) {
+  return max(1u, min(most, items / (3u * grid)));
 }
 constexpr int kTileGrab = 8;   // most tiles taken per atomic of a hand-out counter
 constexpr int kTileMaxDeg = 2048;  // largest degree of the small-tile bucket (default and bound of t_tile)
@@ -735,14 +742,13 @@ __device__ __forceinline__ void tile_select(const RoundCtx& x, const int32_t* ke
   }
 }
 
-template <class T, typename V, bool COMP, int MODE = kModeRate, bool ITV = false>
-__global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(tile_waves_per_eu<T, MODE, COMP>())))
-void k_rate_tile(RoundCtx x, VDesc vd, const int32_t* tiles,
-                                                           const uint32_t* ntiles_p, uint32_t* ctr, TileLayout L) {
+// Workgroup `block` of `grid` that rate the tiles of a list.
+template <class T, typename V, bool COMP, int MODE, bool ITV>
+__device__ __forceinline__ void rate_tiles(const RoundCtx& x, VDesc vd, const int32_t* tiles, const uint32_t* ntiles_p,
+                                           uint32_t* ctr, const TileLayout& L, uint32_t block, uint32_t grid) {
   constexpr int NT = T::kThreads, VT = T::kVerts, ITEMS = T::kItems, SG = T::kSelGroup;
   constexpr int NSG = NT / SG;  // selection groups per workgroup
   extern __shared__ __align__(16) uint8_t smem_raw[];
-  if (*x.done) return;
   const int tid = threadIdx.x;
   const bool weighted = x.g.weighted;
   const uint32_t per = weighted ? 2u : 1u;
@@ -758,11 +764,11 @@ void k_rate_tile(RoundCtx x, VDesc vd, const int32_t* tiles,
   // The workgroups of one XCD take tiles of their own eighth of the list (one
   // counter per eighth), then help with the eighths that have some left.
   const uint32_t T_ = *ntiles_p;
-  const uint32_t grab = grab_size(T_, kTileGrab);
+  const uint32_t grab = grab_size(T_, kTileGrab, grid);
   auto lo_of = [&](uint32_t r) { return (uint32_t)(((uint64_t)T_ * r) >> 3); };
-  auto first_of = [&](uint32_t r) { return ((gridDim.x + 7u - r) >> 3) * grab; };  // tiles of first shares
-  uint32_t xr = blockIdx.x & 7u;
-  uint32_t t = lo_of(xr) + (blockIdx.x >> 3) * grab, tend = min(lo_of(xr + 1), t + grab);
+  auto first_of = [&](uint32_t r) { return ((grid + 7u - r) >> 3) * grab; };  // tiles of first shares
+  uint32_t xr = block & 7u;
+  uint32_t t = lo_of(xr) + (block >> 3) * grab, tend = min(lo_of(xr + 1), t + grab);
   while (true) {
     {
       if (t >= tend) {
@@ -1102,6 +1108,29 @@ void k_rate_tile(RoundCtx x, VDesc vd, const int32_t* tiles,
   }
 }
 
+template <class T, typename V, bool COMP, int MODE = kModeRate, bool ITV = false>
+__global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(tile_waves_per_eu<T, MODE, COMP>())))
+void k_rate_tile(RoundCtx x, VDesc vd, const int32_t* tiles, const uint32_t* ntiles_p, uint32_t* ctr, TileLayout L) {
+  if (*x.done) return;
+  rate_tiles<T, V, COMP, MODE, ITV>(x, vd, tiles, ntiles_p, ctr, L, blockIdx.x, gridDim.x);
+}
+
+// Small tiles and lanes of a round in one launch, tiles first: on graphs
+// where neither fills the device for long, one path's latencies (its code's
+// first fetch among them) hide behind the other's.
+constexpr int32_t kFuseTiles = 1 << 14, kFuseLanes = 1 << 21;  // most vertices of either path
+template <typename V, bool COMP, bool ITV>
+__global__ __launch_bounds__(256) void k_rate_both(RoundCtx x, VDesc vt, const int32_t* tiles,
+                                                   const uint32_t* ntiles_p, uint32_t* ctr, TileLayout L,
+                                                   uint32_t tile_grid, VDesc vl, int32_t nlane) {
+  static_assert(TileSmall::kThreads == 256, "both paths take workgroups of one size");
+  if (*x.done) return;
+  if (blockIdx.x < tile_grid)
+    rate_tiles<TileSmall, V, COMP, kModeRate, ITV>(x, vt, tiles, ntiles_p, ctr, L, blockIdx.x, tile_grid);
+  else
+    rate_lane<COMP, kModeRate, ITV>(x, vl, nlane, blockIdx.x - tile_grid);
+}
+
 // Greedy tiling of a tile bucket: each thread walks kTileSeg consecutive
 // vertices and starts a new tile whenever the next vertex would exceed the
 // tile's edge, vertex or staged-byte budget. COUNT: tiles per segment;
@@ -1338,7 +1367,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void k_hub_piece(RoundCtx x, HubMeta
   uint32_t* nums = (uint32_t*)(A + L.nums_off);
   PieceShared<Cfg>& sh = *(PieceShared<Cfg>*)(A + L.abytes);
   V* rec_r = (V*)hm.rec_r;
-  const uint32_t grab = grab_size((uint32_t)npieces, kPieceGrab);
+  const uint32_t grab = grab_size((uint32_t)npieces, kPieceGrab, gridDim.x);
   const uint32_t first_all = gridDim.x * grab;  // pieces of first shares
   uint32_t pnext = blockIdx.x * grab, pend = min((uint32_t)npieces, pnext + grab);
   while (true) {
@@ -2822,6 +2851,27 @@ lp_status launch_tile(const RoundCtx& x, VDesc vd, const int32_t* tiles, const u
   return last_error();
 }
 
+template <typename V, bool COMP, bool ITV>
+lp_status launch_both_t(const RoundCtx& x, VDesc vt, const int32_t* tiles, const uint32_t* ntiles, uint32_t* ctr,
+                        unsigned grid, VDesc vl, int32_t nlane, bool weighted, hipStream_t s) {
+  const TileLayout L = tile_layout<TileSmall, V>(COMP, weighted);
+  const size_t bytes = (size_t)L.abytes + sizeof(TileShared<TileSmall::kThreads, TileSmall::kVerts>);
+  auto kern = k_rate_both<V, COMP, ITV>;
+  LP_CHECK(set_lds(kern, bytes));
+  hipLaunchKernelGGL(kern, dim3(grid + grid_for(nlane, 256)), dim3(256), bytes, s, x, vt, tiles, ntiles, ctr, L, grid,
+                     vl, nlane);
+  return last_error();
+}
+
+template <typename V>
+lp_status launch_both(const RoundCtx& x, VDesc vt, const int32_t* tiles, const uint32_t* ntiles, uint32_t* ctr,
+                      unsigned grid, VDesc vl, int32_t nlane, bool weighted, hipStream_t s) {
+  if (x.g.offs && x.g.intervals)
+    return launch_both_t<V, true, true>(x, vt, tiles, ntiles, ctr, grid, vl, nlane, weighted, s);
+  if (x.g.offs) return launch_both_t<V, true, false>(x, vt, tiles, ntiles, ctr, grid, vl, nlane, weighted, s);
+  return launch_both_t<V, false, false>(x, vt, tiles, ntiles, ctr, grid, vl, nlane, weighted, s);
+}
+
 template <class T>
 lp_status launch_tile_any(bool comp, RateWidth rw, const RoundCtx& x, VDesc vd, const int32_t* tiles,
                           const uint32_t* ntiles, uint32_t* ctr, unsigned grid, bool weighted, hipStream_t s) {
@@ -3750,12 +3800,20 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
                                               g->weighted, side[1]));
           LP_CHECK(end(side[1]));
         }
-        if (bn[0] > 0) {
+        // (timed phases and side streams keep a launch per path)
+        const bool both = !overlap && !timing && bn[0] > 0 && bn[1] > 0 && bn[0] <= kFuseLanes && bn[1] <= kFuseTiles;
+        if (both) {
+          const RateWidth rw = rate_width(g);
+          auto launch = rw == RateWidth::k16 ? launch_both<uint16_t>
+                                             : rw == RateWidth::k64 ? launch_both<int64_t> : launch_both<int32_t>;
+          LP_CHECK(launch(x, vd_of(1), tps.tiles, tps.ntiles, hand_r, tps.grid, vd_of(0), bn[0], g->weighted, s));
+        }
+        if (bn[0] > 0 && !both) {
           LP_CHECK(begin(LP_PHASE_LANE, side[2]));
           LP_CHECK(launch_lane(x, vd_of(0), bn[0], side[2]));
           LP_CHECK(end(side[2]));
         }
-        if (bn[1] > 0) {
+        if (bn[1] > 0 && !both) {
           LP_CHECK(begin(LP_PHASE_TILE));
           LP_CHECK(launch_tile_any<TileSmall>(g->compressed, rate_width(g), x, vd_of(1), tps.tiles, tps.ntiles,
                                               hand_r, tps.grid,
