@@ -312,10 +312,11 @@ struct TileCfg {
 // LDS allows (six of 256 threads, three of 512) to hide the latency of their
 // gathers and barriers: left alone the compiler takes 81 to 88 for the large
 // tiles, which then run two to a CU (R-MAT 2^24: 1.59 instead of 1.22 ms per
-// round). Other instances keep the compiler's choice.
+// round). Record mode's table has 32-bit sums: five small tiles to a CU. Other
+// instances keep the compiler's choice.
 template <class T, int MODE, bool COMP>
 constexpr int tile_waves_per_eu() {
-  return MODE == kModeRate && COMP ? 6 : 1;
+  return MODE == kModeRate && COMP ? 6 : MODE == kModeRec && T::kThreads == 256 ? 5 : 1;
 }
 using TileSmall = TileCfg<256, 2048, 80>;
 using TileLarge = TileCfg<512, 4096, 4>;
@@ -363,7 +364,8 @@ struct TileShared {
 };
 
 // LDS layout of a tile workgroup: region A holds the staged bytes followed by
-// the decoded numbers, and later the rating table (keys, then values).
+// the decoded numbers, later the rating table (keys, then values), and for
+// contraction records finally those (8 bytes per edge: less than the table).
 struct TileLayout {
   uint32_t table_bytes;  // kSlots * (4 + sizeof(V))
   uint32_t nums_off;     // byte offset of the numbers in region A
@@ -1053,20 +1055,28 @@ __device__ __forceinline__ void rate_tiles(const RoundCtx& x, VDesc vd, const in
           __syncthreads();
 #pragma unroll
           for (int k = 0; k < ITEMS; ++k) {
-            if (vi[k] < 0) continue;
-            const int32_t i = vi[k];
-            const uint32_t loc = e0 + k - sh.ebase[i];
-            const bool lead = vj[k] >= 0 && ((claim >> k) & 1u);
-            x.rec[sh.rb[i] + loc] = lead ? Rec{nb[k], (int32_t)vals[qs[k]]} : Rec{-1, 0};
+            const bool lead = vi[k] >= 0 && vj[k] >= 0 && ((claim >> k) & 1u);
+            wt[k] = lead ? (int32_t)vals[qs[k]] : 0;
+            nb[k] = lead ? nb[k] : -1;
           }
         } else {
 #pragma unroll
-          for (int k = 0; k < ITEMS; ++k) {
-            if (vi[k] < 0) continue;
-            const int32_t i = vi[k];
-            const uint32_t loc = e0 + k - sh.ebase[i];
-            x.rec[sh.rb[i] + loc] = Rec{nb[k] == sh.own_c[i] ? -1 : nb[k], wt[k]};
-          }
+          for (int k = 0; k < ITEMS; ++k)
+            if (vi[k] >= 0 && nb[k] == sh.own_c[vi[k]]) nb[k] = -1;
+        }
+        // a vertex's records lie one after another: gathered in LDS and
+        // written by wavefronts in whole lines (a thread's own run of items
+        // would be a line per lane and store)
+        __syncthreads();
+        Rec* stage = (Rec*)A;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k)
+          if (vi[k] >= 0) stage[e0 + k] = Rec{nb[k], wt[k]};
+        __syncthreads();
+        for (int32_t i = tid / kWave; i < nv; i += NT / kWave) {
+          const uint32_t b0 = sh.ebase[i], dg = sh.ebase[i + 1] - b0;
+          Rec* out = x.rec + sh.rb[i];
+          for (uint32_t q = (uint32_t)(tid % kWave); q < dg; q += kWave) out[q] = stage[b0 + q];
         }
         __syncthreads();
         continue;
@@ -1610,18 +1620,27 @@ __global__ __launch_bounds__(Cfg::kThreads) void k_hub_piece(RoundCtx x, HubMeta
         };
         tile_insert_all<ITEMS, V, decltype(pspan), true>(keys, vals, vj, nb, wt, pspan, qs, &claim);
         __syncthreads();
-        Rec* r = x.rec + x.rbase[own] + x.voff[prop_slot(x, u)] + (uint64_t)pj.y * Cfg::kEdges;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-          if (vi[k] < 0) continue;
-          const bool lead = vj[k] >= 0 && ((claim >> k) & 1u);
-          r[e0 + k] = lead ? Rec{nb[k], (int32_t)vals[qs[k]]} : Rec{-1, 0};
+          const bool lead = vi[k] >= 0 && vj[k] >= 0 && ((claim >> k) & 1u);
+          wt[k] = lead ? (int32_t)vals[qs[k]] : 0;
+          nb[k] = lead ? nb[k] : -1;
         }
       } else {
-        Rec* r = x.rec + x.rbase[own] + x.voff[prop_slot(x, u)] + (uint64_t)pj.y * Cfg::kEdges;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k)
-          if (vi[k] >= 0) r[e0 + k] = Rec{nb[k] == own ? -1 : nb[k], wt[k]};
+          if (vi[k] >= 0 && nb[k] == own) nb[k] = -1;
+      }
+      if constexpr (MODE == kModeRec) {
+        // gathered in LDS and written in whole lines
+        __syncthreads();
+        Rec* stage = (Rec*)A;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k)
+          if (vi[k] >= 0) stage[e0 + k] = Rec{nb[k], wt[k]};
+        __syncthreads();
+        Rec* r = x.rec + x.rbase[own] + x.voff[prop_slot(x, u)] + (uint64_t)pj.y * Cfg::kEdges;
+        for (uint32_t q = tid; q < Et; q += NT) r[q] = stage[q];
       }
       __syncthreads();
       continue;

@@ -4,8 +4,8 @@
 // The coarse neighbourhood of a coarse vertex a is the summed weight of the
 // fine edges leaving cluster a, keyed by the coarse ID of the other end,
 // sorted by that ID. Re-planned for gfx950 in three passes:
-//  1. record pass: every fine vertex reserves a slice of its cluster's record
-//     region with one atomic, and the edge visitor of the rating path (lane,
+//  1. record pass: every fine vertex has a slice of its cluster's record
+//     region, reserved by the atomic that counts the cluster's records, and the edge visitor of the rating path (lane,
 //     tile and hub-piece decoders over the graph's cached plan) writes one
 //     (coarse ID, weight) record per neighbour (coarse ID -1 for edges inside
 //     the cluster).
@@ -62,22 +62,34 @@ __global__ void k_check_mark(const int32_t* C, int32_t n, uint32_t* flags, uint3
   }
 }
 
+// The coarse vertex of every fine one, and the weight, record count and record
+// slices of the coarse vertices: the atomic that counts a vertex's records in
+// its cluster also gives the vertex its slice (voff). PACKED: weight (low 31
+// bits) and count share a word, so a vertex costs one atomic (unit vertex
+// weights and fewer than 2^33 directed edges).
+template <bool PACKED>
 __global__ void k_map(const int32_t* C, int32_t n, const uint32_t* id, const int32_t* deg, const int32_t* vwgt,
-                      int32_t* map, unsigned long long* vw, unsigned long long* dsum) {
+                      int32_t* map, unsigned long long* vw, unsigned long long* dsum, uint64_t* voff) {
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
     const int32_t a = (int32_t)id[C[u]];
     map[u] = a;
-    atomicAdd(&vw[a], (unsigned long long)(vwgt ? vwgt[u] : 1));
-    if (deg[u]) atomicAdd(&dsum[a], (unsigned long long)deg[u]);
+    const unsigned long long d = (unsigned long long)(uint32_t)deg[u];
+    if constexpr (PACKED) {
+      const unsigned long long old = atomicAdd(&dsum[a], (d << 31) + 1ull);
+      if (d) voff[u] = old >> 31;
+    } else {
+      atomicAdd(&vw[a], (unsigned long long)(vwgt ? vwgt[u] : 1));
+      if (d) voff[u] = atomicAdd(&dsum[a], d);
+    }
   }
 }
 
-// Reserves each vertex's slice of its cluster's record region.
-__global__ void k_reserve(const int32_t* map, const int32_t* deg, int32_t n, unsigned long long* cursor,
-                          uint64_t* voff) {
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t d = deg[u];
-    if (d) voff[u] = atomicAdd(&cursor[map[u]], (unsigned long long)d);
+// Takes packed words apart.
+__global__ void k_unpack(unsigned long long* dsum, unsigned long long* vw, int32_t nc) {
+  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < nc; a += (int64_t)gridDim.x * blockDim.x) {
+    const unsigned long long x = dsum[a];
+    vw[a] = x & 0x7FFFFFFFull;
+    dsum[a] = x >> 31;
   }
 }
 
@@ -1275,7 +1287,6 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
     cg->n = nc;
     unsigned long long* vw = sc.alloc<unsigned long long>(nc);
     unsigned long long* dsum = sc.alloc<unsigned long long>(nc);
-    unsigned long long* cursor = sc.alloc<unsigned long long>(nc);
     uint64_t* voff = sc.alloc<uint64_t>(n);
     uint64_t* rbase = sc.alloc<uint64_t>((size_t)nc + 1);
     uint64_t* tcap = sc.alloc<uint64_t>(nc);
@@ -1287,16 +1298,17 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
         graph_alloc(cg, (void**)&cg->xadj, ((size_t)nc + 1) * sizeof(uint64_t)) != hipSuccess) { st = LP_ENOMEM; break; }
     (void)hipMemsetAsync(vw, 0, (size_t)nc * 8, s);
     (void)hipMemsetAsync(dsum, 0, (size_t)nc * 8, s);
-    (void)hipMemsetAsync(cursor, 0, (size_t)nc * 8, s);
     (void)hipMemsetAsync(cdeg, 0, ((size_t)nc + 1) * sizeof(uint64_t), s);
     (void)hipMemsetAsync(heavy, 0, (size_t)nc, s);
-    hipLaunchKernelGGL(k_map, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, labels, n, flags, deg, g->vwgt, map, vw,
-                       dsum);
+    const bool packed = !g->vwgt && g->two_m < (1ull << 33);
+    hipLaunchKernelGGL(packed ? k_map<true> : k_map<false>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, labels, n,
+                       flags, deg, g->vwgt, map, vw, dsum, voff);
+    if (packed)
+      hipLaunchKernelGGL(k_unpack, dim3(grid_for(nc, 256, 65536)), dim3(256), 0, s, dsum, vw, nc);
     st = last_error();
     if (st) break;
     st = scan_exclusive_u64((const uint64_t*)dsum, rbase, nc, &ctl->nrec, sc);
     if (st) break;
-    hipLaunchKernelGGL(k_reserve, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, map, deg, n, cursor, voff);
     hipLaunchKernelGGL(k_cclass, dim3(grid_for(nc, 256, 65536)), dim3(256), 0, s, dsum, vw, nc, tcap, cls, cg->vwgt,
                        &ctl->err);
     hipLaunchKernelGGL(k_class_list, dim3(grid_for(nc, 256 * 8, 65536)), dim3(256), 0, s, cls, nc, ctl->ccount, lists,
