@@ -1320,7 +1320,7 @@ __global__ __launch_bounds__(256) void k_hub_streams(GraphView g, HubMeta hm, in
           const uint64_t p0 = pos;
           const int32_t bv = j == 0 ? u : pv, bw = j == 0 ? 0 : pw;
           (void)group_decode<kWave>(g.bytes, pos, u, cnt, g.weighted, j == 0, pv, pw, dsm[w],
-                                    [](uint32_t, int32_t, int32_t) {});
+                                    [](int32_t) { return 0; }, [](uint32_t, int32_t, int32_t, int32_t) {});
           if (lane < NS)
             st[(uint64_t)j * NS + lane] =
                 lane == 0 ? HubStream{p0, (uint32_t)(pos - p0), cnt | (j == 0 ? kStreamZig : 0u), bv, bw, 0, 0}
@@ -3454,11 +3454,29 @@ lp_status get_plans(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t t
   return LP_OK;
 }
 
+// The cached default plan's degrees, its short neighbourhoods (degree 1 to 16:
+// {vertex, degree, position of the first code or edge (low, high word)}) and its
+// other vertices with edges.
+lp_status plan_degrees(const lp_graph* g, const int32_t** deg, const int4** lane, int32_t* nlane,
+                       const int32_t** longer, int32_t* nlong, hipStream_t s);
+
 lp_status plan_degrees(const lp_graph* g, const int32_t** deg, hipStream_t s) {
+  const int4* lane = nullptr;
+  const int32_t* longer = nullptr;
+  int32_t nlane = 0, nlong = 0;
+  return plan_degrees(g, deg, &lane, &nlane, &longer, &nlong, s);
+}
+
+lp_status plan_degrees(const lp_graph* g, const int32_t** deg, const int4** lane, int32_t* nlane,
+                       const int32_t** longer, int32_t* nlong, hipStream_t s) {
   const Plan* plan = nullptr;
   std::unique_ptr<Plan> tmp;
   LP_CHECK(get_plan(g, 16, kTileMaxDeg, TileLarge::kEdges, kDefaultHubPart, s, &plan, tmp));
   *deg = plan->deg;
+  *lane = plan->vd(0).d;
+  *nlane = plan->bn[0];
+  *longer = plan->order + plan->bstart[1];
+  *nlong = (int32_t)(plan->bstart[kNumBuckets] - plan->bstart[1]);
   return LP_OK;
 }
 

@@ -72,13 +72,16 @@ struct DecodeSmem {
 // true the first code is zigzag(v0 - u) (a chunk start) and the weight
 // differences restart from 0; otherwise decoding continues from prev_v /
 // prev_w. For every decoded neighbour i (0-based within this call) one
-// thread calls f(i, v, w). All NT threads must call this function.
+// thread calls f(i, v, w, pre(v)). pre is called for the (at most four)
+// neighbours that a thread has of a window before f is called for any of
+// them, so that their loads are in flight together; it is called for vertex
+// u where a thread has none. All NT threads must call this function.
 // On return pos points after the last consumed code, prev_v / prev_w hold
 // the last neighbour and weight. Returns false on a malformed stream.
-template <int NT, typename F>
+template <int NT, typename P, typename F>
 __device__ bool group_decode(const uint8_t* __restrict__ bytes, uint64_t& pos, int32_t u, uint32_t count,
                              bool weighted, bool start, int32_t& prev_v, int32_t& prev_w, DecodeSmem<NT>& sm,
-                             F&& f) {
+                             P&& pre, F&& f) {
   const int tid = group_tid<NT>();
   const uint32_t per = weighted ? 2u : 1u;
   if (start) {
@@ -133,8 +136,13 @@ __device__ bool group_decode(const uint8_t* __restrict__ bytes, uint64_t& pos, i
     group_sync<NT>();
     const uint64_t npos = sm.newpos;
     const uint32_t nb = take / per;
-    for (uint32_t b0 = 0; b0 < nb; b0 += NT) {
-      const uint32_t i = b0 + (uint32_t)tid;
+    // a window of 4 * NT bytes holds at most 4 * NT codes
+    int32_t v[4], w[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      v[k] = u;
+      if (k * NT >= nb) continue;
+      const uint32_t i = k * NT + (uint32_t)tid;
       const bool valid = i < nb;
       int32_t dv = 0, dw = 0;
       if (valid) {
@@ -146,10 +154,20 @@ __device__ bool group_decode(const uint8_t* __restrict__ bytes, uint64_t& pos, i
       const int32_t sv = group_scan<NT>(dv, sm.scan, &tv);
       int32_t sw = 0;
       if (weighted) sw = group_scan<NT>(dw, sm.scan, &tw);
-      if (valid) f(done + i, prev_v + sv, weighted ? prev_w + sw : 1);
+      if (valid) v[k] = prev_v + sv;
+      w[k] = weighted ? prev_w + sw : 1;
       prev_v += tv;
       prev_w += tw;
       first_pending = false;
+    }
+    decltype(pre(0)) q[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+      if (k * NT < nb) q[k] = pre(v[k]);
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint32_t i = k * NT + (uint32_t)tid;
+      if (i < nb) f(done + i, v[k], w[k], q[k]);
     }
     done += nb;
     pos = npos;

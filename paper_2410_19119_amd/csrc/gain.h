@@ -22,15 +22,18 @@ struct GainTable {
   bool wide = false;          // int64 affinities
   uint64_t entries = 0;       // slots over all slices
   const int32_t* deg = nullptr;  // degrees (the handle's cached plan)
-  uint64_t* off = nullptr;    // n + 1 slot offsets
-  uint8_t* dense = nullptr;   // n: 1 = dense row of k affinities
+  const int4* lane = nullptr;    // its short neighbourhoods {vertex, degree, position (low, high)}
+  const int32_t* longer = nullptr;  // its other vertices with edges
+  int32_t nlane = 0, nlong = 0;
+  uint64_t* off = nullptr;    // n + 1 slot offsets; a slice of k slots is a dense row, a shorter one a hash slice
   int32_t* key = nullptr;     // entries: block of a hash slot, -1 = empty
   void* val = nullptr;        // entries: affinities (int32 or int64)
   uint32_t* flag = nullptr;   // n: overflowed slice / duplicate check
   int32_t* list = nullptr;    // n: overflowed vertices
   uint32_t* cnt = nullptr;    // [0] overflowed vertices, [1] missing entries, [2] slices rebuilt so far,
-                              // [3] work items
-  int2* items = nullptr;      // work items of a fill (vertex, chunk) or an update (move, chunk)
+                              // [3] work items of wavefronts, [4] of workgroups
+  int2* items = nullptr;      // work items of a fill (vertex, chunk) or an update (move, chunk): wavefronts'
+                              // from the front, workgroups' from the back
   uint64_t nitems_cap = 0;
   uint64_t bytes = 0;
 };

@@ -6,11 +6,14 @@
 
 namespace lp {
 
-lp_status plan_degrees(const lp_graph* g, const int32_t** deg, hipStream_t s);
+lp_status plan_degrees(const lp_graph* g, const int32_t** deg, const int4** lane, int32_t* nlane,
+                       const int32_t** longer, int32_t* nlong, hipStream_t s);
 
 namespace {
 
 constexpr int kGtLaneMax = 16;  // vertices up to this degree are filled / selected by one lane
+constexpr int kGtWaveMax = 512; // and up to this degree by one wavefront; a workgroup takes the rest
+constexpr int kGtThreads = 256; // threads of such a workgroup
 constexpr int kGtWaves = 4;     // wavefronts per 256-thread workgroup
 constexpr int32_t kGtEmpty = -1;
 
@@ -18,7 +21,6 @@ template <typename V>
 struct GtView {
   int32_t n, k;
   const uint64_t* off;
-  const uint8_t* dense;
   int32_t* key;
   V* val;
   uint32_t* flag;
@@ -28,7 +30,7 @@ struct GtView {
 
 template <typename V>
 GtView<V> view_of(const GainTable& t) {
-  return GtView<V>{t.g->n, t.k, t.off, t.dense, t.key, (V*)t.val, t.flag, t.list, t.cnt};
+  return GtView<V>{t.g->n, t.k, t.off, t.key, (V*)t.val, t.flag, t.list, t.cnt};
 }
 
 // Home slot of block b in a hash slice of L = 2^s slots (the top s bits of a
@@ -42,55 +44,88 @@ __device__ __forceinline__ void gt_atomic_add(int64_t* p, int64_t w) {
   atomicAdd((unsigned long long*)p, (unsigned long long)w);
 }
 
-// Slot of block b in u's slice, inserting it if `insert`; -1 if absent (or,
-// when inserting, if the slice has no free slot left).
+// A vertex's slice. Slices of k slots are dense rows: hash slices are shorter.
+struct GtSlice {
+  uint64_t base;
+  uint32_t L;
+};
+
 template <typename V>
-__device__ int64_t gt_slot(const GtView<V>& t, int32_t u, int32_t b, bool insert) {
+__device__ __forceinline__ GtSlice gt_slice(const GtView<V>& t, int32_t u) {
   const uint64_t base = t.off[u];
-  if (t.dense[u]) return (int64_t)(base + (uint32_t)b);
-  const uint32_t L = (uint32_t)(t.off[u + 1] - base);
-  uint32_t h = gt_hash(b, L);
-  for (uint32_t p = 0; p < L; ++p) {
-    const uint64_t s = base + h;
-    const int32_t kk = t.key[s];
+  return GtSlice{base, (uint32_t)(t.off[u + 1] - base)};
+}
+
+template <typename V>
+__device__ __forceinline__ bool gt_dense(const GtView<V>& t, const GtSlice& sl) {
+  return sl.L == (uint32_t)t.k;
+}
+
+// Slot of block b in a hash slice, inserting it if `insert`; -1 if absent (or,
+// when inserting, if the slice has no free slot left). h is b's home slot and
+// kk what it held.
+template <typename V>
+__device__ __forceinline__ int64_t gt_slot(const GtView<V>& t, const GtSlice& sl, int32_t b, uint32_t h, int32_t kk,
+                                           bool insert) {
+  for (uint32_t p = 0; p < sl.L; ++p) {
+    const uint64_t s = sl.base + h;
+    if (p) kk = t.key[s];
     if (kk == b) return (int64_t)s;
     if (kk == kGtEmpty) {
       if (!insert) return -1;
       const int32_t old = atomicCAS(&t.key[s], kGtEmpty, b);
       if (old == kGtEmpty || old == b) return (int64_t)s;
     }
-    h = (h + 1) & (L - 1);
+    h = (h + 1) & (sl.L - 1);
   }
   return -1;
 }
 
 template <typename V>
-__device__ __forceinline__ bool gt_add(const GtView<V>& t, int32_t u, int32_t b, V w) {
-  const int64_t s = gt_slot(t, u, b, true);
-  if (s < 0) return false;
+__device__ __forceinline__ bool gt_add(const GtView<V>& t, const GtSlice& sl, int32_t b, V w) {
+  int64_t s;
+  if (gt_dense(t, sl)) {
+    s = (int64_t)(sl.base + (uint32_t)b);
+  } else {
+    const uint32_t h = gt_hash(b, sl.L);
+    s = gt_slot(t, sl, b, h, t.key[sl.base + h], true);
+    if (s < 0) return false;
+  }
   gt_atomic_add(&t.val[s], w);
   return true;
 }
 
+// The home slot's key and value are read together.
 template <typename V>
 __device__ __forceinline__ V gt_get(const GtView<V>& t, int32_t u, int32_t b) {
-  const int64_t s = gt_slot(t, u, b, false);
+  const GtSlice sl = gt_slice(t, u);
+  if (sl.L == 0) return (V)0;
+  if (gt_dense(t, sl)) return t.val[sl.base + (uint32_t)b];
+  const uint32_t h = gt_hash(b, sl.L);
+  const int32_t kk = t.key[sl.base + h];
+  const V x = t.val[sl.base + h];
+  if (kk == b) return x;
+  const int64_t s = gt_slot(t, sl, b, h, kk, false);
   return s < 0 ? (V)0 : t.val[s];
 }
 
-// Every neighbour (v, w) of u, for one wavefront: chunk c of a chunked
-// neighbourhood, or all of it (c < 0). Plain graphs are cut into the same
-// 1000-edge pieces above the chunking threshold.
-template <typename F>
-__device__ void wave_visit(const GraphView& g, int32_t u, uint32_t deg, int32_t c, DecodeSmem<kWave>& dsm, F&& f) {
+// Every neighbour (v, w) of u, for one group of NT threads: chunk c of a
+// chunked neighbourhood, or all of it (c < 0). Plain graphs are cut into the
+// same 1000-edge pieces above the chunking threshold. f(v, w, pre(v)) is
+// called by one thread per neighbour; pre only loads, so that the loads of
+// several neighbours are in flight at a time.
+template <int NT, typename P, typename F>
+__device__ __forceinline__ void group_visit(const GraphView& g, int32_t u, uint32_t deg, int32_t c,
+                                            DecodeSmem<NT>& dsm, P&& pre, F&& f) {
+  const int tid = group_tid<NT>();
   if (g.offs && g.intervals) {
     // interval-coded: every lane decodes whole chunks on its own
     const Nbh h = nbh_locate(g, u, deg);
     const uint32_t c0 = c < 0 ? 0u : (uint32_t)c, c1 = c < 0 ? h.nchunks : (uint32_t)c + 1;
-    for (uint32_t ch = c0 + (uint32_t)lane_id(); ch < c1; ch += kWave) {
+    for (uint32_t ch = c0 + (uint32_t)tid; ch < c1; ch += NT) {
       const uint32_t first = ch * LP_CHUNK_LEN;
       const uint32_t cnt = h.nchunks > 1 ? min((uint32_t)LP_CHUNK_LEN, deg - first) : deg;
-      lane_decode_chunk(g, u, nbh_chunk_pos(g, h, ch), cnt, [&](uint32_t, int32_t v, int32_t w) { f(v, w); });
+      lane_decode_chunk(g, u, nbh_chunk_pos(g, h, ch), cnt, [&](uint32_t, int32_t v, int32_t w) { f(v, w, pre(v)); });
     }
   } else if (g.offs) {
     const Nbh h = nbh_locate(g, u, deg);
@@ -100,8 +135,9 @@ __device__ void wave_visit(const GraphView& g, int32_t u, uint32_t deg, int32_t 
       const uint32_t first = ch * LP_CHUNK_LEN;
       const uint32_t cnt = h.nchunks > 1 ? min((uint32_t)LP_CHUNK_LEN, deg - first) : deg;
       int32_t pv = 0, pw = 0;
-      (void)group_decode<kWave>(g.bytes, pos, u, cnt, g.weighted, true, pv, pw, dsm,
-                                [&](uint32_t, int32_t v, int32_t w) { f(v, w); });
+      using Q = decltype(pre(0));
+      (void)group_decode<NT>(g.bytes, pos, u, cnt, g.weighted, true, pv, pw, dsm, pre,
+                             [&](uint32_t, int32_t v, int32_t w, const Q& q) { f(v, w, q); });
     }
   } else {
     const uint64_t e0 = g.xadj[u];
@@ -110,8 +146,21 @@ __device__ void wave_visit(const GraphView& g, int32_t u, uint32_t deg, int32_t 
       lo = (uint32_t)c * LP_CHUNK_LEN;
       hi = min(deg, lo + (uint32_t)LP_CHUNK_LEN);
     }
-    for (uint32_t e = lo + (uint32_t)lane_id(); e < hi; e += kWave)
-      f(g.adjncy[e0 + e], g.adjwgt ? g.adjwgt[e0 + e] : 1);
+    for (uint32_t e = lo + (uint32_t)tid; e < hi; e += 4 * NT) {
+      int32_t v[4], w[4];
+      decltype(pre(0)) q[4];
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) {
+        const uint64_t x = e0 + (e + k * NT < hi ? e + k * NT : e);
+        v[k] = g.adjncy[x];
+        w[k] = g.adjwgt ? g.adjwgt[x] : 1;
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) q[k] = pre(v[k]);
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k)
+        if (e + k * NT < hi) f(v[k], w[k], q[k]);
+    }
   }
 }
 
@@ -128,21 +177,16 @@ __device__ __forceinline__ void lane_visit(const GraphView& g, int32_t u, uint32
 
 // Slice length and kind of every vertex: none for isolated vertices, a dense
 // row of k when pow2(2 deg) >= k, else pow2(2 deg) hash slots.
-__global__ void k_gt_len(const int32_t* deg, int32_t n, int32_t k, uint64_t* len, uint8_t* dense) {
+__global__ void k_gt_len(const int32_t* deg, int32_t n, int32_t k, uint64_t* len) {
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
     const uint64_t d = (uint64_t)deg[u];
     uint64_t L = 0;
-    uint8_t dn = 0;
     if (d > 0) {
       L = 2;
       while (L < 2 * d) L <<= 1;
-      if (L >= (uint64_t)k) {
-        L = (uint64_t)k;
-        dn = 1;
-      }
+      if (L >= (uint64_t)k) L = (uint64_t)k;
     }
     len[u] = L;
-    dense[u] = dn;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) len[n] = 0;
 }
@@ -160,45 +204,114 @@ __global__ void k_gt_zero(uint32_t* a, int64_t m) {
     a[i] = 0;
 }
 
-template <typename V>
-__global__ __launch_bounds__(256) void k_gt_fill_lane(GraphView g, const int32_t* deg, const int32_t* blocks,
-                                                      GtView<V> t) {
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < t.n; u += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t d = deg[u];
-    if (d == 0 || d > kGtLaneMax) continue;
-    lane_visit(g, (int32_t)u, (uint32_t)d, [&](int32_t v, int32_t w) { (void)gt_add(t, (int32_t)u, blocks[v], (V)w); });
+// One lane per short neighbourhood: the edges' blocks are gathered together,
+// equal ones summed in registers, and each block placed at its slot by the
+// lane alone (a mask of the taken slots stands for the probing), so a slice
+// costs one plain store per distinct block and array. Bound by the gathers;
+// inserting edge by edge with a compare-and-swap and an add, each waiting for
+// the one before, took 345 us for 2,000,003 R-MAT vertices, 88 us now.
+template <bool COMP, bool ITV, typename V>
+__global__ __launch_bounds__(256) void k_gt_fill_lane(GraphView g, const int4* list, int32_t cnt,
+                                                      const int32_t* blocks, GtView<V> t) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= cnt) return;
+  const int4 v4 = list[i];
+  const int32_t u = v4.x, d = v4.y;
+  const uint64_t pos = (uint64_t)(uint32_t)v4.z | ((uint64_t)(uint32_t)v4.w << 32);
+  int32_t lab[kGtLaneMax], wt[kGtLaneMax];
+  LaneDec dec;
+  VarCursor cur;
+  if constexpr (ITV) dec.init(g, u, pos);
+  else if constexpr (COMP) cur.seek(g.bytes, pos);
+  int32_t v = 0, w = 0;
+#pragma unroll
+  for (int k = 0; k < kGtLaneMax; ++k) {
+    lab[k] = -1;
+    wt[k] = 0;
+    if (k < d) {
+      if constexpr (ITV) {
+        dec.next(v, w);
+      } else if constexpr (COMP) {
+        const uint32_t code = cur.next();
+        v = (k == 0) ? u + unzigzag32(code) : v + (int32_t)code;
+        if (g.weighted) w = (k == 0 ? 0 : w) + unzigzag32(cur.next());
+        else w = 1;
+      } else {
+        v = g.adjncy[pos + k];
+        w = g.adjwgt ? g.adjwgt[pos + k] : 1;
+      }
+      lab[k] = blocks[v];
+      wt[k] = w;
+    }
+  }
+  const GtSlice sl = gt_slice(t, u);
+  const bool dn = gt_dense(t, sl);
+  uint32_t taken = 0;  // a hash slice here has at most 32 slots
+#pragma unroll
+  for (int k = 0; k < kGtLaneMax; ++k) {
+    const int32_t c = lab[k];
+    bool first = c >= 0;
+#pragma unroll
+    for (int j = 0; j < k; ++j) first &= lab[j] != c;
+    if (!first) continue;
+    V sum = 0;
+#pragma unroll
+    for (int j = k; j < kGtLaneMax; ++j) sum += lab[j] == c ? (V)wt[j] : (V)0;
+    uint32_t h = (uint32_t)c;
+    if (!dn) {
+      h = gt_hash(c, sl.L);
+      while ((taken >> h) & 1u) h = (h + 1) & (sl.L - 1);
+      taken |= 1u << h;
+      t.key[sl.base + h] = c;
+    }
+    t.val[sl.base + h] = sum;
   }
 }
+static_assert(2 * kGtLaneMax <= 32, "a lane's hash slice fits a mask of 32 slots");
 
-// Work items of the wavefront fill: one per vertex above kGtLaneMax, one per
-// chunk above the chunking threshold. Every thread takes kGtItemRun
-// consecutive vertices, so that one counter atomic serves a whole workgroup.
-constexpr int kGtItemRun = 16;
+// Work items of the group fill: one per vertex above kGtLaneMax, one per chunk
+// above the chunking threshold. Wavefronts take the neighbourhoods up to
+// kGtWaveMax (from the front of the list), workgroups the longer ones and the
+// chunks (from its end). Every thread takes kGtItemRun of the listed vertices,
+// so that two counter atomics serve that many per thread of a workgroup.
+constexpr int kGtItemRun = 4;
 
 __device__ __forceinline__ uint32_t gt_items_of(uint32_t d, uint32_t thr) {
   return d <= (uint32_t)kGtLaneMax ? 0u : d > thr ? (d + LP_CHUNK_LEN - 1) / LP_CHUNK_LEN : 1u;
 }
 
-__global__ __launch_bounds__(256) void k_gt_items(const int32_t* deg, int32_t n, uint32_t thr, int2* items,
-                                                  uint32_t* nitems) {
+__global__ __launch_bounds__(256) void k_gt_items(const int32_t* list, const int32_t* deg, int32_t n,
+                                                  uint32_t thr, int2* items, uint64_t cap, uint32_t* nitems) {
   __shared__ int32_t scan[256 / kWave + 1];
-  __shared__ uint32_t base_sm;
-  constexpr int64_t kSpan = 256 * kGtItemRun;
-  for (int64_t b = (int64_t)blockIdx.x * kSpan; b < n; b += (int64_t)gridDim.x * kSpan) {
-    const int64_t u0 = b + (int64_t)threadIdx.x * kGtItemRun;
-    const int64_t u1 = min((int64_t)n, u0 + kGtItemRun);
-    uint32_t cnt = 0;
-    for (int64_t u = u0; u < u1; ++u) cnt += gt_items_of((uint32_t)deg[u], thr);
+  __shared__ uint32_t base_sm[2];
+  const int64_t b = (int64_t)blockIdx.x * (256 * kGtItemRun) + threadIdx.x;
+  int2 vd[kGtItemRun];
+  uint32_t cnt[2] = {0, 0}, o[2];
+#pragma unroll
+  for (int r = 0; r < kGtItemRun; ++r) {
+    vd[r] = make_int2(0, 0);
+    if (b + r * 256 < n) vd[r].x = list[b + r * 256];
+  }
+#pragma unroll
+  for (int r = 0; r < kGtItemRun; ++r) {
+    if (b + r * 256 < n) vd[r].y = deg[vd[r].x];
+    cnt[vd[r].y > kGtWaveMax] += gt_items_of((uint32_t)vd[r].y, thr);
+  }
+  for (int x = 0; x < 2; ++x) {
     int32_t tot;
-    const uint32_t incl = (uint32_t)block_incl_scan_add<256, int32_t>((int32_t)cnt, scan, &tot);
-    if (threadIdx.x == 255) base_sm = tot ? atomicAdd(nitems, (uint32_t)tot) : 0u;
+    const uint32_t incl = (uint32_t)block_incl_scan_add<256, int32_t>((int32_t)cnt[x], scan, &tot);
+    if (threadIdx.x == 255) base_sm[x] = tot ? atomicAdd(nitems + x, (uint32_t)tot) : 0u;
     __syncthreads();
-    uint32_t o = base_sm + incl - cnt;
-    for (int64_t u = u0; u < u1; ++u) {
-      const uint32_t ni = gt_items_of((uint32_t)deg[u], thr);
-      for (uint32_t j = 0; j < ni; ++j) items[o++] = make_int2((int)u, ni > 1 ? (int)j : -1);
+    o[x] = base_sm[x] + incl - cnt[x];
+  }
+#pragma unroll
+  for (int r = 0; r < kGtItemRun; ++r) {
+    const uint32_t ni = gt_items_of((uint32_t)vd[r].y, thr);
+    for (uint32_t j = 0; j < ni; ++j) {
+      const int2 it = make_int2(vd[r].x, ni > 1 ? (int)j : -1);
+      if (vd[r].y > kGtWaveMax) items[cap - 1 - o[1]++] = it;
+      else items[o[0]++] = it;
     }
-    __syncthreads();
   }
 }
 
@@ -207,40 +320,55 @@ __device__ __forceinline__ void lds_add_v(int64_t* p, int64_t w) {
   atomicAdd((unsigned long long*)p, (unsigned long long)w);
 }
 
-// One wavefront per work item. A dense row of at most kGtStage blocks is
-// summed in the wavefront's LDS first and flushed with one global atomic per
-// nonzero block, so that the edges of a vertex do not all hit the same few
-// global addresses.
+// One group of NT threads (a wavefront, or a workgroup) per work item. A dense
+// row of at most kGtStage blocks is summed in the group's LDS first, so that
+// the edges of a vertex do not all hit the same few global addresses, and then
+// stored as it is (the whole neighbourhood) or added with one global atomic
+// per nonzero block (a chunk of it). What bounds a group is the chain decode,
+// gather, LDS add of a window of codes: up to four gathers per thread are in
+// flight, and four wavefronts share the longer neighbourhoods, which left a
+// single one the last to end (2,000,003 R-MAT vertices: 648 us for all, now
+// 340 + 277 us).
 constexpr int kGtStage = 1024;
+constexpr int kGtPerCopy = 64;  // edges per copy of a row
 
-template <typename V>
-__global__ __launch_bounds__(256) void k_gt_fill_wave(GraphView g, const int32_t* deg, const int32_t* blocks,
-                                                      const int2* items, const uint32_t* nitems, GtView<V> t) {
-  __shared__ DecodeSmem<kWave> dsm[kGtWaves];
-  __shared__ V stage[kGtWaves][kGtStage];
-  const int w = threadIdx.x / kWave;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-  const uint32_t m = *nitems;
+template <int NT, typename V>
+__global__ __launch_bounds__(256) void k_gt_fill_group(GraphView g, const int32_t* deg, const int32_t* blocks,
+                                                       const int2* items, uint64_t cap, const uint32_t* nitems,
+                                                       GtView<V> t) {
+  constexpr int G = 256 / NT;  // groups of a workgroup
+  __shared__ DecodeSmem<NT> dsm[G];
+  __shared__ V stage[G][kGtStage + 1];
+  const int w = threadIdx.x / NT, tid = group_tid<NT>();
+  const int64_t ng = (int64_t)gridDim.x * G;
+  const uint32_t m = nitems[NT == kWave ? 0 : 1];
   const bool staged_k = t.k <= kGtStage;
-  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave; i < m; i += nw) {
-    const int2 it = items[i];
+  const int32_t ks = t.k | 1;  // a copy's stride: equal blocks of the copies lie in different banks
+  const auto pre = [&](int32_t v) { return blocks[v]; };
+  for (int64_t i = (int64_t)blockIdx.x * G + w; i < m; i += ng) {
+    const int2 it = items[NT == kWave ? i : (int64_t)cap - 1 - i];
     const int32_t u = it.x;
-    if (staged_k && t.dense[u]) {
-      for (int32_t q = lane_id(); q < t.k; q += kWave) stage[w][q] = 0;
-      wave_sync_lds();
-      wave_visit(g, u, (uint32_t)deg[u], it.y, dsm[w],
-                 [&](int32_t v, int32_t wt) { lds_add_v(&stage[w][blocks[v]], (V)wt); });
-      wave_sync_lds();
-      const uint64_t base = t.off[u];
-      for (int32_t q = lane_id(); q < t.k; q += kWave) {
-        const V a = stage[w][q];
-        if (a) gt_atomic_add(&t.val[base + q], a);
+    const GtSlice sl = gt_slice(t, u);
+    if (staged_k && gt_dense(t, sl)) {
+      const uint32_t d = (uint32_t)deg[u];
+      int32_t R = 1;
+      while (R < kWave && 2 * R * ks <= kGtStage && 2 * R * kGtPerCopy <= (int32_t)d) R *= 2;
+      for (int32_t q = tid; q < R * ks; q += NT) stage[w][q] = 0;
+      group_sync<NT>();
+      V* mine = stage[w] + (tid & (R - 1)) * ks;
+      group_visit<NT>(g, u, d, it.y, dsm[w], pre,
+                      [&](int32_t, int32_t wt, int32_t c) { lds_add_v(&mine[c], (V)wt); });
+      group_sync<NT>();
+      for (int32_t q = tid; q < t.k; q += NT) {
+        V a = 0;
+        for (int32_t r = 0; r < R; ++r) a += stage[w][r * ks + q];
+        if (it.y < 0) t.val[sl.base + q] = a;
+        else if (a) gt_atomic_add(&t.val[sl.base + q], a);
       }
-      wave_sync_lds();
+      group_sync<NT>();
     } else {
-      wave_visit(g, u, (uint32_t)deg[u], it.y, dsm[w], [&](int32_t v, int32_t wt) {
-        (void)gt_add(t, u, blocks[v], (V)wt);
-      });
+      group_visit<NT>(g, u, (uint32_t)deg[u], it.y, dsm[w], pre,
+                      [&](int32_t, int32_t wt, int32_t c) { (void)gt_add(t, sl, c, (V)wt); });
     }
   }
 }
@@ -270,9 +398,10 @@ __global__ __launch_bounds__(256) void k_gt_select_lane(GtView<V> t, GtRound r, 
   const int32_t u = list[i];
   const int32_t own_c = r.C[u];
   const int64_t wu = r.vwgt ? r.vwgt[u] : 1;
-  const uint64_t base = t.off[u];
-  const uint32_t L = (uint32_t)(t.off[u + 1] - base);
-  const bool dn = t.dense[u];
+  const GtSlice sl = gt_slice(t, u);
+  const uint64_t base = sl.base;
+  const uint32_t L = sl.L;
+  const bool dn = gt_dense(t, sl);
   int64_t own = 0;
   Cand best = cand_none();
   for (uint32_t q = 0; q < L; ++q) {
@@ -294,9 +423,10 @@ __global__ __launch_bounds__(256) void k_gt_select_wave(GtView<V> t, GtRound r, 
     const int32_t u = list[i];
     const int32_t own_c = r.C[u];
     const int64_t wu = r.vwgt ? r.vwgt[u] : 1;
-    const uint64_t base = t.off[u];
-    const uint32_t L = (uint32_t)(t.off[u + 1] - base);
-    const bool dn = t.dense[u];
+    const GtSlice sl = gt_slice(t, u);
+    const uint64_t base = sl.base;
+    const uint32_t L = sl.L;
+    const bool dn = gt_dense(t, sl);
     int64_t own = 0;
     Cand best = cand_none();
     for (uint32_t q = (uint32_t)lane_id(); q < L; q += kWave) {
@@ -313,53 +443,82 @@ __global__ __launch_bounds__(256) void k_gt_select_wave(GtView<V> t, GtRound r, 
 }
 
 // The update of one neighbour v of a moved vertex: w(u, v) leaves block
-// `from` and joins block `to` in v's slice.
+// `from` and joins block `to` in v's slice. Both home slots are read together.
 template <typename V>
-__device__ __forceinline__ void gt_move_edge(const GtView<V>& t, int32_t v, int32_t from, int32_t to, int32_t wt) {
-  const int64_t s = gt_slot(t, v, from, false);
-  if (s >= 0) gt_atomic_add(&t.val[s], (V)-wt);
+__device__ __forceinline__ void gt_move_edge(const GtView<V>& t, int32_t v, const GtSlice& sl, int32_t from,
+                                             int32_t to, int32_t wt) {
+  if (gt_dense(t, sl)) {
+    gt_atomic_add(&t.val[sl.base + (uint32_t)from], (V)-wt);
+    gt_atomic_add(&t.val[sl.base + (uint32_t)to], (V)wt);
+    return;
+  }
+  const uint32_t hf = gt_hash(from, sl.L), ht = gt_hash(to, sl.L);
+  const int32_t kf = t.key[sl.base + hf], kt = t.key[sl.base + ht];
+  const int64_t f = gt_slot(t, sl, from, hf, kf, false);
+  if (f >= 0) gt_atomic_add(&t.val[f], (V)-wt);
   else atomicAdd(&t.cnt[1], 1u);
-  if (!gt_add(t, v, to, (V)wt) && atomicExch(&t.flag[v], 1u) == 0u) t.list[atomicAdd(&t.cnt[0], 1u)] = v;
+  const int64_t s = gt_slot(t, sl, to, ht, kt, true);
+  if (s >= 0) gt_atomic_add(&t.val[s], (V)wt);
+  else if (atomicExch(&t.flag[v], 1u) == 0u) t.list[atomicAdd(&t.cnt[0], 1u)] = v;
 }
 
 // Work items of an update: one per move of a vertex above kGtLaneMax, one per
-// chunk above the chunking threshold ({move index, chunk or -1}).
+// chunk above the chunking threshold ({move index, chunk or -1}), listed as
+// those of a fill.
 __global__ __launch_bounds__(256) void k_gt_move_items(const int4* moves, const uint32_t* count, const int32_t* deg,
-                                                       uint32_t thr, int2* items, uint32_t* nitems) {
+                                                       uint32_t thr, int2* items, uint64_t cap, uint32_t* nitems) {
   const int64_t m = *count;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x; b < m; b += stride) {
     const int64_t i = b + threadIdx.x;
     uint32_t ni = 0;
+    bool wide = false;
     if (i < m) {
       const int4 mv = moves[i];
-      if (mv.x >= 0 && mv.y != mv.z) ni = gt_items_of((uint32_t)deg[mv.x], thr);  // short ones: k_gt_update_lane
+      if (mv.x >= 0 && mv.y != mv.z) {  // short ones: k_gt_update_lane
+        const uint32_t d = (uint32_t)deg[mv.x];
+        ni = gt_items_of(d, thr);
+        wide = d > (uint32_t)kGtWaveMax;
+      }
     }
-    const uint32_t incl = wave_incl_scan_add(ni);
-    uint32_t base = 0;
-    if (lane_id() == kWave - 1 && incl) base = atomicAdd(nitems, incl);
-    base = __shfl(base, kWave - 1, kWave);
-    for (uint32_t j = 0; j < ni; ++j) items[base + incl - ni + j] = make_int2((int)i, ni > 1 ? (int)j : -1);
+    for (int x = 0; x < 2; ++x) {
+      const uint32_t c = wide == (x == 1) ? ni : 0u;
+      const uint32_t incl = wave_incl_scan_add(c);
+      uint32_t base = 0;
+      if (lane_id() == kWave - 1 && incl) base = atomicAdd(nitems + x, incl);
+      base = __shfl(base, kWave - 1, kWave);
+      for (uint32_t j = 0; j < c; ++j) {
+        const uint64_t o = base + incl - c + j;
+        items[x ? cap - 1 - o : o] = make_int2((int)i, ni > 1 ? (int)j : -1);
+      }
+    }
   }
 }
 
-// Wavefront per update item of a move {u, from, to}: every neighbour v of u
-// (in the item's chunk) moves w(u, v) from block `from` to block `to` in its
-// slice. A slice without a free slot for `to` is listed for a rebuild; a
-// missing `from` entry is counted (cnt[1]; never expected).
-template <typename V>
+// A group of NT threads per update item of a move {u, from, to}: every
+// neighbour v of u (in the item's chunk) moves w(u, v) from block `from` to
+// block `to` in its slice. A slice without a free slot for `to` is listed for
+// a rebuild; a missing `from` entry is counted (cnt[1]; never expected). A
+// chain of dependent loads (code, slice, home slots) ends in two atomics, and
+// a batch has few long neighbourhoods: those get a workgroup each (40,000
+// moves of 2,000,003 R-MAT vertices: 355 us with a wavefront for each, 58 + 144
+// us now).
+template <int NT, typename V>
 __global__ __launch_bounds__(256) void k_gt_update(GraphView g, const int32_t* deg, const int4* moves,
-                                                   const int2* items, const uint32_t* nitems, GtView<V> t) {
-  __shared__ DecodeSmem<kWave> dsm[kGtWaves];
-  const int w = threadIdx.x / kWave;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-  const uint32_t m = *nitems;
-  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave; i < m; i += nw) {
-    const int2 it = items[i];
+                                                   const int2* items, uint64_t cap, const uint32_t* nitems,
+                                                   GtView<V> t) {
+  constexpr int G = 256 / NT;
+  __shared__ DecodeSmem<NT> dsm[G];
+  const int w = threadIdx.x / NT;
+  const int64_t ng = (int64_t)gridDim.x * G;
+  const uint32_t m = nitems[NT == kWave ? 0 : 1];
+  const auto pre = [&](int32_t v) { return gt_slice(t, v); };
+  for (int64_t i = (int64_t)blockIdx.x * G + w; i < m; i += ng) {
+    const int2 it = items[NT == kWave ? i : (int64_t)cap - 1 - i];
     const int4 mv = moves[it.x];
     const int32_t u = mv.x, from = mv.y, to = mv.z;
-    wave_visit(g, u, (uint32_t)deg[u], it.y, dsm[w],
-               [&](int32_t v, int32_t wt) { gt_move_edge(t, v, from, to, wt); });
+    group_visit<NT>(g, u, (uint32_t)deg[u], it.y, dsm[w], pre,
+                    [&](int32_t v, int32_t wt, const GtSlice& sl) { gt_move_edge(t, v, sl, from, to, wt); });
   }
 }
 
@@ -373,7 +532,7 @@ __global__ __launch_bounds__(256) void k_gt_update_lane(GraphView g, const int32
     if (mv.x < 0 || mv.y == mv.z) continue;
     const uint32_t d = (uint32_t)deg[mv.x];
     if (d == 0 || d > (uint32_t)kGtLaneMax) continue;
-    lane_visit(g, mv.x, d, [&](int32_t v, int32_t wt) { gt_move_edge(t, v, mv.y, mv.z, wt); });
+    lane_visit(g, mv.x, d, [&](int32_t v, int32_t wt) { gt_move_edge(t, v, gt_slice(t, v), mv.y, mv.z, wt); });
   }
 }
 
@@ -388,16 +547,15 @@ __global__ __launch_bounds__(256) void k_gt_rebuild(GraphView g, const int32_t* 
   const uint32_t m = t.cnt[0];
   for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave; i < m; i += nw) {
     const int32_t v = t.list[i];
-    const uint64_t base = t.off[v];
-    const uint32_t L = (uint32_t)(t.off[v + 1] - base);
-    for (uint32_t q = (uint32_t)lane_id(); q < L; q += kWave) {
-      t.key[base + q] = kGtEmpty;
-      t.val[base + q] = 0;
+    const GtSlice sl = gt_slice(t, v);
+    for (uint32_t q = (uint32_t)lane_id(); q < sl.L; q += kWave) {
+      t.key[sl.base + q] = kGtEmpty;
+      t.val[sl.base + q] = 0;
     }
     __threadfence();
     __builtin_amdgcn_wave_barrier();
-    wave_visit(g, v, (uint32_t)deg[v], -1, dsm[w],
-               [&](int32_t x, int32_t wt) { (void)gt_add(t, v, blocks[x], (V)wt); });
+    group_visit<kWave>(g, v, (uint32_t)deg[v], -1, dsm[w], [&](int32_t x) { return blocks[x]; },
+                       [&](int32_t, int32_t wt, int32_t c) { (void)gt_add(t, sl, c, (V)wt); });
     if (lane_id() == 0) t.flag[v] = 0;
   }
 }
@@ -417,16 +575,26 @@ lp_status gt_fill(const GainTable& t, const int32_t* blocks, Scratch& sc) {
   hipLaunchKernelGGL(k_gt_clear<V>, dim3(grid_for((int64_t)t.entries, 256, 65536)), dim3(256), 0, s, t.key, (V*)t.val,
                      t.entries);
   LP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_gt_fill_lane<V>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, g->view(), t.deg, blocks, v);
-  LP_CHECK_LAUNCH();
+  if (t.nlane > 0) {
+    auto lane = !g->compressed    ? k_gt_fill_lane<false, false, V>
+                : g->intervals    ? k_gt_fill_lane<true, true, V>
+                                  : k_gt_fill_lane<true, false, V>;
+    hipLaunchKernelGGL(lane, dim3(grid_for(t.nlane, 256)), dim3(256), 0, s, g->view(), t.lane, t.nlane, blocks, v);
+    LP_CHECK_LAUNCH();
+  }
   uint32_t* nitems = t.cnt + 3;
-  hipLaunchKernelGGL(k_gt_zero, dim3(1), dim3(64), 0, s, nitems, (int64_t)1);
+  hipLaunchKernelGGL(k_gt_zero, dim3(1), dim3(64), 0, s, nitems, (int64_t)2);
   LP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_gt_items, dim3(grid_for(n, 256 * kGtItemRun, 65536)), dim3(256), 0, s, t.deg, n,
-                     chunk_threshold(g->intervals), t.items, nitems);
-  LP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_gt_fill_wave<V>, dim3(grid_for(n, 256 / kWave * 8, 16384)), dim3(256), 0, s, g->view(), t.deg,
-                     blocks, t.items, nitems, v);
+  if (t.nlong > 0) {
+    hipLaunchKernelGGL(k_gt_items, dim3(grid_for(t.nlong, 256 * kGtItemRun)), dim3(256), 0, s, t.longer, t.deg,
+                       t.nlong, chunk_threshold(g->intervals), t.items, t.nitems_cap, nitems);
+    LP_CHECK_LAUNCH();
+    hipLaunchKernelGGL((k_gt_fill_group<kGtThreads, V>), dim3(grid_for(t.nlong, 16, 4096)), dim3(256), 0, s,
+                       g->view(), t.deg, blocks, t.items, t.nitems_cap, nitems, v);
+    LP_CHECK_LAUNCH();
+    hipLaunchKernelGGL((k_gt_fill_group<kWave, V>), dim3(grid_for(t.nlong, 256 / kWave, 16384)), dim3(256), 0, s,
+                       g->view(), t.deg, blocks, t.items, t.nitems_cap, nitems, v);
+  }
   return last_error();
 }
 
@@ -451,16 +619,19 @@ lp_status gt_update_t(const GainTable& t, const int4* moves, const uint32_t* cou
                       const int32_t* blocks, hipStream_t s) {
   const GtView<V> v = view_of<V>(t);
   if (max_moves <= 0) return LP_OK;
-  hipLaunchKernelGGL(k_gt_zero, dim3(1), dim3(64), 0, s, t.cnt + 3, (int64_t)1);
+  hipLaunchKernelGGL(k_gt_zero, dim3(1), dim3(64), 0, s, t.cnt + 3, (int64_t)2);
+  LP_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_gt_move_items, dim3(grid_for(max_moves, 256, 16384)), dim3(256), 0, s, moves, count, t.deg,
+                     chunk_threshold(t.g->intervals), t.items, t.nitems_cap, t.cnt + 3);
+  LP_CHECK_LAUNCH();
+  hipLaunchKernelGGL((k_gt_update<kGtThreads, V>), dim3(grid_for(max_moves, 16, 4096)), dim3(256), 0, s, t.g->view(),
+                     t.deg, moves, t.items, t.nitems_cap, t.cnt + 3, v);
+  LP_CHECK_LAUNCH();
+  hipLaunchKernelGGL((k_gt_update<kWave, V>), dim3(grid_for(max_moves, kGtWaves, 8192)), dim3(256), 0, s,
+                     t.g->view(), t.deg, moves, t.items, t.nitems_cap, t.cnt + 3, v);
   LP_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_gt_update_lane<V>, dim3(grid_for(max_moves, 256, 16384)), dim3(256), 0, s, t.g->view(), t.deg,
                      moves, count, v);
-  LP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_gt_move_items, dim3(grid_for(max_moves, 256, 16384)), dim3(256), 0, s, moves, count, t.deg,
-                     chunk_threshold(t.g->intervals), t.items, t.cnt + 3);
-  LP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_gt_update<V>, dim3(grid_for(max_moves, kGtWaves, 8192)), dim3(256), 0, s, t.g->view(), t.deg,
-                     moves, t.items, t.cnt + 3, v);
   LP_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_gt_rebuild<V>, dim3(256), dim3(256), 0, s, t.g->view(), t.deg, blocks, v);
   LP_CHECK_LAUNCH();
@@ -476,25 +647,24 @@ lp_status gt_create(const lp_graph* g, const int32_t* blocks, int32_t k, hipStre
   t->k = k;
   t->wide = g->max_wdeg > 0x7FFFFFFFll;
   const int32_t n = g->n;
-  LP_CHECK(plan_degrees(g, &t->deg, s));
+  LP_CHECK(plan_degrees(g, &t->deg, &t->lane, &t->nlane, &t->longer, &t->nlong, s));
   auto grab = [&](size_t bytes) {
     void* p = cache_alloc(bytes ? bytes : 1, s);
     t->bytes += bytes;
     return p;
   };
   t->off = (uint64_t*)grab(((size_t)n + 1) * 8);
-  t->dense = (uint8_t*)grab((size_t)n);
   t->flag = (uint32_t*)grab((size_t)n * 4);
   t->list = (int32_t*)grab((size_t)n * 4);
-  t->cnt = (uint32_t*)grab(4 * 4);
+  t->cnt = (uint32_t*)grab(8 * 4);
   t->nitems_cap = (uint64_t)n + g->two_m / LP_CHUNK_LEN + 1;
   t->items = (int2*)grab(t->nitems_cap * sizeof(int2));
-  if (!t->off || !t->dense || !t->flag || !t->list || !t->cnt || !t->items) {
+  if (!t->off || !t->flag || !t->list || !t->cnt || !t->items) {
     gt_release(t, s);
     return LP_ENOMEM;
   }
   Scratch sc(s);
-  hipLaunchKernelGGL(k_gt_len, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, t->deg, n, k, t->off, t->dense);
+  hipLaunchKernelGGL(k_gt_len, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, t->deg, n, k, t->off);
   LP_CHECK_LAUNCH();
   LP_CHECK(scan_exclusive_u64(t->off, t->off, (int64_t)n + 1, nullptr, sc));
   uint64_t entries = 0;
@@ -509,13 +679,13 @@ lp_status gt_create(const lp_graph* g, const int32_t* blocks, int32_t k, hipStre
   }
   hipLaunchKernelGGL(k_gt_zero, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, t->flag, (int64_t)n);
   LP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_gt_zero, dim3(1), dim3(64), 0, s, t->cnt, (int64_t)4);
+  hipLaunchKernelGGL(k_gt_zero, dim3(1), dim3(64), 0, s, t->cnt, (int64_t)8);
   LP_CHECK_LAUNCH();
   return t->wide ? gt_fill<int64_t>(*t, blocks, sc) : gt_fill<int32_t>(*t, blocks, sc);
 }
 
 void gt_release(GainTable* t, hipStream_t s) {
-  for (void* p : {(void*)t->off, (void*)t->dense, (void*)t->flag, (void*)t->list, (void*)t->cnt, (void*)t->key, t->val,
+  for (void* p : {(void*)t->off, (void*)t->flag, (void*)t->list, (void*)t->cnt, (void*)t->key, t->val,
                   (void*)t->items})
     if (p) cache_free(p, s);
   *t = GainTable{};
