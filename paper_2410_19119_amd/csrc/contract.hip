@@ -5,18 +5,19 @@
 // fine edges leaving cluster a, keyed by the coarse ID of the other end,
 // sorted by that ID. Re-planned for gfx950 in three passes:
 //  1. record pass: every fine vertex has a slice of its cluster's record
-//     region, reserved by the atomic that counts the cluster's records, and the edge visitor of the rating path (lane,
-//     tile and hub-piece decoders over the graph's cached plan) writes one
-//     (coarse ID, weight) record per neighbour (coarse ID -1 for edges inside
-//     the cluster).
+//     region, reserved by the atomic that counts the cluster's records, and
+//     the edge visitor of the rating path (lane, tile and hub-piece decoders
+//     over the graph's cached plan) writes one (coarse ID, weight) record per
+//     neighbour (coarse ID -1 for edges inside the cluster).
 //  2. aggregation, following the paper's two-phase aggregation
 //     (Section IV-B1): light clusters are aggregated by one wavefront or
-//     workgroup from their contiguous records in an LDS hash table, sorted
-//     in LDS and written back in place; heavy clusters first group their
-//     records by coarse-ID partition (cut at quantiles of a sample of their
-//     IDs) in 4096-record chunks, then one workgroup per (cluster, partition)
-//     aggregates and sorts that partition. Partitions are ID ranges, so their
-//     outputs concatenate in order.
+//     workgroup from their contiguous records, by buckets of IDs in LDS or,
+//     where those come out uneven, in an LDS hash table that is then sorted,
+//     and written back in place; heavy clusters first group their records by
+//     coarse-ID partition (cut at quantiles of a sample of their IDs) in
+//     chunks, then one workgroup per (cluster, partition) aggregates and
+//     sorts that partition in the same two ways. Partitions are ID ranges, so
+//     their outputs concatenate in order.
 //  3. a prefix sum over the coarse degrees places every neighbourhood.
 #include <stdio.h>
 #include <stdlib.h>
@@ -48,6 +49,7 @@ constexpr uint32_t kMaxHeavyParts = 4096;
 constexpr uint32_t kHeavySample = 2048;  // records sampled per heavy cluster for the partition splitters
 constexpr int kLightThreads = 256;
 constexpr int kReduceThreads = 256;
+constexpr int kReduceItems = 4;        // records per thread of the tasks reduced by buckets
 constexpr uint64_t kBigTask = 16384;  // records of a task reduced by the wide configuration
 constexpr int kBigThreads = 1024;
 constexpr uint32_t kBigTable = 8192;
@@ -203,29 +205,31 @@ __device__ __forceinline__ void tbl_add_guarded(int32_t* keys, V* vals, uint32_t
   }
 }
 
-__device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long x, int m) {
+__device__ __forceinline__ unsigned long long shfl_xor_key(unsigned long long x, int m) {
   const uint32_t lo = __shfl_xor((uint32_t)x, m, kWave), hi = __shfl_xor((uint32_t)(x >> 32), m, kWave);
   return ((unsigned long long)hi << 32) | lo;
 }
+__device__ __forceinline__ uint32_t shfl_xor_key(uint32_t x, int m) { return __shfl_xor(x, m, kWave); }
 
-// Sorts k distinct 64-bit values a[0..k) ascending in LDS: every wavefront
-// sorts runs of 64 in registers (bitonic network over lane shuffles), then
-// runs are merged pairwise, each element placed at its run position plus its
-// rank in the partner run (binary search), alternating between a and b.
-// Returns the buffer that holds the result; b needs k entries.
-template <int NT>
-__device__ unsigned long long* lds_sort_u64(unsigned long long* a, unsigned long long* b, uint32_t k) {
+// Sorts k values a[0..k) ascending in LDS: every wavefront sorts runs of 64 in
+// registers (bitonic network over lane shuffles), then runs are merged
+// pairwise, each element placed at its run position plus its rank in the
+// partner run (binary search; equal values of the lower run go first),
+// alternating between a and b. Returns the buffer that holds the result; b
+// needs k entries.
+template <int NT, typename T>
+__device__ T* lds_sort(T* a, T* b, uint32_t k) {
   constexpr int NW = NT / kWave;
   const int lane = lane_id();
   const int w = NT == kWave ? 0 : (int)(threadIdx.x / kWave);
   for (uint32_t c = (uint32_t)w * kWave; c < k; c += NW * kWave) {
     const uint32_t i = c + lane;
-    unsigned long long x = i < k ? a[i] : ~0ull;
+    T x = i < k ? a[i] : (T)~(T)0;
 #pragma unroll
     for (int size = 2; size <= kWave; size <<= 1) {
 #pragma unroll
       for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        const unsigned long long y = shfl_xor_u64(x, stride);
+        const T y = shfl_xor_key(x, stride);
         const bool up = (lane & size) == 0;
         const bool lower = (lane & stride) == 0;
         x = (lower == up) ? (x < y ? x : y) : (x < y ? y : x);
@@ -235,19 +239,20 @@ __device__ unsigned long long* lds_sort_u64(unsigned long long* a, unsigned long
   }
   group_sync<NT>();
   const int tid = group_tid<NT>();
-  unsigned long long *src = a, *dst = b;
+  T *src = a, *dst = b;
   for (uint32_t R = kWave; R < k; R <<= 1) {
     for (uint32_t i = tid; i < k; i += NT) {
-      const unsigned long long x = src[i];
+      const T x = src[i];
       const uint32_t r = i / R, p = i - r * R;
       const uint32_t ps = (r ^ 1u) * R;
+      const bool upper = r & 1u;
       uint32_t rank = 0;
       if (ps < k) {
         uint32_t lo = 0, hi = min(R, k - ps);
-        const unsigned long long* q = src + ps;
+        const T* q = src + ps;
         while (lo < hi) {
           const uint32_t mid = (lo + hi) >> 1;
-          if (q[mid] < x) lo = mid + 1;
+          if (q[mid] < x || (upper && q[mid] == x)) lo = mid + 1;
           else hi = mid;
         }
         rank = lo;
@@ -255,7 +260,7 @@ __device__ unsigned long long* lds_sort_u64(unsigned long long* a, unsigned long
       dst[(r & ~1u) * R + p + rank] = x;
     }
     group_sync<NT>();
-    unsigned long long* t = src;
+    T* t = src;
     src = dst;
     dst = t;
   }
@@ -361,9 +366,228 @@ __device__ bool bucket_rank_write(unsigned long long* a, unsigned long long* b, 
   return true;
 }
 
+constexpr int kBrBins = 8;  // buckets per thread
+
+// LDS of bucket_reduce.
+template <int NT, int ITEMS>
+struct BrShared {
+  static constexpr uint32_t kBins = kBrBins * NT;
+  static constexpr int kWords = NT * ITEMS / kWave;
+  uint32_t key[NT * ITEMS];  // by bucket
+  int32_t wt[NT * ITEMS];
+  __align__(16) uint32_t cnt[kBins + 4];  // records per bucket, then where each begins
+  unsigned long long mask[kWords + 1];
+  uint32_t pre[kWords + 1];
+  int32_t scan[NT / kWave];
+  uint32_t red[2 * (NT / kWave)];
+};
+
+// Sums a group's records (x, ITEMS per thread) per coarse ID and writes the
+// sums to dst in ID order. The IDs lie in [lo, lo + width); width 0: unknown.
+// Records (ID >= 0) go to buckets by a monotone map of their ID, in LDS; the
+// first of equal IDs in a bucket takes their sum, and comes after the leaders
+// of the buckets before (a bit per record and prefix counts) and the smaller
+// ones of its own bucket. Returns the number of sums, or -1, having written
+// nothing, where the buckets are so uneven that walking them would cost more
+// than kRankBudget steps per record (hot IDs, skewed ranges): tables take
+// those. With few equal IDs (R-MAT 2^23: 9 in 10 records differ) most of what
+// a table costs, clearing, probing, compacting and sorting it, is saved: heavy
+// tasks 2.11 -> 1.53 ms, workgroups' clusters 2.08 -> 0.98, wavefronts' 0.60
+// -> 0.28 (with what the tables still take). Bound by instructions: eight
+// buckets per thread keep the walks short (four: heavy tasks 1.80 ms against
+// 1.57, sixteen 1.54 but more to clear and scan in the larger clusters), and
+// loading the next run meanwhile costs more registers than it saves (1.57
+// against 1.42).
+template <int NT, int ITEMS>
+__device__ __forceinline__ int32_t bucket_reduce(const Rec (&x)[ITEMS], uint32_t lo, uint32_t width, Rec* dst,
+                                                 uint32_t* err, BrShared<NT, ITEMS>& sm) {
+  constexpr uint32_t B = BrShared<NT, ITEMS>::kBins;
+  constexpr int W = BrShared<NT, ITEMS>::kWords, NW = NT / kWave;
+  static_assert(W <= kWave && NT * ITEMS <= 1 << 16 && B <= 1 << 16);
+  const int tid = group_tid<NT>();
+#pragma unroll
+  for (int k = 0; k < kBrBins; k += 4) *(uint4*)&sm.cnt[kBrBins * tid + k] = make_uint4(0, 0, 0, 0);
+  if (width == 0) {
+    uint32_t mn = 0xFFFFFFFFu, mx = 0;
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u)
+      if (x[u].b >= 0) {
+        mn = min(mn, (uint32_t)x[u].b);
+        mx = max(mx, (uint32_t)x[u].b);
+      }
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+      mn = min(mn, (uint32_t)__shfl_xor((int)mn, d, kWave));
+      mx = max(mx, (uint32_t)__shfl_xor((int)mx, d, kWave));
+    }
+    if (lane_id() == 0) {
+      sm.red[2 * (tid / kWave)] = mn;
+      sm.red[2 * (tid / kWave) + 1] = mx;
+    }
+    group_sync<NT>();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      mn = min(mn, sm.red[2 * w]);
+      mx = max(mx, sm.red[2 * w + 1]);
+    }
+    lo = mn;
+    width = mx >= mn ? mx - mn + 1 : 1;
+  }
+  group_sync<NT>();
+  const float scale = (float)B / (float)width;
+  auto bucket = [&](uint32_t key) { return min((uint32_t)((float)(key - lo) * scale), B - 1); };
+  uint32_t at[ITEMS];  // bucket and place in it
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u)
+    if (x[u].b >= 0) {
+      const uint32_t q = bucket((uint32_t)x[u].b);
+      at[u] = q | atomicAdd(&sm.cnt[q], 1u) << 16;
+    }
+  group_sync<NT>();
+  uint32_t c[kBrBins], sq = 0;
+  int32_t sum = 0, tot;
+#pragma unroll
+  for (int k = 0; k < kBrBins; k += 4) {
+    const uint4 v = *(const uint4*)&sm.cnt[kBrBins * tid + k];
+    c[k] = v.x;
+    c[k + 1] = v.y;
+    c[k + 2] = v.z;
+    c[k + 3] = v.w;
+  }
+#pragma unroll
+  for (int k = 0; k < kBrBins; ++k) {
+    sum += (int32_t)c[k];
+    sq += __umul24(c[k], c[k]);
+  }
+  sq = wave_reduce_add(sq);
+  if (lane_id() == 0) sm.red[tid / kWave] = sq;
+  uint32_t run = (uint32_t)(block_incl_scan_add<NT, int32_t>(sum, sm.scan, &tot) - sum);
+  if constexpr (NW > 1) {
+    sq = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) sq += sm.red[w];
+  } else {
+    sq = __shfl(sq, 0, kWave);
+  }
+  if (sq > kRankBudget * (uint32_t)tot) {
+    group_sync<NT>();
+    return -1;
+  }
+#pragma unroll
+  for (int k = 0; k < kBrBins; k += 4) {
+    uint4 v;
+    v.x = run;
+    v.y = v.x + c[k];
+    v.z = v.y + c[k + 1];
+    v.w = v.z + c[k + 2];
+    run = v.w + c[k + 3];
+    *(uint4*)&sm.cnt[kBrBins * tid + k] = v;
+  }
+  if (tid == 0) sm.cnt[B] = (uint32_t)tot;
+  group_sync<NT>();
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u)
+    if (x[u].b >= 0) {
+      const uint32_t j = sm.cnt[at[u] & 0xFFFFu] + (at[u] >> 16);
+      sm.key[j] = (uint32_t)x[u].b;
+      sm.wt[j] = x[u].w;
+    }
+  group_sync<NT>();
+  // the sums, by the first record of each ID in its bucket, and the smaller
+  // IDs of the bucket
+  uint32_t leads = 0, less[ITEMS];
+  int32_t sums[ITEMS];
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u) {
+    const uint32_t j = u * NT + tid;
+    bool lead = false;
+    less[u] = 0;
+    if (j < (uint32_t)tot) {
+      const uint32_t key = sm.key[j], q = bucket(key);
+      const uint32_t s0 = sm.cnt[q], e0 = sm.cnt[q + 1];
+      int64_t v = (int64_t)sm.wt[j];
+      lead = true;
+      if (e0 - s0 > 1)
+        for (uint32_t m = s0; m < e0; ++m) {
+          const uint32_t z = sm.key[m];
+          less[u] += z < key;
+          if (z == key && m != j) {
+            if (m < j) lead = false;
+            v += (int64_t)sm.wt[m];
+          }
+        }
+      if (lead && v > 0x7FFFFFFFll) atomicOr(err, kErrOverflow);
+      sums[u] = (int32_t)v;
+    }
+    leads |= (lead ? 1u : 0u) << u;
+    const unsigned long long bal = __ballot(lead);
+    if (lane_id() == 0) sm.mask[j / kWave] = bal;
+  }
+  group_sync<NT>();
+  if (tid < kWave) {
+    const uint32_t p = tid < W ? (uint32_t)__popcll(sm.mask[tid]) : 0u;
+    const uint32_t inc = wave_incl_scan_add(p);
+    if (tid < W) sm.pre[tid + 1] = inc;
+    if (tid == 0) {
+      sm.pre[0] = 0;
+      sm.mask[W] = 0;
+    }
+  }
+  group_sync<NT>();
+  // leaders before place m
+  auto leaders = [&](uint32_t m) {
+    return sm.pre[m / kWave] + (uint32_t)__popcll(sm.mask[m / kWave] & ((1ull << (m % kWave)) - 1ull));
+  };
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u) {
+    if (!((leads >> u) & 1u)) continue;
+    const uint32_t key = sm.key[u * NT + tid], q = bucket(key);
+    const uint32_t s0 = sm.cnt[q], e0 = sm.cnt[q + 1];
+    uint32_t o = leaders(s0);
+    if (e0 - s0 > 1) {
+      if (leaders(e0) - o == e0 - s0) {
+        o += less[u];
+      } else {
+        for (uint32_t m = s0; m < e0; ++m)
+          o += sm.key[m] < key && ((sm.mask[m / kWave] >> (m % kWave)) & 1ull);
+      }
+    }
+    dst[o] = Rec{(int32_t)key, sums[u]};
+  }
+  const int32_t nout = (int32_t)sm.pre[W];
+  group_sync<NT>();
+  return nout;
+}
+
+// One run of records to reduce by buckets.
+struct BrTask {
+  uint64_t base;  // first record
+  uint32_t nrec, lo, width;
+  int32_t id;
+};
+
+// The runs blockIdx.x, blockIdx.x + gridDim.x, ... of a group of NT threads (a
+// workgroup): fetch(i) finds run i, done(run, sums) ends it.
+template <int NT, int ITEMS, typename F, typename D>
+__device__ __forceinline__ void bucket_loop(int64_t cnt, const Rec* rec, Rec* out, uint32_t* err,
+                                            BrShared<NT, ITEMS>& sm, F&& fetch, D&& done) {
+  for (int64_t i = blockIdx.x; i < cnt; i += gridDim.x) {
+    const BrTask t = fetch(i);
+    if (t.nrec == 0) continue;
+    Rec x[ITEMS];
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u) {
+      const uint32_t j = u * NT + threadIdx.x;
+      x[u] = j < t.nrec ? rec[t.base + j] : Rec{-1, 0};
+    }
+    const int32_t k = bucket_reduce<NT, ITEMS>(x, t.lo, t.width, out + t.base, err, sm);
+    if (threadIdx.x == 0) done(t, k);
+  }
+}
+
 // Writes the table's entries to `out` sorted by key: every thread takes its
 // (strided) slots into registers, a prefix count compacts the entries to pk
-// as (key << 32 | value) pairs, which lds_sort_u64 sorts. Returns the entry
+// as (key << 32 | value) pairs, which lds_sort sorts. Returns the entry
 // count. cap <= NT * SLOTS and the table never holds more than cap / 2
 // entries; pk is the start of the table's LDS region (cap * 8 bytes or more:
 // keys and values), so both sort buffers fit in it once the slots are read.
@@ -402,7 +626,7 @@ __device__ uint32_t compact_sort_write(int32_t* keys, V* vals, uint32_t cap, Rec
     while (B < cnt && B < kBucketBins) B <<= 1;
     if (bucket_rank_write<NT>(pk, pk + cnt, cnt, bcnt, B, out, scan_sm, red)) return cnt;
   }
-  const unsigned long long* sorted = lds_sort_u64<NT>(pk, pk + cnt, cnt);
+  const unsigned long long* sorted = lds_sort<NT>(pk, pk + cnt, cnt);
   for (uint32_t i = tid; i < cnt; i += NT) {
     const unsigned long long x = sorted[i];
     out[i] = Rec{(int32_t)(x >> 32), (int32_t)(uint32_t)x};
@@ -451,15 +675,15 @@ struct LightSmem {
   uint32_t overflow;
 };
 
-// Light clusters: NT = 64, one cluster per wavefront (4 per workgroup);
+// Light clusters that buckets cannot take (list, counted in *cnt): NT = 64, one cluster per wavefront (4 per workgroup);
 // NT = 256, one cluster per workgroup. The table has the next power of two
 // >= 2 * min(dsum, nc - 1) entries, at most tmax; if that capacity was
 // clipped and the cluster turns out to have more than half of it distinct
 // neighbours, the cluster is appended to the heavy list instead.
 template <int NT, typename V>
-__global__ __launch_bounds__(kLightThreads) void k_contract_light(AggArgs A, const int32_t* list, int32_t cnt,
-                                                                  uint32_t tmax, int32_t* heavy_list,
-                                                                  uint32_t* nheavy) {
+__global__ __launch_bounds__(kLightThreads) void k_contract_light(AggArgs A, const int32_t* list,
+                                                                  const uint32_t* cnt, uint32_t tmax,
+                                                                  int32_t* heavy_list, uint32_t* nheavy) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   constexpr int G = kLightThreads / NT;
   const int gi = (int)(threadIdx.x / NT);
@@ -469,7 +693,8 @@ __global__ __launch_bounds__(kLightThreads) void k_contract_light(AggArgs A, con
   V* vals = (V*)base;
   int32_t* keys = (int32_t*)(base + (size_t)tmax * sizeof(V));
   LightSmem<NT>& sm = *(LightSmem<NT>*)(base + (size_t)tmax * (4 + sizeof(V)));
-  for (int64_t it = (int64_t)blockIdx.x * G + gi; it < cnt; it += (int64_t)gridDim.x * G) {
+  const int64_t m = *cnt;
+  for (int64_t it = (int64_t)blockIdx.x * G + gi; it < m; it += (int64_t)gridDim.x * G) {
     const int32_t a = list[it];
     const uint32_t want = (uint32_t)A.tcap[a];
     const uint32_t logc = min(ceil_log2(tmax), max(6u, ceil_log2(2 * max(want, 1u))));
@@ -502,6 +727,24 @@ __global__ __launch_bounds__(kLightThreads) void k_contract_light(AggArgs A, con
     if (tid == 0) A.cdeg[a] = k;
     group_sync<NT>();
   }
+}
+
+// Clusters of up to NT * ITEMS records, by buckets; those whose IDs are too
+// uneven for them are listed for the tables. The sums replace the records.
+template <int NT, int ITEMS>
+__global__ __launch_bounds__(NT, 6) void k_contract_bucket(AggArgs A, const int32_t* list, int32_t cnt,
+                                                           int32_t* skewed, uint32_t* nskewed) {
+  __shared__ BrShared<NT, ITEMS> sm;
+  bucket_loop<NT, ITEMS>(
+      cnt, A.rec, A.rec, A.err, sm,
+      [&](int64_t i) {
+        const int32_t a = list[i];
+        return BrTask{A.rbase[a], (uint32_t)A.dsum[a], 0, 0, a};
+      },
+      [&](const BrTask& t, int32_t k) {
+        if (k >= 0) A.cdeg[t.id] = (uint64_t)k;
+        else skewed[atomicAdd(nskewed, 1u)] = t.id;
+      });
 }
 
 // ------------------------------------------------------------- heavy -----
@@ -559,7 +802,7 @@ __global__ void k_heavy_lists(int32_t H, const int32_t* parts, const uint32_t* c
 // partitions beyond about one per kHeavyPart of them stay empty. Partition p
 // holds IDs [bnd[p], bnd[p+1]).
 __global__ __launch_bounds__(256) void k_heavy_splitters(AggArgs A, Heavy hv, int32_t H) {
-  __shared__ unsigned long long sa[kHeavySample], sb[kHeavySample];
+  __shared__ uint32_t sa[kHeavySample], sb[kHeavySample];
   __shared__ int32_t scan[4];
   for (int64_t h = blockIdx.x; h < H; h += gridDim.x) {
     const int32_t a = hv.clusters[h];
@@ -573,12 +816,12 @@ __global__ __launch_bounds__(256) void k_heavy_splitters(AggArgs A, Heavy hv, in
       const int32_t b = r[(uint64_t)j * d / S].b;
       valid += b >= 0;
       // intra-cluster records (b < 0) sort last and are not counted
-      sa[j] = ((unsigned long long)(b >= 0 ? (uint32_t)b : 0xFFFFFFFFu) << 32) | j;
+      sa[j] = b >= 0 ? (uint32_t)b : 0xFFFFFFFFu;
     }
     int32_t V;
     (void)block_incl_scan_add<256, int32_t>(valid, scan, &V);
     __syncthreads();
-    const unsigned long long* srt = lds_sort_u64<256>(sa, sb, S);
+    const uint32_t* srt = lds_sort<256>(sa, sb, S);
     // about kHeavyPart records with a coarse neighbour per partition
     const uint64_t want = ((uint64_t)V * d + (uint64_t)S * kHeavyPart - 1) / ((uint64_t)S * kHeavyPart);
     const uint32_t Pe = (uint32_t)std::min<uint64_t>(P, std::max<uint64_t>(1, want));
@@ -586,7 +829,7 @@ __global__ __launch_bounds__(256) void k_heavy_splitters(AggArgs A, Heavy hv, in
       int32_t v;
       if (p == 0) v = 0;
       else if (p >= Pe || V == 0) v = A.nc;
-      else v = (int32_t)(srt[(uint64_t)p * V / Pe] >> 32);
+      else v = (int32_t)srt[(uint64_t)p * V / Pe];
       bnd[p] = v;
     }
     __syncthreads();
@@ -712,30 +955,64 @@ struct ReduceSmem {
   uint32_t bcnt[kBucketBins];
 };
 
-// One workgroup of NT threads per (cluster, partition): aggregate the
+// Tasks reduced by buckets: up to kReduceItems records per thread over more IDs
+// than a table has entries (narrower ones are summed in a direct array). Tasks
+// that are not, or whose IDs turn out uneven, are listed for the tables:
+// those of up to kBigTask records (list, cnt[0]) and the others (big, cnt[1]).
+__global__ __launch_bounds__(256) void k_heavy_tasks(Heavy hv, int32_t T, BrTask* desc, int32_t* list, int32_t* big,
+                                                     uint32_t* cnt) {
+  const int64_t n = ((int64_t)T + kWave - 1) / kWave * kWave;
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+    bool table = false;
+    if (t < T) {
+      const int2 task = hv.tasks[t];
+      const int32_t* bnd = hv.bnd + hv.tbase[task.x] + task.x + task.y;
+      const uint64_t base = hv.tcnt[t], nrec = hv.tcnt[t + 1] - base;
+      const uint32_t lo = (uint32_t)bnd[0], width = (uint32_t)bnd[1] - lo;
+      const bool br = nrec <= (uint64_t)(kReduceThreads * kReduceItems) && width > kHeavyTable;
+      desc[t] = BrTask{base, br ? (uint32_t)nrec : 0u, lo, width, (int32_t)t};
+      if (nrec == 0) hv.tdeg[t] = 0;
+      else if (nrec > kBigTask) big[atomicAdd(&cnt[1], 1u)] = (int32_t)t;
+      else table = !br;
+    }
+    const uint64_t m = __ballot(table);
+    uint32_t at = 0;
+    if (lane_id() == 0 && m) at = atomicAdd(&cnt[0], (uint32_t)__popcll(m));
+    at = __shfl(at, 0, kWave) + (uint32_t)__popcll(m & lanemask_lt());
+    if (table) list[at] = (int32_t)t;
+  }
+}
+
+__global__ __launch_bounds__(kReduceThreads, 6) void k_heavy_bucket(Heavy hv, int32_t T, const BrTask* desc,
+                                                                    int32_t* list, uint32_t* cnt, uint32_t* err) {
+  __shared__ BrShared<kReduceThreads, kReduceItems> sm;
+  bucket_loop<kReduceThreads, kReduceItems>(
+      T, hv.rec2, hv.out, err, sm,
+      [&](int64_t i) { return desc[i]; },
+      [&](const BrTask& t, int32_t k) {
+        if (k >= 0) hv.tdeg[t.id] = (uint64_t)k;
+        else list[atomicAdd(&cnt[0], 1u)] = t.id;
+      });
+}
+
+// One workgroup of NT threads per listed (cluster, partition): aggregate the
 // partition's records in an LDS table of TABLE entries over coarse-ID windows
 // (a window whose distinct count exceeds half the table is halved and
 // retried), emitting each window sorted. The table is sized by the task's
-// record count. With `list`, the workgroups take the listed tasks; without,
-// every task of at most max_rec records (larger ones are listed for the wide
-// configuration).
+// record count.
 template <int NT, uint32_t TABLE, typename V>
-__global__ __launch_bounds__(NT) void k_heavy_reduce(AggArgs A, Heavy hv, const int32_t* list, int32_t ntasks,
-                                                     uint64_t max_rec) {
+__global__ __launch_bounds__(NT) void k_heavy_reduce(AggArgs A, Heavy hv, const int32_t* list,
+                                                     const uint32_t* ntasks) {
   extern __shared__ __align__(16) uint8_t smem_raw[];
   V* vals = (V*)smem_raw;
   int32_t* keys = (int32_t*)(smem_raw + (size_t)TABLE * sizeof(V));
   ReduceSmem<NT>& sm = *(ReduceSmem<NT>*)(smem_raw + (size_t)TABLE * (4 + sizeof(V)));
   const int tid = threadIdx.x;
-  for (int64_t i = blockIdx.x; i < ntasks; i += gridDim.x) {
-    const int64_t t = list ? (int64_t)list[i] : i;
+  const int64_t m = *ntasks;
+  for (int64_t i = blockIdx.x; i < m; i += gridDim.x) {
+    const int64_t t = list[i];
     const uint64_t obase = hv.tcnt[t];
     const uint64_t nrec = hv.tcnt[t + 1] - obase;
-    if (!list && nrec > max_rec) continue;
-    if (nrec == 0) {
-      if (tid == 0) hv.tdeg[t] = 0;
-      continue;
-    }
     const int2 task = hv.tasks[t];
     const int32_t h = task.x;
     const uint32_t p = (uint32_t)task.y;
@@ -822,13 +1099,6 @@ __global__ __launch_bounds__(NT) void k_heavy_reduce(AggArgs A, Heavy hv, const 
     if (tid == 0) hv.tdeg[t] = written;
     __syncthreads();
   }
-}
-
-// Tasks of more than thr records, in any order (they go to the wide
-// reduction configuration).
-__global__ void k_heavy_big(const uint64_t* tcnt, int32_t T, uint64_t thr, int32_t* list, uint32_t* cnt) {
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < T; t += (int64_t)gridDim.x * blockDim.x)
-    if (tcnt[t + 1] - tcnt[t] > thr) list[atomicAdd(cnt, 1u)] = (int32_t)t;
 }
 
 __global__ void k_heavy_cdeg(Heavy hv, int32_t H, uint64_t* cdeg) {
@@ -1046,27 +1316,28 @@ lp_status set_lds(F* kern, size_t bytes) {
 }
 
 template <int NT, typename V>
-lp_status launch_light(const AggArgs& A, const int32_t* list, uint32_t cnt, uint32_t tmax, int32_t* heavy_list,
-                       uint32_t* nheavy, hipStream_t s) {
-  if (cnt == 0) return LP_OK;
+lp_status launch_light(const AggArgs& A, const int32_t* list, uint32_t most, const uint32_t* cnt, uint32_t tmax,
+                       int32_t* heavy_list, uint32_t* nheavy, hipStream_t s) {
+  if (most == 0) return LP_OK;
   const size_t per = ((size_t)tmax * (4 + sizeof(V)) + sizeof(LightSmem<NT>) + 15) & ~size_t(15);
   const size_t bytes = per * (kLightThreads / NT);
   auto k = k_contract_light<NT, V>;
   LP_CHECK(set_lds(k, bytes));
-  hipLaunchKernelGGL(k, dim3(grid_for(cnt, kLightThreads / NT, 1u << 20)), dim3(kLightThreads), bytes, s, A, list,
-                     (int32_t)cnt, tmax, heavy_list, nheavy);
+  // the list, of `most` clusters at most, is often short: no more workgroups
+  // than run at a time
+  hipLaunchKernelGGL(k, dim3(grid_for(most, kLightThreads / NT, 1024)), dim3(kLightThreads), bytes, s, A, list, cnt,
+                     tmax, heavy_list, nheavy);
   return last_error();
 }
 
 template <int NT, uint32_t TABLE, typename V>
-lp_status launch_reduce(const AggArgs& A, const Heavy& hv, const int32_t* list, int32_t ntasks, uint64_t max_rec,
+lp_status launch_reduce(const AggArgs& A, const Heavy& hv, const int32_t* list, const uint32_t* ntasks, int32_t most,
                         hipStream_t s) {
   const size_t bytes = (size_t)TABLE * (4 + sizeof(V)) + sizeof(ReduceSmem<NT>);
   auto k = k_heavy_reduce<NT, TABLE, V>;
   LP_CHECK(set_lds(k, bytes));
-  // the listed tasks are few and long: at most as many workgroups as fit
-  const uint32_t grid = list ? (uint32_t)std::min<int64_t>(ntasks, 2048) : grid_for(ntasks, 1, 1u << 20);
-  hipLaunchKernelGGL(k, dim3(grid), dim3(NT), bytes, s, A, hv, list, ntasks, max_rec);
+  // at most as many workgroups as fit
+  hipLaunchKernelGGL(k, dim3((unsigned)std::min<int32_t>(most, 2048)), dim3(NT), bytes, s, A, hv, list, ntasks);
   return last_error();
 }
 
@@ -1183,10 +1454,11 @@ lp_status contract_heavy(const AggArgs& A, const int32_t* hl, int32_t H, Rec* re
   LP_CHECK_LAUNCH();
   LP_CHECK(scan_exclusive_u64(tcnt, tcnt, (int64_t)T + 1, &tot[2], sc));
   int32_t* big = sc.alloc<int32_t>((size_t)T + 1);
-  if (!big) return LP_ENOMEM;
-  LP_CHECK_HIP(hipMemsetAsync(tot32 + 2, 0, 4, s));
-  hipLaunchKernelGGL(k_heavy_big, dim3(grid_for(T, 256, 4096)), dim3(256), 0, s, tcnt, T, (uint64_t)kBigTask, big,
-                     tot32 + 2);
+  int32_t* tab = sc.alloc<int32_t>((size_t)T + 1);
+  BrTask* desc = sc.alloc<BrTask>((size_t)T + 1);
+  if (sc.failed) return LP_ENOMEM;
+  LP_CHECK_HIP(hipMemsetAsync(tot32 + 2, 0, 8, s));
+  hipLaunchKernelGGL(k_heavy_tasks, dim3(grid_for(T, 256, 4096)), dim3(256), 0, s, hv, T, desc, tab, big, tot32 + 2);
   LP_CHECK_LAUNCH();
   if (NCH > 0) {
     hipLaunchKernelGGL(k_heavy_scatter, dim3(grid_for(NCH, 1, 1u << 20)), dim3(256), 0, s, A, hv, NCH);
@@ -1195,7 +1467,7 @@ lp_status contract_heavy(const AggArgs& A, const int32_t* hl, int32_t H, Rec* re
   uint64_t nout = 0;
   uint32_t nbig = 0;
   LP_CHECK_HIP(hipMemcpyAsync(&nout, tot + 2, 8, hipMemcpyDeviceToHost, s));
-  LP_CHECK_HIP(hipMemcpyAsync(&nbig, tot32 + 2, 4, hipMemcpyDeviceToHost, s));
+  LP_CHECK_HIP(hipMemcpyAsync(&nbig, tot32 + 3, 4, hipMemcpyDeviceToHost, s));
   LP_CHECK_HIP(hipStreamSynchronize(s));
   const bool debug = getenv("LPGPU_DEBUG") != nullptr;
   if (debug)
@@ -1208,14 +1480,23 @@ lp_status contract_heavy(const AggArgs& A, const int32_t* hl, int32_t H, Rec* re
     for (int i = 0; i < 3; ++i) (void)hipEventCreate(&ev[i]);
     (void)hipEventRecord(ev[0], s);
   }
-  // tasks of up to kBigTask records by 256-thread workgroups; the larger
-  // ones (partitions of the largest clusters, or many records of few coarse
-  // neighbours) by 1024-thread workgroups with four times the table
-  if (narrow) LP_CHECK((launch_reduce<kReduceThreads, kHeavyTable, uint32_t>(A, hv, nullptr, T, kBigTask, s)));
-  else LP_CHECK((launch_reduce<kReduceThreads, kHeavyTable, int64_t>(A, hv, nullptr, T, kBigTask, s)));
+  // what buckets cannot take: tasks of up to kBigTask records by 256-thread
+  // workgroups; the larger ones (partitions of the largest clusters, or many
+  // records of few coarse neighbours) by 1024-thread workgroups with four times
+  // the table
+  const uint32_t* nt = tot32 + 2;
+  if (T > 0) {
+    hipLaunchKernelGGL(k_heavy_bucket, dim3(grid_for(T, 1, 1u << 20)), dim3(kReduceThreads), 0, s, hv, T, desc,
+                       tab, tot32 + 2, A.err);
+    LP_CHECK_LAUNCH();
+    if (narrow) LP_CHECK((launch_reduce<kReduceThreads, kHeavyTable, uint32_t>(A, hv, tab, nt, T, s)));
+    else LP_CHECK((launch_reduce<kReduceThreads, kHeavyTable, int64_t>(A, hv, tab, nt, T, s)));
+  }
   if (debug) (void)hipEventRecord(ev[1], s);
-  if (nbig && narrow) LP_CHECK((launch_reduce<kBigThreads, kBigTable, uint32_t>(A, hv, big, (int32_t)nbig, 0, s)));
-  else if (nbig) LP_CHECK((launch_reduce<kBigThreads, kBigTable, int64_t>(A, hv, big, (int32_t)nbig, 0, s)));
+  if (nbig && narrow)
+    LP_CHECK((launch_reduce<kBigThreads, kBigTable, uint32_t>(A, hv, big, nt + 1, (int32_t)nbig, s)));
+  else if (nbig)
+    LP_CHECK((launch_reduce<kBigThreads, kBigTable, int64_t>(A, hv, big, nt + 1, (int32_t)nbig, s)));
   if (debug) heavy_debug(hv, H, T, nbig, ev, s);
   hipLaunchKernelGGL(k_heavy_cdeg, dim3(grid_for(H, 256, 4096)), dim3(256), 0, s, hv, H, A.cdeg);
   LP_CHECK_LAUNCH();
@@ -1293,7 +1574,7 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
     uint64_t* cdeg = sc.alloc<uint64_t>((size_t)nc + 1);
     uint8_t* cls = sc.alloc<uint8_t>(nc);
     uint8_t* heavy = sc.alloc<uint8_t>(nc);
-    int32_t* lists = sc.alloc<int32_t>((size_t)4 * nc);
+    int32_t* lists = sc.alloc<int32_t>((size_t)6 * nc);
     if (graph_alloc(cg, (void**)&cg->vwgt, (size_t)nc * sizeof(int32_t)) != hipSuccess ||
         graph_alloc(cg, (void**)&cg->xadj, ((size_t)nc + 1) * sizeof(uint64_t)) != hipSuccess) { st = LP_ENOMEM; break; }
     (void)hipMemsetAsync(vw, 0, (size_t)nc * 8, s);
@@ -1340,20 +1621,28 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
     // weights and fewer than 2^32 adjacency entries (a coarse edge counts
     // fine edges of one direction, at most half of them)
     const bool narrow = !g->weighted && g->two_m < (1ull << 32);
+    int32_t* skewed = lists + 4 * stride;
+    uint32_t* nskewed = &ctl->ccount[5];
+    const uint32_t nblock = h.ccount[2] + h.ccount[3];
+    if (h.ccount[1])
+      hipLaunchKernelGGL((k_contract_bucket<kWave, kClassWave / kWave>), dim3(grid_for(h.ccount[1], 1, 1u << 20)),
+                         dim3(kWave), 0, s, A, lists, (int32_t)h.ccount[1], skewed + stride, nskewed + 1);
+    if (h.ccount[2])
+      hipLaunchKernelGGL((k_contract_bucket<kLightThreads, kClassBlockS / kLightThreads>),
+                         dim3(grid_for(h.ccount[2], 1, 1u << 20)), dim3(kLightThreads), 0, s, A, lists + stride, (int32_t)h.ccount[2], skewed, nskewed);
+    if (h.ccount[3])
+      hipLaunchKernelGGL((k_contract_bucket<kLightThreads, kClassBlockL / kLightThreads>),
+                         dim3(grid_for(h.ccount[3], 1, 1u << 20)), dim3(kLightThreads), 0, s, A, lists + 2 * stride, (int32_t)h.ccount[3], skewed, nskewed);
+    st = last_error();
+    if (st) break;
     if (narrow) {
-      st = launch_light<kWave, uint32_t>(A, lists, h.ccount[1], 2 * kClassWave, hlist, nheavy, s);
+      st = launch_light<kWave, uint32_t>(A, skewed + stride, h.ccount[1], nskewed + 1, 2 * kClassWave, hlist, nheavy, s);
       if (!st)
-        st = launch_light<kLightThreads, uint32_t>(A, lists + stride, h.ccount[2], 2 * kClassBlockS, hlist, nheavy, s);
-      if (!st)
-        st = launch_light<kLightThreads, uint32_t>(A, lists + 2 * stride, h.ccount[3], 2 * kClassBlockL, hlist, nheavy,
-                                                   s);
+        st = launch_light<kLightThreads, uint32_t>(A, skewed, nblock, nskewed, 2 * kClassBlockL, hlist, nheavy, s);
     } else {
-      st = launch_light<kWave, int64_t>(A, lists, h.ccount[1], 2 * kClassWave, hlist, nheavy, s);
+      st = launch_light<kWave, int64_t>(A, skewed + stride, h.ccount[1], nskewed + 1, 2 * kClassWave, hlist, nheavy, s);
       if (!st)
-        st = launch_light<kLightThreads, int64_t>(A, lists + stride, h.ccount[2], 2 * kClassBlockS, hlist, nheavy, s);
-      if (!st)
-        st = launch_light<kLightThreads, int64_t>(A, lists + 2 * stride, h.ccount[3], 2 * kClassBlockL, hlist, nheavy,
-                                                  s);
+        st = launch_light<kLightThreads, int64_t>(A, skewed, nblock, nskewed, 2 * kClassBlockL, hlist, nheavy, s);
     }
     if (st) break;
     const uint32_t heavy0 = h.ccount[4];
@@ -1361,9 +1650,9 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
         hipStreamSynchronize(s) != hipSuccess) { st = LP_EDEVICE; break; }
     if (debug)
       fprintf(stderr,
-              "[lpgpu] contract n=%d nc=%d records %llu pieces %u classes wave %u blockS %u blockL %u heavy %u "
-              "(+%u handed over)\n",
-              n, nc, (unsigned long long)h.nrec, h.npieces, h.ccount[1], h.ccount[2], h.ccount[3], heavy0,
+              "[lpgpu] contract n=%d nc=%d records %llu pieces %u classes wave %u blockS %u blockL %u (%u + %u by tables) "
+              "heavy %u (+%u handed over)\n",
+              n, nc, (unsigned long long)h.nrec, h.npieces, h.ccount[1], h.ccount[2], h.ccount[3], h.ccount[6], h.ccount[5], heavy0,
               h.ccount[4] - heavy0);
     Heavy hv{};
     int32_t T = 0;
