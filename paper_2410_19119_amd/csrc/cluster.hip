@@ -1206,8 +1206,17 @@ struct PieceCfg {
 using PieceHub = PieceCfg<512, kHubPiece, kHubStreams, false>;
 using PieceWhole16 = PieceCfg<1024, 16 * LP_CHUNK_LEN, 16, true>;
 using PieceWhole32 = PieceCfg<1024, 12 * LP_CHUNK_LEN, 12, true>;
-static_assert(PieceHub::kEdges == PieceHub::kStreams * LP_CHUNK_LEN && PieceWhole16::kEdges == PieceWhole16::kStreams * LP_CHUNK_LEN &&
-                  PieceWhole32::kEdges == PieceWhole32::kStreams * LP_CHUNK_LEN,
+// Whole hubs of at most half that size: half the threads and half the LDS, so
+// that a CU holds two and one works while the other waits at a barrier or for
+// its gathers (R-MAT 2^24, hubs of 4097 to 8000 edges: 1.46 ms a round with
+// workgroups of 1024, 0.95 with these).
+using PieceHalf16 = PieceCfg<512, 8 * LP_CHUNK_LEN, 8, true>;
+using PieceHalf32 = PieceCfg<512, 6 * LP_CHUNK_LEN, 6, true>;
+constexpr int kHalfHubs = 512;  // with more whole hubs than this
+template <class Cfg>
+constexpr bool whole_chunks() { return Cfg::kEdges == Cfg::kStreams * LP_CHUNK_LEN; }
+static_assert(whole_chunks<PieceHub>() && whole_chunks<PieceWhole16>() && whole_chunks<PieceWhole32>() &&
+                  whole_chunks<PieceHalf16>() && whole_chunks<PieceHalf32>(),
               "a piece holds whole chunks, one stream each");
 constexpr int kMaxParts = 1024;
 constexpr int kPieceGrab = 4;  // most pieces taken per atomic of the hand-out counter
@@ -1360,8 +1369,10 @@ struct PieceShared {
 };
 
 // H1: one workgroup per hub piece (of a whole hub: H1 to H3 at once).
+// Whole hubs fill a CU with 16 wavefronts (one workgroup, or two of half size)
+// at up to 128 registers.
 template <class Cfg, typename V, bool COMP, int MODE = kModeRate, bool ITV = false>
-__global__ __launch_bounds__(Cfg::kThreads) void k_hub_piece(RoundCtx x, HubMeta hm, int32_t npieces,
+__global__ __launch_bounds__(Cfg::kThreads, Cfg::kWhole ? 4 : 1) void k_hub_piece(RoundCtx x, HubMeta hm, int32_t npieces,
                                                             uint32_t* ctr, TileLayout L) {
   constexpr int NT = Cfg::kThreads, ITEMS = Cfg::kItems, NS = Cfg::kStreams;
   constexpr bool WHOLE = Cfg::kWhole;
@@ -2973,11 +2984,14 @@ lp_status launch_piece(bool wide, const RoundCtx& x, const HubMeta& hm, int32_t 
   return launch_piece_t<PieceHub, int32_t, MODE>(x, hm, npieces, ctr, s);
 }
 
-// The whole hubs: 16-bit ratings for unit edge weights, else 32-bit (graphs
-// with 64-bit ratings have none).
+// The whole hubs of one size: 16-bit ratings for unit edge weights, else 32-bit
+// (graphs with 64-bit ratings have none).
 template <int MODE = kModeRate>
-lp_status launch_whole(bool weighted, const RoundCtx& x, const HubMeta& hw, int32_t nwhole, uint32_t* ctr,
+lp_status launch_whole(bool weighted, bool half, const RoundCtx& x, const HubMeta& hw, int32_t nwhole, uint32_t* ctr,
                        hipStream_t s) {
+  if (nwhole <= 0) return LP_OK;
+  if (half && !weighted) return launch_piece_t<PieceHalf16, uint16_t, MODE>(x, hw, nwhole, ctr, s);
+  if (half) return launch_piece_t<PieceHalf32, int32_t, MODE>(x, hw, nwhole, ctr, s);
   if (!weighted) return launch_piece_t<PieceWhole16, uint16_t, MODE>(x, hw, nwhole, ctr, s);
   return launch_piece_t<PieceWhole32, int32_t, MODE>(x, hw, nwhole, ctr, s);
 }
@@ -3081,9 +3095,9 @@ struct Plan {
   uint32_t* vlen = nullptr;
   TilePlan tps, tpl;
   HubMeta hm{};  // static parts only; per-call buffers are set by the caller
-  HubMeta hw{};  // the hubs rated whole (u, deg, pieces, streams)
+  HubMeta hw[2];  // the hubs rated whole (u, deg, pieces, streams): large, half size
   int32_t H = 0, npieces = 0, ntasks = 0;  // hubs cut into pieces
-  int32_t nwhole = 0;
+  int32_t nwhole[2] = {0, 0};
   uint64_t rsum = 0, psum = 0;
   unsigned long long bsums[2 * kNumBuckets] = {};
   PlanMem mem;
@@ -3165,7 +3179,8 @@ lp_status build_plan(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t 
   // are cut into pieces.
   const int32_t Hall = P.bn[3];
   P.H = 0;
-  P.nwhole = 0;
+  P.nwhole[0] = P.nwhole[1] = 0;
+  std::vector<int32_t> wh;
   if (Hall > 0) {
     std::vector<int32_t> au(Hall), ad(Hall);
     std::vector<uint64_t> ab(Hall, 0);
@@ -3184,53 +3199,64 @@ lp_status build_plan(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t 
     LP_CHECK_HIP(hipMemcpyAsync(au.data(), P.order + P.bstart[3], Hall * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     LP_CHECK_HIP(hipMemcpyAsync(ad.data(), hdeg_dev, Hall * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     LP_CHECK_HIP(hipStreamSynchronize(s));
-    std::vector<int32_t> hu, hd, wu, wd;
+    std::vector<int32_t> hu, hd, wu[2], wd[2];
     const bool comp = g->compressed != 0;
     const TileLayout WL = g->weighted ? piece_layout_of<PieceWhole32, int32_t>(comp, true)
                                       : piece_layout_of<PieceWhole16, uint16_t>(comp, false);
+    const TileLayout HL = g->weighted ? piece_layout_of<PieceHalf32, int32_t>(comp, true)
+                                      : piece_layout_of<PieceHalf16, uint16_t>(comp, false);
     for (int32_t i = 0; i < Hall; ++i) {
+      const bool half = !P.wide && (g->weighted ? whole_fits<PieceHalf32>(HL, comp, ad[i], ab[i])
+                                                : whole_fits<PieceHalf16>(HL, comp, ad[i], ab[i]));
       const bool whole = !P.wide && (g->weighted ? whole_fits<PieceWhole32>(WL, comp, ad[i], ab[i])
                                                  : whole_fits<PieceWhole16>(WL, comp, ad[i], ab[i]));
-      (whole ? wu : hu).push_back(au[i]);
-      (whole ? wd : hd).push_back(ad[i]);
+      (half ? wu[1] : whole ? wu[0] : hu).push_back(au[i]);
+      (half ? wd[1] : whole ? wd[0] : hd).push_back(ad[i]);
+    }
+    // a launch for each size pays where every CU gets several hubs; fewer hubs
+    // are over sooner in one, a whole CU each (a batch of 48 graphs with 38
+    // hubs: 41 us a round against 74)
+    if (wu[0].size() + wu[1].size() <= (size_t)kHalfHubs) {
+      wu[0].insert(wu[0].end(), wu[1].begin(), wu[1].end());
+      wd[0].insert(wd[0].end(), wd[1].begin(), wd[1].end());
+      wu[1].clear();
+      wd[1].clear();
     }
     const int32_t H = (int32_t)hu.size();
-    const int32_t HW = (int32_t)wu.size();
     P.H = H;
-    P.nwhole = HW;
-    if (HW > 0) {
-      HubMeta& hw = P.hw;
-      const int NSW = g->weighted ? PieceWhole32::kStreams : PieceWhole16::kStreams;
-      std::vector<int32_t> ones(HW, 1), idx(HW);
-      std::vector<int2> wp(HW);
-      for (int32_t i = 0; i < HW; ++i) {
-        idx[i] = i;
-        wp[i] = make_int2(i, 0);
+    // per size: one piece each {hub, 0}, the hubs' vertices, degrees, numbers
+    // of pieces and first pieces
+    for (int half = 0; half < 2; ++half) {
+      const int32_t HW = P.nwhole[half] = (int32_t)wu[half].size();
+      for (int32_t i = 0; i < HW; ++i) wh.insert(wh.end(), {i, 0});
+      wh.insert(wh.end(), wu[half].begin(), wu[half].end());
+      wh.insert(wh.end(), wd[half].begin(), wd[half].end());
+      wh.insert(wh.end(), HW, 1);
+      for (int32_t i = 0; i < HW; ++i) wh.push_back(i);
+    }
+    if (!wh.empty()) {
+      int32_t* d_wh = P.mem.alloc<int32_t>(wh.size());
+      if (!d_wh) return LP_ENOMEM;
+      LP_CHECK_HIP(hipMemcpyAsync(d_wh, wh.data(), wh.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+      for (int half = 0; half < 2; ++half) {
+        const int32_t HW = P.nwhole[half];
+        if (HW == 0) continue;
+        const int NSW = half ? (g->weighted ? PieceHalf32::kStreams : PieceHalf16::kStreams)
+                             : (g->weighted ? PieceWhole32::kStreams : PieceWhole16::kStreams);
+        HubMeta& hw = P.hw[half];
+        hw.streams = P.mem.alloc<HubStream>((size_t)HW * NSW);
+        if (P.mem.failed) return LP_ENOMEM;
+        hw.pieces = (const int2*)d_wh;
+        hw.u = d_wh + 2 * (size_t)HW;
+        hw.deg = hw.u + HW;
+        hw.npieces = hw.deg + HW;
+        hw.piece_base = hw.npieces + HW;
+        d_wh += 6 * (size_t)HW;
+        auto streams = half ? (g->weighted ? k_hub_streams<PieceHalf32> : k_hub_streams<PieceHalf16>)
+                            : (g->weighted ? k_hub_streams<PieceWhole32> : k_hub_streams<PieceWhole16>);
+        hipLaunchKernelGGL(streams, dim3(grid_for(HW, 4, 4096)), dim3(256), 0, s, g->view(), hw, HW);
+        LP_CHECK_LAUNCH();
       }
-      int32_t* d_u = P.mem.alloc<int32_t>(HW);
-      int32_t* d_deg = P.mem.alloc<int32_t>(HW);
-      int32_t* d_one = P.mem.alloc<int32_t>(HW);
-      int32_t* d_idx = P.mem.alloc<int32_t>(HW);
-      int2* d_wp = P.mem.alloc<int2>(HW);
-      hw.streams = P.mem.alloc<HubStream>((size_t)HW * NSW);
-      if (P.mem.failed) return LP_ENOMEM;
-      LP_CHECK_HIP(hipMemcpyAsync(d_u, wu.data(), HW * sizeof(int32_t), hipMemcpyHostToDevice, s));
-      LP_CHECK_HIP(hipMemcpyAsync(d_deg, wd.data(), HW * sizeof(int32_t), hipMemcpyHostToDevice, s));
-      LP_CHECK_HIP(hipMemcpyAsync(d_one, ones.data(), HW * sizeof(int32_t), hipMemcpyHostToDevice, s));
-      LP_CHECK_HIP(hipMemcpyAsync(d_idx, idx.data(), HW * sizeof(int32_t), hipMemcpyHostToDevice, s));
-      LP_CHECK_HIP(hipMemcpyAsync(d_wp, wp.data(), HW * sizeof(int2), hipMemcpyHostToDevice, s));
-      hw.u = d_u;
-      hw.deg = d_deg;
-      hw.npieces = d_one;
-      hw.piece_base = d_idx;
-      hw.pieces = d_wp;
-      if (g->weighted)
-        hipLaunchKernelGGL(k_hub_streams<PieceWhole32>, dim3(grid_for(HW, 4, 4096)), dim3(256), 0, s, g->view(), hw,
-                           HW);
-      else
-        hipLaunchKernelGGL(k_hub_streams<PieceWhole16>, dim3(grid_for(HW, 4, 4096)), dim3(256), 0, s, g->view(), hw,
-                           HW);
-      LP_CHECK_LAUNCH();
     }
     if (H > 0) {
       // partitions of about hub_part records (at most kMaxParts)
@@ -3392,7 +3418,8 @@ lp_status visit_edges_mode(const lp_graph* g, const int32_t* C, const uint64_t* 
       LP_CHECK((launch_tile<TileLarge, int32_t, false, MODE>(x, plan->vd(2), plan->tpl.tiles, plan->tpl.ntiles,
                                                              zero + 16, plan->tpl.grid, g->weighted, s)));
   }
-  if (plan->nwhole > 0) LP_CHECK(launch_whole<MODE>(g->weighted, x, plan->hw, plan->nwhole, zero + 28, s));
+  for (int half = 0; half < 2; ++half)
+    LP_CHECK(launch_whole<MODE>(g->weighted, half, x, plan->hw[half], plan->nwhole[half], zero + 28 + half, s));
   if (plan->H > 0) LP_CHECK(launch_piece<MODE>(false, x, plan->hm, plan->npieces, zero + 24, s));
   return LP_OK;
 }
@@ -3792,12 +3819,13 @@ static lp_status cluster_impl(const lp_graph* g, int64_t cap, const int64_t* cap
         LP_CHECK(end());
       }
       size_t hub_mark = 0;
-      if (!use_gt && (H > 0 || plan->nwhole > 0)) {
+      if (!use_gt && (H > 0 || plan->nwhole[0] + plan->nwhole[1] > 0)) {
         hub_mark = marks.size();
         LP_CHECK(begin(LP_PHASE_HUB));
-        if (plan->nwhole > 0) {
+        if (plan->nwhole[0] + plan->nwhole[1] > 0) {
           LP_CHECK(begin(LP_PHASE_HUB_WHOLE));
-          LP_CHECK(launch_whole(g->weighted, x, plan->hw, plan->nwhole, hand_r + 20, s));
+          for (int half = 0; half < 2; ++half)
+            LP_CHECK(launch_whole(g->weighted, half, x, plan->hw[half], plan->nwhole[half], hand_r + 20 + half, s));
           LP_CHECK(end());
         }
         if (H > 0) {
