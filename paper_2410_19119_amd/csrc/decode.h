@@ -70,7 +70,7 @@ struct DecodeSmem {
 
 // Decodes `count` neighbours whose codes start at byte `pos`. If `start` is
 // true the first code is zigzag(v0 - u) (a chunk start) and the weight
-// differences restart from 0; otherwise decoding continues from prev_v /
+// differences restart from 0 (from prev_w with keep_w); otherwise decoding continues from prev_v /
 // prev_w. For every decoded neighbour i (0-based within this call) one
 // thread calls f(i, v, w, pre(v)). pre is called for the (at most four)
 // neighbours that a thread has of a window before f is called for any of
@@ -81,12 +81,12 @@ struct DecodeSmem {
 template <int NT, typename P, typename F>
 __device__ bool group_decode(const uint8_t* __restrict__ bytes, uint64_t& pos, int32_t u, uint32_t count,
                              bool weighted, bool start, int32_t& prev_v, int32_t& prev_w, DecodeSmem<NT>& sm,
-                             P&& pre, F&& f) {
+                             P&& pre, F&& f, bool keep_w = false) {
   const int tid = group_tid<NT>();
   const uint32_t per = weighted ? 2u : 1u;
   if (start) {
     prev_v = 0;
-    prev_w = 0;
+    if (!keep_w) prev_w = 0;
   }
   bool first_pending = start;
   uint32_t done = 0;
