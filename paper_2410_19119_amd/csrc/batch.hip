@@ -92,7 +92,7 @@ __global__ void k_batch_shift(const int32_t* const* adj, const uint64_t* ebase, 
 // graph g's lies at out + unit * base[g]. A thread takes sixteen bytes of the
 // union at a time, from one unaligned load unless they end in another graph.
 // Bound by the copy; a copy per graph cost more in launches than in bytes (48
-// graphs of 2000 to 200,000 vertices: 110 us in 48 copies, 23 us now).
+// graphs of 1000 to 200,000 vertices: 110 us in 48 copies, 23 us now).
 __global__ __launch_bounds__(256) void k_batch_join(const uint8_t* const* src, const uint64_t* base, uint64_t unit,
                                                     int32_t G, uint8_t* out) {
   const uint64_t total = unit * base[G];
