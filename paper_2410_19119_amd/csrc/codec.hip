@@ -244,10 +244,11 @@ __device__ __forceinline__ void ct_entries(const CtEntries<WGT>& en, const CtSpa
 // stretch's vertices (tdeg[c]) and weighted degree (tw[c]) and, with SIZE,
 // the stretch's code bytes (tsize[c], gap-only format). Weighted degrees of
 // vertices that continue into other stretches are summed in wspan[stretch
-// that starts them] (zeroed).
+// that starts them] (zeroed). c0: the launch's first stretch (here and in the
+// kernels below).
 template <bool WGT, bool SIZE>
-__global__ __launch_bounds__(kCtThreads) void k_csr_scan(CsrIn g, const int64_t* blk, int64_t nb, CsrAcc* acc,
-                                                         uint32_t* tdeg, unsigned long long* tw,
+__global__ __launch_bounds__(kCtThreads) void k_csr_scan(CsrIn g, const int64_t* blk, int64_t nb, int64_t c0,
+                                                         CsrAcc* acc, uint32_t* tdeg, unsigned long long* tw,
                                                          unsigned long long* wspan, uint64_t* tsize) {
   __shared__ __align__(16) uint16_t own[kCtWork];
   __shared__ unsigned long long wsum[WGT ? kCtWork + 1 : 1];
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(kCtThreads) void k_csr_scan(CsrIn g, const int64_t*
   __shared__ uint32_t red32[kCtThreads / kWave], redl[kCtThreads / kWave];
   __shared__ unsigned long long red[kCtThreads / kWave];
   if (acc->xerr) return;
-  const int64_t c = blockIdx.x;
+  const int64_t c = c0 + blockIdx.x;
   const CtSpan sp = ct_span(g, blk, nb, c);
   const CtEntries<WGT> en(g, sp);
   *(uint4*)&own[threadIdx.x * kCtItems] = make_uint4(0, 0, 0, 0);
@@ -385,7 +386,7 @@ __device__ __forceinline__ void ct_flush(const uint8_t* buf, uint8_t* out, uint6
 // vertices in split_list. WIDE: a number may take ten bytes (first-edge IDs
 // of 2^35 on), otherwise five.
 template <bool WGT, bool WIDE>
-__global__ __launch_bounds__(kCtThreads) void k_csr_encode(CsrIn g, const int64_t* blk, int64_t nb,
+__global__ __launch_bounds__(kCtThreads) void k_csr_encode(CsrIn g, const int64_t* blk, int64_t nb, int64_t c0,
                                                            const uint64_t* tbase, uint64_t* offs, uint64_t* cpos,
                                                            int32_t* split_list, uint32_t* nsplit, uint8_t* out) {
   // each position takes at most one header, or one neighbour code and weight code
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(kCtThreads) void k_csr_encode(CsrIn g, const int64_
   __shared__ uint16_t hx[kCtWork + 1];  // header bytes of the stretch's vertices before each one
   __shared__ uint16_t sx[kCtWork + 1];  // code bytes of the stretch's entries before each one
   __shared__ int32_t scan[kCtThreads / kWave];
-  const int64_t c = blockIdx.x;
+  const int64_t c = c0 + blockIdx.x;
   const CtSpan sp = ct_span(g, blk, nb, c);
   const CtEntries<WGT> en(g, sp);
   const int32_t t0 = (int32_t)threadIdx.x * kCtItems;
@@ -860,11 +861,11 @@ __device__ uint32_t itv_run(const CsrIn& g, ItvShared& sh, const ItvRun& r, uint
 // at tsize[c] (the stretch's first byte by then); vertices split into chunks
 // are listed for k_chunk_tables.
 template <bool WGT, bool WRITE>
-__global__ __launch_bounds__(kItvThreads) void k_itv(CsrIn g, const int64_t* blk, int64_t nb, uint64_t* tsize,
-                                                     uint64_t* offs, uint64_t* cpos, int32_t* split_list,
-                                                     uint32_t* nsplit, uint8_t* out) {
+__global__ __launch_bounds__(kItvThreads) void k_itv(CsrIn g, const int64_t* blk, int64_t nb, int64_t c0,
+                                                     uint64_t* tsize, uint64_t* offs, uint64_t* cpos,
+                                                     int32_t* split_list, uint32_t* nsplit, uint8_t* out) {
   __shared__ ItvShared sh;
-  const int64_t c = blockIdx.x;
+  const int64_t c = c0 + blockIdx.x;
   const int64_t v0 = blk[c], v1 = blk[c + 1];
   const uint64_t two_m = g.xadj[g.n];
   const uint64_t e0 = (uint64_t)c * kItvWork - (uint64_t)v0;
@@ -1291,11 +1292,12 @@ __device__ __forceinline__ bool decode_run(const uint8_t* __restrict__ bytes, De
 // err[0]: malformed records; err[1]: the offsets decrease (blk is incomplete).
 template <bool WGT>
 __global__ __launch_bounds__(kDecThreads) void k_decode(GraphView g, const uint64_t* xadj, const int64_t* blk,
-                                                        int64_t nb, int32_t* adjncy, int32_t* adjwgt, uint32_t* err) {
+                                                        int64_t nb, int64_t c0, int32_t* adjncy, int32_t* adjwgt,
+                                                        uint32_t* err) {
   __shared__ DecShared sh;
   if (err[1]) return;
   constexpr uint32_t per = WGT ? 2u : 1u;
-  const int64_t c = blockIdx.x;
+  const int64_t c = c0 + blockIdx.x;
   const int64_t v0 = blk[c], v1 = blk[c + 1];
   const uint64_t e0 = (uint64_t)c * kDecWork - (uint64_t)v0;
   const uint64_t e1 = c + 1 < nb ? (uint64_t)(c + 1) * kDecWork - (uint64_t)v1 : g.two_m;
@@ -1377,7 +1379,6 @@ lp_status check_csr(const CsrIn& in, bool size, Scratch& sc, CsrPlan* P) {
   if (x0 != 0) return LP_EINVAL;
   P->two_m = xn;
   P->nb = merged_stretches(xn, in.n, kCtWork);
-  if (P->nb > 0x7FFFFFFFll) return LP_EUNSUPPORTED;
   const bool wgt = in.adjwgt != nullptr;
   P->blk = sc.alloc<int64_t>((size_t)P->nb + 1);
   CsrAcc* acc = sc.alloc<CsrAcc>(1);
@@ -1392,9 +1393,9 @@ lp_status check_csr(const CsrIn& in, bool size, Scratch& sc, CsrPlan* P) {
   LP_CHECK(merged_blocks(in.xadj, in.n, kCtWork, P->nb, P->blk, &acc->xerr, s));
   auto kern = wgt ? (size ? k_csr_scan<true, true> : k_csr_scan<true, false>)
                   : (size ? k_csr_scan<false, true> : k_csr_scan<false, false>);
-  hipLaunchKernelGGL(kern, dim3((unsigned)P->nb), dim3(kCtThreads), 0, s, in, P->blk, P->nb, acc, tdeg, tw,
-                     wspan, P->tbase);
-  LP_CHECK_LAUNCH();
+  LP_CHECK(launch_sliced(P->nb, kCtThreads, [&](int64_t first, dim3 grid) {
+    hipLaunchKernelGGL(kern, grid, dim3(kCtThreads), 0, s, in, P->blk, P->nb, first, acc, tdeg, tw, wspan, P->tbase);
+  }));
   hipLaunchKernelGGL(k_csr_max, dim3(grid_for(P->nb, 1024, 64)), dim3(256), 0, s, tdeg, tw, wspan, P->nb, acc);
   LP_CHECK_LAUNCH();
   if (in.vwgt && in.n > 0) {
@@ -1499,16 +1500,17 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
       cp.nb = merged_stretches(two_m, n, kItvWork);
       cp.blk = sc.alloc<int64_t>((size_t)cp.nb + 1);
       cp.tbase = sc.alloc<uint64_t>(cp.nb);
-      if (cp.nb > 0x7FFFFFFFll || sc.failed) {
-        st = sc.failed ? LP_ENOMEM : LP_EUNSUPPORTED;
+      if (sc.failed) {
+        st = LP_ENOMEM;
         break;
       }
       st = merged_blocks(xadj, n, kItvWork, cp.nb, cp.blk, &cp.acc->xerr, s);
       if (st) break;
-      hipLaunchKernelGGL((g->weighted ? k_itv<true, false> : k_itv<false, false>), dim3((unsigned)cp.nb),
-                         dim3(kItvThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, (uint64_t*)nullptr, (uint64_t*)nullptr,
-                         (int32_t*)nullptr, (uint32_t*)nullptr, (uint8_t*)nullptr);
-      st = last_error();
+      st = launch_sliced(cp.nb, kItvThreads, [&](int64_t first, dim3 grid) {
+        hipLaunchKernelGGL((g->weighted ? k_itv<true, false> : k_itv<false, false>), grid, dim3(kItvThreads), 0, s, in,
+                           cp.blk, cp.nb, first, cp.tbase, (uint64_t*)nullptr, (uint64_t*)nullptr, (int32_t*)nullptr,
+                           (uint32_t*)nullptr, (uint8_t*)nullptr);
+      });
       if (!st) st = scan_exclusive_u64(cp.tbase, cp.tbase, cp.nb, &cp.acc->nbytes, sc);
       if (st) break;
       if (hipMemcpyAsync(&nbytes, &cp.acc->nbytes, sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -1539,16 +1541,18 @@ static lp_status make_handle(int32_t n, const uint64_t* xadj, const int32_t* adj
         break;
       }
       if (intervals) {
-        hipLaunchKernelGGL((g->weighted ? k_itv<true, true> : k_itv<false, true>), dim3((unsigned)cp.nb),
-                           dim3(kItvThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, g->offs, cpos, list,
-                           &cp.acc->nsplit, g->bytes);
+        st = launch_sliced(cp.nb, kItvThreads, [&](int64_t first, dim3 grid) {
+          hipLaunchKernelGGL((g->weighted ? k_itv<true, true> : k_itv<false, true>), grid, dim3(kItvThreads), 0, s, in,
+                             cp.blk, cp.nb, first, cp.tbase, g->offs, cpos, list, &cp.acc->nsplit, g->bytes);
+        });
       } else {
         auto kern = g->weighted ? k_csr_encode<true, true>
                                 : two_m < (1ull << 35) ? k_csr_encode<false, false> : k_csr_encode<false, true>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)cp.nb), dim3(kCtThreads), 0, s, in, cp.blk, cp.nb, cp.tbase, g->offs,
-                           cpos, list, &cp.acc->nsplit, g->bytes);
+        st = launch_sliced(cp.nb, kCtThreads, [&](int64_t first, dim3 grid) {
+          hipLaunchKernelGGL(kern, grid, dim3(kCtThreads), 0, s, in, cp.blk, cp.nb, first, cp.tbase, g->offs, cpos, list,
+                             &cp.acc->nsplit, g->bytes);
+        });
       }
-      st = last_error();
       if (st || !split) break;
       hipLaunchKernelGGL(k_chunk_tables, dim3(grid_for((int64_t)(two_m / thr + 1), 4, 1024)), dim3(256),
                          0, s, in, list, &cp.acc->nsplit, g->offs, cpos, g->bytes);
@@ -1637,13 +1641,13 @@ extern "C" lp_status lp_decompress(const lp_graph* g, uint64_t* xadj, int32_t* a
     LP_CHECK_LAUNCH();
   } else if (g->two_m) {
     const int64_t nb = merged_stretches(g->two_m, g->n, kDecWork);
-    if (nb > 0x7FFFFFFFll) return LP_EUNSUPPORTED;
     int64_t* blk = sc.alloc<int64_t>((size_t)nb + 1);
     if (!blk) return LP_ENOMEM;
     LP_CHECK(merged_blocks(xadj, g->n, kDecWork, nb, blk, err + 1, s));
-    hipLaunchKernelGGL(g->weighted ? k_decode<true> : k_decode<false>, dim3((unsigned)nb), dim3(kDecThreads), 0, s, v,
-                       xadj, blk, nb, adjncy, adjwgt, err);
-    LP_CHECK_LAUNCH();
+    LP_CHECK(launch_sliced(nb, kDecThreads, [&](int64_t first, dim3 grid) {
+      hipLaunchKernelGGL(g->weighted ? k_decode<true> : k_decode<false>, grid, dim3(kDecThreads), 0, s, v, xadj, blk, nb,
+                         first, adjncy, adjwgt, err);
+    }));
   }
   uint32_t h[2] = {0, 0};
   LP_CHECK_HIP(hipMemcpyAsync(h, err, sizeof(h), hipMemcpyDeviceToHost, s));

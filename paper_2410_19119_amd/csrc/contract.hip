@@ -1126,7 +1126,7 @@ constexpr int kPlItems = 8;
 constexpr int kPlWork = kPlThreads * kPlItems;
 
 __global__ __launch_bounds__(kPlThreads) void k_place_light(const uint64_t* cx, const int64_t* blk, int64_t nb,
-                                                            uint64_t two_m, const uint64_t* rbase,
+                                                            int64_t c0, uint64_t two_m, const uint64_t* rbase,
                                                             const uint8_t* heavy, const Rec* rec, int32_t* adjncy,
                                                             int32_t* adjwgt, unsigned long long* tw, uint32_t* td,
                                                             unsigned long long* wspan) {
@@ -1138,7 +1138,7 @@ __global__ __launch_bounds__(kPlThreads) void k_place_light(const uint64_t* cx, 
   __shared__ int32_t scan[kPlThreads / kWave];
   __shared__ unsigned long long redw[kPlThreads / kWave];
   __shared__ uint32_t redd[kPlThreads / kWave];
-  const int64_t c = blockIdx.x;
+  const int64_t c = c0 + blockIdx.x;
   const int64_t v0 = blk[c], v1 = blk[c + 1];
   const uint64_t e0 = (uint64_t)c * kPlWork - (uint64_t)v0;
   const uint64_t e1 = c + 1 < nb ? (uint64_t)(c + 1) * kPlWork - (uint64_t)v1 : two_m;
@@ -1688,8 +1688,11 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
     if (!st && H > 0) st = zero_u32((uint32_t*)hsum, 2 * (int64_t)H, s);
     if (!st) st = merged_blocks(cg->xadj, nc, kPlWork, nst, blk, (uint32_t*)(mx + 2), s);
     if (st) break;
-    hipLaunchKernelGGL(k_place_light, dim3((unsigned)nst), dim3(kPlThreads), 0, s, cg->xadj, blk, nst, h.two_mc, rbase,
-                       heavy, rec, cg->adjncy, cg->adjwgt, tw, td, mx + 3);
+    st = launch_sliced(nst, kPlThreads, [&](int64_t first, dim3 grid) {
+      hipLaunchKernelGGL(k_place_light, grid, dim3(kPlThreads), 0, s, cg->xadj, blk, nst, first, h.two_mc, rbase, heavy,
+                         rec, cg->adjncy, cg->adjwgt, tw, td, mx + 3);
+    });
+    if (st) break;
     hipLaunchKernelGGL(k_place_max, dim3(grid_for(nst, 1024, 64)), dim3(256), 0, s, tw, td, mx + 3, nst, mx);
     if (T > 0) {
       hipLaunchKernelGGL(k_place_heavy, dim3(grid_for((int64_t)T * kWave, 256, 65536)), dim3(256), 0, s, hv, T, tscan,

@@ -144,4 +144,17 @@ inline unsigned grid_for(int64_t items, int per_block, unsigned cap = 1u << 20) 
 
 #define LP_CHECK_LAUNCH() LP_CHECK(last_error())
 
+// One workgroup of `threads` per item of [0, count): launch(first, grid) starts
+// the workgroups of items first .. first + grid - 1. One launch unless count *
+// threads reaches 2^32 threads, which HIP does not launch at once.
+template <typename L>
+lp_status launch_sliced(int64_t count, int threads, L&& launch) {
+  const int64_t most = 0xFFFFFFFFll / threads;
+  for (int64_t first = 0; first < count; first += most) {
+    launch(first, dim3((unsigned)(count - first < most ? count - first : most)));
+    LP_CHECK_LAUNCH();
+  }
+  return LP_OK;
+}
+
 }  // namespace lp
