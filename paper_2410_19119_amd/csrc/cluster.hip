@@ -126,7 +126,7 @@ __device__ __forceinline__ void consider(const RoundCtx& x, const VParams& p, in
 // ------------------------------------------------------- lane per vertex --
 template <bool COMP, int MODE, bool ITV>
 __device__ __forceinline__ void rate_lane(const RoundCtx& x, VDesc vd, int32_t cnt, uint32_t block) {
-  const int32_t i = block * 256 + threadIdx.x;
+  const int64_t i = (int64_t)block * 256 + threadIdx.x;
   if constexpr (MODE == kModeCut) {
     __shared__ unsigned long long red[4];
     unsigned long long c = 0;

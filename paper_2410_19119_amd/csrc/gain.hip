@@ -425,7 +425,7 @@ __device__ __forceinline__ void gt_emit(const GtRound& r, int32_t u, const Cand&
 template <typename V>
 __global__ __launch_bounds__(256) void k_gt_select_lane(GtView<V> t, GtRound r, const int32_t* list, int32_t cnt) {
   if (*r.done) return;
-  const int32_t i = blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= cnt) return;
   const int32_t u = list[i];
   const int32_t own_c = r.C[u];

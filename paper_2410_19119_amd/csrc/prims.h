@@ -120,7 +120,10 @@ lp_status zero_u32(uint32_t* p, int64_t n, hipStream_t s);
 
 #define last_error() ::lp::hip_fail(hipGetLastError(), "kernel launch", __FILE__, __LINE__)
 
-inline unsigned grid_for(int64_t items, int per_block, unsigned cap = 1u << 20) {
+// Workgroups for `items` of which one takes per_block. Only kernels that loop
+// may be given a cap: most of the lists that a kernel walks with one item per
+// thread reach the number of vertices, 2^31 - 1.
+inline unsigned grid_for(int64_t items, int per_block, unsigned cap = 0x7FFFFFFF) {
   int64_t b = (items + per_block - 1) / per_block;
   if (b < 1) b = 1;
   if (b > (int64_t)cap) b = cap;
