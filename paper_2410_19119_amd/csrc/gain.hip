@@ -476,6 +476,8 @@ __global__ __launch_bounds__(256) void k_gt_select_wave(GtView<V> t, GtRound r, 
 
 // The update of one neighbour v of a moved vertex: w(u, v) leaves block
 // `from` and joins block `to` in v's slice. Both home slots are read together.
+// A vertex without neighbours of its own (the graph is not symmetric, which
+// nothing checks) has no slots: `from` is missing and `to` finds no place.
 template <typename V>
 __device__ __forceinline__ void gt_move_edge(const GtView<V>& t, int32_t v, const GtSlice& sl, int32_t from,
                                              int32_t to, int32_t wt) {
@@ -484,8 +486,14 @@ __device__ __forceinline__ void gt_move_edge(const GtView<V>& t, int32_t v, cons
     gt_atomic_add(&t.val[sl.base + (uint32_t)to], (V)wt);
     return;
   }
-  const uint32_t hf = gt_hash(from, sl.L), ht = gt_hash(to, sl.L);
-  const int32_t kf = t.key[sl.base + hf], kt = t.key[sl.base + ht];
+  uint32_t hf = 0, ht = 0;
+  int32_t kf = kGtEmpty, kt = kGtEmpty;
+  if (sl.L) {
+    hf = gt_hash(from, sl.L);
+    ht = gt_hash(to, sl.L);
+    kf = t.key[sl.base + hf];
+    kt = t.key[sl.base + ht];
+  }
   const int64_t f = gt_slot(t, sl, from, hf, kf, false);
   if (f >= 0) gt_atomic_add(&t.val[f], (V)-wt);
   else atomicAdd(&t.cnt[1], 1u);
