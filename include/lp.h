@@ -470,8 +470,10 @@ void lp_trim_memory(void);
  * The caller's device allocator (the boundary's allocator of scratch memory;
  * e.g. a framework's caching allocator). alloc returns `bytes` of device
  * memory on the current device usable in the order of `stream` (NULL when
- * out of memory: the call then fails with LP_ENOMEM); free releases a block
- * in the order of `stream` (the stream of the library's last use of it).
+ * out of memory: it is asked once more if the library had memory of freed
+ * handles to give back to the device, else the call fails with LP_ENOMEM);
+ * free releases a block in the order of `stream` (the stream of the library's
+ * last use of it).
  * Both are called from the thread of the library call, with no lock of the
  * library held, and must be thread-safe if several threads call the library.
  */

@@ -112,6 +112,20 @@ void handle_trim_locked(HandlePool& hp, int dev, size_t keep) {
   clear_error();
 }
 
+// Frees every idle handle block of the current device; false if there was none.
+bool handle_trim_device() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kCacheDevices) {
+    clear_error();
+    return false;
+  }
+  HandlePool& hp = handle_pool();
+  std::lock_guard<std::mutex> lock(hp.mu);
+  const bool any = hp.cached[dev] > 0;
+  handle_trim_locked(hp, dev, 0);
+  return any;
+}
+
 // The caller's allocator (lp_set_allocator): when set, every scratch block
 // and every buffer of a handle made inside a call comes from it. Blocks keep
 // the allocator that made them, so switching allocators never mixes them up.
@@ -138,6 +152,8 @@ void* cache_alloc(size_t bytes, hipStream_t s) {
   }
   if (ext) {
     void* p = a.alloc(bytes ? bytes : 1, (void*)s, a.ctx);
+    // out of memory: what freed handles left behind is the device's, not this allocator's
+    if (!p && handle_trim_device()) p = a.alloc(bytes ? bytes : 1, (void*)s, a.ctx);
     if (!p) return nullptr;
     std::lock_guard<std::mutex> lock(g_ext_mu);
     g_ext_live[p] = ExtBlock{bytes, a};
@@ -183,12 +199,7 @@ void* cache_alloc(size_t bytes, hipStream_t s) {
     if (cache_log()) fprintf(stderr, "[lpgpu-cache] out of memory for %zu bytes: emptying %zu cached\n", need, c->cached);
     (void)hipDeviceSynchronize();
     trim_locked(*c, 0);
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) {
-      HandlePool& hp = handle_pool();
-      std::lock_guard<std::mutex> hlock(hp.mu);
-      handle_trim_locked(hp, dev, 0);
-    }
+    (void)handle_trim_device();
     if (hipMalloc(&p, need) != hipSuccess) {
       clear_error();
       return nullptr;
