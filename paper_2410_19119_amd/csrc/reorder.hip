@@ -79,8 +79,8 @@ void ro_delete(void* p) {
   if (!r) return;
   (void)hipDeviceSynchronize();
   if (r->g) lp_graph_free(r->g);
-  (void)hipFree(r->orig);
-  (void)hipFree(r->pos);
+  handle_free(r->orig);
+  handle_free(r->pos);
   delete r;
 }
 
@@ -99,8 +99,9 @@ lp_status build(const lp_graph* g, hipStream_t s, Reorder* R) {
   uint64_t* nxadj = sc.alloc<uint64_t>((size_t)n + 1);
   int32_t* nvwgt = g->vwgt ? sc.alloc<int32_t>(n) : nullptr;
   if (sc.failed) return LP_ENOMEM;
-  LP_CHECK_HIP(hipMalloc((void**)&R->orig, (size_t)n * sizeof(int32_t)));
-  LP_CHECK_HIP(hipMalloc((void**)&R->pos, (size_t)n * sizeof(int32_t)));
+  R->orig = (int32_t*)handle_alloc((size_t)n * sizeof(int32_t));
+  R->pos = (int32_t*)handle_alloc((size_t)n * sizeof(int32_t));
+  if (!R->orig || !R->pos) return LP_ENOMEM;
   LP_CHECK(compute_degrees(g, deg, s));
   const uint32_t nh = (uint32_t)n;
   LP_CHECK_HIP(hipMemcpyAsync(cnt, &nh, sizeof(uint32_t), hipMemcpyHostToDevice, s));
