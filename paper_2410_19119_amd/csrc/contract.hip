@@ -86,25 +86,20 @@ __global__ void k_map(const int32_t* C, int32_t n, const uint32_t* id, const int
   }
 }
 
-// Takes packed words apart.
-__global__ void k_unpack(unsigned long long* dsum, unsigned long long* vw, int32_t nc) {
-  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < nc; a += (int64_t)gridDim.x * blockDim.x) {
-    const unsigned long long x = dsum[a];
-    vw[a] = x & 0x7FFFFFFFull;
-    dsum[a] = x >> 31;
-  }
-}
-
 // Class 0: no records; 1: wavefront; 2, 3: workgroup (small / large table);
-// 4: heavy. Staging capacity of light classes = min(dsum, nc - 1).
-__global__ void k_cclass(const unsigned long long* dsum, const unsigned long long* vw, int32_t nc, uint64_t* tcap,
+// 4: heavy. Staging capacity of light classes = min(dsum, nc - 1). PACKED:
+// takes k_map's words apart.
+template <bool PACKED>
+__global__ void k_cclass(unsigned long long* dsum, const unsigned long long* vw, int32_t nc, uint64_t* tcap,
                          uint8_t* cls, int32_t* vwgt_out, uint32_t* err) {
   for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < nc; a += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t d = dsum[a];
+    const unsigned long long x = dsum[a];
+    const uint64_t d = PACKED ? x >> 31 : x;
+    if constexpr (PACKED) dsum[a] = d;
     const uint8_t c = d == 0 ? 0 : d <= kClassWave ? 1 : d <= kClassBlockS ? 2 : d <= kClassBlockL ? 3 : 4;
     cls[a] = c;
     tcap[a] = std::min<uint64_t>(d, (uint64_t)nc - 1);
-    const unsigned long long w = vw[a];
+    const unsigned long long w = PACKED ? x & 0x7FFFFFFFull : vw[a];
     if (w > 0x7FFFFFFFull) atomicOr(err, kErrOverflow);
     vwgt_out[a] = (int32_t)w;
   }
@@ -675,8 +670,9 @@ struct LightSmem {
   uint32_t overflow;
 };
 
-// Light clusters that buckets cannot take (list, counted in *cnt): NT = 64, one cluster per wavefront (4 per workgroup);
-// NT = 256, one cluster per workgroup. The table has the next power of two
+// Light clusters that buckets cannot take (list, counted in *cnt): NT = 64,
+// one cluster per wavefront (4 per workgroup); NT = 256, one cluster per
+// workgroup. The table has the next power of two
 // >= 2 * min(dsum, nc - 1) entries, at most tmax; if that capacity was
 // clipped and the cluster turns out to have more than half of it distinct
 // neighbours, the cluster is appended to the heavy list instead.
@@ -1566,35 +1562,33 @@ extern "C" lp_status lp_contract(const lp_graph* g, const int32_t* labels, int32
     if (h.err) { st = LP_EINVAL; break; }
     const int32_t nc = (int32_t)h.nc;
     cg->n = nc;
-    unsigned long long* vw = sc.alloc<unsigned long long>(nc);
-    unsigned long long* dsum = sc.alloc<unsigned long long>(nc);
+    const bool packed = !g->vwgt && g->two_m < (1ull << 33);
+    // cleared at once (a small contraction is bound by its launches): the
+    // coarse degrees, record counts, weights unless packed, heavy marks
+    const size_t nclear = 2 * ((packed ? 2 : 3) * (size_t)nc + 1) + ((size_t)nc + 3) / 4;
+    uint64_t* cdeg = (uint64_t*)sc.alloc<uint32_t>(nclear);
+    unsigned long long* dsum = (unsigned long long*)cdeg + nc + 1;
+    unsigned long long* vw = packed ? nullptr : dsum + nc;
+    uint8_t* heavy = (uint8_t*)(dsum + (packed ? 1 : 2) * (size_t)nc);
     uint64_t* voff = sc.alloc<uint64_t>(n);
     uint64_t* rbase = sc.alloc<uint64_t>((size_t)nc + 1);
     uint64_t* tcap = sc.alloc<uint64_t>(nc);
-    uint64_t* cdeg = sc.alloc<uint64_t>((size_t)nc + 1);
     uint8_t* cls = sc.alloc<uint8_t>(nc);
-    uint8_t* heavy = sc.alloc<uint8_t>(nc);
     int32_t* lists = sc.alloc<int32_t>((size_t)6 * nc);
     if (graph_alloc(cg, (void**)&cg->vwgt, (size_t)nc * sizeof(int32_t)) != hipSuccess ||
         graph_alloc(cg, (void**)&cg->xadj, ((size_t)nc + 1) * sizeof(uint64_t)) != hipSuccess) { st = LP_ENOMEM; break; }
-    (void)hipMemsetAsync(vw, 0, (size_t)nc * 8, s);
-    (void)hipMemsetAsync(dsum, 0, (size_t)nc * 8, s);
-    (void)hipMemsetAsync(cdeg, 0, ((size_t)nc + 1) * sizeof(uint64_t), s);
-    (void)hipMemsetAsync(heavy, 0, (size_t)nc, s);
-    const bool packed = !g->vwgt && g->two_m < (1ull << 33);
+    if (sc.failed) { st = LP_ENOMEM; break; }
+    st = zero_u32((uint32_t*)cdeg, (int64_t)nclear, s);
+    if (st) break;
     hipLaunchKernelGGL(packed ? k_map<true> : k_map<false>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, labels, n,
                        flags, deg, g->vwgt, map, vw, dsum, voff);
-    if (packed)
-      hipLaunchKernelGGL(k_unpack, dim3(grid_for(nc, 256, 65536)), dim3(256), 0, s, dsum, vw, nc);
-    st = last_error();
-    if (st) break;
-    st = scan_exclusive_u64((const uint64_t*)dsum, rbase, nc, &ctl->nrec, sc);
-    if (st) break;
-    hipLaunchKernelGGL(k_cclass, dim3(grid_for(nc, 256, 65536)), dim3(256), 0, s, dsum, vw, nc, tcap, cls, cg->vwgt,
-                       &ctl->err);
+    hipLaunchKernelGGL(packed ? k_cclass<true> : k_cclass<false>, dim3(grid_for(nc, 256, 65536)), dim3(256), 0, s, dsum,
+                       vw, nc, tcap, cls, cg->vwgt, &ctl->err);
     hipLaunchKernelGGL(k_class_list, dim3(grid_for(nc, 256 * 8, 65536)), dim3(256), 0, s, cls, nc, ctl->ccount, lists,
                        (int64_t)nc);
     st = last_error();
+    if (st) break;
+    st = scan_exclusive_u64((const uint64_t*)dsum, rbase, nc, &ctl->nrec, sc);
     if (st) break;
     // record pass: the edge visitor shared with rating and the cut
     Rec* rec = sc.alloc<Rec>(g->two_m);
