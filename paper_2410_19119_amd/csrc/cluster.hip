@@ -312,8 +312,10 @@ struct TileCfg {
 // LDS allows (six of 256 threads, three of 512) to hide the latency of their
 // gathers and barriers: left alone the compiler takes 81 to 88 for the large
 // tiles, which then run two to a CU (R-MAT 2^24: 1.59 instead of 1.22 ms per
-// round). Record mode's table has 32-bit sums: five small tiles to a CU. Other
-// instances keep the compiler's choice.
+// round). Record mode's table has 32-bit sums: five small tiles to a CU, at 96
+// registers. Other instances keep the compiler's choice. No instance spills:
+// with the caps alone nine record kernels did (2 to 7 registers, reloaded once
+// per tile or hub; R-MAT 2^23 contracts in 11.83 ms with them, 11.70 without).
 template <class T, int MODE, bool COMP>
 constexpr int tile_waves_per_eu() {
   return MODE == kModeRate && COMP ? 6 : MODE == kModeRec && T::kThreads == 256 ? 5 : 1;
@@ -331,7 +333,7 @@ constexpr int kTileSeg = 128;  // vertices walked by one thread of the tiling pa
 // kept eight workgroups busy while 2048 queued on the counters, 0.27 ms per
 // round for what takes 0.02.
 __device__ __forceinline__ uint32_t grab_size(uint32_t items, uint32_t most, uint32_t grid) {
-  return max(1u, min(most, items / (3u * grid)));
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)max(1u, min(most, items / (3u * grid))));
 }
 constexpr int kTileGrab = 8;   // most tiles taken per atomic of a hand-out counter
 constexpr int kTileMaxDeg = 2048;  // largest degree of the small-tile bucket (default and bound of t_tile)
@@ -396,6 +398,25 @@ __host__ __device__ inline TileLayout tile_layout(bool comp, bool weighted) {
   if (L.abytes < L.table_bytes) L.abytes = L.table_bytes;
   L.abytes = (L.abytes + 15u) & ~15u;
   return L;
+}
+
+// The thread's number, not known to be the same in the next tile or piece: addresses
+// made from it are not kept in registers from one to the next.
+__device__ __forceinline__ uint32_t here(uint32_t tid) {
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+// Records go out from a base in scalar registers (the same in all lanes) and a
+// 32-bit offset: a 64-bit address per lane is what the record kernels have no
+// register for.
+__device__ __forceinline__ Rec* uniform_ptr(Rec* p) {
+  const uint64_t a = (uint64_t)p;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  return (Rec*)(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ void put_rec(Rec* base, uint32_t i, Rec r) {
+  *(Rec*)((uint8_t*)base + (uint32_t)(i * (uint32_t)sizeof(Rec))) = r;
 }
 
 __device__ __forceinline__ uint32_t tile_slots(uint32_t d) { return d + (d >> 1) + 1; }
@@ -482,7 +503,7 @@ __device__ __forceinline__ ItvTable itv_table(uint32_t* area, const uint32_t* nu
   t.L = area + (MAXSEG + 1);
   t.start = (int32_t*)(area + 2 * MAXSEG + 2);
   t.cum = area + 2 * MAXSEG + 2 + MAXITV;
-  const int tid = threadIdx.x;
+  const int tid = (int)here(threadIdx.x);
   uint32_t kk = 0;
   if (tid < nseg && ebase[tid + 1] > ebase[tid]) kk = nums[rstart[tid]];  // empty segments have no count
   int32_t tot;
@@ -1055,14 +1076,14 @@ __device__ __forceinline__ void rate_tiles(const RoundCtx& x, VDesc vd, const in
           __syncthreads();
 #pragma unroll
           for (int k = 0; k < ITEMS; ++k) {
-            const bool lead = vi[k] >= 0 && vj[k] >= 0 && ((claim >> k) & 1u);
+            const bool lead = (claim >> k) & 1u;
             wt[k] = lead ? (int32_t)vals[qs[k]] : 0;
             nb[k] = lead ? nb[k] : -1;
           }
         } else {
 #pragma unroll
           for (int k = 0; k < ITEMS; ++k)
-            if (vi[k] >= 0 && nb[k] == sh.own_c[vi[k]]) nb[k] = -1;
+            if (vi[k] < 0 || nb[k] == sh.own_c[vi[k]]) nb[k] = -1;
         }
         // a vertex's records lie one after another: gathered in LDS and
         // written by wavefronts in whole lines (a thread's own run of items
@@ -1071,12 +1092,12 @@ __device__ __forceinline__ void rate_tiles(const RoundCtx& x, VDesc vd, const in
         Rec* stage = (Rec*)A;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k)
-          if (vi[k] >= 0) stage[e0 + k] = Rec{nb[k], wt[k]};
+          if ((uint32_t)k < Dd && e0 + k < Et) stage[e0 + k] = Rec{nb[k], wt[k]};
         __syncthreads();
-        for (int32_t i = tid / kWave; i < nv; i += NT / kWave) {
+        for (int32_t i = __builtin_amdgcn_readfirstlane(tid / kWave); i < nv; i += NT / kWave) {
           const uint32_t b0 = sh.ebase[i], dg = sh.ebase[i + 1] - b0;
-          Rec* out = x.rec + sh.rb[i];
-          for (uint32_t q = (uint32_t)(tid % kWave); q < dg; q += kWave) out[q] = stage[b0 + q];
+          Rec* out = uniform_ptr(x.rec + sh.rb[i]);
+          for (uint32_t q = (uint32_t)lane_id(); q < dg; q += kWave) put_rec(out, q, stage[b0 + q]);
         }
         __syncthreads();
         continue;
@@ -1370,7 +1391,7 @@ struct PieceShared {
 
 // H1: one workgroup per hub piece (of a whole hub: H1 to H3 at once).
 // Whole hubs fill a CU with 16 wavefronts (one workgroup, or two of half size)
-// at up to 128 registers.
+// at up to 128 registers, which the 16-bit record kernels use up.
 template <class Cfg, typename V, bool COMP, int MODE = kModeRate, bool ITV = false>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWhole ? 4 : 1) void k_hub_piece(RoundCtx x, HubMeta hm, int32_t npieces,
                                                             uint32_t* ctr, TileLayout L) {
@@ -1410,6 +1431,8 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWhole ? 4 : 1) void k_hub_piec
     // 0. streams
     if (tid == 0) {
       uint32_t e = 0, dw = 0, nn = 0;
+      constexpr int kAhead = MODE == kModeRec && NS > 4 ? NS / 2 : NS;  // streams read at a time
+#pragma unroll kAhead
       for (int s = 0; s < NS; ++s) {
         const HubStream hs = hm.streams[pc * NS + s];
         const uint32_t cnt = hs.cnt & ~kStreamZig;
@@ -1617,9 +1640,9 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWhole ? 4 : 1) void k_hub_piec
         // the tiles): the edge that put a neighbour into the table carries
         // the sum, the others become empty records
         __syncthreads();  // numbers consumed: region A becomes the table
-        const uint32_t S = tile_slots(Et);
-        for (uint32_t q = tid; q < S; q += NT) keys[q] = kEmpty;
-        for (uint32_t q = tid; q < S; q += NT) vals[q] = 0;
+        const uint32_t S = tile_slots(Et), t0 = here(tid);
+        for (uint32_t q = t0; q < S; q += NT) keys[q] = kEmpty;
+        for (uint32_t q = t0; q < S; q += NT) vals[q] = 0;
         __syncthreads();
         int32_t vj[ITEMS];
 #pragma unroll
@@ -1633,14 +1656,14 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWhole ? 4 : 1) void k_hub_piec
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-          const bool lead = vi[k] >= 0 && vj[k] >= 0 && ((claim >> k) & 1u);
+          const bool lead = (claim >> k) & 1u;
           wt[k] = lead ? (int32_t)vals[qs[k]] : 0;
           nb[k] = lead ? nb[k] : -1;
         }
       } else {
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k)
-          if (vi[k] >= 0 && nb[k] == own) nb[k] = -1;
+          if (vi[k] < 0 || nb[k] == own) nb[k] = -1;
       }
       if constexpr (MODE == kModeRec) {
         // gathered in LDS and written in whole lines
@@ -1648,10 +1671,10 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWhole ? 4 : 1) void k_hub_piec
         Rec* stage = (Rec*)A;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k)
-          if (vi[k] >= 0) stage[e0 + k] = Rec{nb[k], wt[k]};
+          if ((uint32_t)k < Dd && e0 + k < Et) stage[e0 + k] = Rec{nb[k], wt[k]};
         __syncthreads();
-        Rec* r = x.rec + x.rbase[own] + x.voff[prop_slot(x, u)] + (uint64_t)pj.y * Cfg::kEdges;
-        for (uint32_t q = tid; q < Et; q += NT) r[q] = stage[q];
+        Rec* r = uniform_ptr(x.rec + x.rbase[own] + x.voff[prop_slot(x, u)] + (uint64_t)pj.y * Cfg::kEdges);
+        for (uint32_t q = here(tid); q < Et; q += NT) put_rec(r, q, stage[q]);
       }
       __syncthreads();
       continue;
