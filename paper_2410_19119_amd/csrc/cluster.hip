@@ -3506,19 +3506,20 @@ lp_status get_plans(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t t
 
 // The cached default plan's degrees, its short neighbourhoods (degree 1 to 16:
 // {vertex, degree, position of the first code or edge (low, high word)}) and its
-// other vertices with edges.
+// other vertices with edges, whose degrees add up to *long_edges.
 lp_status plan_degrees(const lp_graph* g, const int32_t** deg, const int4** lane, int32_t* nlane,
-                       const int32_t** longer, int32_t* nlong, hipStream_t s);
+                       const int32_t** longer, int32_t* nlong, uint64_t* long_edges, hipStream_t s);
 
 lp_status plan_degrees(const lp_graph* g, const int32_t** deg, hipStream_t s) {
   const int4* lane = nullptr;
   const int32_t* longer = nullptr;
   int32_t nlane = 0, nlong = 0;
-  return plan_degrees(g, deg, &lane, &nlane, &longer, &nlong, s);
+  uint64_t long_edges = 0;
+  return plan_degrees(g, deg, &lane, &nlane, &longer, &nlong, &long_edges, s);
 }
 
 lp_status plan_degrees(const lp_graph* g, const int32_t** deg, const int4** lane, int32_t* nlane,
-                       const int32_t** longer, int32_t* nlong, hipStream_t s) {
+                       const int32_t** longer, int32_t* nlong, uint64_t* long_edges, hipStream_t s) {
   const Plan* plan = nullptr;
   std::unique_ptr<Plan> tmp;
   LP_CHECK(get_plan(g, 16, kTileMaxDeg, TileLarge::kEdges, kDefaultHubPart, s, &plan, tmp));
@@ -3527,6 +3528,8 @@ lp_status plan_degrees(const lp_graph* g, const int32_t** deg, const int4** lane
   *nlane = plan->bn[0];
   *longer = plan->order + plan->bstart[1];
   *nlong = (int32_t)(plan->bstart[kNumBuckets] - plan->bstart[1]);
+  *long_edges = 0;
+  for (int b = 1; b < kNumBuckets; ++b) *long_edges += plan->bsums[b];
   return LP_OK;
 }
 

@@ -25,6 +25,7 @@ struct GainTable {
   const int4* lane = nullptr;    // its short neighbourhoods {vertex, degree, position (low, high)}
   const int32_t* longer = nullptr;  // its other vertices with edges
   int32_t nlane = 0, nlong = 0;
+  int32_t wave_max = 0;          // largest degree that a wavefront takes alone
   uint64_t* off = nullptr;    // n + 1 slot offsets; a slice of k slots is a dense row, a shorter one a hash slice
   int32_t* key = nullptr;     // entries: block of a hash slot, -1 = empty
   void* val = nullptr;        // entries: affinities (int32 or int64)

@@ -1,18 +1,26 @@
 // Sparse gain table (Section V of the paper; layout in gain.h), the public
 // lp_gain_table handle, and the table-driven selection step that lp_refine
 // uses instead of re-rating every neighbourhood in each round.
+#include <algorithm>
+
 #include "decode.h"
 #include "gain.h"
 
 namespace lp {
 
 lp_status plan_degrees(const lp_graph* g, const int32_t** deg, const int4** lane, int32_t* nlane,
-                       const int32_t** longer, int32_t* nlong, hipStream_t s);
+                       const int32_t** longer, int32_t* nlong, uint64_t* long_edges, hipStream_t s);
 
 namespace {
 
 constexpr int kGtLaneMax = 16;  // vertices up to this degree are filled / selected by one lane
-constexpr int kGtWaveMax = 512; // and up to this degree by one wavefront; a workgroup takes the rest
+// A wavefront takes a longer neighbourhood, which uses the device best as long
+// as no neighbourhood lasts much longer than the others (RGG-3D of 20,001
+// vertices, degree 1000, k = 3000: build, 2 % moves and queries 1.33 ms, with a
+// workgroup for each 1.68). One of more than this degree and more than twice
+// the mean of the longer ones gets a workgroup (R-MAT, 30,001 vertices, degree
+// 64, k = 64: 0.33 ms, with wavefronts for all 0.39).
+constexpr int kGtWaveMax = 512;
 constexpr int kGtThreads = 256; // threads of such a workgroup
 constexpr int kGtCounters = 8;
 constexpr int kGtWaves = 4;     // wavefronts per 256-thread workgroup
@@ -303,9 +311,10 @@ static_assert(2 * kGtLaneMax <= 32, "a lane's hash slice fits a mask of 32 slots
 
 // Work items of the group fill: one per vertex above kGtLaneMax, one per chunk
 // above the chunking threshold. Wavefronts take the neighbourhoods up to
-// kGtWaveMax (from the front of the list), workgroups the longer ones and the
-// chunks (from its end). Every thread takes kGtItemRun of the listed vertices,
-// so that two counter atomics serve that many per thread of a workgroup.
+// wave_max (from the front of the list), workgroups the longer ones (from its
+// end), chunks like the neighbourhood they are of. Every thread takes
+// kGtItemRun of the listed vertices, so that two counter atomics serve that
+// many per thread of a workgroup.
 constexpr int kGtItemRun = 4;
 
 __device__ __forceinline__ uint32_t gt_items_of(uint32_t d, uint32_t thr) {
@@ -313,7 +322,8 @@ __device__ __forceinline__ uint32_t gt_items_of(uint32_t d, uint32_t thr) {
 }
 
 __global__ __launch_bounds__(256) void k_gt_items(const int32_t* list, const int32_t* deg, int32_t n,
-                                                  uint32_t thr, int2* items, uint64_t cap, uint32_t* nitems) {
+                                                  uint32_t thr, int32_t wave_max, int2* items, uint64_t cap,
+                                                  uint32_t* nitems) {
   __shared__ int32_t scan[256 / kWave + 1];
   __shared__ uint32_t base_sm[2];
   const int64_t b = (int64_t)blockIdx.x * (256 * kGtItemRun) + threadIdx.x;
@@ -327,7 +337,7 @@ __global__ __launch_bounds__(256) void k_gt_items(const int32_t* list, const int
 #pragma unroll
   for (int r = 0; r < kGtItemRun; ++r) {
     if (b + r * 256 < n) vd[r].y = deg[vd[r].x];
-    cnt[vd[r].y > kGtWaveMax] += gt_items_of((uint32_t)vd[r].y, thr);
+    cnt[vd[r].y > wave_max] += gt_items_of((uint32_t)vd[r].y, thr);
   }
   for (int x = 0; x < 2; ++x) {
     int32_t tot;
@@ -341,7 +351,7 @@ __global__ __launch_bounds__(256) void k_gt_items(const int32_t* list, const int
     const uint32_t ni = gt_items_of((uint32_t)vd[r].y, thr);
     for (uint32_t j = 0; j < ni; ++j) {
       const int2 it = make_int2(vd[r].x, ni > 1 ? (int)j : -1);
-      if (vd[r].y > kGtWaveMax) items[cap - 1 - o[1]++] = it;
+      if (vd[r].y > wave_max) items[cap - 1 - o[1]++] = it;
       else items[o[0]++] = it;
     }
   }
@@ -358,8 +368,8 @@ __device__ __forceinline__ void lds_add_v(int64_t* p, int64_t w) {
 // stored as it is (the whole neighbourhood) or added with one global atomic
 // per nonzero block (a chunk of it). What bounds a group is the chain decode,
 // gather, LDS add of a window of codes: up to four gathers per thread are in
-// flight, and four wavefronts share the longer neighbourhoods, which left a
-// single one the last to end (2,000,003 R-MAT vertices: 648 us for all, now
+// flight, and four wavefronts share the neighbourhoods much longer than the
+// others, which left a single one the last to end (2,000,003 R-MAT vertices: 648 us for all, now
 // 340 + 277 us).
 constexpr int kGtStage = 1024;
 constexpr int kGtPerCopy = 64;  // edges per copy of a row
@@ -506,7 +516,7 @@ __device__ __forceinline__ void gt_move_edge(const GtView<V>& t, int32_t v, cons
 // chunk above the chunking threshold ({move index, chunk or -1}), listed as
 // those of a fill.
 __global__ __launch_bounds__(256) void k_gt_move_items(const int4* moves, const uint32_t* count, const int32_t* deg,
-                                                       uint32_t thr, int2* items, uint64_t cap,
+                                                       uint32_t thr, int32_t wave_max, int2* items, uint64_t cap,
                                                        uint32_t* nitems) {
   const int64_t m = *count;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -519,7 +529,7 @@ __global__ __launch_bounds__(256) void k_gt_move_items(const int4* moves, const 
       if (mv.x >= 0 && mv.y != mv.z) {  // short ones: k_gt_update_lane
         const uint32_t d = (uint32_t)deg[mv.x];
         ni = gt_items_of(d, thr);
-        wide = d > (uint32_t)kGtWaveMax;
+        wide = d > (uint32_t)wave_max;
       }
     }
     for (int x = 0; x < 2; ++x) {
@@ -626,7 +636,7 @@ lp_status gt_fill(const GainTable& t, const int32_t* blocks, Scratch& sc) {
   uint32_t* nitems = t.cnt + 3;
   if (t.nlong > 0) {
     hipLaunchKernelGGL(k_gt_items, dim3(grid_for(t.nlong, 256 * kGtItemRun)), dim3(256), 0, s, t.longer, t.deg,
-                       t.nlong, chunk_threshold(g->intervals), t.items, t.nitems_cap, nitems);
+                       t.nlong, chunk_threshold(g->intervals), t.wave_max, t.items, t.nitems_cap, nitems);
     LP_CHECK_LAUNCH();
     hipLaunchKernelGGL((k_gt_fill_group<kGtThreads, V>), dim3(grid_for(t.nlong, 16, 4096)), dim3(256), 0, s,
                        g->view(), t.deg, blocks, t.items, t.nitems_cap, nitems, v);
@@ -661,7 +671,7 @@ lp_status gt_update_t(const GainTable& t, const int4* moves, const uint32_t* cou
   hipLaunchKernelGGL(k_gt_zero, dim3(1), dim3(64), 0, s, t.cnt + 3, (int64_t)2);
   LP_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_gt_move_items, dim3(grid_for(max_moves, 256, 16384)), dim3(256), 0, s, moves, count, t.deg,
-                     chunk_threshold(t.g->intervals), t.items, t.nitems_cap, t.cnt + 3);
+                     chunk_threshold(t.g->intervals), t.wave_max, t.items, t.nitems_cap, t.cnt + 3);
   LP_CHECK_LAUNCH();
   hipLaunchKernelGGL((k_gt_update<kGtThreads, V>), dim3(grid_for(max_moves, 16, 4096)), dim3(256), 0, s, t.g->view(),
                      t.deg, moves, t.items, t.nitems_cap, t.cnt + 3, v);
@@ -686,7 +696,10 @@ lp_status gt_create(const lp_graph* g, const int32_t* blocks, int32_t k, hipStre
   t->k = k;
   t->wide = g->max_wdeg > 0x7FFFFFFFll;
   const int32_t n = g->n;
-  LP_CHECK(plan_degrees(g, &t->deg, &t->lane, &t->nlane, &t->longer, &t->nlong, s));
+  uint64_t long_edges = 0;
+  LP_CHECK(plan_degrees(g, &t->deg, &t->lane, &t->nlane, &t->longer, &t->nlong, &long_edges, s));
+  const uint64_t twice_mean = 2 * long_edges / (uint64_t)std::max(t->nlong, 1);
+  t->wave_max = (int32_t)std::min<uint64_t>(std::max<uint64_t>(kGtWaveMax, twice_mean), 0x7FFFFFFF);
   auto grab = [&](size_t bytes) {
     void* p = cache_alloc(bytes ? bytes : 1, s);
     t->bytes += bytes;
