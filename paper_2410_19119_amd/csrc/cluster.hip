@@ -1230,10 +1230,18 @@ using PieceWhole32 = PieceCfg<1024, 12 * LP_CHUNK_LEN, 12, true>;
 // Whole hubs of at most half that size: half the threads and half the LDS, so
 // that a CU holds two and one works while the other waits at a barrier or for
 // its gathers (R-MAT 2^24, hubs of 4097 to 8000 edges: 1.46 ms a round with
-// workgroups of 1024, 0.95 with these).
+// workgroups of 1024, 0.95 with these). A launch of their own pays from
+// kHalfAlone hubs on, more than there are CUs, if there are no larger whole
+// hubs (degree 5000: 256 hubs 35 us a round either way, 257 hubs 57 against
+// 38). Next to larger ones, whose launch then has an end of its own to wait
+// for, it takes kHalfBeside of them, and with few larger ones (less than two of
+// those to a CU) kHalfBesideFew: 300 beside 2000 of degree 12000 373 us
+// together, 386 apart; 500 beside 1000 233 and 221, 448 beside 448 142 and 138;
+// 600 beside 100 99 and 115; R-MAT 2^23 1.39 ms and 0.98. R-MAT 2^26 has none:
+// its degrees lie in groups, and none between 4097 and 8000.
 using PieceHalf16 = PieceCfg<512, 8 * LP_CHUNK_LEN, 8, true>;
 using PieceHalf32 = PieceCfg<512, 6 * LP_CHUNK_LEN, 6, true>;
-constexpr int kHalfHubs = 512;  // with more whole hubs than this
+constexpr size_t kHalfAlone = 257, kHalfBeside = 448, kHalfBesideFew = 1024;
 template <class Cfg>
 constexpr bool whole_chunks() { return Cfg::kEdges == Cfg::kStreams * LP_CHUNK_LEN; }
 static_assert(whole_chunks<PieceHub>() && whole_chunks<PieceWhole16>() && whole_chunks<PieceWhole32>() &&
@@ -3236,10 +3244,9 @@ lp_status build_plan(const lp_graph* g, int32_t t_lane, int32_t t_tile, int32_t 
       (half ? wu[1] : whole ? wu[0] : hu).push_back(au[i]);
       (half ? wd[1] : whole ? wd[0] : hd).push_back(ad[i]);
     }
-    // a launch for each size pays where every CU gets several hubs; fewer hubs
-    // are over sooner in one, a whole CU each (a batch of 48 graphs with 38
-    // hubs: 41 us a round against 74)
-    if (wu[0].size() + wu[1].size() <= (size_t)kHalfHubs) {
+    // few hubs are over sooner in one launch, a whole CU each (a batch of 48
+    // graphs with 38 hubs: 41 us a round against 74)
+    if (wu[1].size() < (wu[0].empty() ? kHalfAlone : wu[0].size() < kHalfBeside ? kHalfBesideFew : kHalfBeside)) {
       wu[0].insert(wu[0].end(), wu[1].begin(), wu[1].end());
       wd[0].insert(wd[0].end(), wd[1].begin(), wd[1].end());
       wu[1].clear();
