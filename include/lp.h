@@ -201,7 +201,9 @@ typedef struct {
   int32_t t_tile;    /* t_lane..2048, default 2048 */
   int32_t t_block;   /* t_tile..4096, default 4096 */
   int32_t hub_part;  /* target edges per hub partition, 256..8192, default 2048 */
-  int32_t timing;    /* nonzero: time each phase with HIP events (stats must be given) */
+  int32_t timing;    /* nonzero: time each phase with HIP events (stats must be given). Every rating
+                        path then has a launch of its own; without it, a small graph's lanes and tiles
+                        share one, so its call takes less than its phases add up to */
   int32_t subrounds; /* sub-rounds per round, 1..64, default 1 (plain synchronous rounds) */
   int32_t gain_table; /* lp_refine only: nonzero rates from a sparse gain table (see lp_gain_table);
                          result-invariant; lp_cluster rejects it (LP_EINVAL) */

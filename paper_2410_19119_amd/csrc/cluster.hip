@@ -1148,8 +1148,12 @@ void k_rate_tile(RoundCtx x, VDesc vd, const int32_t* tiles, const uint32_t* nti
 
 // Small tiles and lanes of a round in one launch, tiles first: on graphs
 // where neither fills the device for long, one path's latencies (its code's
-// first fetch among them) hide behind the other's.
-constexpr int32_t kFuseTiles = 1 << 14, kFuseLanes = 1 << 21;  // most vertices of either path
+// first fetch among them) hide behind the other's. Calls of five rounds, apart
+// and together: RGG-3D of 24,001 vertices (22,424 in tiles) 523 us and 457;
+// RGG-2D of 8,000,001 (7,967,013 in lanes) 4266 and 4192. With more tiles it
+// becomes a wash (weighted R-MAT, 43,461 in tiles: 2060 us and 2092), then a
+// loss, lanes being held to the tiles' LDS (RGG-3D of 2,000,003: 3.71 and 3.89 ms).
+constexpr int32_t kFuseTiles = 1 << 15, kFuseLanes = 1 << 23;  // most vertices of either path
 template <typename V, bool COMP, bool ITV>
 __global__ __launch_bounds__(256) void k_rate_both(RoundCtx x, VDesc vt, const int32_t* tiles,
                                                    const uint32_t* ntiles_p, uint32_t* ctr, TileLayout L,
