@@ -517,7 +517,9 @@ lp_status scan_exclusive_t(const T* in, T* out, int64_t n, T* total_dev, Scratch
 // pairs 7 us.
 constexpr int kRsThreads = 256;
 // Pairs per thread: tiles of 2048 pairs keep more workgroups busy on few
-// pairs, tiles of 4096 halve the look-back of many.
+// pairs, tiles of 4096 halve the look-back of many (the acceptance of a round of
+// RGG-2D graphs with one and the other: 20,001 vertices 47 and 56 us, 1,048,576
+// 129 and 133, 2,000,001 183 and 177, 4,000,001 273 and 255).
 constexpr int kRsItemsFew = 8, kRsItemsMany = 16;
 constexpr int64_t kRsFew = 1 << 20;  // most pairs sorted in small tiles
 constexpr int kRsBack = 4;           // predecessors read at a time in a look-back
