@@ -770,7 +770,6 @@ template <class T, typename V, bool COMP, int MODE, bool ITV>
 __device__ __forceinline__ void rate_tiles(const RoundCtx& x, VDesc vd, const int32_t* tiles, const uint32_t* ntiles_p,
                                            uint32_t* ctr, const TileLayout& L, uint32_t block, uint32_t grid) {
   constexpr int NT = T::kThreads, VT = T::kVerts, ITEMS = T::kItems, SG = T::kSelGroup;
-  constexpr int NSG = NT / SG;  // selection groups per workgroup
   extern __shared__ __align__(16) uint8_t smem_raw[];
   const int tid = threadIdx.x;
   const bool weighted = x.g.weighted;
@@ -781,8 +780,6 @@ __device__ __forceinline__ void rate_tiles(const RoundCtx& x, VDesc vd, const in
   V* vals = (V*)(A + (size_t)T::kSlots * 4);
   uint32_t* nums = (uint32_t*)(A + L.nums_off);
   TileShared<NT, VT>& sh = *(TileShared<NT, VT>*)(A + L.abytes);
-  const int sgi = tid / SG;           // selection group of this thread
-  const int sl = tid % SG;            // lane within the selection group
 
   // The workgroups of one XCD take tiles of their own eighth of the list (one
   // counter per eighth), then help with the eighths that have some left.

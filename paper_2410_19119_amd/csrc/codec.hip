@@ -22,8 +22,6 @@ __device__ __forceinline__ uint32_t varint_len(uint64_t x) {
   return ((70u - (uint32_t)__clzll((long long)(x | 1u))) * 37u) >> 8;  // ceil(bits / 7) for 1..64 bits
 }
 
-__device__ __forceinline__ uint64_t zigzag(int64_t x) { return ((uint64_t)x << 1) ^ (uint64_t)(x >> 63); }
-
 __device__ __forceinline__ uint32_t varint_put(uint8_t* out, uint64_t x) {
   uint32_t k = 0;
   while (x >= 0x80) {

@@ -158,9 +158,6 @@ __device__ __forceinline__ uint32_t ceil_log2(uint32_t x) { return x <= 1 ? 0 : 
 
 // Table values: 64-bit sums, or 32-bit sums where no sum can reach 2^31 (a
 // graph with unit edge weights and fewer than 2^31 directed edges).
-__device__ __forceinline__ void tbl_val_add(unsigned long long* v, int64_t w) {
-  atomicAdd(v, (unsigned long long)w);
-}
 __device__ __forceinline__ void tbl_val_add(int64_t* v, int64_t w) {
   atomicAdd((unsigned long long*)v, (unsigned long long)w);
 }

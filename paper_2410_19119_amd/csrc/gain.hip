@@ -622,7 +622,6 @@ lp_status gt_fill(const GainTable& t, const int32_t* blocks, Scratch& sc) {
   hipStream_t s = sc.stream();
   const lp_graph* g = t.g;
   const GtView<V> v = view_of<V>(t);
-  const int32_t n = g->n;
   hipLaunchKernelGGL(k_gt_clear<V>, dim3(grid_for((int64_t)t.entries, 256, 65536)), dim3(256), 0, s, t.key, (V*)t.val,
                      t.entries);
   LP_CHECK_LAUNCH();

@@ -15,8 +15,7 @@
 
 namespace lp {
 
-// [31:0] value, [32] a segment starts in the tile, [34:33] 1 = tile total,
-// 2 = inclusive prefix, [63:35] launch
+// [31:0] value, [34:33] 1 = tile total, 2 = inclusive prefix, [63:35] launch
 struct LookArgs {
   uint64_t* words;
   uint32_t* ticket;  // zero between launches
@@ -25,8 +24,8 @@ struct LookArgs {
 
 constexpr uint32_t kLookTotal = 1, kLookPrefix = 2;
 
-__device__ __forceinline__ uint64_t look_word(uint32_t launch, uint32_t state, uint32_t seg, uint32_t v) {
-  return ((uint64_t)(launch & 0x1FFFFFFFu) << 35) | ((uint64_t)state << 33) | ((uint64_t)seg << 32) | v;
+__device__ __forceinline__ uint64_t look_word(uint32_t launch, uint32_t state, uint32_t v) {
+  return ((uint64_t)(launch & 0x1FFFFFFFu) << 35) | ((uint64_t)state << 33) | v;
 }
 __device__ __forceinline__ void look_put(uint64_t* p, uint64_t w) {
   __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -38,7 +37,6 @@ __device__ __forceinline__ uint64_t look_get(const uint64_t* p) {
 __device__ __forceinline__ uint32_t look_state(uint64_t w, uint32_t launch) {
   return (uint32_t)(w >> 35) == (launch & 0x1FFFFFFFu) ? (uint32_t)(w >> 33) & 3u : 0u;
 }
-__device__ __forceinline__ uint32_t look_seg(uint64_t w) { return (uint32_t)(w >> 32) & 1u; }
 
 // The workgroup's tile among `tiles` (called by exactly that many workgroups
 // of the launch); `sm` is one word of LDS. The last one resets the counter.
@@ -90,7 +88,7 @@ __device__ __forceinline__ LookStep look_step(const uint32_t (&st)[kLookPer]) {
 // called by one whole wavefront.
 __device__ __forceinline__ uint32_t look_sum(const LookArgs& a, uint32_t tile, uint32_t total) {
   const int lane = lane_id();
-  if (lane == 0) look_put(&a.words[tile], look_word(a.launch, tile ? kLookTotal : kLookPrefix, 0, total));
+  if (lane == 0) look_put(&a.words[tile], look_word(a.launch, tile ? kLookTotal : kLookPrefix, total));
   uint32_t sum = 0;
   for (int64_t at = (int64_t)tile - 1; at >= 0;) {
     uint64_t w[kLookPer];
@@ -98,7 +96,7 @@ __device__ __forceinline__ uint32_t look_sum(const LookArgs& a, uint32_t tile, u
 #pragma unroll
     for (int k = 0; k < kLookPer; ++k) {
       const int64_t t = at - lane * kLookPer - k;
-      w[k] = t >= 0 ? look_get(&a.words[t]) : look_word(a.launch, kLookPrefix, 0, 0);
+      w[k] = t >= 0 ? look_get(&a.words[t]) : look_word(a.launch, kLookPrefix, 0);
     }
 #pragma unroll
     for (int k = 0; k < kLookPer; ++k) st[k] = look_state(w[k], a.launch);
@@ -115,7 +113,7 @@ __device__ __forceinline__ uint32_t look_sum(const LookArgs& a, uint32_t tile, u
     if (ls.stop >= 0) break;
     at -= kWave * kLookPer;
   }
-  if (lane == 0 && tile) look_put(&a.words[tile], look_word(a.launch, kLookPrefix, 0, sum + total));
+  if (lane == 0 && tile) look_put(&a.words[tile], look_word(a.launch, kLookPrefix, sum + total));
   return sum;
 }
 
@@ -127,7 +125,7 @@ __device__ __forceinline__ int64_t look_seg_sum(const LookArgs& a, uint32_t tile
   const uint32_t mine = tile == 0 || seg ? kLookPrefix : kLookTotal;
   if (lane < 2)
     look_put(&a.words[2 * (uint64_t)tile + lane],
-             look_word(a.launch, mine, seg, (uint32_t)((uint64_t)tail >> (32 * lane))));
+             look_word(a.launch, mine, (uint32_t)((uint64_t)tail >> (32 * lane))));
   uint64_t sum = 0;
   for (int64_t at = (int64_t)tile - 1; at >= 0;) {
     uint64_t lo[kLookPer], hi[kLookPer];
@@ -135,7 +133,7 @@ __device__ __forceinline__ int64_t look_seg_sum(const LookArgs& a, uint32_t tile
 #pragma unroll
     for (int k = 0; k < kLookPer; ++k) {
       const int64_t t = at - lane * kLookPer - k;
-      lo[k] = hi[k] = look_word(a.launch, kLookPrefix, 0, 0);
+      lo[k] = hi[k] = look_word(a.launch, kLookPrefix, 0);
       if (t >= 0) {
         lo[k] = look_get(&a.words[2 * t]);
         hi[k] = look_get(&a.words[2 * t + 1]);
@@ -161,7 +159,7 @@ __device__ __forceinline__ int64_t look_seg_sum(const LookArgs& a, uint32_t tile
   }
   if (mine == kLookTotal && lane < 2)
     look_put(&a.words[2 * (uint64_t)tile + lane],
-             look_word(a.launch, kLookPrefix, 0, (uint32_t)((sum + (uint64_t)tail) >> (32 * lane))));
+             look_word(a.launch, kLookPrefix, (uint32_t)((sum + (uint64_t)tail) >> (32 * lane))));
   return (int64_t)sum;
 }
 

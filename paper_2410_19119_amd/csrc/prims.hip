@@ -392,18 +392,6 @@ __device__ __forceinline__ T shfl_up_any(T x, int d) {
   return b.t;
 }
 
-template <typename T>
-__device__ __forceinline__ T shfl_any(T x, int src) {
-  union U {
-    T t;
-    uint32_t w[sizeof(T) / 4];
-  } a, b;
-  a.t = x;
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) b.w[i] = __shfl(a.w[i], src, kWave);
-  return b.t;
-}
-
 // In-order (non-commutative safe) block inclusive scan of one value per thread.
 template <typename T, typename Op>
 __device__ __forceinline__ T block_scan_incl(T x, T* sm, T* total) {
@@ -644,7 +632,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_pass(SortedPairs b, const uin
     cnt += c;
   }
   uint64_t* words = look.words + (uint64_t)tile * kRsBins + t;
-  look_put(words, look_word(look.launch, tile ? kLookTotal : kLookPrefix, 0, cnt));
+  look_put(words, look_word(look.launch, tile ? kLookTotal : kLookPrefix, cnt));
   int32_t tot;
   const uint32_t ds = (uint32_t)block_incl_scan_add<kRsThreads, int32_t>((int32_t)cnt, scan, &tot) - cnt;
   dstart[t] = ds;
@@ -662,7 +650,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_pass(SortedPairs b, const uin
     uint64_t wd[kRsBack];
 #pragma unroll
     for (int k = 0; k < kRsBack; ++k)
-      wd[k] = q >= k ? look_get(look.words + (uint64_t)(q - k) * kRsBins + t) : look_word(look.launch, kLookPrefix, 0, 0);
+      wd[k] = q >= k ? look_get(look.words + (uint64_t)(q - k) * kRsBins + t) : look_word(look.launch, kLookPrefix, 0);
     bool known = false, open = false;
 #pragma unroll
     for (int k = 0; k < kRsBack; ++k) {
@@ -679,7 +667,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_pass(SortedPairs b, const uin
     if (known) break;
     if (open) __builtin_amdgcn_s_sleep(1);
   }
-  if (tile) look_put(words, look_word(look.launch, kLookPrefix, 0, before + cnt));
+  if (tile) look_put(words, look_word(look.launch, kLookPrefix, before + cnt));
   gbase[t] = first + before - ds;
   __syncthreads();
   const uint32_t have = (uint32_t)min((int64_t)kRsTile, n - (int64_t)tile * kRsTile);
